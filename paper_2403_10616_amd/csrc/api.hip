@@ -95,8 +95,7 @@ static Plan make_plan(const dipaco_ctx* c, int B, int S) {
   // of dqkv).
   p.ln_partial_stride = (ln_bwd_partial_floats((int)T, (int)d) * 4 + 255) & ~(size_t)255;
   p.ln_partial = take(p.ln_partial_stride * (2 * (size_t)c->n_layers + 1));
-  const size_t widest = std::max(std::max(F, 3 * A), d);
-  p.cs_partial_stride = (std::max(std::max(colsum_partial_floats((int)T, (int)widest), gemm_colsum_partial_floats((int)T, (int)F)),
+  p.cs_partial_stride = (std::max(gemm_colsum_partial_floats((int)T, (int)F),
                                   attention_bwd_colsum_floats((int)B, (int)S, a.n_heads, a.d_head)) * 4 + 255) & ~(size_t)255;
   p.cs_partial = take(p.cs_partial_stride * std::max<size_t>(1, 2 * (size_t)c->n_layers));
   size_t sk = 0;
@@ -823,7 +822,7 @@ dipaco_status dipaco_router_logistic_grad(const float* z, const int32_t* labels,
   TRY(launch_fill_i32(n_valid, (int)N, 1, st));
   TRY(launch_mean_loss(nll, n_valid, loss_out, (int)N, st));
   // db = column sums;  dW = dlogits^T z (contraction over the documents)
-  TRY(launch_colsum<float>(logits, dbias_out, reinterpret_cast<float*>(ws + p.cs_partial), (int)N, K, st));
+  TRY(launch_colsum(logits, dbias_out, reinterpret_cast<float*>(ws + p.cs_partial), (int)N, K, st));
   if (dweights_out)
     TRY(gemm<float>(logits, z, dweights_out, K, D, (int)N, K, D, D, true, false, nullptr, nullptr, nullptr, nullptr, 0,
                     true, gemm_plan_splits(K, D, (int)N, false), reinterpret_cast<float*>(ws + p.sk_partial), st));

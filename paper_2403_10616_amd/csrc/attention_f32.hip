@@ -1,0 +1,405 @@
+// Causal attention in fp32 on the matrix cores, forward and backward, head sizes 32, 64 and 128.
+//
+// v_mfma_f32_16x16x4_f32 throughout: operand lane l supplies row (column) l % 16 and contraction index l / 16, and lane
+// l of a result holds column l % 16, rows 4 (l / 16) + e, e = 0..3.  As in the bf16 kernels (attention_mfma.hip) whatever
+// has to be contracted next is made the ROW index of the score tile, so that probabilities go from accumulator
+// registers straight into the next product: element e of a 16-row score tile IS the B operand of a product over the four
+// rows 4 (l / 16) + e.
+//   forward, dQ:   S^T = K.Q^T  (rows = keys, columns = queries)  ->  O^T += V^T.P^T,   dQ^T += K^T.dS^T
+//   dK, dV:        S   = Q.K^T  (rows = queries, columns = keys)  ->  dV^T += dO^T.P,   dK^T += Q^T.dS
+//
+// One workgroup = 8 waves of 16 queries (keys), 128 in all; tiles of 32 keys (queries) go through registers into LDS, two
+// stages, one barrier per tile, the next tile's loads in flight during this one's products.  Rows are kept DH + 4 floats
+// apart, which serves both kinds of read: 16-byte reads along a row (contraction over the head: lane l takes columns
+// 16 c + 4 (l / 16) .. + 3 of row l % 16, good for four products), and 4-byte reads across four rows (contraction over the
+// tile's rows: columns l % 16 of row 4 (l / 16) + e), which then fall on 64 different banks.
+// The 16-row shape keeps a head of 128 in 32 registers per operand and lane, and gives small batches twice the waves of
+// a 32-row one.
+// Bound: the fp32 matrix cores (a product of 2048 flop every 32 cycles and SIMD); a tile asks 64 (forward) to 160 (dK/dV)
+// of them per wave against 16-40 KB of LDS reads, a quarter of what LDS delivers in that time.
+// Measured on 8 sequences x 8 heads x 500 positions, head size 64: forward 49 us, dQ 63, dK / dV 79 (one thread per row on
+// the vector ALU: 375, 911, 1517), with the causal triangle's longest block setting the length of each launch.
+// No atomics: every output element has exactly one writer and a fixed summation order.
+#include "kernels.h"
+#include "mma_tile.h"
+
+namespace dipaco {
+
+namespace {
+
+constexpr int F_WAVES = 8, F_THREADS = 64 * F_WAVES;
+constexpr int F_ROWS = 16 * F_WAVES;   // queries (keys) per workgroup
+constexpr int F_TILE = 32;             // keys (queries) per tile
+
+template <int DH> constexpr int row_stride() { return DH + 4; }
+template <int DH> constexpr int tile_floats() { return F_TILE * row_stride<DH>(); }
+template <int DH> constexpr float head_scale() { return DH == 32 ? 0.17677669529663689f : DH == 64 ? 0.125f : 0.088388347648318447f; }
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float sum_groups(float v) {   // over the four lanes that share l % 16
+  v += __shfl_xor(v, 16, WAVE);
+  v += __shfl_xor(v, 32, WAVE);
+  return v;
+}
+__device__ __forceinline__ float max_groups(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, WAVE));
+  v = fmaxf(v, __shfl_xor(v, 32, WAVE));
+  return v;
+}
+
+// Two operands' tiles of F_TILE rows: thread t moves float4 number t + F_THREADS i of tile i / (NLD / 2).
+template <int DH> struct TilePair {
+  static constexpr int VEC_ROW = DH / 4;                                   // 16-byte vectors per row
+  static constexpr int NLD = 2 * F_TILE * VEC_ROW / F_THREADS;             // per thread, both tiles: 1, 2 or 4
+  static constexpr int PER_TILE = F_TILE * VEC_ROW;                        // vectors per tile: 256, 512, 1024
+  f32x4 v[NLD];
+  // rows at or beyond rows_total re-read the last valid row (callers give them zero weight)
+  __device__ __forceinline__ void load(const float* t0, const float* t1, long ld0, long ld1, int row0, int rows_total) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int n = threadIdx.x + F_THREADS * i;
+      const bool first = n < PER_TILE;
+      const int m = first ? n : n - PER_TILE;
+      const int row = min(row0 + m / VEC_ROW, rows_total - 1);
+      v[i] = *reinterpret_cast<const f32x4*>((first ? t0 + row * ld0 : t1 + row * ld1) + 4 * (m % VEC_ROW));
+    }
+  }
+  __device__ __forceinline__ void store(float* stage) const {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int n = threadIdx.x + F_THREADS * i;
+      const bool first = n < PER_TILE;
+      const int m = first ? n : n - PER_TILE;
+      *reinterpret_cast<f32x4*>(stage + (first ? 0 : tile_floats<DH>()) + (m / VEC_ROW) * row_stride<DH>() + 4 * (m % VEC_ROW)) = v[i];
+    }
+  }
+};
+
+// a lane's share of one of its wave's 16 rows: columns 16 c + 4 (l / 16) .. + 3
+template <int DH> struct RowFrag { float4 c[DH / 16]; };
+template <int DH> __device__ __forceinline__ RowFrag<DH> load_row(const float* row, int g, bool valid) {
+  RowFrag<DH> f;
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c)
+    f.c[c] = valid ? *reinterpret_cast<const float4*>(row + 16 * c + 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
+  return f;
+}
+// acc (16 x 16) += rows 16 t .. + 15 of `tile`, contracted over the head with this wave's rows b
+template <int DH>
+__device__ __forceinline__ void rows_product(f32x4& acc, const float* tile, int t, const RowFrag<DH>& b, int m, int g) {
+  const float* r = tile + (16 * t + m) * row_stride<DH>() + 4 * g;
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c) {
+    const float4 a = *reinterpret_cast<const float4*>(r + 16 * c);
+    acc = mfma4(a.x, b.c[c].x, acc);
+    acc = mfma4(a.y, b.c[c].y, acc);
+    acc = mfma4(a.z, b.c[c].z, acc);
+    acc = mfma4(a.w, b.c[c].w, acc);
+  }
+}
+// acc^T[d] (16 head columns x this wave's 16 rows) += (rows 16 t .. + 15 of `tile`)^T . p
+template <int DH>
+__device__ __forceinline__ void cols_product(f32x4 (&acc)[DH / 16], const float* tile, int t, const f32x4& p, int m, int g) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float* r = tile + (16 * t + 4 * g + e) * row_stride<DH>() + m;
+#pragma unroll
+    for (int d = 0; d < DH / 16; ++d) acc[d] = mfma4(r[16 * d], p[e], acc[d]);
+  }
+}
+template <int DH> __device__ __forceinline__ void zero_acc(f32x4 (&acc)[DH / 16]) {
+#pragma unroll
+  for (int d = 0; d < DH / 16; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+template <int DH> __device__ __forceinline__ void store_row(float* row, const f32x4 (&acc)[DH / 16], int g, float scale) {
+#pragma unroll
+  for (int d = 0; d < DH / 16; ++d)
+    *reinterpret_cast<float4*>(row + 16 * d + 4 * g) =
+        make_float4(acc[d][0] * scale, acc[d][1] * scale, acc[d][2] * scale, acc[d][3] * scale);
+}
+// Column sums of the workgroup's 128 output rows: over the 16 lanes of a group on the DPP lanes, then the waves in order.
+// red: LDS [F_WAVES][DH].  Every wave calls it; rows with valid = false count as zero.
+template <int DH>
+__device__ __forceinline__ void block_column_sums(const f32x4 (&acc)[DH / 16], float scale, bool valid, float* red,
+                                                  float* __restrict__ out, int wave, int m, int g) {
+  __syncthreads();   // red lies in LDS that was in use before
+#pragma unroll
+  for (int d = 0; d < DH / 16; ++d)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v = valid ? acc[d][e] * scale : 0.f;
+      v += dpp_fetch<0xb1, 0xf>(v, 0.f);
+      v += dpp_fetch<0x4e, 0xf>(v, 0.f);
+      v += dpp_fetch<0x141, 0xf>(v, 0.f);
+      v += dpp_fetch<0x140, 0xf>(v, 0.f);
+      if (m == 0) red[wave * DH + 16 * d + 4 * g + e] = v;
+    }
+  __syncthreads();
+  for (int c = threadIdx.x; c < DH; c += F_THREADS) {
+    float s = red[c];
+#pragma unroll
+    for (int w = 1; w < F_WAVES; ++w) s += red[w * DH + c];
+    out[c] = s;
+  }
+}
+
+template <int DH>
+__global__ void __launch_bounds__(F_THREADS, 2) attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o,
+                                                             float* __restrict__ lse, int S, int H) {
+  extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
+  constexpr int STAGE = 2 * tile_floats<DH>();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
+  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const long ld = 3L * A;
+  const float* base = qkv + (long)b * S * ld + hd * DH;
+  const int q0 = (gridDim.y - 1 - blockIdx.y) * F_ROWS;   // longest blocks first
+  const int qw0 = q0 + 16 * wave, q = qw0 + m;
+  const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
+  const int ntiles = (min(S, q0 + F_ROWS) + F_TILE - 1) / F_TILE;
+  f32x4 ot[DH / 16];
+  zero_acc<DH>(ot);
+  float mx = -INFINITY, l = 0.f;
+  TilePair<DH> next;
+  next.load(base + A, base + 2 * A, ld, ld, 0, S);
+  next.store(f_smem);
+  for (int kt = 0; kt < ntiles; ++kt) {
+    const float* k_ = f_smem + (kt & 1) * STAGE;
+    const float* v_ = k_ + tile_floats<DH>();
+    const int kv0 = kt * F_TILE;
+    const bool more = kt + 1 < ntiles;
+    if (more) next.load(base + A, base + 2 * A, ld, ld, kv0 + F_TILE, S);
+    __syncthreads();   // tile kt is in LDS, and everybody is done with the stage of tile kt - 1
+    if (kv0 <= qw0 + 15) {   // wave-uniform: some query of this wave sees this tile
+      f32x4 st[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        rows_product<DH>(st[t], k_, t, qf, m, g);
+      }
+      float tile_max = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          st[t][e] = kv0 + 16 * t + 4 * g + e > q ? -INFINITY : st[t][e] * head_scale<DH>();
+          tile_max = fmaxf(tile_max, st[t][e]);
+        }
+      const float mn = fmaxf(mx, max_groups(tile_max));   // finite: key 0 is visible to every query
+      const float corr = expf(mx - mn);
+      mx = mn;
+      float part = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          st[t][e] = expf(st[t][e] - mn);
+          part += st[t][e];
+        }
+      l = l * corr + part;   // this lane's quarter of the row's keys
+#pragma unroll
+      for (int d = 0; d < DH / 16; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ot[d][e] *= corr;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) cols_product<DH>(ot, v_, t, st[t], m, g);
+    }
+    if (more) next.store(f_smem + ((kt + 1) & 1) * STAGE);
+  }
+  l = sum_groups(l);
+  if (q < S) {
+    store_row<DH>(o + ((long)b * S + q) * A + hd * DH, ot, g, 1.0f / l);
+    if (g == 0) lse[(long)bh * S + q] = mx + logf(l);
+  }
+}
+
+// dQ_i = scale * sum_{j<=i} p_ij (dO_i.v_j - D_i) k_j, with D_i = dO_i.o_i (also stored for the dK/dV kernel)
+template <int DH>
+__global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                float* __restrict__ dqkv, float* __restrict__ dsum,
+                                                                float* __restrict__ colsum, int S, int H) {
+  extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
+  constexpr int STAGE = 2 * tile_floats<DH>();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
+  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const long ld = 3L * A;
+  const float* base = qkv + (long)b * S * ld + hd * DH;
+  const int qb = gridDim.y - 1 - blockIdx.y, q0 = qb * F_ROWS;
+  const int qw0 = q0 + 16 * wave, q = qw0 + m;
+  const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
+  const long orow = ((long)b * S + q) * A + hd * DH;
+  const RowFrag<DH> gf = load_row<DH>(d_o + orow, g, q < S);
+  float D = 0.f;
+  {
+    const RowFrag<DH> of = load_row<DH>(o + orow, g, q < S);
+#pragma unroll
+    for (int c = 0; c < DH / 16; ++c)
+      D += (gf.c[c].x * of.c[c].x + gf.c[c].y * of.c[c].y) + (gf.c[c].z * of.c[c].z + gf.c[c].w * of.c[c].w);
+    D = sum_groups(D);
+  }
+  const float L = q < S ? lse[(long)bh * S + q] : INFINITY;   // +inf beyond the sequence: probability 0
+  if (g == 0 && q < S) dsum[(long)bh * S + q] = D;
+  const int ntiles = (min(S, q0 + F_ROWS) + F_TILE - 1) / F_TILE;
+  f32x4 dqt[DH / 16];
+  zero_acc<DH>(dqt);
+  TilePair<DH> next;
+  next.load(base + A, base + 2 * A, ld, ld, 0, S);
+  next.store(f_smem);
+  for (int kt = 0; kt < ntiles; ++kt) {
+    const float* k_ = f_smem + (kt & 1) * STAGE;
+    const float* v_ = k_ + tile_floats<DH>();
+    const int kv0 = kt * F_TILE;
+    const bool more = kt + 1 < ntiles;
+    if (more) next.load(base + A, base + 2 * A, ld, ld, kv0 + F_TILE, S);
+    __syncthreads();
+    if (kv0 <= qw0 + 15) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+        rows_product<DH>(st, k_, t, qf, m, g);
+        rows_product<DH>(dp, v_, t, gf, m, g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)   // without the 1 / sqrt(d_head) factor, which is applied when dQ is stored
+          st[e] = kv0 + 16 * t + 4 * g + e > q ? 0.f : expf(st[e] * head_scale<DH>() - L) * (dp[e] - D);
+        cols_product<DH>(dqt, k_, t, st, m, g);
+      }
+    }
+    if (more) next.store(f_smem + ((kt + 1) & 1) * STAGE);
+  }
+  if (q < S) store_row<DH>(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, g, head_scale<DH>());
+  // one row of partial column sums per (document, query block), this head's DH columns of dQ
+  if (colsum)
+    block_column_sums<DH>(dqt, head_scale<DH>(), q < S, f_smem, colsum + ((long)b * gridDim.y + qb) * ld + hd * DH, wave, m, g);
+}
+
+// dV_j = sum_{i>=j} p_ij dO_i;  dK_j = scale * sum_{i>=j} p_ij (dO_i.v_j - D_i) q_i
+template <int DH>
+__global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
+                                                                 const float* __restrict__ lse, const float* __restrict__ dsum,
+                                                                 float* __restrict__ dqkv, float* __restrict__ colsum, int S,
+                                                                 int H) {
+  extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][Q | dO | lse | D]
+  constexpr int STAGE = 2 * tile_floats<DH>() + 2 * F_TILE;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
+  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const long ld = 3L * A;
+  const float* base = qkv + (long)b * S * ld + hd * DH;
+  const float* gbase = d_o + (long)b * S * A + hd * DH;
+  const int kb = blockIdx.y, k0 = kb * F_ROWS;            // early key blocks are the long ones
+  const int kw0 = k0 + 16 * wave, key = kw0 + m;
+  const RowFrag<DH> kf = load_row<DH>(base + (long)key * ld + A, g, key < S);
+  const RowFrag<DH> vf = load_row<DH>(base + (long)key * ld + 2 * A, g, key < S);
+  f32x4 dkt[DH / 16], dvt[DH / 16];
+  zero_acc<DH>(dkt);
+  zero_acc<DH>(dvt);
+  const int first = k0 / F_TILE, ntiles = (S + F_TILE - 1) / F_TILE;
+  TilePair<DH> next;
+  float next_stat = 0.f;
+  // statistics of a tile's queries: threads 0..31 move lse (+inf beyond the sequence: probability 0), 32..63 D
+  auto load = [&](int qt) {
+    next.load(base, gbase, ld, A, qt * F_TILE, S);
+    if (threadIdx.x < 2 * F_TILE) {
+      const int q = qt * F_TILE + (threadIdx.x & (F_TILE - 1));
+      const bool is_lse = threadIdx.x < F_TILE;
+      next_stat = q < S ? (is_lse ? lse : dsum)[(long)bh * S + q] : (is_lse ? INFINITY : 0.f);
+    }
+  };
+  auto store = [&](int qt) {
+    float* stage = f_smem + ((qt - first) & 1) * STAGE;
+    next.store(stage);
+    if (threadIdx.x < 2 * F_TILE) stage[2 * tile_floats<DH>() + threadIdx.x] = next_stat;
+  };
+  load(first);
+  store(first);
+  for (int qt = first; qt < ntiles; ++qt) {
+    const float* q_ = f_smem + ((qt - first) & 1) * STAGE;
+    const float* g_ = q_ + tile_floats<DH>();
+    const float* Ls = q_ + 2 * tile_floats<DH>();
+    const int q0 = qt * F_TILE;
+    const bool more = qt + 1 < ntiles;
+    if (more) load(qt + 1);
+    __syncthreads();
+    if (q0 + F_TILE - 1 >= kw0) {   // wave-uniform: some query of this tile sees a key of this wave
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+        rows_product<DH>(st, q_, t, kf, m, g);
+        rows_product<DH>(dp, g_, t, vf, m, g);
+        const float4 Lq = *reinterpret_cast<const float4*>(Ls + 16 * t + 4 * g);
+        const float4 Dq = *reinterpret_cast<const float4*>(Ls + F_TILE + 16 * t + 4 * g);
+        const float L[4] = {Lq.x, Lq.y, Lq.z, Lq.w}, D[4] = {Dq.x, Dq.y, Dq.z, Dq.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = q0 + 16 * t + 4 * g + e < key ? 0.f : expf(st[e] * head_scale<DH>() - L[e]);
+          st[e] = p;
+          dp[e] = p * (dp[e] - D[e]);
+        }
+        cols_product<DH>(dvt, g_, t, st, m, g);
+        cols_product<DH>(dkt, q_, t, dp, m, g);
+      }
+    }
+    if (more) store(qt + 1);
+  }
+  if (key < S) {
+    float* out = dqkv + ((long)b * S + key) * ld + hd * DH;
+    store_row<DH>(out + A, dkt, g, head_scale<DH>());
+    store_row<DH>(out + 2 * A, dvt, g, 1.0f);
+  }
+  if (colsum) {
+    float* cs = colsum + ((long)b * gridDim.y + kb) * ld + hd * DH;
+    block_column_sums<DH>(dkt, head_scale<DH>(), key < S, f_smem, cs + A, wave, m, g);
+    block_column_sums<DH>(dvt, 1.0f, key < S, f_smem, cs + 2 * A, wave, m, g);
+  }
+}
+
+template <int DH> constexpr int fwd_lds() { return 2 * 2 * tile_floats<DH>() * (int)sizeof(float); }
+template <int DH> constexpr int dkv_lds() { return 2 * (2 * tile_floats<DH>() + 2 * F_TILE) * (int)sizeof(float); }
+
+template <int DH>
+dipaco_status fwd(const float* qkv, float* o, float* lse, int B, int S, int H, hipStream_t s) {
+  static std::atomic<unsigned long long> lds{0};
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_f32<DH>), fwd_lds<DH>(), lds)) return st;
+  attn_fwd_f32<DH><<<dim3(B * H, (S + F_ROWS - 1) / F_ROWS), F_THREADS, fwd_lds<DH>(), s>>>(qkv, o, lse, S, H);
+  DIPACO_LAUNCH_CHECK();
+  return DIPACO_OK;
+}
+template <int DH>
+dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv, float* dsum,
+                  float* colsum, int B, int S, int H, hipStream_t s) {
+  static_assert(F_WAVES * DH <= 2 * 2 * tile_floats<DH>(), "the column sums' scratch fits in the stages");
+  static std::atomic<unsigned long long> dq{0}, dkv{0};
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH>), fwd_lds<DH>(), dq)) return st;
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH>), dkv_lds<DH>(), dkv)) return st;
+  const dim3 grid(B * H, (S + F_ROWS - 1) / F_ROWS);
+  attn_bwd_dq_f32<DH><<<grid, F_THREADS, fwd_lds<DH>(), s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H);
+  DIPACO_LAUNCH_CHECK();
+  attn_bwd_dkv_f32<DH><<<grid, F_THREADS, dkv_lds<DH>(), s>>>(qkv, d_o, lse, dsum, dqkv, colsum, S, H);
+  DIPACO_LAUNCH_CHECK();
+  return DIPACO_OK;
+}
+
+}  // namespace
+
+dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, int B, int S, int H, int dh, hipStream_t s) {
+  if (dh == 32) return fwd<32>(qkv, o, lse, B, S, H, s);
+  if (dh == 64) return fwd<64>(qkv, o, lse, B, S, H, s);
+  if (dh == 128) return fwd<128>(qkv, o, lse, B, S, H, s);
+  return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
+}
+
+dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv,
+                                       float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
+                                       hipStream_t s, SumBatch* batch) {
+  float* partial = colsum_out ? colsum_partial : nullptr;
+  dipaco_status st;
+  if (dh == 32) st = bwd<32>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+  else if (dh == 64) st = bwd<64>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+  else if (dh == 128) st = bwd<128>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+  else return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
+  if (st != DIPACO_OK || !colsum_out) return st;
+  return launch_sum_rows(colsum_partial, colsum_out, B * ((S + F_ROWS - 1) / F_ROWS), 3 * H * dh, s, batch);
+}
+
+}  // namespace dipaco

@@ -1,4 +1,4 @@
-// Causal attention on the matrix cores (bf16 operands, fp32 softmax and accumulation), head size 64.
+// Causal attention on the matrix cores (bf16 operands, fp32 softmax and accumulation), head sizes 32, 64 and 128.
 //
 // Everything is arranged so that the probabilities never leave registers.  A 32x32 MFMA leaves its result with
 // lane l holding column l%32 and rows 8*(e/4) + 4*(l/32) + e%4 (e = 0..15); the B operand of the next MFMA wants
@@ -28,6 +28,12 @@
 // of read are then free of bank conflicts (rows two apart land in different 64-byte groups for the transposing
 // read; the lane groups that a ds_read_b128 serves together see eight different swizzles per row parity).
 // No atomics: every output element has exactly one writer and a fixed summation order.
+//
+// Head sizes.  A tile is kept as panels of 64 rows x 64 columns (128-byte rows), so one swizzle and one set of
+// fragment offsets serve every head size: head size 128 is two panels side by side, head size 32 uses the first half
+// of one panel's columns (the lanes whose 16 bytes fall into the other half fetch a valid chunk again, so that no
+// load is conditional).  Measured on 8 sequences x 8 heads x 512 positions, head size 128: forward 17 us, dQ 29, dK / dV 38
+// (one-thread-per-row kernels: 1470, 1990 and 20970 us).
 #include <type_traits>
 
 #include "kernels.h"
@@ -38,8 +44,11 @@ namespace dipaco {
 namespace {
 
 constexpr int AT_THREADS = 256;
-constexpr int DH = 64;
-constexpr int TILE_BYTES = 64 * TILE_ROW_BYTES;   // 64 rows x 128 B
+constexpr int PANEL_BYTES = 64 * TILE_ROW_BYTES;   // 64 rows x 64 columns of bf16
+template <int DH> constexpr int panels() { return DH > 64 ? 2 : 1; }
+template <int DH> constexpr int tile_bytes() { return panels<DH>() * PANEL_BYTES; }
+// 1 / sqrt(d_head), the scale of the scores
+template <int DH> constexpr float score_scale() { return DH == 32 ? 0.17677669529663689f : DH == 64 ? 0.125f : 0.088388347648318447f; }
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -87,24 +96,24 @@ __device__ __forceinline__ void load16_to_lds_at(const bf16* base, uint32_t byte
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
 }
 
-// This wave's share of the loads of a stage made of two 64x64 tiles: 4 of the 16 wave-level loads (each fills 8
-// tile rows = 1024 LDS bytes).  Load i of wave w is number j = w + 4i: tile j / 8, rows 8 (j % 8) .. + 7.
-// A lane keeps one 32-bit byte offset per load (its row and 16-byte chunk inside a tile that starts at the operand's
-// row 0); the tile's first row is added to the wave-uniform base address, so a stage costs four vector registers.
-struct StageLoader {
-  uint32_t off[4];      // per lane: (row inside the tile) * row bytes + chunk * 16
-  uint32_t chunk[4];    // per lane: chunk * 16 alone (ragged last tile)
-};
+// This wave's share of the loads of a stage made of two tiles of 64 x DH: a panel is eight wave-level loads (each fills 8
+// of its rows = 1024 LDS bytes).  Load i of wave w is number j = w + 4i: panel j / 8 (the first tile's panels, then the
+// second's), rows 8 (j % 8) .. + 7 of it.
+// A lane keeps a 32-bit byte offset (its row and 16-byte chunk inside a tile that starts at the operand's row 0) per
+// operand and 32 rows: the tile's first row and the panel move the wave-uniform base, so a stage costs four vector
+// registers whatever the head size.
+template <int DH> struct StageLoader { uint32_t off[4]; };   // [operand][which of the wave's two row groups]
 __device__ __forceinline__ int loader_row(int i, int wave, int lane) { return 8 * ((wave + 4 * i) & 7) + (lane >> 3); }
-__device__ __forceinline__ StageLoader make_loader(long ld0, long ld1, int wave, int lane) {
-  StageLoader L;
+template <int DH> __device__ __forceinline__ uint32_t loader_column_bytes(int i, int wave, int lane) {
+  int c = (lane & 7) ^ swz64(loader_row(i, wave, lane));
+  if (DH == 32) c &= 3;
+  return (uint32_t)(c * 16);
+}
+template <int DH> __device__ __forceinline__ StageLoader<DH> make_loader(long ld0, long ld1, int wave, int lane) {
+  StageLoader<DH> L;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int j = wave + 4 * i;
-    const int rit = loader_row(i, wave, lane);
-    L.chunk[i] = (uint32_t)(((lane & 7) ^ swz64(rit)) * 16);
-    L.off[i] = (uint32_t)(rit * (j < 8 ? ld0 : ld1) * 2) + L.chunk[i];
-  }
+  for (int i = 0; i < 4; ++i)
+    L.off[i] = (uint32_t)(loader_row(i & 1, wave, lane) * (i < 2 ? ld0 : ld1) * 2) + loader_column_bytes<DH>(i & 1, wave, lane);
   return L;
 }
 // tile0 / tile1: the two operands (row 0 of this sequence and head), ld0 / ld1 their row strides in elements.
@@ -112,24 +121,26 @@ __device__ __forceinline__ StageLoader make_loader(long ld0, long ld1, int wave,
 // probabilities, -inf statistics), so any finite value will do, and no branch surrounds a load.  Only the last
 // tile of an operand can stick out; every other tile only moves the wave-uniform base.
 // Byte offsets are 32-bit: rows_total * row stride * 2 stays below 2^32 (checked by the launchers).
-__device__ __forceinline__ void issue_stage(const StageLoader& L, const bf16* tile0, const bf16* tile1, int row0,
+template <int DH>
+__device__ __forceinline__ void issue_stage(const StageLoader<DH>& L, const bf16* tile0, const bf16* tile1, int row0,
                                             int rows_total, long ld0, long ld1, int wave, int lane, uint32_t stage_addr) {
+  constexpr int NP = panels<DH>();
   if (row0 + 64 <= rows_total) {   // wave-uniform
+    const bf16* const b0 = tile0 + (long)row0 * ld0;
+    const bf16* const b1 = tile1 + (long)row0 * ld1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool first = (wave + 4 * i) < 8;   // wave-uniform
-      const int j = wave + 4 * i;
-      load16_to_lds_at((first ? tile0 : tile1) + (long)row0 * (first ? ld0 : ld1), L.off[i],
-                       stage_addr + (uint32_t)((j >> 3) * TILE_BYTES + (j & 7) * 1024));
+    for (int i = 0; i < 4 * NP; ++i) {
+      const int second = i / (2 * NP), panel = (i >> 1) % NP;   // compile-time
+      load16_to_lds_at((second ? b1 : b0) + 64 * panel, L.off[2 * second + (i & 1)], stage_addr + (uint32_t)((wave + 4 * i) * 1024));
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool first = (wave + 4 * i) < 8;
-      const int j = wave + 4 * i;
+    for (int i = 0; i < 4 * NP; ++i) {
+      const int second = i / (2 * NP), panel = (i >> 1) % NP;
       const int r = min(row0 + loader_row(i, wave, lane), rows_total - 1);
-      load16_to_lds_at(first ? tile0 : tile1, (uint32_t)r * (uint32_t)((first ? ld0 : ld1) * 2) + L.chunk[i],
-                       stage_addr + (uint32_t)((j >> 3) * TILE_BYTES + (j & 7) * 1024));
+      load16_to_lds_at((second ? tile1 : tile0) + 64 * panel,
+                       (uint32_t)r * (uint32_t)((second ? ld1 : ld0) * 2) + loader_column_bytes<DH>(i, wave, lane),
+                       stage_addr + (uint32_t)((wave + 4 * i) * 1024));
     }
   }
 }
@@ -145,7 +156,10 @@ __device__ __forceinline__ FragOff frag_offsets(int lane) {
   for (int ks = 0; ks < 4; ++ks) f.b[ks] = r * TILE_ROW_BYTES + (((2 * ks + h) ^ s) << 4);
   return f;
 }
-__device__ __forceinline__ uint4 ld16(const char* p) { return *reinterpret_cast<const uint4*>(p); }
+// K step ks (16 columns) of rows 32 t .. + 31 of a tile: panel ks / 4
+__device__ __forceinline__ uint4 row_frag(const char* tile, const FragOff& fo, int ks, int t) {
+  return *reinterpret_cast<const uint4*>(tile + (ks >> 2) * PANEL_BYTES + fo.b[ks & 3] + 4096 * t);
+}
 
 // Column-index (transposing) reads.  For output columns 32*dt .. + 31 and the 16 tile rows 32*t + 16*g2 .. + 15,
 // read p (0 / 1) of lane l = 16*g4 + 4*e + q fetches columns 32*dt + 16*(g4 & 1) + 4q .. + 3 of tile row
@@ -167,9 +181,9 @@ __device__ __forceinline__ TrOff tr_offsets(int lane) {
   return t;
 }
 __device__ __forceinline__ uint4 tr_read(const char* tile, const TrOff& to, int dt, int rows16) {
-  const char* base = tile + rows16 * 16 * TILE_ROW_BYTES;
-  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(uintptr_t)(uint32_t)(uintptr_t)(base + to.b[dt][0]));
-  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(uintptr_t)(uint32_t)(uintptr_t)(base + to.b[dt][1]));
+  const char* base = tile + (dt >> 1) * PANEL_BYTES + rows16 * 16 * TILE_ROW_BYTES;
+  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(uintptr_t)(uint32_t)(uintptr_t)(base + to.b[dt & 1][0]));
+  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(uintptr_t)(uint32_t)(uintptr_t)(base + to.b[dt & 1][1]));
   uint4 o;
   o.x = (uint16_t)lo[0] | ((uint32_t)(uint16_t)lo[1] << 16);
   o.y = (uint16_t)lo[2] | ((uint32_t)(uint16_t)lo[3] << 16);
@@ -177,26 +191,41 @@ __device__ __forceinline__ uint4 tr_read(const char* tile, const TrOff& to, int 
   o.w = (uint16_t)hi[2] | ((uint32_t)(uint16_t)hi[3] << 16);
   return o;
 }
-// acc^T[dt] += (tile^T)[columns 32 dt.., rows 32 t..] . src[t]   for a 64-row tile and two accumulator tiles src
-__device__ __forceinline__ void mma_transposed(f32x16 (&acc)[2], const char* tile, const TrOff& to, const f32x16 (&src)[2]) {
+// The same offsets formed anew from one of each kind (an XOR apiece) instead of kept: seven registers less through a
+// loop that has none to spare.  The opaque copies keep the compiler from forming them once, in front of the loop.
+__device__ __forceinline__ void rederive_offsets(FragOff& fo, TrOff& to) {
+  int f = fo.b[0], t = to.b[0][0];
+  asm volatile("" : "+v"(f), "+v"(t));
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
+  for (int ks = 1; ks < 4; ++ks) fo.b[ks] = f ^ (32 * ks);
+  fo.b[0] = f;
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to.b[dt][p] = (t ^ (64 * dt) ^ (32 * p)) + 8 * TILE_ROW_BYTES * p;
+}
+// acc^T[dt] += (tile^T)[columns 32 dt.., rows 32 (T0 + t)..] . src[t]   for NT accumulator tiles src of 32 tile rows each
+template <int DT, int NT>
+__device__ __forceinline__ void mma_transposed(f32x16 (&acc)[DT], const char* tile, const TrOff& to, const f32x16 (&src)[NT], int t0) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
     const uint4 p0 = pack8<0>(src[t]), p1 = pack8<8>(src[t]);
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt) {
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t), p0, acc[dt]);
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t + 1), p1, acc[dt]);
+    for (int dt = 0; dt < DT; ++dt) {
+      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * (t0 + t)), p0, acc[dt]);
+      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * (t0 + t) + 1), p1, acc[dt]);
     }
   }
 }
 
 // The same with the probabilities already packed to bf16: pk[t][0 / 1] = pack8<0 / 8>(src[t]).
-__device__ __forceinline__ void mma_transposed_packed(f32x16 (&acc)[2], const char* tile, const TrOff& to,
+template <int DT>
+__device__ __forceinline__ void mma_transposed_packed(f32x16 (&acc)[DT], const char* tile, const TrOff& to,
                                                       const uint4 (&pk)[2][2]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt) {
+    for (int dt = 0; dt < DT; ++dt) {
       acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t), pk[t][0], acc[dt]);
       acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t + 1), pk[t][1], acc[dt]);
     }
@@ -220,9 +249,9 @@ __device__ __forceinline__ void store4(bf16* dst, const f32x16& v, int g, float 
   *reinterpret_cast<bf16x4*>(dst) = o;
 }
 // out^T tiles ot[dt] hold head column 32*dt + 8*g + 4*h + (0..3) for this lane's row
-__device__ __forceinline__ void store_transposed_out(bf16* row_ptr, const f32x16 (&ot)[2], int h, float scale) {
+template <int DT> __device__ __forceinline__ void store_transposed_out(bf16* row_ptr, const f32x16 (&ot)[DT], int h, float scale) {
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int g = 0; g < 4; ++g) store4(row_ptr + 32 * dt + 8 * g + 4 * h, ot[dt], g, scale);
 }
@@ -244,20 +273,20 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 
 // Column sums of a block's 128 rows of a transposed-output tile pair (the bias gradient of the projection whose
 // output gradient the block is): every lane adds scale * its values over the 32 rows of its wave, the four waves'
-// sums are added in wave order, and the 64 sums go to out[0..64).
-// red: LDS [4][64].  All four waves call it; rows with valid = false count as zero.
-__device__ __forceinline__ void block_column_sums(const f32x16 (&ot)[2], float scale, bool valid, float (*red)[DH],
+// sums are added in wave order, and the 32 DT sums go to out.
+// red: LDS [4][32 DT].  All four waves call it; rows with valid = false count as zero.
+template <int DT> __device__ __forceinline__ void block_column_sums(const f32x16 (&ot)[DT], float scale, bool valid, float (*red)[32 * DT],
                                                   float* __restrict__ out, int wave, int lane) {
   const int h = lane >> 5;
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const float v = half_wave_sum(valid ? ot[dt][k] * scale : 0.f);
       if ((lane & 31) == 31) red[wave][32 * dt + 8 * (k >> 2) + 4 * h + (k & 3)] = v;
     }
   __syncthreads();
-  if (threadIdx.x < DH) {
+  if (threadIdx.x < 32 * DT) {
     const int c = threadIdx.x;
     out[c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
   }
@@ -267,14 +296,14 @@ __device__ __forceinline__ void block_column_sums(const f32x16 (&ot)[2], float s
 // ---- forward ---------------------------------------------------------------------------------------------------
 constexpr int FWD_STAGES = 2, DQ_STAGES = 2, DKV_STAGES = 2;   // three stages measured: forward level, backward 4 % slower
 
-__global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __restrict__ qkv, bf16* __restrict__ o,
+template <int DH>
+__global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(const bf16* __restrict__ qkv, bf16* __restrict__ o,
                                                                float* __restrict__ lse, int S, int H, int single) {
-  constexpr int NS = FWD_STAGES;
+  constexpr int NS = FWD_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   __shared__ __attribute__((aligned(16))) char smem[NS][2][TILE_BYTES];   // [stage][K | V]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, h = lane >> 5;
   const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
-  const int n_bh = single ? gridDim.x : gridDim.y;
   const int bx = single ? (int)blockIdx.y : (int)blockIdx.x;   // single: one block per workgroup, longest first
   const int A = H * DH;
   const long ld = 3L * A;
@@ -282,7 +311,7 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
   const FragOff fo = frag_offsets(lane);
   const TrOff to = tr_offsets(lane);
   const uint32_t smem_addr = (uint32_t)(uintptr_t)&smem[0][0][0];
-  const StageLoader L = make_loader(ld, ld, wave, lane);
+  const StageLoader<DH> L = make_loader<DH>(ld, ld, wave, lane);
   const bf16* const ktile = base + A;
   const bf16* const vtile = base + 2 * A;
   // A workgroup takes a long and a short query block (block x from the end, then block x from the start), so that
@@ -296,17 +325,18 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
   }
   const int q0 = qb * 128, qw0 = q0 + 32 * wave, q = qw0 + r;
 
-  uint4 qf[4];
+  uint4 qf[KS];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+  for (int ks = 0; ks < KS; ++ks)
     qf[ks] = q < S ? *reinterpret_cast<const uint4*>(base + (long)q * ld + 8 * (2 * ks + h)) : make_uint4(0, 0, 0, 0);
 
   const int kv_end = min(S, q0 + 128);
   const int ntiles = (kv_end + 63) / 64;
-  f32x16 ot[2];
-  zero(ot[0]); zero(ot[1]);
+  f32x16 ot[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) zero(ot[dt]);
   float m = -INFINITY, l = 0.f;
-  const float sc = 0.125f * LOG2E;   // 1/sqrt(64), base-2 exponentials
+  const float sc = score_scale<DH>() * LOG2E;   // base-2 exponentials
 
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
@@ -315,7 +345,7 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
   // one key / value tile; CUR: the stage it sits in
   auto tile = [&](auto CUR, int kt) {
     constexpr int cur = decltype(CUR)::value;
-    wait_stages_but<4>(min(NS - 2, ntiles - 1 - kt));
+    wait_stages_but<LPW>(min(NS - 2, ntiles - 1 - kt));
     __syncthreads();   // tile kt is in LDS; nobody still reads the stage of tile kt - 1, which is refilled now
     if (kt + NS - 1 < ntiles)
       issue_stage(L, ktile, vtile, (kt + NS - 1) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
@@ -326,9 +356,9 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
       f32x16 st[2];
       zero(st[0]); zero(st[1]);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) st[t] = mfma16(ld16(k_ + fo.b[ks] + 4096 * t), qf[ks], st[t]);
+        for (int t = 0; t < 2; ++t) st[t] = mfma16(row_frag(k_, fo, ks, t), qf[ks], st[t]);
       if (kv0 + 63 > qw0) {   // wave-uniform: the tile crosses the diagonal of some query
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -348,7 +378,7 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
         const float corr = __builtin_amdgcn_exp2f(m - mn);
         l *= corr;
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
           for (int e = 0; e < 16; ++e) ot[dt][e] *= corr;
         m = mn;
@@ -386,11 +416,12 @@ __global__ void __launch_bounds__(AT_THREADS, 3) attn_fwd_mfma(const bf16* __res
 }
 
 // ---- backward, dQ (also writes D = rowsum(dO * O)) --------------------------------------------------------------
+template <int DH>
 __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                                   const bf16* __restrict__ d_o,
                                                                   const float* __restrict__ lse, bf16* __restrict__ dqkv,
                                                                   float* __restrict__ dsum, float* __restrict__ colsum, int S, int H, int single) {
-  constexpr int NS = DQ_STAGES;
+  constexpr int NS = DQ_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   __shared__ float cs_red[4][DH];
   extern __shared__ __attribute__((aligned(16))) char dq_smem[];   // [stage][K | V]
   char (*smem)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(dq_smem);
@@ -405,7 +436,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
   const FragOff fo = frag_offsets(lane);
   const TrOff to = tr_offsets(lane);
   const uint32_t smem_addr = (uint32_t)(uintptr_t)dq_smem;
-  const StageLoader L = make_loader(ld, ld, wave, lane);
+  const StageLoader<DH> L = make_loader<DH>(ld, ld, wave, lane);
   const bf16* const ktile = base + A;
   const bf16* const vtile = base + 2 * A;
   const int nqb = (S + 127) / 128;
@@ -417,10 +448,10 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
   }
   const int q0 = qb * 128, qw0 = q0 + 32 * wave, q = qw0 + r;
 
-  uint4 qf[4], gf[4];
+  uint4 qf[KS], gf[KS];
   float D = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
+  for (int ks = 0; ks < KS; ++ks) {
     const int c = 8 * (2 * ks + h);
     if (q < S) {
       qf[ks] = *reinterpret_cast<const uint4*>(base + (long)q * ld + c);
@@ -447,16 +478,17 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
 
   const int kv_end = min(S, q0 + 128);
   const int ntiles = (kv_end + 63) / 64;
-  f32x16 dqt[2];
-  zero(dqt[0]); zero(dqt[1]);
-  const float sc = 0.125f * LOG2E;
+  f32x16 dqt[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) zero(dqt[dt]);
+  const float sc = score_scale<DH>() * LOG2E;
 
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < ntiles) issue_stage(L, ktile, vtile, s * 64, S, ld, ld, wave, lane, smem_addr + s * 2 * TILE_BYTES);
   int cur = 0;
   for (int kt = 0; kt < ntiles; ++kt, cur = cur + 1 == NS ? 0 : cur + 1) {
-    wait_stages_but<4>(min(NS - 2, ntiles - 1 - kt));
+    wait_stages_but<LPW>(min(NS - 2, ntiles - 1 - kt));
     __syncthreads();   // tile kt is in LDS; nobody still reads the stage of tile kt - 1, which is refilled now
     if (kt + NS - 1 < ntiles)
       issue_stage(L, ktile, vtile, (kt + NS - 1) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
@@ -467,11 +499,11 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
       f32x16 st[2], dp[2];
       zero(st[0]); zero(st[1]); zero(dp[0]); zero(dp[1]);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-          st[t] = mfma16(ld16(k_ + fo.b[ks] + 4096 * t), qf[ks], st[t]);
-          dp[t] = mfma16(ld16(v_ + fo.b[ks] + 4096 * t), gf[ks], dp[t]);
+          st[t] = mfma16(row_frag(k_, fo, ks, t), qf[ks], st[t]);
+          dp[t] = mfma16(row_frag(v_, fo, ks, t), gf[ks], dp[t]);
         }
       // dS^T without the 1/sqrt(d_head) factor (applied once when dQ is stored)
 #pragma unroll
@@ -486,23 +518,25 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
           for (int e = 0; e < 16; ++e)
             if (kv0 + 32 * t + acc_row(e, lane) > q) st[t][e] = 0.f;
       }
-      mma_transposed(dqt, k_, to, st);
+      mma_transposed<DT, 2>(dqt, k_, to, st, 0);
     }
   }
-  if (q < S) store_transposed_out(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, h, 0.125f);
+  if (q < S) store_transposed_out(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, h, score_scale<DH>());
   // one row of partial column sums per (document, query block): [b * nqb + qb][3 A], this head's 64 dQ columns
-  if (colsum) block_column_sums(dqt, 0.125f, q < S, cs_red, colsum + ((long)b * nqb + qb) * ld + hd * DH, wave, lane);
+  if (colsum) block_column_sums(dqt, score_scale<DH>(), q < S, cs_red, colsum + ((long)b * nqb + qb) * ld + hd * DH, wave, lane);
   }
 }
 
 // ---- backward, dK and dV ------------------------------------------------------------------------------------------
-constexpr int DKV_STAGE = 2 * TILE_BYTES + 2 * 64 * (int)sizeof(float);   // Q | dO | -lse2 | D
+template <int DH> constexpr int dkv_stage() { return 2 * tile_bytes<DH>() + 2 * 64 * (int)sizeof(float); }   // Q | dO | -lse2 | D
 
+template <int DH>
 __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
                                                                    const bf16* __restrict__ d_o,
                                                                    const float* __restrict__ dsum,
                                                                    bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H, int single) {
-  constexpr int NS = DKV_STAGES;
+  constexpr int NS = DKV_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
+  constexpr int DKV_STAGE = dkv_stage<DH>();
   __shared__ float cs_red[4][DH];
   extern __shared__ __attribute__((aligned(16))) char dkv_smem[];   // NS stages of DKV_STAGE bytes
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -514,8 +548,8 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
   const long ld = 3L * A;
   const bf16* base = qkv + (long)b * S * ld + hd * DH;
   const bf16* gbase = d_o + (long)b * S * A + hd * DH;
-  const FragOff fo = frag_offsets(lane);
-  const TrOff to = tr_offsets(lane);
+  FragOff fo = frag_offsets(lane);
+  TrOff to = tr_offsets(lane);
   const uint32_t smem_addr = (uint32_t)(uintptr_t)dkv_smem;
   const int nkb = (S + 127) / 128;
   const int ntiles = (S + 63) / 64;
@@ -525,7 +559,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
   const long Sp = (long)nkb * 128;
   const float* stat_src = dsum + ((wave & 1) ? 0 : (long)n_bh * Sp) + bh * Sp + lane;
   const uint32_t stat_dst = 2 * TILE_BYTES + ((wave & 1) ? 256 : 0);
-  const StageLoader L = make_loader(ld, A, wave, lane);
+  const StageLoader<DH> L = make_loader<DH>(ld, A, wave, lane);
   auto issue = [&](int qt, int stage) {
     issue_stage(L, base, gbase, qt * 64, S, ld, A, wave, lane, smem_addr + stage * DKV_STAGE);
     load4_to_lds(stat_src + qt * 64, smem_addr + stage * DKV_STAGE + stat_dst);
@@ -538,16 +572,17 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
   }
   const int k0 = kb * 128, kw0 = k0 + 32 * wave, key = kw0 + r;
 
-  uint4 kf[4], vf[4];
+  uint4 kf[KS], vf[KS];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
+  for (int ks = 0; ks < KS; ++ks) {
     const int c = 8 * (2 * ks + h);
     kf[ks] = key < S ? *reinterpret_cast<const uint4*>(base + (long)key * ld + A + c) : make_uint4(0, 0, 0, 0);
     vf[ks] = key < S ? *reinterpret_cast<const uint4*>(base + (long)key * ld + 2 * A + c) : make_uint4(0, 0, 0, 0);
   }
-  f32x16 dkt[2], dvt[2];
-  zero(dkt[0]); zero(dkt[1]); zero(dvt[0]); zero(dvt[1]);
-  const float sc = 0.125f * LOG2E;
+  f32x16 dkt[DT], dvt[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) { zero(dkt[dt]); zero(dvt[dt]); }
+  const float sc = score_scale<DH>() * LOG2E;
 
   const int first = k0 / 64;               // first query tile that can see a key of this block
 #pragma unroll
@@ -555,7 +590,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
     if (first + s < ntiles) issue(first + s, s);
   int cur = 0;
   for (int qt = first; qt < ntiles; ++qt, cur = cur + 1 == NS ? 0 : cur + 1) {
-    wait_stages_but<5>(min(NS - 2, ntiles - 1 - qt));
+    wait_stages_but<LPW + 1>(min(NS - 2, ntiles - 1 - qt));
     __syncthreads();
     if (qt + NS - 1 < ntiles) issue(qt + NS - 1, cur == 0 ? NS - 1 : cur - 1);
     const int q0 = qt * 64;
@@ -564,50 +599,60 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
       const char* g_ = q_ + TILE_BYTES;
       const float* nlse2s = reinterpret_cast<const float*>(q_ + 2 * TILE_BYTES);
       const float* Ds = nlse2s + 64;
-      f32x16 st[2], dp[2];
-      zero(st[0]); zero(st[1]); zero(dp[0]); zero(dp[1]);
+      // TG blocks of 32 queries at a time: with head size 128 the two accumulators and the K / V fragments leave room
+      // for one
+      constexpr int TG = DH == 128 ? 1 : 2;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int t0 = 0; t0 < 2; t0 += TG) {
+        if constexpr (TG == 1) rederive_offsets(fo, to);
+        f32x16 st[TG], dp[TG];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          st[t] = mfma16(ld16(q_ + fo.b[ks] + 4096 * t), kf[ks], st[t]);
-          dp[t] = mfma16(ld16(g_ + fo.b[ks] + 4096 * t), vf[ks], dp[t]);
-        }
-      // accumulator elements 4g..4g+3 are queries 32t + 8g + 4h + (0..3): their statistics are 16 contiguous bytes
+        for (int t = 0; t < TG; ++t) { zero(st[t]); zero(dp[t]); }
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 Lq = *reinterpret_cast<const float4*>(nlse2s + 32 * t + 8 * g + 4 * h);
-          const float4 Dv = *reinterpret_cast<const float4*>(Ds + 32 * t + 8 * g + 4 * h);
-          const float Ls[4] = {Lq.x, Lq.y, Lq.z, Lq.w}, Dd[4] = {Dv.x, Dv.y, Dv.z, Dv.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int e = 4 * g + i;
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[t][e], sc, Ls[i]));
-            st[t][e] = p;
-            dp[t][e] = p * (dp[t][e] - Dd[i]);   // dS without 1/sqrt(d_head) (applied when dK is stored)
+          for (int t = 0; t < TG; ++t) {
+            st[t] = mfma16(row_frag(q_, fo, ks, t0 + t), kf[ks], st[t]);
+            dp[t] = mfma16(row_frag(g_, fo, ks, t0 + t), vf[ks], dp[t]);
           }
+        // accumulator elements 4g..4g+3 are queries 32t + 8g + 4h + (0..3): their statistics are 16 contiguous bytes
+#pragma unroll
+        for (int t = 0; t < TG; ++t)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const float4 Lq = *reinterpret_cast<const float4*>(nlse2s + 32 * (t0 + t) + 8 * g + 4 * h);
+            const float4 Dv = *reinterpret_cast<const float4*>(Ds + 32 * (t0 + t) + 8 * g + 4 * h);
+            const float Ls[4] = {Lq.x, Lq.y, Lq.z, Lq.w}, Dd[4] = {Dv.x, Dv.y, Dv.z, Dv.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int e = 4 * g + i;
+              const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[t][e], sc, Ls[i]));
+              st[t][e] = p;
+              dp[t][e] = p * (dp[t][e] - Dd[i]);   // dS without 1/sqrt(d_head) (applied when dK is stored)
+            }
+          }
+        if (q0 < kw0 + 31) {   // wave-uniform: the tile crosses the diagonal of some key
+#pragma unroll
+          for (int t = 0; t < TG; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (q0 + 32 * (t0 + t) + acc_row(e, lane) < key) { st[t][e] = 0.f; dp[t][e] = 0.f; }
         }
-      if (q0 < kw0 + 31) {   // wave-uniform: the tile crosses the diagonal of some key
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (q0 + 32 * t + acc_row(e, lane) < key) { st[t][e] = 0.f; dp[t][e] = 0.f; }
+        mma_transposed<DT, TG>(dvt, g_, to, st, t0);
+        mma_transposed<DT, TG>(dkt, q_, to, dp, t0);
       }
-      mma_transposed(dvt, g_, to, st);
-      mma_transposed(dkt, q_, to, dp);
     }
   }
-  if (key < S) {
-    bf16* out = dqkv + ((long)b * S + key) * ld + hd * DH;
-    store_transposed_out(out + A, dkt, h, 0.125f);
+  int key_out = key;   // as in the forward kernel: output addresses are formed behind the loop
+  asm volatile("" : "+v"(key_out));
+  if (key_out < S) {
+    bf16* out = dqkv + ((long)b * S + key_out) * ld + hd * DH;
+    store_transposed_out(out + A, dkt, h, score_scale<DH>());
     store_transposed_out(out + 2 * A, dvt, h, 1.0f);
   }
   if (colsum) {
     float* cs = colsum + ((long)b * nkb + kb) * ld + hd * DH;
-    block_column_sums(dkt, 0.125f, key < S, cs_red, cs + A, wave, lane);
+    block_column_sums(dkt, score_scale<DH>(), key < S, cs_red, cs + A, wave, lane);
     block_column_sums(dvt, 1.0f, key < S, cs_red, cs + 2 * A, wave, lane);
   }
   }
@@ -618,32 +663,50 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* _
 std::atomic<int> g_attn_single_block{1};   // test / tuning hook; measured 3-5 % faster than pairing a long with a short block
 void set_attention_single_block(int on) { g_attn_single_block = on ? 1 : 0; }
 
-dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, hipStream_t s) {
+namespace {
+template <int DH>
+dipaco_status fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, hipStream_t s) {
   const int single = g_attn_single_block;
   const int nqb = (S + 127) / 128;
   dim3 grid = single ? dim3(B * H, nqb) : dim3((nqb + 1) / 2, B * H);   // one or two query blocks per workgroup
-  attn_fwd_mfma<<<grid, AT_THREADS, 0, s>>>(qkv, o, lse, S, H, single);
+  attn_fwd_mfma<DH><<<grid, AT_THREADS, 0, s>>>(qkv, o, lse, S, H, single);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
 
-size_t attention_colsum_partial_floats(int B, int S, int H) { return (size_t)B * ((S + 127) / 128) * 3 * H * DH; }
-
-dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv,
-                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H,
-                                        hipStream_t s, SumBatch* batch) {
+template <int DH>
+dipaco_status bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv, float* dsum,
+                       float* colsum_out, float* colsum_partial, int B, int S, int H, hipStream_t s, SumBatch* batch) {
+  constexpr int DQ_LDS = DQ_STAGES * 2 * tile_bytes<DH>(), DKV_LDS = DKV_STAGES * dkv_stage<DH>();
   const int single = g_attn_single_block;
   const int nqb = (S + 127) / 128;
   dim3 grid = single ? dim3(B * H, nqb) : dim3((nqb + 1) / 2, B * H);   // one or two query (key) blocks per workgroup
   static std::atomic<unsigned long long> dq_lds{0}, dkv_lds{0};
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_mfma), DQ_STAGES * 2 * TILE_BYTES, dq_lds)) return st;
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_mfma), DKV_STAGES * DKV_STAGE, dkv_lds)) return st;
-  attn_bwd_dq_mfma<<<grid, AT_THREADS, DQ_STAGES * 2 * TILE_BYTES, s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum_out ? colsum_partial : nullptr, S, H, single);
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH>), DQ_LDS, dq_lds)) return st;
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH>), DKV_LDS, dkv_lds)) return st;
+  attn_bwd_dq_mfma<DH><<<grid, AT_THREADS, DQ_LDS, s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum_out ? colsum_partial : nullptr, S, H, single);
   DIPACO_LAUNCH_CHECK();
-  attn_bwd_dkv_mfma<<<grid, AT_THREADS, DKV_STAGES * DKV_STAGE, s>>>(qkv, d_o, dsum, dqkv, colsum_out ? colsum_partial : nullptr, S, H, single);
+  attn_bwd_dkv_mfma<DH><<<grid, AT_THREADS, DKV_LDS, s>>>(qkv, d_o, dsum, dqkv, colsum_out ? colsum_partial : nullptr, S, H, single);
   DIPACO_LAUNCH_CHECK();
   if (colsum_out) return launch_sum_rows(colsum_partial, colsum_out, B * nqb, 3 * H * DH, s, batch);
   return DIPACO_OK;
+}
+}  // namespace
+
+dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, int dh, hipStream_t s) {
+  if (dh == 32) return fwd_mfma<32>(qkv, o, lse, B, S, H, s);
+  if (dh == 64) return fwd_mfma<64>(qkv, o, lse, B, S, H, s);
+  if (dh == 128) return fwd_mfma<128>(qkv, o, lse, B, S, H, s);
+  return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
+}
+
+dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv,
+                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
+                                        hipStream_t s, SumBatch* batch) {
+  if (dh == 32) return bwd_mfma<32>(qkv, o, d_o, lse, dqkv, dsum, colsum_out, colsum_partial, B, S, H, s, batch);
+  if (dh == 64) return bwd_mfma<64>(qkv, o, d_o, lse, dqkv, dsum, colsum_out, colsum_partial, B, S, H, s, batch);
+  if (dh == 128) return bwd_mfma<128>(qkv, o, d_o, lse, dqkv, dsum, colsum_out, colsum_partial, B, S, H, s, batch);
+  return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
 }
 
 }  // namespace dipaco

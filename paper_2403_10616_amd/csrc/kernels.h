@@ -172,8 +172,7 @@ dipaco_status flush_sum_batch(SumBatch& batch, hipStream_t s);
 dipaco_status launch_sum_rows(const float* partial, float* out, int n_partials, int cols, hipStream_t s,
                               SumBatch* batch = nullptr);
 // out[n] = sum_m x[m,n] (fp32, fixed order);  partial: colsum_partial_floats scratch
-template <typename T>
-dipaco_status launch_colsum(const T* x, float* out, float* partial, int rows, int cols, hipStream_t s);
+dipaco_status launch_colsum(const float* x, float* out, float* partial, int rows, int cols, hipStream_t s);
 size_t colsum_partial_floats(int rows, int cols);
 // out[b, :] (fp32) = mean over positions of x[b*S + p, :]
 template <typename T> dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipStream_t s);
@@ -212,15 +211,19 @@ constexpr int ISSUE_PROBE_BLOCKS = 256;   // one workgroup per compute unit
 // out: ISSUE_PROBE_BLOCKS * 256 * waves_per_simd floats
 dipaco_status launch_issue_probe(int mode, int waves_per_simd, int iters, float* out, hipStream_t s);
 
-// ---- attention_mfma.hip: bf16, head size 64, matrix cores ---------------------------------------------
-dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, hipStream_t s);
-// colsum_out (nullable): fp32 [3 H 64], the column sums of dqkv (the bias gradient of the QKV projection), from the
-// kernels' epilogues; colsum_partial: attention_colsum_partial_floats(B, S, H) floats of scratch
+// ---- attention_mfma.hip: bf16, matrix cores ------------------------------------------------------------
+dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, int dh, hipStream_t s);
+// colsum_out (nullable): fp32 [3 H dh], the column sums of dqkv (the bias gradient of the QKV projection), from the
+// kernels' epilogues; colsum_partial: attention_bwd_colsum_floats(B, S, H, dh) floats of scratch
 dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv,
-                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H,
+                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
                                         hipStream_t s, SumBatch* batch = nullptr);
-size_t attention_colsum_partial_floats(int B, int S, int H);
-// 0: a workgroup takes a long and a short block of the causal triangle; 1: one block per workgroup, longest first
+// ---- attention_f32.hip: fp32, matrix cores; arguments as above -------------------------------------------
+dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, int B, int S, int H, int dh, hipStream_t s);
+dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv,
+                                       float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
+                                       hipStream_t s, SumBatch* batch = nullptr);
+// bf16 kernels: 0: a workgroup takes a long and a short block of the causal triangle; 1: one block per workgroup, longest first
 void set_attention_single_block(int on);
 
 }  // namespace dipaco

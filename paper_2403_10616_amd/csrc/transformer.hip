@@ -325,10 +325,9 @@ __global__ void __launch_bounds__(SP_COLS * SP_PHASES) sum_partials_batch_kernel
 
 // ---- column sums -----------------------------------------------------------------------------------------
 constexpr int CS_ROWS = 256;   // rows per workgroup
-template <typename T>
-__global__ void __launch_bounds__(ROW_THREADS) colsum_kernel(const T* __restrict__ x, float* __restrict__ partial,
+__global__ void __launch_bounds__(ROW_THREADS) colsum_kernel(const float* __restrict__ x, float* __restrict__ partial,
                                                              int rows, int cols) {
-  constexpr int VEC = Vec16<T>::N;
+  constexpr int VEC = Vec16<float>::N;
   // workgroup: 64 column chunks (16 B each) x 4 row phases
   __shared__ float red[ROWS_PER_BLOCK][WAVE * VEC];
   const int lane = threadIdx.x & 63, phase = threadIdx.x >> 6;
@@ -707,12 +706,11 @@ dipaco_status flush_sum_batch(SumBatch& batch, hipStream_t s) {
 
 size_t colsum_partial_floats(int rows, int cols) { return (size_t)((rows + CS_ROWS - 1) / CS_ROWS) * cols; }
 
-template <typename T>
-dipaco_status launch_colsum(const T* x, float* out, float* partial, int rows, int cols, hipStream_t s) {
-  constexpr int VEC = Vec16<T>::N;
+dipaco_status launch_colsum(const float* x, float* out, float* partial, int rows, int cols, hipStream_t s) {
+  constexpr int VEC = Vec16<float>::N;
   const int chunks = (rows + CS_ROWS - 1) / CS_ROWS;
   dim3 grid((cols + WAVE * VEC - 1) / (WAVE * VEC), chunks);
-  colsum_kernel<T><<<grid, ROW_THREADS, 0, s>>>(x, partial, rows, cols);
+  colsum_kernel<<<grid, ROW_THREADS, 0, s>>>(x, partial, rows, cols);
   DIPACO_LAUNCH_CHECK();
   sum_partials_kernel<<<(cols + SP_COLS - 1) / SP_COLS, SP_COLS * SP_PHASES, 0, s>>>(partial, out, out, nullptr, chunks, cols, cols);
   DIPACO_LAUNCH_CHECK();
@@ -824,7 +822,6 @@ dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipS
   template dipaco_status launch_layernorm_bwd<T>(const T*, const T*, const T*, const float*, const float*, const T*, \
                                                  T*, float*, float*, float*, float*, int, int, hipStream_t,         \
                                                  SumBatch*);                                                        \
-  template dipaco_status launch_colsum<T>(const T*, float*, float*, int, int, hipStream_t);                          \
   template dipaco_status launch_mean_pool<T>(const T*, float*, int, int, int, hipStream_t);                          \
   template dipaco_status launch_softmax_xent<T>(T*, const int*, const int*, float*, int, int, bool, hipStream_t);          \
   template dipaco_status launch_embed_bwd<T>(const T*, const int*, float*, float*, int*, int, int, int, int, int,    \

@@ -213,6 +213,16 @@ def test_attention_forward_backward(dtype, B, S, H, dh, attn_blocks):
     assert torch.equal(dqkv2, dqkv)
 
 
+@pytest.mark.parametrize("dtype", [dp.F32, dp.BF16])
+@pytest.mark.parametrize("B,S,H,dh", [(1, 1, 1, 32), (2, 31, 3, 32), (1, 129, 2, 32), (1, 515, 1, 32), (1, 1, 1, 128),
+                                      (2, 33, 1, 128), (1, 64, 2, 128), (1, 127, 1, 128), (2, 256, 2, 128),
+                                      (1, 515, 3, 128), (3, 17, 1, 64), (1, 96, 5, 64)])
+def test_attention_head_sizes_at_tile_edges(dtype, B, S, H, dh):
+    """Head sizes 32 (half a panel) and 128 (two panels; one 32-query block at a time in dK/dV) and the fp32 kernels'
+    16-row waves: one position, one row past a wave / tile / block, several blocks with a ragged last one."""
+    test_attention_forward_backward(dtype, B, S, H, dh, 1)
+
+
 # ---- the benchmarked kernels at the step's own shapes, element by element ---------------------------------------
 def _bf16_ulp(x):
     """Spacing of bf16 numbers at |x| (8 significant bits)."""
