@@ -45,15 +45,9 @@ constexpr int DL_BK_MIN = 32;                               // K tiles are 32 or
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s* lds_v4s_ptr;
 
-__device__ __forceinline__ void load16_to_lds(const bf16* gptr, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
-}
 // the same with a wave-uniform base address (scalar registers) and a 32-bit per-lane byte offset
 __device__ __forceinline__ void load16_to_lds_at(const char* base, uint32_t byte_off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vmcnt() {   // vmcnt only: expcnt and lgkmcnt fields at maximum
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // Load plan of one wave: wave-level load j of a stage fills LDS bytes [1024 j, 1024 j + 1024) of it; j < NLA: A tile, else

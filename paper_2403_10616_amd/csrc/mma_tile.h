@@ -29,6 +29,15 @@ namespace dipaco {
 constexpr int TILE_ROW_BYTES = 128;
 constexpr int GEMM_THREADS = 256;
 
+// Global memory straight into LDS: lane l of the wave fetches 16 bytes at gptr into LDS bytes [lds_addr + 16 l, + 16).
+// Counted in vmcnt; the wave waits for it with wait_vmcnt (other waves' reads also need the barrier behind that).
+template <typename T> __device__ __forceinline__ void load16_to_lds(const T* gptr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vmcnt() {   // vmcnt only: expcnt and lgkmcnt fields at maximum
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
 template <typename T> struct MmaTraits;
 template <> struct MmaTraits<bf16> { static constexpr int VEC = 8; static constexpr int BK = 64; };
 template <> struct MmaTraits<float> { static constexpr int VEC = 4; static constexpr int BK = 32; };

@@ -280,6 +280,203 @@ __global__ void __launch_bounds__(R_THREADS) route_kernel(const float* __restric
   }
 }
 
+// ---- few points, or few centroids ----------------------------------------------------------------------------
+// A workgroup of route_kernel owns 256 points and multiplies them with 256 centroids at a time: a batch of N points runs
+// on N / 256 compute units and takes the time of one workgroup, a serial walk over 256 D, however small it is, and fewer
+// than 256 centroids are padded.  Here a wave owns 16 PT points and 32 centroids of a sweep (v_mfma_f32_16x16x4_f32): wc
+// waves of a workgroup take different centroids, 8 / wc different points.  A wave stages its own operand rows, K tiles of
+// 32 in a ring of ST stages, straight into LDS: a lane-to-row assignment in which eight adjacent lanes read one 128-byte
+// line (fragments fetched directly would touch 16 lines per 16 lanes: measured 44 us against 25 at 100 x 896 x 256).
+// Nothing is shared between waves before the end, so there is no barrier in the loop.  The product is computed transposed
+// (centroids are the rows of the accumulator), so a lane holds scores of one point for ascending centroids and folds
+// them into its running entry without a merge.
+constexpr int RS_WAVES = 8;
+constexpr int RS_LDS_HIST = 256;
+template <int PT> struct RouteSmall {
+  static constexpr int ST = PT == 1 ? 3 : 2;                  // 144 KB / 128 KB of LDS
+  static constexpr int STAGE = (32 + 16 * PT) * TILE_ROW_BYTES;
+  static constexpr int LOADS = STAGE / 1024;                  // wave-level loads per stage
+  static constexpr int LDS = RS_WAVES * ST * STAGE;
+};
+
+// Bounds: point and centroid rows are clamped to the last valid one (their scores are dropped, or +inf); K indices
+// beyond D read the last four elements and are zeroed on both sides when they are used.
+template <bool TOP2, int PT>
+__global__ void __launch_bounds__(RS_WAVES * WAVE) route_small_kernel(const float* __restrict__ z, long ldz,
+                                                                      const float* __restrict__ c,
+                                                                      const float* __restrict__ lin_bias, long N, int D,
+                                                                      int K, int wc, int* __restrict__ idx,
+                                                                      unsigned long long* __restrict__ hist,
+                                                                      float* __restrict__ margin) {
+  using P = RouteSmall<PT>;
+  constexpr int PTS = 16 * PT, ST = P::ST, STAGE = P::STAGE, LOADS = P::LOADS;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ float red_s1[RS_WAVES][PTS], red_s2[RS_WAVES][PTS];
+  __shared__ int red_i1[RS_WAVES][PTS], red_i2[RS_WAVES][PTS];
+  __shared__ unsigned int lhist[RS_LDS_HIST];
+  const bool use_lhist = K <= RS_LDS_HIST;   // more centroids: a workgroup's few points go to the global counts directly
+  if (use_lhist && threadIdx.x < RS_LDS_HIST) lhist[threadIdx.x] = 0;   // its first use is behind the barrier below
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kg = lane >> 4;
+  const int wk = wave & (wc - 1), wp = wave / wc;              // wc is a power of two
+  const long m0 = ((long)blockIdx.x * (RS_WAVES / wc) + wp) * PTS;
+  const int rows_left = (int)max(0L, min((long)PTS, N - m0));   // wave-uniform
+  const float dot_mul = lin_bias ? 1.0f : 2.0f;
+
+  Best run[PT];
+#pragma unroll
+  for (int p = 0; p < PT; ++p) { run[p].s1 = INFINITY; run[p].i1 = NO_INDEX; run[p].s2 = INFINITY; run[p].i2 = NO_INDEX; }
+
+  // load i of a stage covers tile rows 8 i .. 8 i + 7 (rows 0..31 centroids, then the points), lane l chunk l & 7 of row
+  // l >> 3 at chunk position (l & 7): the swizzle is applied by choosing which chunk that is
+  char* const ring = smem + wave * ST * STAGE;
+  const uint32_t ring_addr = (uint32_t)(uintptr_t)ring;
+  const int nst = (D + RBK - 1) / RBK;
+  const int lrow = lane >> 3;
+  for (int c0 = 32 * wk; rows_left > 0 && c0 < K; c0 += 32 * wc) {   // wave-uniform
+    const float* src[LOADS];
+    int chunk[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int row = 8 * i + lrow;
+      src[i] = row < 32 ? c + (long)min(c0 + row, K - 1) * D : z + (m0 + min(row - 32, rows_left - 1)) * ldz;
+      chunk[i] = 4 * ((lane & 7) ^ swz(row));
+    }
+    auto issue = [&](int kt, int stage) {
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i)
+        load16_to_lds(src[i] + min(kt * RBK + chunk[i], D - 4), ring_addr + stage * STAGE + i * 1024);
+    };
+    f32x4 acc[2][PT];
+    float nrm[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int p = 0; p < PT; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][p][e] = 0.f;
+
+#pragma unroll
+    for (int s = 0; s < ST; ++s)
+      if (s < nst) issue(s, s);
+    int stage = 0;
+    for (int kt = 0; kt < nst; ++kt) {
+      // own loads of tile kt have landed: all but those of the tiles behind it
+      const int behind = min(ST - 1, nst - 1 - kt);
+      if (ST > 2 && behind == 2) wait_vmcnt<2 * LOADS>();
+      else if (behind == 1) wait_vmcnt<LOADS>();
+      else wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      char* const tile = ring + stage * STAGE;
+      float4 fc[2][2], fz[2][PT];   // [16-deep half][row tile]
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fc[h][j] = *reinterpret_cast<const float4*>(tile_chunk(tile, 16 * j + r, 4 * h + kg));
+#pragma unroll
+        for (int p = 0; p < PT; ++p) fz[h][p] = *reinterpret_cast<const float4*>(tile_chunk(tile, 32 + 16 * p + r, 4 * h + kg));
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments are in registers: the stage may be refilled
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + ST < nst) issue(kt + ST, stage);
+      stage = stage + 1 == ST ? 0 : stage + 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (kt * RBK + 16 * h + 4 * kg >= D) {   // only in the last tile
+#pragma unroll
+          for (int j = 0; j < 2; ++j) fc[h][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int p = 0; p < PT; ++p) fz[h][p] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float4 v = fc[h][j];
+          nrm[j] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)   // the same K on both operands; 2 PT independent accumulators in turn
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int p = 0; p < PT; ++p)
+              acc[j][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fc[h][j])[q],
+                                                               reinterpret_cast<const float*>(&fz[h][p])[q], acc[j][p], 0, 0, 0);
+      }
+    }
+
+    // ||c||^2 of centroid row r of a tile: summed over the four lane groups, then handed to the lanes that hold the row
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      nrm[j] += __shfl_xor(nrm[j], 16, WAVE);
+      nrm[j] += __shfl_xor(nrm[j], 32, WAVE);
+      const int mine = c0 + 16 * j + r;
+      const float cn = mine < K ? (lin_bias ? -lin_bias[mine] : nrm[j]) : INFINITY;   // beyond K: never enters an entry
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 4 * kg + e;
+        const float cne = __shfl(cn, row, WAVE);
+#pragma unroll
+        for (int p = 0; p < PT; ++p)
+          best_push_ascending<TOP2>(run[p], __builtin_fmaf(-dot_mul, acc[j][p][e], cne), c0 + 16 * j + row);
+      }
+    }
+  }
+
+  // the four lane groups of a point, then the wc waves that share its points (disjoint centroids: a selection in the (score, index) order)
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+#pragma unroll
+    for (int m = 16; m < WAVE; m <<= 1) {
+      Best o;
+      o.s1 = __shfl_xor(run[p].s1, m, WAVE); o.i1 = __shfl_xor(run[p].i1, m, WAVE); o.s2 = __shfl_xor(run[p].s2, m, WAVE);
+      o.i2 = TOP2 ? __shfl_xor(run[p].i2, m, WAVE) : NO_INDEX;
+      run[p] = best_merge<TOP2>(run[p], o);
+    }
+    if (lane < 16) {
+      red_s1[wave][16 * p + r] = run[p].s1; red_s2[wave][16 * p + r] = run[p].s2;
+      red_i1[wave][16 * p + r] = run[p].i1; red_i2[wave][16 * p + r] = run[p].i2;
+    }
+  }
+  __syncthreads();
+  const bool on = wk == 0 && lane < rows_left;
+  Best b;
+  b.i1 = -1; b.i2 = -1;
+  if (on) {
+    b.s1 = red_s1[wave][lane]; b.i1 = red_i1[wave][lane]; b.s2 = red_s2[wave][lane]; b.i2 = red_i2[wave][lane];
+    for (int w = wave + 1; w < wave + wc; ++w) {
+      Best o;
+      o.s1 = red_s1[w][lane]; o.i1 = red_i1[w][lane]; o.s2 = red_s2[w][lane]; o.i2 = red_i2[w][lane];
+      b = best_merge<TOP2>(b, o);
+    }
+    if (b.i1 == NO_INDEX) {   // no score below +inf (NaN or infinite features): as in route_kernel
+      b.i1 = 0;
+      b.i2 = K > 1 ? 1 : NO_INDEX;
+      b.s1 = b.s2 = __builtin_nanf("");
+    }
+    if (TOP2) {
+      if (b.i2 == NO_INDEX) b.i2 = -1;
+      idx[2 * (m0 + lane)] = b.i1;
+      idx[2 * (m0 + lane) + 1] = b.i2;
+    } else {
+      idx[m0 + lane] = b.i1;
+    }
+    if (margin) margin[m0 + lane] = b.s2 - b.s1;
+  }
+  if (on) {
+    if (use_lhist) {
+      atomicAdd(&lhist[b.i1], 1u);
+      if (TOP2 && b.i2 >= 0) atomicAdd(&lhist[b.i2], 1u);
+    } else {
+      atomicAdd(&hist[b.i1], 1ull);
+      if (TOP2 && b.i2 >= 0) atomicAdd(&hist[b.i2], 1ull);
+    }
+  }
+  if (use_lhist) {
+    __syncthreads();
+    if (tid < K && lhist[tid]) atomicAdd(&hist[tid], (unsigned long long)lhist[tid]);
+  }
+}
+
 // ---- K-class logistic regression: per-row softmax cross-entropy --------------------------------------------------
 // One wave per row of logits [rows, K] (K a multiple of 4, at most LOGIT_MAX_K): nll[row] = logsumexp - logit[label],
 // and in place logits <- (softmax - onehot(label)) * inv_n.  A row whose label is outside [0, K) gives 0 and zeros.
@@ -401,18 +598,50 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
   return DIPACO_OK;
 }
 
+// Waves of a small-kernel workgroup along the centroids: as many as there are groups of 32, so that none is idle.
+static int route_small_wc(int K) { return K > 128 ? 8 : K > 64 ? 4 : K > 32 ? 2 : 1; }
+
+// 1 / 2: route_small_kernel with 16 / 32 points per wave, 0: route_kernel.  All take time in whole rounds over the 256
+// compute units, one workgroup each, proportional to D.  Measured at D = 896: a round of route_kernel (65536 points x 256
+// centroids) 230 us, of the small kernel with 32 points per wave (2048 wave tasks) 43 us, with 16 points 28 us.  So the 16-point form
+// is taken where one round of it holds everything (100 x 256: 228 -> 25 us), else the cheaper of the other two (32768 x 896 x 256:
+// 239 -> 176; 65536: 252 against 337, kept; 300000 x 768 x 16: 1001 -> 202; x 100: 1001 -> 663).
+static int route_pick(int64_t N, int K) {
+  const int64_t wc = route_small_wc(K), sweeps = (K + 32 * wc - 1) / (32 * wc), tasks = 256 * RS_WAVES;
+  if ((N + 15) / 16 * wc <= tasks) return 1;
+  const int64_t small = 43 * (((N + 31) / 32 * wc + tasks - 1) / tasks) * sweeps;
+  const int64_t big = 230 * ((N + 256 * RBM - 1) / (256 * RBM)) * ((K + RBN - 1) / RBN);
+  return small < big ? 2 : 0;
+}
+
 dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const float* lin_bias, int64_t N, int D, int K,
                            int n_best, int* idx, long long* hist, float* margin, hipStream_t s) {
   dipaco_status st = launch_fill_i64(hist, 0, (size_t)K, s);
   if (st != DIPACO_OK) return st;
   if (N == 0) return DIPACO_OK;
+  auto* h = reinterpret_cast<unsigned long long*>(hist);
+  const int wc = route_small_wc(K);
+  auto small = [&](auto PTC) -> dipaco_status {
+    constexpr int PT = decltype(PTC)::value, LDS = RouteSmall<PT>::LDS;
+    static std::atomic<unsigned long long> set_one{0}, set_two{0};
+    if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_small_kernel<false, PT>), LDS, set_one)) return e;
+    if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_small_kernel<true, PT>), LDS, set_two)) return e;
+    const int64_t pts = 16 * PT * (RS_WAVES / wc), nb = (N + pts - 1) / pts;
+    if (nb > 0x7fffffffLL) return fail(DIPACO_ESHAPE, "route: N too large");
+    if (n_best == 2) route_small_kernel<true, PT><<<(unsigned)nb, RS_WAVES * WAVE, LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, wc, idx, h, margin);
+    else route_small_kernel<false, PT><<<(unsigned)nb, RS_WAVES * WAVE, LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, wc, idx, h, margin);
+    DIPACO_LAUNCH_CHECK();
+    return DIPACO_OK;
+  };
+  const int pick = route_pick(N, K);
+  if (pick == 1) return small(std::integral_constant<int, 1>{});
+  if (pick == 2) return small(std::integral_constant<int, 2>{});
   constexpr size_t smem = 2 * (size_t)R_STAGE;
   static std::atomic<unsigned long long> lds_one{0}, lds_two{0};
   if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<false>), (int)smem, lds_one)) return e;
   if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<true>), (int)smem, lds_two)) return e;
   const int64_t blocks = (N + RBM - 1) / RBM;
   if (blocks > 0x7fffffffLL) return fail(DIPACO_ESHAPE, "route: N too large");
-  auto* h = reinterpret_cast<unsigned long long*>(hist);
   if (n_best == 2) route_kernel<true><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
   else route_kernel<false><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
   DIPACO_LAUNCH_CHECK();

@@ -395,3 +395,31 @@ def test_rows_without_a_nearest_centroid_go_to_centroid_zero_with_nan_margin():
     assert np.array_equal(i2[bad], [[0, 1]] * 3) and np.all(np.isnan(host(m2)[bad]))
     assert np.array_equal(i2[good], o2[good]) and i2[256].min() >= 0 and i2[256].max() < 40
     assert np.array_equal(host(hist2), np.bincount(i2.ravel(), minlength=40)) and host(hist2).sum() == 1400
+
+
+@pytest.mark.parametrize("N,D,K,bias", [
+    (4096, 36, 256, False), (16, 4, 33, False), (1, 896, 129, True), (30000, 20, 32, False),      # 16 points per wave
+    (4097, 36, 256, False), (40001, 100, 20, False), (9000, 20, 65, True), (70000, 20, 257, False),   # 32 points per wave
+    (66000, 16, 256, False), (140000, 12, 250, True),                                              # 256 points per workgroup
+])
+def test_route_kernels_agree_with_fp64_on_both_sides_of_every_size_rule(N, D, K, bias):
+    """Integer points and centroids: every fp32 score is exact (|score| < 2^24), so indices, ties, counts and margins are."""
+    print(f"route rule N={N} D={D} K={K} bias={bias}", flush=True)
+    g = torch.Generator().manual_seed(N + K)
+    z = torch.randint(-3, 4, (N, D), generator=g).float().to(DEV)
+    c = torch.randint(-3, 4, (K, D), generator=g).float().to(DEV)
+    b = torch.randint(-5, 6, (K,), generator=g).float().to(DEV)
+    score = -(z.double() @ c.double().T + b.double()) if bias else (c.double() ** 2).sum(1) - 2 * z.double() @ c.double().T
+    order = torch.sort(score, dim=1, stable=True)
+    for n_best in ((1,) if bias else (1, 2)):
+        idx = torch.full((N * n_best,), -9, dtype=torch.int32, device=DEV)
+        hist = torch.full((K,), -7, dtype=torch.int64, device=DEV)
+        margin = torch.zeros(N, device=DEV)
+        if bias:
+            dp.dipaco_route_linear(z, D, c, b, N, D, K, idx, hist, margin)
+        else:
+            dp.dipaco_route_prefix_top(z, D, c, N, D, K, n_best, idx, hist, margin)
+        want = order.indices[:, :n_best].reshape(-1)
+        assert torch.equal(idx.long(), want)
+        assert torch.equal(hist, torch.bincount(want, minlength=K))
+        assert torch.equal(margin.double(), order.values[:, 1] - order.values[:, 0])
