@@ -38,10 +38,10 @@ dipaco_status dipaco_k_gemm_colsum(int32_t dtype, int32_t trans_a, int32_t trans
                                    void* aux_out, const void* aux_in, int32_t act, float* colsum_out,
                                    float* colsum_scratch, void* stream);
 
-/* Force the GEMM workgroup tile for every later call in this process: 0 = automatic (default), 1 = 128x128,
- * 2 = 256x128, 3 = 256x256 with four waves, 4 = 256x256 with eight waves, 5 = the bf16 kernel that loads its
- * 256x256 tiles from global memory straight into LDS, for every shape it takes (K a multiple of 32, 16-byte rows;
- * other shapes and fp32 keep the automatic choice), 6 / 7 = the same kernel with its 256x256 / 256x128 tile forced,
+/* Force the GEMM workgroup tile for every later call in this process: 0 = automatic (default), 1 / 2 / 3 / 4 / 14 = the
+ * kernel for every type, layout and size with its 32x64 / 64x128 / 96x128 / 128x128 / 160x128 tile (fp32 and weight
+ * gradients: the nearest built one), 5 = the bf16 kernel with 256x256 tiles, for every shape it takes (K a multiple of
+ * 32, 16-byte rows; other shapes and fp32 keep the automatic choice), 6 / 7 = the same kernel with its 256x256 / 256x128 tile forced,
  * 8 / 9 = the same with 128x512 / 512x128 tiles for weight gradients (fp32 output) and 256x256 for the rest,
  * 10 = the same with tile columns every 224 wherever N is a multiple of 224 (bf16 output), 11 = its eight-wave 256x256
  * tile with K tiles of 64 in a ring of two (K a multiple of 64, no split-K), 12 / 13 = the 256x256 tile computed with

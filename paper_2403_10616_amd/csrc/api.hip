@@ -929,7 +929,7 @@ dipaco_status dipaco_k_gemm_colsum(int32_t dtype, int32_t trans_a, int32_t trans
 }
 
 dipaco_status dipaco_k_set_gemm_tile(int32_t tile) {
-  if (tile < 0 || tile > 13) return fail(DIPACO_EINVAL, "dipaco_k_set_gemm_tile: tile must be 0..13");
+  if (tile < 0 || tile > 14) return fail(DIPACO_EINVAL, "dipaco_k_set_gemm_tile: tile must be 0..14");
   set_gemm_tile(tile);
   return DIPACO_OK;
 }

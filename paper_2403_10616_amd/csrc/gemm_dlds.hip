@@ -45,11 +45,6 @@ constexpr int DL_BK_MIN = 32;                               // K tiles are 32 or
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s* lds_v4s_ptr;
 
-// the same with a wave-uniform base address (scalar registers) and a 32-bit per-lane byte offset
-__device__ __forceinline__ void load16_to_lds_at(const char* base, uint32_t byte_off, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
-}
-
 // Load plan of one wave: wave-level load j of a stage fills LDS bytes [1024 j, 1024 j + 1024) of it; j < NLA: A tile, else
 // B tile.  Load i of this wave is j = wave + NW i: its lane's source at K tile 0 (gp), the source's advance per K tile
 // (gstep) and the LDS address in stage 0 (ldst).  Rows (columns) beyond the operand re-read its last ones: they only
@@ -162,7 +157,6 @@ __device__ __forceinline__ void gemm_dlds_wave(const GemmDev& g, char* smem, int
   constexpr int DL_TILE_A = DL_BM * DL_ROWB, DL_TILE_B = DL_BN * DL_ROWB;   // bytes of an operand tile (either kind)
   constexpr int DL_STAGE = DL_TILE_A + DL_TILE_B;
   constexpr int KROW_A = DL_BM * 2, KROW_B = DL_BN * 2;     // bytes of a K-row of a row-contiguous tile
-  constexpr int NLA = DL_TILE_A / 1024;                     // wave-level loads of the A tile
   constexpr int LPS = DL_STAGE / 1024 / NW;                 // wave-level loads per wave and stage
   constexpr int NM = TM * TN, NR = TM + TN;
   const bool active = m0 + rb0 * 32 < g.M && n0 + cb0 * 32 < g.N;   // wave-uniform
@@ -758,18 +752,22 @@ bool gemm_dlds_eligible(const GemmArgs& a) {
 
 void set_gemm_dlds_shape(int shape) { g_dlds_shape = shape; }
 
-int gemm_dlds_plan_slices(int M, int N, int K, int max_slices, bool any_shape) {
-  UnevenPlan up;
-  const int square = plan_uneven(M, N, K, 256, 256, 2, 4, max_slices, up) ? up.s[0] : 0;
-  const int narrow = plan_uneven(M, N, K, 256, 128, 2, 2, max_slices, up) ? up.s[0] : 0;
-  const int wide = plan_uneven(M, N, K, 128, 512, 1, 8, max_slices, up) ? up.s[0] : 0;
-  const int tall = plan_uneven(M, N, K, 512, 128, 4, 2, max_slices, up) ? up.s[0] : 0;
-  if (any_shape) return std::max(std::max(square, narrow), std::max(wide, tall));
+int gemm_dlds_plan_slices(int M, int N, int K, int max_slices, bool any_shape, double* length) {
+  UnevenPlan up[4];
+  const bool ok[4] = {plan_uneven(M, N, K, 256, 256, 2, 4, max_slices, up[0]), plan_uneven(M, N, K, 256, 128, 2, 2, max_slices, up[1]),
+                      plan_uneven(M, N, K, 128, 512, 1, 8, max_slices, up[2]), plan_uneven(M, N, K, 512, 128, 4, 2, max_slices, up[3])};
+  if (any_shape) {
+    int most = 0;
+    for (int i = 0; i < 4; ++i) most = std::max(most, ok[i] ? up[i].s[0] : 0);
+    return most;
+  }
   GemmArgs a{};
   a.M = M; a.N = N; a.K = K; a.splits = max_slices;
   const int oblong = oblong_plan_wins(a);
-  if (oblong) return oblong == 1 ? wide : tall;
-  return g_dlds_shape == 2 ? narrow : square;
+  const int pick = oblong ? oblong + 1 : g_dlds_shape == 2 ? 1 : 0;
+  if (!ok[pick]) return 0;
+  if (length) *length = K * plan_makespan(up[pick]);
+  return up[pick].s[0];
 }
 
 // Host-only view of the split-K plan a weight gradient X^T dY of these sizes would be launched with, for tests:

@@ -1,0 +1,492 @@
+// Matrix-core GEMM for every product that does not fill the chip with 256 x 256 tiles, and for every fp32 product and
+// ragged contraction: bf16 (v_mfma_f32_16x16x32_bf16) or fp32 (v_mfma_f32_16x16x4_f32), all three operand layouts of the
+// path step, any M, N, K that launch_gemm accepts.
+//
+// What bounds these products is the number of compute units at work and the latency of a K loop, not the matrix cores.
+// So the tile is fitted to the grid: its height BM is chosen among 64 .. 160 rows (BN = 128) so that the tiles make whole
+// rounds over the 256 compute units (3000 x 896: 96-row tiles, 224 workgroups; 5700 x 896: 160-row tiles, 252), and a
+// product of few tiles takes 32 x 64 ones.  A workgroup is eight waves in G groups along K x WM x WN over the tile:
+// group g multiplies the g-th 64 bytes of K of every stage, so that two waves share a SIMD with 64 x 64 outputs each
+// (fewer LDS bytes per flop than eight waves of 64 x 32), and a 32 x 64 tile walks K eight steps at a time.  The groups'
+// partial sums are added in group order through LDS in front of the epilogue.
+//
+// Operand tiles go from global memory straight into LDS (16-byte global_load_lds, linear in the lane, swizzles applied on
+// the global side) in a ring of ST stages of 64 G bytes of K:
+//   * operand contiguous along K: tile row r is 64 G bytes; 16-byte chunk c at c ^ sw(r) (sw below).  A fragment is one
+//     ds_read_b128: lane l holds row l % 16, K chunk l / 16 of its group's 64 bytes: 8 bf16, or 4 floats = 4 MFMAs.
+//   * operand contiguous along its rows: K-row t is the tile's rows; 16-row blocks are permuted by rc_pos(block, t).  bf16
+//     fragments come from two transposing ds_read_b64_tr_b16 (K-rows 8 (l / 16) + 0..3 and + 4..7), fp32 ones from four
+//     ds_read_b32 (K-rows 4 (l / 16) + 0..3): the same K per lane and element as above, so any mix multiplies correctly.
+// The chunk and block permutations make the lanes that the LDS serves together touch different slots of the 256-byte bank
+// space (see mma_tile.h for the lane sets); the one exception is fp32 in 32-row blocks of K-rows (two lanes per bank).
+//
+// Loop, one barrier per stage: own loads of stage t have landed (vmcnt) and own fragments of t - 1 are in registers ->
+// barrier -> the stage t - 1 occupied is refilled, the fragments of t are read, and the MFMAs of t - 1 run over both.
+// K beyond the range: loads re-read the last valid K, groups beyond it skip their MFMAs, a group that straddles it zeroes
+// the excess in its fragments (both operands).  Rows beyond M or N re-read the last ones and are not stored.
+#include <algorithm>
+#include <type_traits>
+
+#include "gemm_common.h"
+#include "kernels.h"
+#include "mma_tile.h"
+
+namespace dipaco {
+
+namespace {
+
+constexpr int FIT_WAVES = 8;
+constexpr int FIT_STEP = 64;   // bytes of K per group and stage
+
+typedef short fit_v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) fit_v4s* fit_lds_ptr;
+
+// position of 16-row block blk in K-row t of a row-contiguous tile whose K-rows are R bytes (its own inverse)
+template <typename T, int R> __device__ __forceinline__ int rc_pos(int blk, int t) {
+  if constexpr (sizeof(T) == 2) {
+    if constexpr (R >= 256) return (((blk >> 1) ^ (t & 3)) << 1) | ((blk ^ (t >> 3)) & 1);
+    else if constexpr (R == 128) return blk ^ (t & 2) ^ ((t >> 3) & 1);
+    else return blk ^ ((t >> 3) & 1);
+  } else {
+    if constexpr (R >= 256) return blk ^ ((t >> 2) & 3);
+    else return blk ^ ((t >> 2) & 1);
+  }
+}
+
+template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST> struct Fit {
+  static_assert(WM * WN * G == FIT_WAVES && (G == 2 || G == 8), "eight waves; swizzles for rows of 128 and 512 bytes");
+  static constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
+  static constexpr int E = 16 / sizeof(T);                 // elements per 16-byte chunk
+  static constexpr int KD = FIT_STEP / sizeof(T);          // K per group and stage
+  static constexpr int BK = KD * G;                        // K per stage
+  static constexpr int ROWB = FIT_STEP * G;                // bytes of a K-contiguous tile row
+  static constexpr int TILE_A = BM * ROWB, TILE_B = BN * ROWB, STAGE = TILE_A + TILE_B;
+  static constexpr int RA = BM * (int)sizeof(T), RB = BN * (int)sizeof(T);   // bytes of a K-row
+  static constexpr int NLA = TILE_A / 1024, NL = STAGE / 1024;               // wave-level loads of a stage
+  static constexpr int LPS = (NL + FIT_WAVES - 1) / FIT_WAVES;
+  static constexpr int LDW = BN + 4;                       // padded row of the epilogue region (floats)
+  static constexpr int IC = TM <= 4 ? TM : 3;              // 16-row blocks per wave and epilogue pass
+  static constexpr int EPI = G * WM * 16 * IC * LDW * 4;
+  static constexpr int LDS = ST * STAGE > EPI ? ST * STAGE : EPI;
+  static_assert(A_KC || (BM & (BM - 1)) == 0, "row-contiguous tiles have power-of-two sides");
+  static_assert(LDS <= 160 * 1024 && TILE_A % 1024 == 0 && STAGE % 1024 == 0 && (ST == 3 || ST == 4), "ring");
+};
+
+// chunk swizzle of a K-contiguous tile row
+template <int G> __device__ __forceinline__ int kc_sw(int row) { return G == 2 ? (row >> 1) & 7 : row & 15; }
+
+// Where lane `lane` of wave-level load jj of an operand tile reads: row (relative to the tile) and K offset (elements,
+// relative to the stage) of its 16 bytes
+template <typename T, bool KC, int ROWB, int R, int G>
+__device__ __forceinline__ void fit_source(int jj, int lane, int& row, int& k) {
+  constexpr int E = 16 / sizeof(T);
+  if constexpr (KC) {
+    constexpr int LPR = ROWB / 16;
+    row = jj * (64 / LPR) + lane / LPR;
+    k = ((lane % LPR) ^ kc_sw<G>(row)) * E;
+  } else {
+    const int byte = jj * 1024 + lane * 16;
+    k = byte / R;
+    const int in_row = byte % R, bb = 16 * (int)sizeof(T);   // bytes of a 16-row block
+    row = rc_pos<T, R>(in_row / bb, k) * 16 + (in_row % bb) / (int)sizeof(T);
+  }
+}
+
+template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST>
+__global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmDev g) {
+  using F = Fit<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
+  constexpr int BM = F::BM, BN = F::BN, E = F::E, KD = F::KD, BK = F::BK, ROWB = F::ROWB, LPS = F::LPS;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
+  const int r = lane & 15, kg = lane >> 4;
+
+  int split, tile_m, tile_n;
+  if (g.splits > 1) {   // split-K: each XCD gets a contiguous, slice-major range (neighbours share operand panels in its L2)
+    const int tiles = g.tiles_m * g.tiles_n, v = xcd_contiguous(blockIdx.x, tiles * g.splits);
+    split = v / tiles;
+    tile_m = (v - split * tiles) % g.tiles_m;
+    tile_n = (v - split * tiles) / g.tiles_m;
+  } else {
+    gemm_tile_of_block(g, blockIdx.x, split, tile_m, tile_n);
+  }
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int k_begin = split * g.k_per_split, k_end = min(g.K, k_begin + g.k_per_split);
+  const int nkt = (k_end - k_begin + BK - 1) / BK;
+
+  // ---- loads: wave-level load i of this wave is number wave + 8 i of the stage (the last number is repeated to fill up) ----
+  const char* base_a = static_cast<const char*>(g.A) + (A_KC ? (long)m0 * g.lda + k_begin : (long)k_begin * g.lda + m0) * (long)sizeof(T);
+  const char* base_b = static_cast<const char*>(g.B) + (B_KC ? (long)n0 * g.ldb + k_begin : (long)k_begin * g.ldb + n0) * (long)sizeof(T);
+  const long adv_a = A_KC ? ROWB : (long)BK * g.lda * (long)sizeof(T), adv_b = B_KC ? ROWB : (long)BK * g.ldb * (long)sizeof(T);
+  const uint32_t smem_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + 1024 * wave);
+  // byte offset of load i relative to its operand's base at the stage's first K; klim: K left in the range there
+  auto source = [&](int i, int klim) -> uint32_t {
+    const int j = min(wave + FIT_WAVES * i, F::NL - 1);
+    int row, k;
+    if (j < F::NLA) {
+      fit_source<T, A_KC, ROWB, F::RA, G>(j, lane, row, k);
+      if (A_KC) return (uint32_t)(((long)min(row, g.M - 1 - m0) * g.lda + min(k, klim - E)) * (long)sizeof(T));
+      return (uint32_t)(((long)min(k, klim - 1) * g.lda + min(row, g.M - E - m0)) * (long)sizeof(T));
+    }
+    fit_source<T, B_KC, ROWB, F::RB, G>(j - F::NLA, lane, row, k);
+    if (B_KC) return (uint32_t)(((long)min(row, g.N - 1 - n0) * g.ldb + min(k, klim - E)) * (long)sizeof(T));
+    return (uint32_t)(((long)min(k, klim - 1) * g.ldb + min(row, g.N - E - n0)) * (long)sizeof(T));
+  };
+  uint32_t off[LPS], ldst[LPS];
+  bool is_a[LPS];
+#pragma unroll
+  for (int i = 0; i < LPS; ++i) {
+    off[i] = source(i, 1 << 30);
+    ldst[i] = smem_base + 1024 * (min(wave + FIT_WAVES * i, F::NL - 1) - wave);
+    is_a[i] = min(wave + FIT_WAVES * i, F::NL - 1) < F::NLA;
+  }
+  auto issue = [&](int i, int kt, int slot) {   // load i of a stage that lies in the range
+    load16_to_lds_at(is_a[i] ? base_a + kt * adv_a : base_b + kt * adv_b, off[i],
+                     __builtin_amdgcn_readfirstlane(ldst[i] + slot * F::STAGE));
+  };
+  auto issue_any = [&](int kt, int slot) {      // all loads of stage kt, if it exists
+    if (kt >= nkt) return;
+    const int klim = k_end - k_begin - kt * BK;
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) {
+      if (klim < BK) off[i] = source(i, klim);   // the last stage, where the range ends inside it: clamped K
+      issue(i, kt, slot);
+    }
+  };
+
+  // ---- fragments ----
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  uint4 fa[2][TM], fb[2][TN];
+  const int koff = r * ROWB + (((4 * grp + kg) ^ kc_sw<G>(r)) << 4);   // K-contiguous tile
+  // row-contiguous tile: this lane's part of 16-row block i (j) of its group's K step
+  int toffa[TM], toffb[TN];
+  auto rc_off = [&](int blk, auto Rc) {
+    constexpr int R = decltype(Rc)::value;
+    const int t = sizeof(T) == 2 ? 32 * grp + 8 * kg + (r >> 2) : 16 * grp + 4 * kg;
+    return t * R + rc_pos<T, R>(blk, t) * 16 * (int)sizeof(T) + (sizeof(T) == 2 ? 8 * (r & 3) : 4 * r);
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i) toffa[i] = A_KC ? (wm * TM + i) * 16 * ROWB + koff : rc_off(wm * TM + i, std::integral_constant<int, F::RA>{});
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    toffb[j] = F::TILE_A + (B_KC ? (wn * TN + j) * 16 * ROWB + koff : rc_off(wn * TN + j, std::integral_constant<int, F::RB>{}));
+  auto rc_read = [&](const char* p, auto Rc) {
+    constexpr int R = decltype(Rc)::value;
+    uint4 o;
+    if constexpr (sizeof(T) == 2) {
+      const fit_v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((fit_lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)p);
+      const fit_v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((fit_lds_ptr)(uintptr_t)(uint32_t)(uintptr_t)(p + 4 * R));
+      o.x = (uint16_t)lo[0] | ((uint32_t)(uint16_t)lo[1] << 16);
+      o.y = (uint16_t)lo[2] | ((uint32_t)(uint16_t)lo[3] << 16);
+      o.z = (uint16_t)hi[0] | ((uint32_t)(uint16_t)hi[1] << 16);
+      o.w = (uint16_t)hi[2] | ((uint32_t)(uint16_t)hi[3] << 16);
+    } else {
+      const uint32_t* w = reinterpret_cast<const uint32_t*>(p);
+      o.x = w[0]; o.y = w[R / 4]; o.z = w[2 * (R / 4)]; o.w = w[3 * (R / 4)];
+    }
+    return o;
+  };
+  constexpr int NR = TM + TN;
+  auto read = [&](auto SET, int q, const char* stage) {   // fragment q of a stage: B first, then A
+    constexpr int set = decltype(SET)::value;
+    if (q < TN) {
+      if constexpr (B_KC) fb[set][q] = *reinterpret_cast<const uint4*>(stage + toffb[q]);
+      else fb[set][q] = rc_read(stage + toffb[q], std::integral_constant<int, F::RB>{});
+    } else {
+      if constexpr (A_KC) fa[set][q - TN] = *reinterpret_cast<const uint4*>(stage + toffa[q - TN]);
+      else fa[set][q - TN] = rc_read(stage + toffa[q - TN], std::integral_constant<int, F::RA>{});
+    }
+  };
+  // MFMA m of a step
+  constexpr int NM = TM * TN * (sizeof(T) == 2 ? 1 : 4);
+  auto mfma = [&](auto SET, int m) {
+    constexpr int set = decltype(SET)::value;
+    if constexpr (sizeof(T) == 2) {
+      const int i = m / TN, j = m % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[set][i]),
+                                                          __builtin_bit_cast(bf16x8, fb[set][j]), acc[i][j], 0, 0, 0);
+    } else {
+      const int q = m / (TM * TN), i = m % (TM * TN) / TN, j = m % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&fa[set][i])[q],
+                                                       reinterpret_cast<const float*>(&fb[set][j])[q], acc[i][j], 0, 0, 0);
+    }
+  };
+  // the last stage: `left` = K of this group's step that lies in the range (may be <= 0 or >= KD)
+  auto multiply_last = [&](auto SET) {
+    constexpr int set = decltype(SET)::value;
+    const int left = k_end - k_begin - (nkt - 1) * BK - grp * KD;   // wave-uniform
+    if (left <= 0) return;
+    if (left < KD) {
+      constexpr int PER = 4 / sizeof(T);   // elements per 32-bit word
+      const int keep = left - E * kg;      // elements of this lane's fragments that count
+      uint32_t m[4];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) m[d] = keep >= PER * (d + 1) ? 0xffffffffu : (PER == 2 && keep == 2 * d + 1) ? 0xffffu : 0u;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) { fa[set][i].x &= m[0]; fa[set][i].y &= m[1]; fa[set][i].z &= m[2]; fa[set][i].w &= m[3]; }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) { fb[set][j].x &= m[0]; fb[set][j].y &= m[1]; fb[set][j].z &= m[2]; fb[set][j].w &= m[3]; }
+    }
+#pragma unroll
+    for (int x = 0; x < NM; ++x) mfma(SET, x);
+  };
+
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  // own loads of every stage but the n newest have landed
+  auto wait_but = [&](int n) {
+    if (ST > 3 && n >= 2) wait_vmcnt<2 * LPS>();
+    else if (n >= 1) wait_vmcnt<LPS>();
+    else wait_vmcnt<0>();
+  };
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s) issue_any(s, s);
+  wait_but(min(ST - 2, nkt - 1));
+  __syncthreads();
+  issue_any(ST - 1, ST - 1);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) read(C0{}, q, smem);
+  int slot = 1;   // of stage t
+  // stage t >= 1.  STEADY: stage t + ST - 1 exists and lies in the range, no conditions.
+  auto step = [&](auto SET, auto STEADY, int t) {
+    using Prev = std::integral_constant<int, decltype(SET)::value ^ 1>;
+    constexpr bool steady = decltype(STEADY)::value;
+    if (steady) wait_vmcnt<(ST - 2) * LPS>();
+    else wait_but(min(ST - 2, nkt - 1 - t));
+    __syncthreads();   // also waits for this wave's fragments of t - 1
+    const char* stage = smem + slot * F::STAGE;
+    const int refill = slot == 0 ? ST - 1 : slot - 1;
+    if (!steady) issue_any(t + ST - 1, refill);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      if (m < NR) read(SET, m, stage);
+      if (steady) {
+#pragma unroll
+        for (int i = m * LPS / NM; i < (m + 1) * LPS / NM; ++i) issue(i, t + ST - 1, refill);
+      }
+      mfma(Prev{}, m);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    slot = slot + 1 == ST ? 0 : slot + 1;
+  };
+  static_assert(NR <= NM, "a stage's fragments are read under the MFMAs of a step");
+  const int nfull = (k_end - k_begin) / BK;
+  int t = 1;
+  for (; t + ST < nfull; t += 2) {
+    step(C1{}, std::true_type{}, t);
+    step(C0{}, std::true_type{}, t + 1);
+  }
+  for (; t < nkt; t += 2) {
+    step(C1{}, std::false_type{}, t);
+    if (t + 1 < nkt) step(C0{}, std::false_type{}, t + 1);
+  }
+  if (nkt & 1) multiply_last(C0{});
+  else multiply_last(C1{});
+
+  // ---- epilogue: groups added in order, then bias / activation / residual on eight columns per item ----
+  constexpr int CG = BN / 8, IC = F::IC, LDW = F::LDW;
+  static_assert((64 * FIT_WAVES) % CG == 0, "a thread keeps its column group over the items");
+  float* const red = reinterpret_cast<float*>(smem);
+  const int cg = tid % CG, col = n0 + 8 * cg;
+  const bool col_ok = col < g.N, partial = g.splits > 1;
+  const T* const bias = static_cast<const T*>(g.bias);
+  const T* const resid = static_cast<const T*>(g.resid);
+  const T* const aux_in = static_cast<const T*>(g.aux_in);
+  const bool want_aux = g.act == 2 || g.act == 4;
+  const T* const ahead = want_aux ? aux_in : resid;
+  const long ldc = g.ldc;
+  float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (bias && col_ok) OutVec<T>::load(bias + col, bv);
+  auto pass = [&](auto I0, auto N16) {   // 16-row blocks I0 .. I0 + N16 - 1 of every wave
+    constexpr int i0 = decltype(I0)::value, n16 = decltype(N16)::value;
+    constexpr int ROWS = WM * 16 * n16, ITERS = (ROWS * CG + 64 * FIT_WAVES - 1) / (64 * FIT_WAVES);
+    auto row_of = [&](int rr) { return m0 + (rr / (16 * n16)) * 16 * TM + 16 * i0 + rr % (16 * n16); };
+    Raw8<T> rin[ITERS];
+    if (ahead) {
+#pragma unroll
+      for (int it = 0; it < ITERS; ++it) {
+        const int rr = (tid + 64 * FIT_WAVES * it) / CG, row = row_of(rr);
+        if (rr < ROWS && row < g.M && col_ok) rin[it] = raw8_load(ahead + (size_t)row * ldc + col);
+      }
+    }
+    __syncthreads();   // the ring (or the pass before) has been read
+#pragma unroll
+    for (int i = 0; i < n16; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          red[((grp * WM + wm) * 16 * n16 + 16 * i + 4 * kg + e) * LDW + (wn * TN + j) * 16 + r] = acc[i0 + i][j][e];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const int rr = (tid + 64 * FIT_WAVES * it) / CG, row = row_of(rr);
+      if (rr >= ROWS || row >= g.M || !col_ok) continue;
+      float v[8];
+      OutVec<float>::load(red + rr * LDW + 8 * cg, v);
+#pragma unroll
+      for (int q = 1; q < G; ++q) {
+        float w[8];
+        OutVec<float>::load(red + (q * ROWS + rr) * LDW + 8 * cg, w);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] += w[c];
+      }
+      if (partial) {
+        OutVec<float>::store(g.partial + ((size_t)split * g.M + row) * g.N + col, v);
+        continue;
+      }
+      const size_t o = (size_t)row * ldc + col;
+      if constexpr (std::is_same<T, TC>::value) {
+        if (bias) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] += bv[c];
+        }
+        if (g.act == 1) {
+          OutVec<T>::store(static_cast<T*>(g.aux_out) + o, v);   // GELU is applied to the stored value
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] = gelu_t<T>(to_f32(from_f32<T>(v[c])));
+        } else if (g.act == 3) {
+          float dv[8];
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv[c]);
+          OutVec<T>::store(static_cast<T*>(g.aux_out) + o, dv);
+        } else if (want_aux) {
+          float u[8];
+          raw8_unpack(rin[it], u);
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] *= g.act == 2 ? gelu_grad_t<T>(u[c]) : u[c];
+        }
+        if (resid) {
+          float rv[8];
+          raw8_unpack(want_aux ? raw8_load(resid + o) : rin[it], rv);
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] += rv[c];
+        }
+      }
+      OutVec<TC>::store(static_cast<TC*>(g.C) + o, v);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) cs[c] += v[c];
+    }
+  };
+  pass(C0{}, std::integral_constant<int, IC>{});
+  if constexpr (TM > IC) pass(std::integral_constant<int, IC>{}, std::integral_constant<int, TM - IC>{});
+  if (g.colsum_partial) {   // one row of column sums per tile: lanes with the same columns, then the waves in order
+#pragma unroll
+    for (int m = CG; m < WAVE; m <<= 1)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) cs[c] += __shfl_xor(cs[c], m, WAVE);
+    __syncthreads();
+    if (lane < CG) OutVec<float>::store(red + wave * BN + 8 * lane, cs);
+    __syncthreads();
+    if (tid < CG && col_ok) {
+      float s[8];
+      OutVec<float>::load(red + 8 * tid, s);
+#pragma unroll
+      for (int w = 1; w < FIT_WAVES; ++w) {
+        float x[8];
+        OutVec<float>::load(red + w * BN + 8 * tid, x);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) s[c] += x[c];
+      }
+      OutVec<float>::store(g.colsum_partial + (size_t)tile_m * g.N + col, s);
+    }
+  }
+}
+
+template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST>
+dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
+  using F = Fit<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
+  auto kern = gemm_fit_kernel<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
+  static std::atomic<unsigned long long> lds_set{0};   // per instantiation
+  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), F::LDS, lds_set)) return e;
+  GemmDev g;
+  g.A = a.A; g.B = a.B; g.C = a.C; g.M = a.M; g.N = a.N; g.K = a.K;
+  g.lda = a.lda; g.ldb = a.ldb; g.ldc = a.ldc;
+  g.bias = a.bias; g.resid = a.resid; g.aux_out = a.aux_out; g.aux_in = a.aux_in; g.act = a.act;
+  g.partial = a.partial;
+  g.tiles_m = (a.M + F::BM - 1) / F::BM;
+  g.tiles_n = (a.N + F::BN - 1) / F::BN;
+  const int steps = (a.K + F::BK - 1) / F::BK;
+  const int want = std::max(1, std::min(a.splits, steps));
+  g.k_per_split = (steps + want - 1) / want * F::BK;
+  g.splits = (a.K + g.k_per_split - 1) / g.k_per_split;
+  const long blocks = (long)g.tiles_m * g.tiles_n * g.splits;
+  if (blocks > 0x7fffffffL) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
+  g.colsum_partial = a.colsum ? a.colsum_partial : nullptr;
+  kern<<<(unsigned)blocks, 64 * FIT_WAVES, F::LDS, s>>>(g);
+  DIPACO_LAUNCH_CHECK();
+  if (g.splits > 1) return launch_splitk_reduce(a.partial, static_cast<float*>(a.C), a.M, a.N, a.ldc, g.splits, s);
+  if (a.colsum) return launch_sum_rows(a.colsum_partial, a.colsum, g.tiles_m, a.N, s, a.sum_batch);
+  return DIPACO_OK;
+}
+
+// Tile shapes: 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 rows x 128.  fp32 has 1 and 2 (its matrix-core steps are sixteen times as
+// long: 64 x 128 tiles, two workgroups per compute unit, were the fastest of the 128-column ones on every product measured);
+// row-contiguous A 1, 2 and 4.
+bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || (bf16_operands && (a_kc || t == 4)); }
+
+// Microseconds of `tiles` tiles over K: rounds of 256 workgroups x (fixed + per 1000 of K).  Fitted to launches of 256 .. 8192
+// rows, K 64 .. 8192 (rel. error 15 %): 3000 x 896 x 3584 bf16 34.8 / 26.0 / 28.8 / 33.7 us for shapes 2 .. 5, 5700 x 896 x 3584
+// 51 / 49 / 53 / 38, 1000 x 896 x 3584 20 (shape 1) / 21 / 24 / 28, 256 x 896 x 3584 10.5 / 19.
+double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands) {
+  static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
+  const int bm = 32 * t, bn = t == 1 ? 64 : 128;
+  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
+  const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
+  return 3.0 + (double)((tiles + 255) / 256) * (f + k * K * 1e-3);
+}
+
+std::atomic<int> g_forced_fit{0};
+int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
+  if (g_forced_fit) {
+    int t = g_forced_fit;
+    while (!fit_built(t, bf16_operands, a_kc)) --t;
+    return t;
+  }
+  int best = 1;
+  for (int t = 2; t <= 5; ++t)
+    if (fit_built(t, bf16_operands, a_kc) &&
+        shape_cost(t, M, N, K, splits, bf16_operands) < shape_cost(best, M, N, K, splits, bf16_operands)) best = t;
+  return best;
+}
+
+template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_shape(const GemmArgs& a, hipStream_t s) {
+  const int splits = std::max(1, a.splits);
+  const int t = pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
+  if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
+  if constexpr (sizeof(T) == 2) {
+    if constexpr (A_KC) {
+      if (t == 3) return run_fit<T, TC, A_KC, B_KC, 3, 4, 2, 2, 2, 4>(a, s);
+      if (t == 5) return run_fit<T, TC, A_KC, B_KC, 5, 4, 2, 2, 2, 4>(a, s);
+    }
+    if (t == 4) return run_fit<T, TC, A_KC, B_KC, 4, 4, 2, 2, 2, 4>(a, s);
+  }
+  return run_fit<T, TC, A_KC, B_KC, 2, 4, 2, 2, 2, 3>(a, s);
+}
+
+}  // namespace
+
+void set_gemm_fit_shape(int t) { g_forced_fit = t; }
+
+double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous) {
+  double best = 1e30;
+  for (int t = 1; t <= 5; ++t)
+    if (fit_built(t, bf16_operands, a_k_contiguous)) best = std::min(best, shape_cost(t, M, N, K, splits, bf16_operands));
+  return best;
+}
+
+template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& a, hipStream_t s) {
+  if (a.out_f32) return run_fit_shape<T, float, false, false>(a, s);
+  if (!a.trans_b) return run_fit_shape<T, T, true, false>(a, s);
+  return run_fit_shape<T, T, true, true>(a, s);
+}
+template dipaco_status launch_gemm_fit<float>(const GemmArgs&, hipStream_t);
+template dipaco_status launch_gemm_fit<bf16>(const GemmArgs&, hipStream_t);
+
+}  // namespace dipaco

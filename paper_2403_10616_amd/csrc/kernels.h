@@ -115,19 +115,24 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& g, hipStream_t s
 bool gemm_dlds_eligible(const GemmArgs& g);
 dipaco_status launch_gemm_dlds(const GemmArgs& g, hipStream_t s);
 void set_gemm_dlds_shape(int shape);   // 0 = automatic, 1 = 256 x 256, 2 = 256 x 128, 3 / 4 = 128 x 512 / 512 x 128 for weight gradients, 5 = 224-column tiles where N % 224 == 0
+// gemm_fit.hip: any type, layout and size that launch_gemm accepts; tiles fitted to the grid
+template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& g, hipStream_t s);
+void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 x 128
 // C[m, n] = sum over z < splits of partial[z, m, n], in index order
 dipaco_status launch_splitk_reduce(const float* partial, float* C, int M, int N, long ldc, int splits, hipStream_t s);
-// 0 = automatic; 1 = 128x128, 2 = 256x128, 3 / 4 = 256x256 workgroup tiles with four / eight waves, 5 = the
-// direct-to-LDS kernel wherever the shape allows, 6 / 7 / 8 / 9 / 10 = the same with its 256x256 / 256x128 / 128x512 / 512x128 (these two: weight gradients) / 224-column shape forced
-// (tuning and tests)
+// microseconds of a product of `splits` slices of K each with the best tile shape
+double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous);
+// 0 = automatic; 1 .. 4, 14 = gemm_fit.hip with 32x64, 64x128, 96x128, 128x128, 160x128 tiles, 5 = the direct-to-LDS kernel
+// wherever the shape allows, 6 .. 13 = the same with the shapes of set_gemm_dlds_shape (tuning and tests)
 void set_gemm_tile(int t);
 // the same where the number of slices depends on the tile class of the element:
 // n_slices[(row >= row_edge) + 2 * (col >= col_edge)]
 dipaco_status launch_splitk_reduce_classes(const float* partial, float* C, int M, int N, long ldc, int row_edge,
                                            int col_edge, const int (&n_slices)[4], hipStream_t s);
 // direct-to-LDS kernel: slices of a full tile in its uneven split-K plan with at most max_slices, 0 if it has none
-// (for the tile shape in force, or the larger count over both shapes)
-int gemm_dlds_plan_slices(int M, int N, int K, int max_slices, bool any_shape);
+// (for the tile shape in force, or the largest count over all shapes); length (nullable): K of its longest workgroup, in
+// steps of a full tile
+int gemm_dlds_plan_slices(int M, int N, int K, int max_slices, bool any_shape, double* length);
 void gemm_dlds_plan_info(int M, int N, int K, int max_slices, int* out);   // host-only, for tests: see gemm_dlds.hip
 constexpr int GEMM_SLICE_CAP = 32;
 // split count the weight-gradient products are launched with

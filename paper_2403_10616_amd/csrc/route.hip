@@ -122,8 +122,8 @@ __global__ void __launch_bounds__(R_THREADS) route_kernel(const float* __restric
   const float dot_mul = lin_bias ? 1.0f : 2.0f;
   if (use_lhist) for (int k = tid; k < K; k += R_THREADS) lhist[k] = 0;
 
-  using LZ = TileLoader<float, RBM, false, R_THREADS>;
-  using LC = TileLoader<float, RBN, false, R_THREADS>;
+  using LZ = TileLoader<float, RBM, R_THREADS>;
+  using LC = TileLoader<float, RBN, R_THREADS>;
   const int nkt = (D + RBK - 1) / RBK;
 
   // Running best / second best of one row per lane and pair of row tiles: after the reduction at the end of a

@@ -325,3 +325,34 @@ def test_bf16_weight_gradient_products_of_the_step_element_by_element(name, M, N
     rms = math.sqrt(float(np.mean(ref * ref)))
     err = np.abs(host(C).astype(np.float64) - ref)
     assert err.max() <= 1e-4 * rms, (name, np.unravel_index(int(np.argmax(err)), ref.shape), err.max() / rms)
+
+
+# Edges of the fitted tiles (heights 32, 64, 96, 128, 160; widths 64 and 128), of a group's 64 bytes of K and of a stage of two
+# or eight groups; contractions that end inside a group.  Bounds: fp32 sums of K products, 2^-24 sqrt(K) each side, and one
+# bf16 rounding (2^-9) of the output.
+@pytest.mark.parametrize("dtype", [dp.F32, dp.BF16])
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 14])
+@pytest.mark.parametrize("M,N,K", [(33, 72, 8), (65, 136, 24), (161, 128, 40), (320, 264, 264), (159, 120, 520), (97, 8, 2056),
+                                   (160, 1160, 96)])
+def test_gemm_fitted_tiles_at_their_edges(dtype, tile, M, N, K):
+    print(f"gemm fit dtype={dtype} tile={tile} M={M} N={N} K={K}", flush=True)
+    g = torch.Generator().manual_seed(M + N + K)
+    mk = lambda *shape: torch.randn(shape, generator=g).to(TDT[dtype]).to(DEV)
+    A, B, Bt, R = mk(M, K), mk(K, N), mk(N, K), mk(M, N)
+    X, Y = mk(K + 5, ((M + 7) // 8) * 8), mk(K + 5, N)        # weight gradient: the contraction need not be a multiple of 8
+    C = torch.empty((M, N), dtype=TDT[dtype], device=DEV)
+    W = torch.full((X.shape[1], N), float("nan"), device=DEV)
+    P = torch.empty((3,) + tuple(W.shape), device=DEV)
+    rel = lambda got, ref: float((got.double() - ref).norm() / ref.norm())
+    tol = 1e-6 if dtype == dp.F32 else 2.0 ** -9
+    dp.dipaco_k_set_gemm_tile(tile)
+    try:
+        dp.dipaco_k_gemm(dtype, False, False, False, M, N, K, A, B, C, resid=R)
+        assert rel(C, A.double() @ B.double() + R.double()) <= tol
+        dp.dipaco_k_gemm(dtype, False, True, False, M, N, K, A, Bt, C)
+        assert rel(C, A.double() @ Bt.double().T) <= tol
+        for splits in (1, 3):
+            dp.dipaco_k_gemm(dtype, True, False, True, W.shape[0], N, K + 5, X, Y, W, splits=splits, partial=P)
+            assert rel(W, X.double().T @ Y.double()) <= 1e-6
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
