@@ -238,7 +238,7 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   FeaturePlan p;
   p.x_a = take(T * d * es); p.x_b = take(T * d * es); p.h = take(T * d * es); p.mean = take(T * 4); p.rstd = take(T * 4);
   p.qkv = take(T * 3 * A * es); p.o = take(T * A * es); p.lse = take((size_t)B * a.n_heads * S * 4);
-  p.x_mid = take(T * d * es); p.u = take(T * F * es); p.act = take(T * F * es);
+  p.x_mid = take(T * d * es); p.u = take(T * F * es); p.act = take(T * F * es);   // u: GELU', which only a step keeps; the plan's size is part of the interface
   p.logits = p.nll = p.n_valid = 0;
   if (with_head) { p.logits = take(T * (size_t)a.vocab * es); p.nll = take(T * 4); p.n_valid = take(256); }
   p.total = pos;
@@ -267,8 +267,9 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
                 false, 1, nullptr, st));
     TRY(launch_layernorm_fwd<T>(buf(p.x_mid), W + o.ln2_g, W + o.ln2_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d,
                                 a.ln_eps, st));
-    TRY(gemm<T>(buf(p.h), W + o.w_up, buf(p.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, buf(p.u), nullptr,
-                3, false, 1, nullptr, st));
+    // no backward pass: GELU' is neither kept nor written (act 5)
+    TRY(gemm<T>(buf(p.h), W + o.w_up, buf(p.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, nullptr, nullptr,
+                5, false, 1, nullptr, st));
     TRY(gemm<T>(buf(p.act), W + o.w_down, x_other, T_, d, F, F, d, d, false, false, W + o.b_down, buf(p.x_mid), nullptr,
                 nullptr, 0, false, 1, nullptr, st));
     std::swap(x, x_other);
@@ -909,6 +910,7 @@ dipaco_status dipaco_k_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int
   g.bias = bias; g.resid = resid; g.aux_out = aux_out; g.aux_in = aux_in; g.act = act;
   g.trans_a = trans_a; g.trans_b = trans_b; g.out_f32 = out_f32; g.splits = splits; g.partial = partial;
   if (!A || !B || !C) return fail(DIPACO_EINVAL, "dipaco_k_gemm: NULL operand");
+  if (act > 4) return fail(DIPACO_EINVAL, "gemm: act must be 0..4");
   hipStream_t st = static_cast<hipStream_t>(stream);
   return dtype == DIPACO_BF16 ? launch_gemm<bf16>(g, st) : launch_gemm<float>(g, st);
 }
@@ -924,6 +926,7 @@ dipaco_status dipaco_k_gemm_colsum(int32_t dtype, int32_t trans_a, int32_t trans
   g.trans_a = trans_a; g.trans_b = trans_b; g.out_f32 = 0; g.splits = 1; g.partial = nullptr;
   g.colsum = colsum_out; g.colsum_partial = colsum_scratch;
   if (!A || !B || !C || !colsum_out || !colsum_scratch) return fail(DIPACO_EINVAL, "dipaco_k_gemm_colsum: NULL argument");
+  if (act > 4) return fail(DIPACO_EINVAL, "gemm: act must be 0..4");
   hipStream_t st = static_cast<hipStream_t>(stream);
   return dtype == DIPACO_BF16 ? launch_gemm<bf16>(g, st) : launch_gemm<float>(g, st);
 }

@@ -240,6 +240,10 @@ __device__ __forceinline__ void gemm_epilogue(const ACC& acc, float* stg, int la
 #pragma unroll
         for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv[c]);
         OutVec<T>::store(aux_out + off, dv);
+      } else if (g_act == 5) {
+        float dv;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv);
       } else if (want_aux) {
         float u[8];
         raw8_unpack(rin[i & 1][it], u);
@@ -340,6 +344,10 @@ __device__ __forceinline__ void gemm_epilogue_fixed(const ACC& acc, float* stg, 
 #pragma unroll
           for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv[c]);
           OutVec<T>::store(static_cast<T*>(g.aux_out) + off, dv);
+        } else if (ACT == 5) {
+          float dv;   // not stored: the compiler drops its arithmetic, the value is that of ACT 3
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv);
         } else if (AUX_IN) {
           float u[8];
           raw8_unpack(rin[i & 1][it], u);
@@ -393,6 +401,7 @@ __device__ __forceinline__ void gemm_epilogue_dispatch(const ACC& acc, float* st
       if (bias && resid) { DIPACO_EPI(0, true, true, false, false); return; }
     }
     if (act == 3 && bias && !resid && !cs) { DIPACO_EPI(3, true, false, false, false); return; }
+    if (act == 5 && bias && !resid && !cs) { DIPACO_EPI(5, true, false, false, false); return; }
     if (act == 4 && !bias && !resid) {
       if (cs) { DIPACO_EPI(4, false, false, true, false); return; }
       DIPACO_EPI(4, false, false, false, false);
@@ -408,7 +417,7 @@ __device__ __forceinline__ void gemm_epilogue_dispatch(const ACC& acc, float* st
 // host: does a bf16-output product with these epilogue options take one of the compile-time epilogues above?
 inline bool gemm_epilogue_is_fixed(int act, bool bias, bool resid, bool colsum) {
   if (act == 0 && !colsum) return (!bias && !resid) || bias;
-  if (act == 3) return bias && !resid && !colsum;
+  if (act == 3 || act == 5) return bias && !resid && !colsum;
   if (act == 4) return !bias && !resid;
   return false;
 }

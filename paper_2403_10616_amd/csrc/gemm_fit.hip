@@ -356,6 +356,10 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
 #pragma unroll
           for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv[c]);
           OutVec<T>::store(static_cast<T*>(g.aux_out) + o, dv);
+        } else if (g.act == 5) {
+          float dv;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv);
         } else if (want_aux) {
           float u[8];
           raw8_unpack(rin[it], u);

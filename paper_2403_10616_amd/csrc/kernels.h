@@ -84,6 +84,7 @@ dipaco_status launch_kmeans_update(const float* z, long ldz, const int* idx, lon
 //   trans_b = 0: B is [K,N] row-major (ldb);  1: B is [N,K] row-major (ldb)
 // Epilogue (all optional, applied in this order): + bias[n];  act = 1: aux_out = value, value = GELU(value);
 // act = 2: value *= GELU'(aux_in);  act = 3: aux_out = GELU'(value), value = GELU(value);  act = 4: value *= aux_in;
+// act = 5: value = GELU(value) (act 3 for callers that need no derivative);
 // + resid[m,n].  aux and resid have row stride ldc.  (The path step uses the pair 3 / 4: the forward pass leaves the
 // derivative itself, which it gets almost for free beside GELU, and the backward epilogue is one multiplication.)
 // out_f32 = 1 writes fp32 (used for weight gradients), else T.
