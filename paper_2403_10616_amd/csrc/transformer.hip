@@ -131,11 +131,14 @@ __global__ void __launch_bounds__(ROW_THREADS) ln_fwd_reg_kernel(const T* __rest
 }
 
 // ---- LayerNorm backward -----------------------------------------------------------------------------------
-// Each workgroup owns LN_BWD_ROWS consecutive rows (one wave per row at a time), writes dx for them and one
+// Each workgroup owns rows_per_block consecutive rows (one wave per row at a time), writes dx for them and one
 // partial row of dg / db / column sums of dx; a second kernel sums the partial rows in block order.  The column
 // sums of dx (of the values as stored, i.e. rounded to T) are the bias gradient of the linear layer whose output
 // gradient dx is.
-constexpr int LN_BWD_ROWS = 32;
+// 32 rows a workgroup, and 8 (two per wave) while that gives no more than 1024 workgroups: 3000 rows are 94 workgroups of
+// 32 on 256 compute units, each eight rows deep in every wave.
+constexpr int LN_BWD_ROWS = 32, LN_BWD_FEW_ROWS = 8;
+inline int ln_bwd_rows(int rows) { return rows <= 1024 * LN_BWD_FEW_ROWS ? LN_BWD_FEW_ROWS : LN_BWD_ROWS; }
 constexpr int LN_MAX_IT = 4;   // column chunks per lane: d <= 64 * VEC * LN_MAX_IT
 
 template <typename T, int NIT>   // NIT column chunks of 16 bytes per lane: d <= 64 * VEC * NIT
@@ -624,7 +627,8 @@ dipaco_status launch_layernorm_fwd(const T* x, const T* g, const T* b, T* y, flo
 }
 
 size_t ln_bwd_partial_floats(int rows, int d) {
-  return (size_t)((rows + LN_BWD_ROWS - 1) / LN_BWD_ROWS) * 3 * d;
+  const int per = ln_bwd_rows(rows);
+  return (size_t)((rows + per - 1) / per) * 3 * d;
 }
 
 template <typename T>
@@ -642,7 +646,7 @@ dipaco_status launch_layernorm_bwd(const T* dy, const T* x, const T* g, const fl
   // (packed lds << 8 | resident; a host thread that loses a race merely asks again)
   static std::atomic<unsigned long long> occupancy[3];
   auto run = [&](auto kern, int variant) -> dipaco_status {
-    // Rows per workgroup: LN_BWD_ROWS, unless that gives a little more than a whole number of rounds of resident
+    // Rows per workgroup: ln_bwd_rows, unless 32 give a little more than a whole number of rounds of resident
     // workgroups (1024 workgroups over 768 slots run as two rounds): then as many rows as fill the slots once.
     const unsigned long long seen = occupancy[variant].load(std::memory_order_relaxed);
     int resident = (seen >> 8) == lds ? (int)(seen & 255) : 0;
@@ -653,9 +657,9 @@ dipaco_status launch_layernorm_bwd(const T* dy, const T* x, const T* g, const fl
       occupancy[variant].store(((unsigned long long)lds << 8) | (unsigned)resident, std::memory_order_relaxed);
     }
     const long slots = 256L * resident;
-    int rpb = LN_BWD_ROWS;
-    const long base_blocks = (rows + LN_BWD_ROWS - 1) / LN_BWD_ROWS;
-    if (base_blocks > slots && base_blocks < 2 * slots) {
+    int rpb = ln_bwd_rows(rows);
+    const long base_blocks = (rows + rpb - 1) / rpb;
+    if (rpb == LN_BWD_ROWS && base_blocks > slots && base_blocks < 2 * slots) {
       rpb = (int)((rows + slots - 1) / slots);
       rpb = (rpb + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK * ROWS_PER_BLOCK;
     }
