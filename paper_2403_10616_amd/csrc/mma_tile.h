@@ -30,7 +30,7 @@ template <typename T> __device__ __forceinline__ void load16_to_lds(const T* gpt
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
 }
 // the same with a wave-uniform base address (scalar registers) and a 32-bit per-lane byte offset
-__device__ __forceinline__ void load16_to_lds_at(const char* base, uint32_t byte_off, uint32_t lds_addr) {
+template <typename T> __device__ __forceinline__ void load16_to_lds_at(const T* base, uint32_t byte_off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
 }
 template <int N> __device__ __forceinline__ void wait_vmcnt() {   // vmcnt only: expcnt and lgkmcnt fields at maximum

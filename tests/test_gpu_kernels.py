@@ -356,3 +356,10 @@ def test_gemm_fitted_tiles_at_their_edges(dtype, tile, M, N, K):
             assert rel(W, X.double().T @ Y.double()) <= 1e-6
     finally:
         dp.dipaco_k_set_gemm_tile(0)
+
+
+@pytest.mark.parametrize("B,S,H,dh", [(3, 32, 3, 64), (5, 17, 1, 64), (2, 32, 3, 128), (1, 5, 1, 128), (5, 32, 1, 32), (1, 33, 1, 64)])
+def test_attention_of_short_sequences(B, S, H, dh):
+    """Up to 32 positions a wave owns a sequence and head: full and ragged workgroups of four, every head size; 33 is the first
+    length of the tiled kernel."""
+    test_attention_forward_backward(dp.BF16, B, S, H, dh, 1)
