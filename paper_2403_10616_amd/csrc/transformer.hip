@@ -520,16 +520,55 @@ __global__ void __launch_bounds__(1024) mean_loss_kernel(const float* __restrict
 constexpr int TG_WAVES = 16;
 constexpr int TG_UNROLL = 8;   // row loads in flight per wave
 constexpr int TG_MAX_D = 2048;   // widest model: 16 partial rows of 2048 floats = 128 KB of the 160 KB of LDS
-template <typename T>
+// SCAN: up to TG_SCAN_ROWS positions the workgroup finds its token's positions itself, by ballots over all of them (the
+// same increasing order), instead of the sort's seven launches of 4 - 12 us each in front of this one.
+constexpr int TG_SCAN_ROWS = 4 * TG_WAVES * WAVE;
+template <typename T, bool SCAN>
 __global__ void __launch_bounds__(TG_WAVES * WAVE) tok_grad_kernel(const T* __restrict__ dx,
                                                                    const int* __restrict__ offsets,
                                                                    const int* __restrict__ order,
+                                                                   const int* __restrict__ tokens, int rows,
                                                                    float* __restrict__ d_tok, int d) {
   constexpr int VEC = Vec16<T>::N;
-  extern __shared__ float tg_red[];   // [TG_WAVES][d]
+  extern __shared__ float tg_red[];   // [TG_WAVES][d], SCAN: then the positions
   const int v = blockIdx.x;
-  const int lo = offsets[v], hi = offsets[v + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int lo = 0, hi;
+  if constexpr (SCAN) {
+    __shared__ unsigned long long found[64];   // ballot of 64 positions at a time: chunk q of 1024, wave w at 16 q + w
+    int* const list = reinterpret_cast<int*>(tg_red + TG_WAVES * d);
+    unsigned long long mine[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = q * TG_WAVES * WAVE + threadIdx.x;
+      bool is = false;
+      if (j < rows) {
+        const int t = tokens[j];
+        is = (t < 0 ? 0 : (t >= (int)gridDim.x ? (int)gridDim.x - 1 : t)) == v;
+      }
+      mine[q] = __builtin_amdgcn_ballot_w64(is);
+      if (lane == 0) found[q * TG_WAVES + wave] = mine[q];
+    }
+    __syncthreads();
+    const int cnt = __builtin_popcountll(found[lane]);
+    int upto = cnt;   // inclusive scan over the 64 groups
+#pragma unroll
+    for (int s = 1; s < WAVE; s <<= 1) {
+      const int below = __shfl_up(upto, s, WAVE);
+      if (lane >= s) upto += below;
+    }
+    hi = __shfl(upto, WAVE - 1, WAVE);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int before = __shfl(upto - cnt, q * TG_WAVES + wave, WAVE);
+      if ((mine[q] >> lane) & 1) list[before + __builtin_popcountll(mine[q] & ((1ull << lane) - 1ull))] = q * TG_WAVES * WAVE + threadIdx.x;
+    }
+    __syncthreads();
+    order = list;
+  } else {
+    lo = offsets[v];
+    hi = offsets[v + 1];
+  }
   float* o = d_tok + (size_t)v * d;
   if (hi - lo <= 1) {   // most of the vocabulary: nothing to add
     for (int c = threadIdx.x * VEC; c < d; c += TG_WAVES * WAVE * VEC) {
@@ -761,22 +800,31 @@ template <typename T>
 dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, float* d_pos, int* scratch, int B,
                                int S, int d, int vocab, int max_seq, hipStream_t s) {
   const int rows = B * S;
-  int* count = scratch;
-  int* offsets = scratch + vocab;
-  int* order = offsets + vocab + 1;
-  int* sort_scratch = order + rows;
-  // positions grouped by token id, earlier positions first (stable sort: integer work only), so that every
-  // vocabulary row is summed in a fixed order
-  dipaco_status st = launch_key_offsets(tokens, rows, vocab, count, offsets, nullptr, s);
-  if (st != DIPACO_OK) return st;
-  st = launch_stable_sort_indices(tokens, rows, vocab, order, sort_scratch, s);
-  if (st != DIPACO_OK) return st;
   // 16 partial rows of d floats: above 64 KB (d_model > 1024) the kernel's dynamic-LDS limit has to be raised
-  static std::atomic<unsigned long long> tg_lds{0};
-  st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T>), TG_WAVES * TG_MAX_D * (int)sizeof(float), tg_lds);
-  if (st != DIPACO_OK) return st;
   if (d > TG_MAX_D) return fail(DIPACO_ESHAPE, "embedding gradient: d_model above 2048");
-  tok_grad_kernel<T><<<vocab, TG_WAVES * WAVE, TG_WAVES * d * sizeof(float), s>>>(dx, offsets, order, d_tok, d);
+  const size_t lds = TG_WAVES * d * sizeof(float);
+  static std::atomic<unsigned long long> tg_lds{0}, tg_scan_lds{0};   // per element type
+  dipaco_status st;
+  if (rows <= TG_SCAN_ROWS) {
+    st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, true>),
+                            TG_WAVES * TG_MAX_D * (int)sizeof(float) + TG_SCAN_ROWS * (int)sizeof(int), tg_scan_lds);
+    if (st != DIPACO_OK) return st;
+    tok_grad_kernel<T, true><<<vocab, TG_WAVES * WAVE, lds + rows * sizeof(int), s>>>(dx, nullptr, nullptr, tokens, rows, d_tok, d);
+  } else {
+    int* count = scratch;
+    int* offsets = scratch + vocab;
+    int* order = offsets + vocab + 1;
+    int* sort_scratch = order + rows;
+    // positions grouped by token id, earlier positions first (stable sort: integer work only), so that every
+    // vocabulary row is summed in a fixed order
+    st = launch_key_offsets(tokens, rows, vocab, count, offsets, nullptr, s);
+    if (st != DIPACO_OK) return st;
+    st = launch_stable_sort_indices(tokens, rows, vocab, order, sort_scratch, s);
+    if (st != DIPACO_OK) return st;
+    st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, false>), TG_WAVES * TG_MAX_D * (int)sizeof(float), tg_lds);
+    if (st != DIPACO_OK) return st;
+    tok_grad_kernel<T, false><<<vocab, TG_WAVES * WAVE, lds, s>>>(dx, offsets, order, nullptr, rows, d_tok, d);
+  }
   DIPACO_LAUNCH_CHECK();
   pos_grad_kernel<T><<<max_seq, 128, 0, s>>>(dx, d_pos, B, S, d);
   DIPACO_LAUNCH_CHECK();

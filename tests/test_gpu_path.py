@@ -246,3 +246,20 @@ def test_path_scores_match_oracle_and_training_loss(name, B, S, compute, mask):
     st = PathState(ctx, theta, B, S)
     st.fwd_bwd(tok, tgt)
     assert np.abs(host(st.nll) - host(nll)).max() <= (1e-5 if compute == dp.F32 else 5e-2)
+
+
+@pytest.mark.parametrize("B,S", [(1, 1), (64, 64), (17, 241), (3, 1000)])
+def test_embedding_gradient_on_both_sides_of_its_row_limit(B, S):
+    """Up to 4096 rows every vocabulary row's workgroup finds its positions by scanning the tokens, above by a sort; the two add
+    the same rows in the same order.  The token gradient of a path is checked against the oracle (fp32, rel 1e-4)."""
+    cfg = dict(layers_per_level=(1,), d_model=32, n_heads=1, d_head=32, d_mlp=32, vocab=40, max_seq=1000)
+    a, ctx = make_arch(cfg, dp.F32)
+    theta = gen.random_params(orc.param_count(a), seed=8, scale=0.08)
+    tok, tgt = _batch(cfg, B, S, 3, zipf=True)
+    tok = tok.copy()
+    tok[0, 0] = 39
+    st = PathState(ctx, theta, B, S)
+    st.fwd_bwd(tok, tgt)
+    _, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
+    worst, where = per_tensor_rel(orc.param_layout(a), host(st.grads).astype(np.float64), o_grad)
+    assert worst <= 1e-4, (worst, where)
