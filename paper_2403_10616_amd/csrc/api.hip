@@ -228,6 +228,9 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
 // ---- prefix features: forward through the blocks only, one set of layer buffers reused by every block -------
 struct FeaturePlan {
   size_t x_a, x_b, h, mean, rstd, qkv, o, lse, x_mid, u, act, logits, nll, n_valid, total;
+  // small batches: planes of the two products that write the residual stream, cut over K (1: not cut)
+  size_t planes = 0;
+  int splits_o = 1, splits_down = 1;
 };
 static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool with_head = false) {
   const dipaco_arch& a = c->arch;
@@ -241,6 +244,14 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   p.x_mid = take(T * d * es); p.u = take(T * F * es); p.act = take(T * F * es);   // u: GELU', which only a step keeps; the plan's size is part of the interface
   p.logits = p.nll = p.n_valid = 0;
   if (with_head) { p.logits = take(T * (size_t)a.vocab * es); p.nll = take(T * 4); p.n_valid = take(256); }
+  p.splits_o = gemm_raw_splits((int)T, (int)d, (int)A, es == 2);
+  p.splits_down = gemm_raw_splits((int)T, (int)d, (int)F, es == 2);
+  if (std::max(p.splits_o, p.splits_down) > 1) {
+    const size_t before = pos;
+    p.planes = take(std::max(p.splits_o, p.splits_down) * T * d * 4);
+    // what fits the static scratch without the planes keeps fitting it
+    if (before <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) { pos = before; p.splits_o = p.splits_down = 1; }
+  }
   p.total = pos;
   return p;
 }
@@ -257,26 +268,40 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
   T* x = buf(p.x_a);
   T* x_other = buf(p.x_b);
   TRY(launch_embed<T>(W + c->tok_emb, W + c->pos_emb, tokens, x, B, S, d, V, st));
+  // x_new = resid + X Wt + bias, and h = LayerNorm(x_new) under ln_g / ln_b (null: none follows)
+  auto residual = [&](const T* X, size_t w_off, size_t b_off, int K, int splits, const T* resid, T* x_new, const T* ln_g,
+                      const T* ln_b) -> dipaco_status {
+    if (splits > 1) {
+      GemmArgs g;
+      g.A = X; g.B = W + w_off; g.C = x_new; g.M = T_; g.N = d; g.K = K; g.lda = K; g.ldb = d; g.ldc = d;
+      g.bias = g.resid = g.aux_in = nullptr; g.aux_out = nullptr; g.act = 0; g.trans_a = g.trans_b = 0; g.out_f32 = 0;
+      g.splits = splits; g.partial = fbuf(p.planes); g.raw_planes = true;
+      TRY(launch_gemm<T>(g, st));
+      return launch_sum_layernorm<T>(fbuf(p.planes), splits, W + b_off, resid, x_new, ln_g, ln_b, ln_g ? buf(p.h) : nullptr, T_, d,
+                                     a.ln_eps, st);
+    }
+    TRY(gemm<T>(X, W + w_off, x_new, T_, d, K, K, d, d, false, false, W + b_off, resid, nullptr, nullptr, 0, false, 1, nullptr, st));
+    if (!ln_g) return DIPACO_OK;
+    return launch_layernorm_fwd<T>(x_new, ln_g, ln_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st);
+  };
+  // the LayerNorm in front of block l; behind the last block the final one, which only scoring needs
+  auto ln_g = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_g : targets ? W + c->lnf_g : nullptr; };
+  auto ln_b = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_b : targets ? W + c->lnf_b : nullptr; };
+  if (ln_g(0)) TRY(launch_layernorm_fwd<T>(x, ln_g(0), ln_b(0), buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st));
   for (int l = 0; l < c->n_layers; ++l) {
     const BlockOff& o = c->blocks[l];
-    TRY(launch_layernorm_fwd<T>(x, W + o.ln1_g, W + o.ln1_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st));
     TRY(gemm<T>(buf(p.h), W + o.w_qkv, buf(p.qkv), T_, 3 * A, d, d, 3 * A, 3 * A, false, false, W + o.b_qkv, nullptr,
                 nullptr, nullptr, 0, false, 1, nullptr, st));
     TRY(launch_attention_fwd<T>(buf(p.qkv), buf(p.o), fbuf(p.lse), B, S, H, dh, st));
-    TRY(gemm<T>(buf(p.o), W + o.w_o, buf(p.x_mid), T_, d, A, A, d, d, false, false, W + o.b_o, x, nullptr, nullptr, 0,
-                false, 1, nullptr, st));
-    TRY(launch_layernorm_fwd<T>(buf(p.x_mid), W + o.ln2_g, W + o.ln2_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d,
-                                a.ln_eps, st));
+    TRY(residual(buf(p.o), o.w_o, o.b_o, A, p.splits_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b));
     // no backward pass: GELU' is neither kept nor written (act 5)
     TRY(gemm<T>(buf(p.h), W + o.w_up, buf(p.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, nullptr, nullptr,
                 5, false, 1, nullptr, st));
-    TRY(gemm<T>(buf(p.act), W + o.w_down, x_other, T_, d, F, F, d, d, false, false, W + o.b_down, buf(p.x_mid), nullptr,
-                nullptr, 0, false, 1, nullptr, st));
+    TRY(residual(buf(p.act), o.w_down, o.b_down, F, p.splits_down, buf(p.x_mid), x_other, ln_g(l + 1), ln_b(l + 1)));
     std::swap(x, x_other);
   }
   if (!targets) return launch_mean_pool<T>(x, out, B, S, d, st);
-  // scoring: final LayerNorm, head, per-token negative log-likelihood, summed per document
-  TRY(launch_layernorm_fwd<T>(x, W + c->lnf_g, W + c->lnf_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st));
+  // scoring: head on the final LayerNorm, per-token negative log-likelihood, summed per document
   TRY(gemm<T>(buf(p.h), W + c->w_head, buf(p.logits), T_, V, d, d, V, V, false, false, nullptr, nullptr, nullptr, nullptr,
               0, false, 1, nullptr, st));
   float* nll = nll_out ? nll_out : fbuf(p.nll);

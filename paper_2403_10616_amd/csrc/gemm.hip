@@ -153,6 +153,11 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   if (a.out_f32 && (a.bias || a.resid || a.act)) return fail(DIPACO_EINVAL, "gemm: fp32 output takes no epilogue");
   if (a.colsum && (!a.colsum_partial || a.splits > 1 || a.out_f32 || !aligned16(a.colsum_partial)))
     return fail(DIPACO_EINVAL, "gemm: column sums need their scratch, no split-K and an output of the operands' type");
+  if (a.raw_planes) {
+    if (a.splits < 2 || a.out_f32 || a.trans_a || a.trans_b || a.bias || a.resid || a.act || a.colsum || !a.partial)
+      return fail(DIPACO_EINVAL, "gemm: raw planes come from a split forward product without an epilogue");
+    return launch_gemm_fit<T>(a, s);
+  }
   if (a.splits > 1 && (!a.out_f32 || a.bias || a.resid || a.act || !a.partial))
     return fail(DIPACO_EINVAL, "gemm: split-K needs fp32 output, a partial buffer and no epilogue");
   if (a.out_f32 && !(a.trans_a && !a.trans_b)) return fail(DIPACO_EUNSUPPORTED, "gemm: fp32 output only for A^T.B");

@@ -425,6 +425,7 @@ dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
   g.colsum_partial = a.colsum ? a.colsum_partial : nullptr;
   kern<<<(unsigned)blocks, 64 * FIT_WAVES, F::LDS, s>>>(g);
   DIPACO_LAUNCH_CHECK();
+  if (a.raw_planes) return g.splits == a.splits ? DIPACO_OK : fail(DIPACO_EINVAL, "gemm: raw planes take the splits of gemm_raw_splits");
   if (g.splits > 1) return launch_splitk_reduce(a.partial, static_cast<float*>(a.C), a.M, a.N, a.ldc, g.splits, s);
   if (a.colsum) return launch_sum_rows(a.colsum_partial, a.colsum, g.tiles_m, a.N, s, a.sum_batch);
   return DIPACO_OK;
@@ -462,7 +463,7 @@ int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
 
 template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_shape(const GemmArgs& a, hipStream_t s) {
   const int splits = std::max(1, a.splits);
-  const int t = pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
+  const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
   if constexpr (sizeof(T) == 2) {
     if constexpr (A_KC) {
@@ -477,6 +478,17 @@ template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_s
 }  // namespace
 
 void set_gemm_fit_shape(int t) { g_forced_fit = t; }
+
+// 32 x 896 x 3584 is 14 workgroups of 32 x 64, each a serial walk over 14 stages (10 - 12 us, a few CUs' worth of bandwidth); cut
+// into up to eight slices, two stages each, the chip reads the weights at once and the LayerNorm behind the product adds the planes.
+int gemm_raw_splits(int M, int N, int K, bool bf16_operands) {
+  const int bk = 8 * FIT_STEP / (bf16_operands ? 2 : 4);
+  const int tiles = ((M + 31) / 32) * ((N + 63) / 64), steps = (K + bk - 1) / bk;
+  const int want = std::min(std::min(8, steps), 256 / std::max(tiles, 1));
+  if (want < 2) return 1;
+  const int per = (steps + want - 1) / want;
+  return (steps + per - 1) / per;
+}
 
 double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous) {
   double best = 1e30;

@@ -107,6 +107,9 @@ struct GemmArgs {
   // colsum_partial = gemm_colsum_partial_floats(M, N) floats of scratch.  Not with split-K.
   float* colsum = nullptr;
   float* colsum_partial = nullptr;
+  // the `splits` planes of `partial` are the result (splits >= 2, from gemm_raw_splits): C, bias and residual are left to the
+  // kernel that reads them (launch_sum_layernorm)
+  bool raw_planes = false;
   SumBatch* sum_batch = nullptr;   // where the final sum of colsum_partial is deferred to (nullptr: summed at once)
 };
 size_t gemm_colsum_partial_floats(int M, int N);
@@ -121,6 +124,8 @@ template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& g, hipStream
 void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 x 128
 // C[m, n] = sum over z < splits of partial[z, m, n], in index order
 dipaco_status launch_splitk_reduce(const float* partial, float* C, int M, int N, long ldc, int splits, hipStream_t s);
+// K splits of a small forward product whose planes are summed by the next kernel: 1 = not worth it
+int gemm_raw_splits(int M, int N, int K, bool bf16_operands);
 // microseconds of a product of `splits` slices of K each with the best tile shape
 double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous);
 // 0 = automatic; 1 .. 4, 14 = gemm_fit.hip with 32x64, 64x128, 96x128, 128x128, 160x128 tiles, 5 = the direct-to-LDS kernel
@@ -147,6 +152,10 @@ dipaco_status launch_embed(const T* tok_emb, const T* pos_emb, const int* tokens
 template <typename T>
 dipaco_status launch_layernorm_fwd(const T* x, const T* g, const T* b, T* y, float* mean, float* rstd, int rows,
                                    int d, float eps, hipStream_t s);
+// x = sum of n_planes fp32 planes [rows, d] + bias + resid, rounded to T;  y (nullable, with g and b) = LayerNorm of x as stored
+template <typename T>
+dipaco_status launch_sum_layernorm(const float* planes, int n_planes, const T* bias, const T* resid, T* x, const T* g, const T* b,
+                                   T* y, int rows, int d, float eps, hipStream_t s);
 // dx = resid_grad (nullable) + LN backward of dy;  dg/db fp32 via `partial` ([ln_bwd_partial_floats] scratch);
 // dcol (nullable) = column sums of dx as stored: the bias gradient of the linear layer that dx is the output gradient of.
 template <typename T>

@@ -130,6 +130,74 @@ __global__ void __launch_bounds__(ROW_THREADS) ln_fwd_reg_kernel(const T* __rest
   }
 }
 
+// The sum of a split product's planes, its bias and residual, and the LayerNorm behind it, one wave per row: what the
+// product's epilogue and ln_fwd_reg_kernel do, in their order and on the value rounded to T, so that a small product may be
+// split over K without a pass of its own for the sum.
+template <typename T, int NIT>
+__global__ void __launch_bounds__(WAVE) sum_layernorm_kernel(const float* __restrict__ planes, int n_planes,
+                                                             const T* __restrict__ bias, const T* __restrict__ resid,
+                                                             T* __restrict__ x, const T* __restrict__ g, const T* __restrict__ b,
+                                                             T* __restrict__ y, int rows, int d, float eps) {
+  constexpr int VEC = Vec16<T>::N;
+  const int row = blockIdx.x, lane = threadIdx.x;
+  const size_t at = (size_t)row * d, plane = (size_t)rows * d;
+  float a[NIT][VEC], gg[NIT][VEC], bb[NIT][VEC];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int c = (lane + WAVE * it) * VEC;
+    if (c < d) {
+      float bi[VEC], re[VEC];
+      load_vec16(bias + c, bi);
+      load_vec16(resid + at + c, re);
+      if (y) { load_vec16(g + c, gg[it]); load_vec16(b + c, bb[it]); }
+      float4 v[8][VEC / 4];
+#pragma unroll
+      for (int z = 0; z < 8; ++z)
+        if (z < n_planes) {
+#pragma unroll
+          for (int q = 0; q < VEC / 4; ++q) v[z][q] = *reinterpret_cast<const float4*>(planes + z * plane + at + c + 4 * q);
+        }
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) {
+        float4 s = v[0][q];
+#pragma unroll
+        for (int z = 1; z < 8; ++z)
+          if (z < n_planes) { s.x += v[z][q].x; s.y += v[z][q].y; s.z += v[z][q].z; s.w += v[z][q].w; }
+        a[it][4 * q] = s.x; a[it][4 * q + 1] = s.y; a[it][4 * q + 2] = s.z; a[it][4 * q + 3] = s.w;
+      }
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) a[it][i] = to_f32(from_f32<T>((a[it][i] + bi[i]) + re[i]));
+      store_vec16(x + at + c, a[it]);
+    }
+  }
+  if (!y) return;
+  float s = 0.f;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+    if ((lane + WAVE * it) * VEC < d) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) s += a[it][i];
+    }
+  const float mu = wave_sum(s) / d;
+  float q = 0.f;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+    if ((lane + WAVE * it) * VEC < d) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) { float t = a[it][i] - mu; q += t * t; }
+    }
+  const float rs = 1.0f / sqrtf(wave_sum(q) / d + eps);
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int c = (lane + WAVE * it) * VEC;
+    if (c < d) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) a[it][i] = (a[it][i] - mu) * rs * gg[it][i] + bb[it][i];
+      store_vec16(y + at + c, a[it]);
+    }
+  }
+}
+
 // ---- LayerNorm backward -----------------------------------------------------------------------------------
 // Each workgroup owns rows_per_block consecutive rows (one wave per row at a time), writes dx for them and one
 // partial row of dg / db / column sums of dx; a second kernel sums the partial rows in block order.  The column
@@ -665,6 +733,21 @@ dipaco_status launch_layernorm_fwd(const T* x, const T* g, const T* b, T* y, flo
   return DIPACO_OK;
 }
 
+template <typename T>
+dipaco_status launch_sum_layernorm(const float* planes, int n_planes, const T* bias, const T* resid, T* x, const T* g, const T* b,
+                                   T* y, int rows, int d, float eps, hipStream_t s) {
+  constexpr int VEC = Vec16<T>::N;
+  const int chunks = (d + WAVE * VEC - 1) / (WAVE * VEC);
+  if (n_planes < 2 || n_planes > 8 || d > 2048) return fail(DIPACO_ESHAPE, "plane sum: 2 to 8 planes, d_model up to 2048");
+  auto run = [&](auto kern) { kern<<<rows, WAVE, 0, s>>>(planes, n_planes, bias, resid, x, g, b, y, rows, d, eps); };
+  if (chunks <= 1) run(sum_layernorm_kernel<T, 1>);
+  else if (chunks <= 2) run(sum_layernorm_kernel<T, 2>);
+  else if (chunks <= 4) run(sum_layernorm_kernel<T, 4>);
+  else if constexpr (VEC == 4) run(sum_layernorm_kernel<T, 8>);   // bf16 rows of up to 2048 are four chunks a lane
+  DIPACO_LAUNCH_CHECK();
+  return DIPACO_OK;
+}
+
 size_t ln_bwd_partial_floats(int rows, int d) {
   const int per = ln_bwd_rows(rows);
   return (size_t)((rows + per - 1) / per) * 3 * d;
@@ -895,6 +978,8 @@ dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipS
   template dipaco_status launch_layernorm_bwd<T>(const T*, const T*, const T*, const float*, const float*, const T*, \
                                                  T*, float*, float*, float*, float*, int, int, hipStream_t,         \
                                                  SumBatch*);                                                        \
+  template dipaco_status launch_sum_layernorm<T>(const float*, int, const T*, const T*, T*, const T*, const T*, T*, int, int, \
+                                                 float, hipStream_t);                                               \
   template dipaco_status launch_mean_pool<T>(const T*, float*, int, int, int, hipStream_t);                          \
   template dipaco_status launch_softmax_xent<T>(T*, const int*, const int*, float*, int, int, bool, hipStream_t);          \
   template dipaco_status launch_embed_bwd<T>(const T*, const int*, float*, float*, int*, int, int, int, int, int,    \

@@ -69,3 +69,30 @@ def test_static_scratch_refuses_what_does_not_fit():
     tok = torch.zeros((B, S), dtype=torch.int32, device=DEV)
     with pytest.raises(dp.DipacoError, match="static scratch"):
         dp.dipaco_path_prefix_features_static(ctx, master, master.to(torch.bfloat16), tok, B, S, out)
+
+
+@pytest.mark.parametrize("compute,tol", [(dp.F32, 1e-5), (dp.BF16, 1e-2)])
+@pytest.mark.parametrize("d_model,d_mlp,B,S", [(72, 1040, 1, 1), (264, 776, 3, 11), (520, 2056, 1, 32), (1032, 264, 2, 33), (64, 512, 90, 32)])
+def test_features_and_scores_of_small_batches(compute, tol, d_model, d_mlp, B, S):
+    """The products that write the residual stream are cut over K up to a few hundred tokens and their planes are added in
+    front of the LayerNorm: widths of one to four chunks a lane, two to eight planes, one cut and one whole product, no cut."""
+    cfg = dict(layers_per_level=(1, 1), d_model=d_model, n_heads=3, d_head=32, d_mlp=d_mlp, vocab=264, max_seq=40)
+    a, ctx = make_arch(cfg, compute)
+    theta = gen.random_params(orc.param_count(a), seed=61, scale=min(0.08, 1.5 / np.sqrt(d_model)))
+    ref = theta if compute == dp.F32 else gen.round_to_bf16(theta)
+    master = dev(theta.astype(np.float32))
+    lowp = master.to(torch.bfloat16) if compute == dp.BF16 else None
+    seqs = gen.uniform_tokens((B, S + 1), cfg["vocab"], 62)
+    tok, tgt = gen.split_inputs_targets(seqs)
+    print(f"small batch d={d_model} F={d_mlp} B={B} S={S} compute={compute}", flush=True)
+    tok_d, tgt_d = dev(tok.astype(np.int32)), dev(tgt.astype(np.int32))
+    out = torch.empty((B, d_model), device=DEV)
+    ws = torch.empty(dp.dipaco_features_workspace_bytes(ctx, B, S), dtype=torch.uint8, device=DEV)
+    dp.dipaco_path_prefix_features(ctx, master, lowp, tok_d, B, S, out, ws)
+    assert rel_l2(host(out), orc.prefix_features(ref, a, tok)) <= tol
+    doc, nll = torch.empty(B, device=DEV), torch.empty((B, S), device=DEV)
+    ws = torch.empty(dp.dipaco_score_workspace_bytes(ctx, B, S), dtype=torch.uint8, device=DEV)
+    dp.dipaco_path_score(ctx, master, lowp, tok_d, tgt_d, B, S, doc, nll, ws)
+    want = orc.path_token_nll(ref, a, tok, tgt)
+    assert rel_l2(host(nll), np.asarray(want).reshape(B, S)) <= tol
+    assert rel_l2(host(doc), orc.path_doc_scores(ref, a, tok, tgt)) <= tol
