@@ -133,25 +133,27 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
     return (uint32_t)(((long)min(k, klim - 1) * g.ldb + min(row, g.N - E - n0)) * (long)sizeof(T));
   };
   uint32_t off[LPS], ldst[LPS];
-  bool is_a[LPS];
 #pragma unroll
   for (int i = 0; i < LPS; ++i) {
     off[i] = source(i, 1 << 30);
     ldst[i] = smem_base + 1024 * (min(wave + FIT_WAVES * i, F::NL - 1) - wave);
-    is_a[i] = min(wave + FIT_WAVES * i, F::NL - 1) < F::NLA;
   }
-  auto issue = [&](int i, int kt, int slot) {   // load i of a stage that lies in the range
-    load16_to_lds_at(is_a[i] ? base_a + kt * adv_a : base_b + kt * adv_b, off[i],
-                     __builtin_amdgcn_readfirstlane(ldst[i] + slot * F::STAGE));
+  // Stages are requested in order: the bases move on with them.  Which operand load i belongs to is known at compile time but
+  // for the one i whose eight numbers straddle the operands.
+  auto issue = [&](int i, int slot) {   // load i of the next stage, inside the range
+    const bool a = FIT_WAVES * i + FIT_WAVES <= F::NLA || (FIT_WAVES * i < F::NLA && wave + FIT_WAVES * i < F::NLA);
+    load16_to_lds_at(a ? base_a : base_b, off[i], __builtin_amdgcn_readfirstlane(ldst[i] + slot * F::STAGE));
   };
-  auto issue_any = [&](int kt, int slot) {      // all loads of stage kt, if it exists
+  auto issued = [&] { base_a += adv_a; base_b += adv_b; };
+  auto issue_any = [&](int kt, int slot) {   // all loads of stage kt, the next one, if it exists
     if (kt >= nkt) return;
     const int klim = k_end - k_begin - kt * BK;
 #pragma unroll
     for (int i = 0; i < LPS; ++i) {
       if (klim < BK) off[i] = source(i, klim);   // the last stage, where the range ends inside it: clamped K
-      issue(i, kt, slot);
+      issue(i, slot);
     }
+    issued();
   };
 
   // ---- fragments ----
@@ -268,11 +270,12 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
       if (m < NR) read(SET, m, stage);
       if (steady) {
 #pragma unroll
-        for (int i = m * LPS / NM; i < (m + 1) * LPS / NM; ++i) issue(i, t + ST - 1, refill);
+        for (int i = m * LPS / NM; i < (m + 1) * LPS / NM; ++i) issue(i, refill);
       }
       mfma(Prev{}, m);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (steady) issued();
     slot = slot + 1 == ST ? 0 : slot + 1;
   };
   static_assert(NR <= NM, "a stage's fragments are read under the MFMAs of a step");
