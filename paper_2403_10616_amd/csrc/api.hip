@@ -1002,10 +1002,10 @@ dipaco_status dipaco_k_attention_bwd(int32_t dtype, const void* qkv, const void*
   return dtype == DIPACO_BF16
              ? launch_attention_bwd<bf16>(static_cast<const bf16*>(qkv), static_cast<const bf16*>(o),
                                           static_cast<const bf16*>(d_o), lse, static_cast<bf16*>(dqkv), dsum, colsum_out,
-                                          colsum_scratch, B, S, H, dh, st)
+                                          colsum_scratch, B, S, H, dh, st, nullptr, true)
              : launch_attention_bwd<float>(static_cast<const float*>(qkv), static_cast<const float*>(o),
                                            static_cast<const float*>(d_o), lse, static_cast<float*>(dqkv), dsum, colsum_out,
-                                           colsum_scratch, B, S, H, dh, st);
+                                           colsum_scratch, B, S, H, dh, st, nullptr, true);
 }
 
 }  // extern "C"

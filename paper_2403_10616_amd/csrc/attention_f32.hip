@@ -8,7 +8,7 @@
 //   forward, dQ:   S^T = K.Q^T  (rows = keys, columns = queries)  ->  O^T += V^T.P^T,   dQ^T += K^T.dS^T
 //   dK, dV:        S   = Q.K^T  (rows = queries, columns = keys)  ->  dV^T += dO^T.P,   dK^T += Q^T.dS
 //
-// One workgroup = 8 waves of 16 queries (keys), 128 in all; tiles of 32 keys (queries) go through registers into LDS, two
+// One workgroup = 8 waves of 16 queries (keys), 128 in all, or 4 waves where the launch is small (few_waves); tiles of 32 keys (queries) go through registers into LDS, two
 // stages, one barrier per tile, the next tile's loads in flight during this one's products.  Rows are kept DH + 4 floats
 // apart, which serves both kinds of read: 16-byte reads along a row (contraction over the head: lane l takes columns
 // 16 c + 4 (l / 16) .. + 3 of row l % 16, good for four products), and 4-byte reads across four rows (contraction over the
@@ -17,9 +17,12 @@
 // a 32-row one.
 // Bound: the fp32 matrix cores (a product of 2048 flop every 32 cycles and SIMD); a tile asks 64 (forward) to 160 (dK/dV)
 // of them per wave against 16-40 KB of LDS reads, a quarter of what LDS delivers in that time.
-// Measured on 8 sequences x 8 heads x 500 positions, head size 64: forward 49 us, dQ 63, dK / dV 79 (one thread per row on
-// the vector ALU: 375, 911, 1517), with the causal triangle's longest block setting the length of each launch.
+// Measured on 8 sequences x 8 heads x 500 positions, head size 64: forward 41 us, dQ 54, dK / dV 66 with four waves; 49, 64, 81
+// with eight (256 workgroups on 256 compute units, the causal triangle's longest block setting the length of each launch);
+// one thread per row on the vector ALU: 375, 911, 1517.
 // No atomics: every output element has exactly one writer and a fixed summation order.
+#include <type_traits>
+
 #include "kernels.h"
 #include "mma_tile.h"
 
@@ -27,8 +30,10 @@ namespace dipaco {
 
 namespace {
 
-constexpr int F_WAVES = 8, F_THREADS = 64 * F_WAVES;
-constexpr int F_ROWS = 16 * F_WAVES;   // queries (keys) per workgroup
+// NW waves of 16 queries (keys) make a workgroup: 8, or 4 where the launch would otherwise be about one workgroup per
+// compute unit and as long as the causal triangle's longest block
+constexpr int F_MANY = 8, F_FEW = 4;
+inline bool few_waves(int B, int S, int H) { return (long)B * H * ((S + 127) / 128) <= 512; }
 constexpr int F_TILE = 32;             // keys (queries) per tile
 
 template <int DH> constexpr int row_stride() { return DH + 4; }
@@ -49,17 +54,17 @@ __device__ __forceinline__ float max_groups(float v) {
   return v;
 }
 
-// Two operands' tiles of F_TILE rows: thread t moves float4 number t + F_THREADS i of tile i / (NLD / 2).
-template <int DH> struct TilePair {
+// Two operands' tiles of F_TILE rows: thread t moves float4 number t + 64 NW i of tile i / (NLD / 2).
+template <int DH, int NW> struct TilePair {
   static constexpr int VEC_ROW = DH / 4;                                   // 16-byte vectors per row
-  static constexpr int NLD = 2 * F_TILE * VEC_ROW / F_THREADS;             // per thread, both tiles: 1, 2 or 4
+  static constexpr int NLD = 2 * F_TILE * VEC_ROW / (64 * NW);             // per thread, both tiles: 1 .. 8
   static constexpr int PER_TILE = F_TILE * VEC_ROW;                        // vectors per tile: 256, 512, 1024
   f32x4 v[NLD];
   // rows at or beyond rows_total re-read the last valid row (callers give them zero weight)
   __device__ __forceinline__ void load(const float* t0, const float* t1, long ld0, long ld1, int row0, int rows_total) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      const int n = threadIdx.x + F_THREADS * i;
+      const int n = threadIdx.x + 64 * NW * i;
       const bool first = n < PER_TILE;
       const int m = first ? n : n - PER_TILE;
       const int row = min(row0 + m / VEC_ROW, rows_total - 1);
@@ -69,7 +74,7 @@ template <int DH> struct TilePair {
   __device__ __forceinline__ void store(float* stage) const {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      const int n = threadIdx.x + F_THREADS * i;
+      const int n = threadIdx.x + 64 * NW * i;
       const bool first = n < PER_TILE;
       const int m = first ? n : n - PER_TILE;
       *reinterpret_cast<f32x4*>(stage + (first ? 0 : tile_floats<DH>()) + (m / VEC_ROW) * row_stride<DH>() + 4 * (m % VEC_ROW)) = v[i];
@@ -119,9 +124,9 @@ template <int DH> __device__ __forceinline__ void store_row(float* row, const f3
     *reinterpret_cast<float4*>(row + 16 * d + 4 * g) =
         make_float4(acc[d][0] * scale, acc[d][1] * scale, acc[d][2] * scale, acc[d][3] * scale);
 }
-// Column sums of the workgroup's 128 output rows: over the 16 lanes of a group on the DPP lanes, then the waves in order.
-// red: LDS [F_WAVES][DH].  Every wave calls it; rows with valid = false count as zero.
-template <int DH>
+// Column sums of the workgroup's 16 NW output rows: over the 16 lanes of a group on the DPP lanes, then the waves in order.
+// red: LDS [NW][DH].  Every wave calls it; rows with valid = false count as zero.
+template <int DH, int NW>
 __device__ __forceinline__ void block_column_sums(const f32x4 (&acc)[DH / 16], float scale, bool valid, float* red,
                                                   float* __restrict__ out, int wave, int m, int g) {
   __syncthreads();   // red lies in LDS that was in use before
@@ -137,16 +142,16 @@ __device__ __forceinline__ void block_column_sums(const f32x4 (&acc)[DH / 16], f
       if (m == 0) red[wave * DH + 16 * d + 4 * g + e] = v;
     }
   __syncthreads();
-  for (int c = threadIdx.x; c < DH; c += F_THREADS) {
+  for (int c = threadIdx.x; c < DH; c += 64 * NW) {
     float s = red[c];
 #pragma unroll
-    for (int w = 1; w < F_WAVES; ++w) s += red[w * DH + c];
+    for (int w = 1; w < NW; ++w) s += red[w * DH + c];
     out[c] = s;
   }
 }
 
-template <int DH>
-__global__ void __launch_bounds__(F_THREADS, 2) attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o,
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o,
                                                              float* __restrict__ lse, int S, int H) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
   constexpr int STAGE = 2 * tile_floats<DH>();
@@ -154,14 +159,14 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_fwd_f32(const float* __rest
   const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
-  const int q0 = (gridDim.y - 1 - blockIdx.y) * F_ROWS;   // longest blocks first
+  const int q0 = (gridDim.y - 1 - blockIdx.y) * (16 * NW);   // longest blocks first
   const int qw0 = q0 + 16 * wave, q = qw0 + m;
   const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
-  const int ntiles = (min(S, q0 + F_ROWS) + F_TILE - 1) / F_TILE;
+  const int ntiles = (min(S, q0 + (16 * NW)) + F_TILE - 1) / F_TILE;
   f32x4 ot[DH / 16];
   zero_acc<DH>(ot);
   float mx = -INFINITY, l = 0.f;
-  TilePair<DH> next;
+  TilePair<DH, NW> next;
   next.load(base + A, base + 2 * A, ld, ld, 0, S);
   next.store(f_smem);
   for (int kt = 0; kt < ntiles; ++kt) {
@@ -215,8 +220,8 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_fwd_f32(const float* __rest
 }
 
 // dQ_i = scale * sum_{j<=i} p_ij (dO_i.v_j - D_i) k_j, with D_i = dO_i.o_i (also stored for the dK/dV kernel)
-template <int DH>
-__global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
                                                                 const float* __restrict__ d_o, const float* __restrict__ lse,
                                                                 float* __restrict__ dqkv, float* __restrict__ dsum,
                                                                 float* __restrict__ colsum, int S, int H) {
@@ -226,7 +231,7 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dq_f32(const float* __r
   const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
-  const int qb = gridDim.y - 1 - blockIdx.y, q0 = qb * F_ROWS;
+  const int qb = gridDim.y - 1 - blockIdx.y, q0 = qb * (16 * NW);
   const int qw0 = q0 + 16 * wave, q = qw0 + m;
   const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
   const long orow = ((long)b * S + q) * A + hd * DH;
@@ -241,10 +246,10 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dq_f32(const float* __r
   }
   const float L = q < S ? lse[(long)bh * S + q] : INFINITY;   // +inf beyond the sequence: probability 0
   if (g == 0 && q < S) dsum[(long)bh * S + q] = D;
-  const int ntiles = (min(S, q0 + F_ROWS) + F_TILE - 1) / F_TILE;
+  const int ntiles = (min(S, q0 + (16 * NW)) + F_TILE - 1) / F_TILE;
   f32x4 dqt[DH / 16];
   zero_acc<DH>(dqt);
-  TilePair<DH> next;
+  TilePair<DH, NW> next;
   next.load(base + A, base + 2 * A, ld, ld, 0, S);
   next.store(f_smem);
   for (int kt = 0; kt < ntiles; ++kt) {
@@ -271,12 +276,12 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dq_f32(const float* __r
   if (q < S) store_row<DH>(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, g, head_scale<DH>());
   // one row of partial column sums per (document, query block), this head's DH columns of dQ
   if (colsum)
-    block_column_sums<DH>(dqt, head_scale<DH>(), q < S, f_smem, colsum + ((long)b * gridDim.y + qb) * ld + hd * DH, wave, m, g);
+    block_column_sums<DH, NW>(dqt, head_scale<DH>(), q < S, f_smem, colsum + ((long)b * gridDim.y + qb) * ld + hd * DH, wave, m, g);
 }
 
 // dV_j = sum_{i>=j} p_ij dO_i;  dK_j = scale * sum_{i>=j} p_ij (dO_i.v_j - D_i) q_i
-template <int DH>
-__global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                                  const float* __restrict__ lse, const float* __restrict__ dsum,
                                                                  float* __restrict__ dqkv, float* __restrict__ colsum, int S,
                                                                  int H) {
@@ -287,7 +292,7 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dkv_f32(const float* __
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
   const float* gbase = d_o + (long)b * S * A + hd * DH;
-  const int kb = blockIdx.y, k0 = kb * F_ROWS;            // early key blocks are the long ones
+  const int kb = blockIdx.y, k0 = kb * (16 * NW);            // early key blocks are the long ones
   const int kw0 = k0 + 16 * wave, key = kw0 + m;
   const RowFrag<DH> kf = load_row<DH>(base + (long)key * ld + A, g, key < S);
   const RowFrag<DH> vf = load_row<DH>(base + (long)key * ld + 2 * A, g, key < S);
@@ -295,7 +300,7 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dkv_f32(const float* __
   zero_acc<DH>(dkt);
   zero_acc<DH>(dvt);
   const int first = k0 / F_TILE, ntiles = (S + F_TILE - 1) / F_TILE;
-  TilePair<DH> next;
+  TilePair<DH, NW> next;
   float next_stat = 0.f;
   // statistics of a tile's queries: threads 0..31 move lse (+inf beyond the sequence: probability 0), 32..63 D
   auto load = [&](int qt) {
@@ -349,33 +354,37 @@ __global__ void __launch_bounds__(F_THREADS, 2) attn_bwd_dkv_f32(const float* __
   }
   if (colsum) {
     float* cs = colsum + ((long)b * gridDim.y + kb) * ld + hd * DH;
-    block_column_sums<DH>(dkt, head_scale<DH>(), key < S, f_smem, cs + A, wave, m, g);
-    block_column_sums<DH>(dvt, 1.0f, key < S, f_smem, cs + 2 * A, wave, m, g);
+    block_column_sums<DH, NW>(dkt, head_scale<DH>(), key < S, f_smem, cs + A, wave, m, g);
+    block_column_sums<DH, NW>(dvt, 1.0f, key < S, f_smem, cs + 2 * A, wave, m, g);
   }
 }
 
 template <int DH> constexpr int fwd_lds() { return 2 * 2 * tile_floats<DH>() * (int)sizeof(float); }
 template <int DH> constexpr int dkv_lds() { return 2 * (2 * tile_floats<DH>() + 2 * F_TILE) * (int)sizeof(float); }
 
-template <int DH>
-dipaco_status fwd(const float* qkv, float* o, float* lse, int B, int S, int H, hipStream_t s) {
+template <int DH, int NW>
+dipaco_status fwd_rows(const float* qkv, float* o, float* lse, int B, int S, int H, hipStream_t s) {
   static std::atomic<unsigned long long> lds{0};
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_f32<DH>), fwd_lds<DH>(), lds)) return st;
-  attn_fwd_f32<DH><<<dim3(B * H, (S + F_ROWS - 1) / F_ROWS), F_THREADS, fwd_lds<DH>(), s>>>(qkv, o, lse, S, H);
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_f32<DH, NW>), fwd_lds<DH>(), lds)) return st;
+  attn_fwd_f32<DH, NW><<<dim3(B * H, (S + 16 * NW - 1) / (16 * NW)), 64 * NW, fwd_lds<DH>(), s>>>(qkv, o, lse, S, H);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
 template <int DH>
+dipaco_status fwd(const float* qkv, float* o, float* lse, int B, int S, int H, hipStream_t s) {
+  return few_waves(B, S, H) ? fwd_rows<DH, F_FEW>(qkv, o, lse, B, S, H, s) : fwd_rows<DH, F_MANY>(qkv, o, lse, B, S, H, s);
+}
+template <int DH, int NW>
 dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv, float* dsum,
                   float* colsum, int B, int S, int H, hipStream_t s) {
-  static_assert(F_WAVES * DH <= 2 * 2 * tile_floats<DH>(), "the column sums' scratch fits in the stages");
+  static_assert(NW * DH <= 2 * 2 * tile_floats<DH>(), "the column sums' scratch fits in the stages");
   static std::atomic<unsigned long long> dq{0}, dkv{0};
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH>), fwd_lds<DH>(), dq)) return st;
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH>), dkv_lds<DH>(), dkv)) return st;
-  const dim3 grid(B * H, (S + F_ROWS - 1) / F_ROWS);
-  attn_bwd_dq_f32<DH><<<grid, F_THREADS, fwd_lds<DH>(), s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H);
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>), fwd_lds<DH>(), dq)) return st;
+  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>), dkv_lds<DH>(), dkv)) return st;
+  const dim3 grid(B * H, (S + 16 * NW - 1) / (16 * NW));
+  attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H);
   DIPACO_LAUNCH_CHECK();
-  attn_bwd_dkv_f32<DH><<<grid, F_THREADS, dkv_lds<DH>(), s>>>(qkv, d_o, lse, dsum, dqkv, colsum, S, H);
+  attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv, d_o, lse, dsum, dqkv, colsum, S, H);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
@@ -389,17 +398,24 @@ dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, i
   return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
 }
 
+size_t attention_bwd_colsum_rows_f32(int B, int S, int H) { return (size_t)B * ((S + (few_waves(B, S, H) ? 63 : 127)) / (few_waves(B, S, H) ? 64 : 128)); }
+
 dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv,
                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
-                                       hipStream_t s, SumBatch* batch) {
+                                       hipStream_t s, SumBatch* batch, bool coarse) {
   float* partial = colsum_out ? colsum_partial : nullptr;
-  dipaco_status st;
-  if (dh == 32) st = bwd<32>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
-  else if (dh == 64) st = bwd<64>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
-  else if (dh == 128) st = bwd<128>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
-  else return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
+  const bool few = few_waves(B, S, H) && !(coarse && colsum_out);
+  auto run = [&](auto NWc) -> dipaco_status {
+    constexpr int NW = decltype(NWc)::value;
+    if (dh == 32) return bwd<32, NW>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+    if (dh == 64) return bwd<64, NW>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+    if (dh == 128) return bwd<128, NW>(qkv, o, d_o, lse, dqkv, dsum, partial, B, S, H, s);
+    return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
+  };
+  const dipaco_status st = few ? run(std::integral_constant<int, F_FEW>{}) : run(std::integral_constant<int, F_MANY>{});
   if (st != DIPACO_OK || !colsum_out) return st;
-  return launch_sum_rows(colsum_partial, colsum_out, B * ((S + F_ROWS - 1) / F_ROWS), 3 * H * dh, s, batch);
+  const int per = 16 * (few ? F_FEW : F_MANY);
+  return launch_sum_rows(colsum_partial, colsum_out, B * ((S + per - 1) / per), 3 * H * dh, s, batch);
 }
 
 }  // namespace dipaco

@@ -218,7 +218,9 @@ dipaco_status launch_attention_fwd(const T* qkv, T* o, float* lse, int B, int S,
 template <typename T>
 dipaco_status launch_attention_bwd(const T* qkv, const T* o, const T* d_o, const float* lse, T* dqkv,
                                    float* dscratch, float* colsum_out, float* colsum_partial, int B, int S, int H,
-                                   int dh, hipStream_t s, SumBatch* batch = nullptr);
+                                   int dh, hipStream_t s, SumBatch* batch = nullptr, bool coarse = false);
+// coarse: colsum_partial holds only B * ceil(S / 128) rows (the kernel-level entry point's documented scratch)
+size_t attention_bwd_colsum_rows_f32(int B, int S, int H);
 size_t attention_bwd_colsum_floats(int B, int S, int H, int dh);
 
 // ---- probe.hip: register-only instruction-issue loops (measurement aid) --------------------------------
@@ -237,7 +239,7 @@ dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf
 dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, int B, int S, int H, int dh, hipStream_t s);
 dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv,
                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
-                                       hipStream_t s, SumBatch* batch = nullptr);
+                                       hipStream_t s, SumBatch* batch, bool coarse);
 // bf16 kernels: 0: a workgroup takes a long and a short block of the causal triangle; 1: one block per workgroup, longest first
 void set_attention_single_block(int on);
 
