@@ -442,12 +442,16 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || (bf16_op
 // Microseconds of `tiles` tiles over K: rounds of 256 workgroups x (fixed + per 1000 of K).  Fitted to launches of 256 .. 8192
 // rows, K 64 .. 8192 (rel. error 15 %): 3000 x 896 x 3584 bf16 34.8 / 26.0 / 28.8 / 33.7 us for shapes 2 .. 5, 5700 x 896 x 3584
 // 51 / 49 / 53 / 38, 1000 x 896 x 3584 20 (shape 1) / 21 / 24 / 28, 256 x 896 x 3584 10.5 / 19.
-double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands) {
+// The 64 x 128 shape runs two workgroups on a compute unit.  In a weight gradient, whose workgroups all end together, 257 .. 512
+// of them are one round of twice the length, and a third 256 behind them lands two to a unit again: 256 x 768 over 2^20 rows in
+// fp32 2930 us in 504 workgroups, 3500 - 3900 in 768, 2980 in 1536.
+double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
   const int bm = 32 * t, bn = t == 1 ? 64 : 128;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
   const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
-  return 3.0 + (double)((tiles + 255) / 256) * (f + k * K * 1e-3);
+  const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
+  return 3.0 + (double)rounds * (f + k * K * 1e-3);
 }
 
 std::atomic<int> g_forced_fit{0};
@@ -460,7 +464,7 @@ int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   int best = 1;
   for (int t = 2; t <= 5; ++t)
     if (fit_built(t, bf16_operands, a_kc) &&
-        shape_cost(t, M, N, K, splits, bf16_operands) < shape_cost(best, M, N, K, splits, bf16_operands)) best = t;
+        shape_cost(t, M, N, K, splits, bf16_operands, a_kc) < shape_cost(best, M, N, K, splits, bf16_operands, a_kc)) best = t;
   return best;
 }
 
@@ -496,7 +500,7 @@ int gemm_raw_splits(int M, int N, int K, bool bf16_operands) {
 double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous) {
   double best = 1e30;
   for (int t = 1; t <= 5; ++t)
-    if (fit_built(t, bf16_operands, a_k_contiguous)) best = std::min(best, shape_cost(t, M, N, K, splits, bf16_operands));
+    if (fit_built(t, bf16_operands, a_k_contiguous)) best = std::min(best, shape_cost(t, M, N, K, splits, bf16_operands, a_k_contiguous));
   return best;
 }
 
