@@ -141,7 +141,7 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   if ((a.trans_a ? a.M : a.K) % VEC || (a.trans_b ? a.K : a.N) % VEC || a.lda % VEC || a.ldb % VEC)
     return fail(DIPACO_ESHAPE, "gemm: contiguous extents and leading dimensions must be multiples of 16 bytes");
   if (a.ldc % 8 || a.N % 8) return fail(DIPACO_ESHAPE, "gemm: N and ldc must be multiples of 8");
-  // per-thread element offsets are 32-bit
+  // the declared range; inside it gemm_fit.hip addresses every operand (rows too far apart for its 32-bit offsets: in 64 bits)
   const long ext_a = (a.trans_a ? 64 : (long)a.M) * a.lda + a.M, ext_b = (a.trans_b ? (long)a.N : 64) * a.ldb + a.N;
   if (ext_a >= (1L << 32) || ext_b >= (1L << 32)) return fail(DIPACO_ESHAPE, "gemm: operand above 2^32 elements");
   if (!aligned16(a.A) || !aligned16(a.B) || !aligned16(a.C) || !aligned16(a.bias) || !aligned16(a.resid) ||

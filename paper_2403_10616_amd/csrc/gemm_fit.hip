@@ -24,6 +24,8 @@
 // barrier -> the stage t - 1 occupied is refilled, the fragments of t are read, and the MFMAs of t - 1 run over both.
 // K beyond the range: loads re-read the last valid K, groups beyond it skip their MFMAs, a group that straddles it zeroes
 // the excess in its fragments (both operands).  Rows beyond M or N re-read the last ones and are not stored.
+// A lane's byte offsets into a stage's operand tile are 32-bit; rows so far apart that a tile spans 4 GiB or more take the
+// 32 x 64 tile with 64-bit addresses (FAR).
 #include <algorithm>
 #include <type_traits>
 
@@ -92,7 +94,14 @@ __device__ __forceinline__ void fit_source(int jj, int lane, int& row, int& k) {
   }
 }
 
-template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST>
+// Bytes from the first to past the last byte that a stage's loads touch in one operand tile, `rows` x `depth` of K at most
+// (both clamped to the operand); what a lane's offset has to hold.
+inline uint64_t fit_span(bool k_contiguous, int rows, int depth, int extent, int K, long ld, int elem) {
+  const uint64_t r = std::min(rows, extent), k = std::min(depth, K);
+  return (k_contiguous ? (r - 1) * ld + k : (k - 1) * ld + r) * elem;
+}
+
+template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST, bool FAR>
 __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmDev g) {
   using F = Fit<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
   constexpr int BM = F::BM, BN = F::BN, E = F::E, KD = F::KD, BK = F::BK, ROWB = F::ROWB, LPS = F::LPS;
@@ -120,19 +129,21 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
   const long adv_a = A_KC ? ROWB : (long)BK * g.lda * (long)sizeof(T), adv_b = B_KC ? ROWB : (long)BK * g.ldb * (long)sizeof(T);
   const uint32_t smem_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + 1024 * wave);
   // byte offset of load i relative to its operand's base at the stage's first K; klim: K left in the range there
-  auto source = [&](int i, int klim) -> uint32_t {
+  using Off = std::conditional_t<FAR, uint64_t, uint32_t>;
+  auto source = [&](int i, int klim) -> Off {
     const int j = min(wave + FIT_WAVES * i, F::NL - 1);
     int row, k;
     if (j < F::NLA) {
       fit_source<T, A_KC, ROWB, F::RA, G>(j, lane, row, k);
-      if (A_KC) return (uint32_t)(((long)min(row, g.M - 1 - m0) * g.lda + min(k, klim - E)) * (long)sizeof(T));
-      return (uint32_t)(((long)min(k, klim - 1) * g.lda + min(row, g.M - E - m0)) * (long)sizeof(T));
+      if (A_KC) return (Off)(((long)min(row, g.M - 1 - m0) * g.lda + min(k, klim - E)) * (long)sizeof(T));
+      return (Off)(((long)min(k, klim - 1) * g.lda + min(row, g.M - E - m0)) * (long)sizeof(T));
     }
     fit_source<T, B_KC, ROWB, F::RB, G>(j - F::NLA, lane, row, k);
-    if (B_KC) return (uint32_t)(((long)min(row, g.N - 1 - n0) * g.ldb + min(k, klim - E)) * (long)sizeof(T));
-    return (uint32_t)(((long)min(k, klim - 1) * g.ldb + min(row, g.N - E - n0)) * (long)sizeof(T));
+    if (B_KC) return (Off)(((long)min(row, g.N - 1 - n0) * g.ldb + min(k, klim - E)) * (long)sizeof(T));
+    return (Off)(((long)min(k, klim - 1) * g.ldb + min(row, g.N - E - n0)) * (long)sizeof(T));
   };
-  uint32_t off[LPS], ldst[LPS];
+  Off off[LPS];
+  uint32_t ldst[LPS];
 #pragma unroll
   for (int i = 0; i < LPS; ++i) {
     off[i] = source(i, 1 << 30);
@@ -142,7 +153,9 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
   // for the one i whose eight numbers straddle the operands.
   auto issue = [&](int i, int slot) {   // load i of the next stage, inside the range
     const bool a = FIT_WAVES * i + FIT_WAVES <= F::NLA || (FIT_WAVES * i < F::NLA && wave + FIT_WAVES * i < F::NLA);
-    load16_to_lds_at(a ? base_a : base_b, off[i], __builtin_amdgcn_readfirstlane(ldst[i] + slot * F::STAGE));
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(ldst[i] + slot * F::STAGE);
+    if constexpr (FAR) load16_to_lds((a ? base_a : base_b) + off[i], dst);
+    else load16_to_lds_at(a ? base_a : base_b, off[i], dst);
   };
   auto issued = [&] { base_a += adv_a; base_b += adv_b; };
   auto issue_any = [&](int kt, int slot) {   // all loads of stage kt, the next one, if it exists
@@ -406,10 +419,15 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_kernel(const GemmD
   }
 }
 
-template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST>
+template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST, bool FAR = false>
 dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
   using F = Fit<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
-  auto kern = gemm_fit_kernel<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST>;
+  if constexpr (!FAR) {
+    constexpr uint64_t most = 1ull << 32;
+    if (fit_span(A_KC, F::BM, F::BK, a.M, a.K, a.lda, sizeof(T)) >= most || fit_span(B_KC, F::BN, F::BK, a.N, a.K, a.ldb, sizeof(T)) >= most)
+      return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3, true>(a, s);
+  }
+  auto kern = gemm_fit_kernel<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST, FAR>;
   static std::atomic<unsigned long long> lds_set{0};   // per instantiation
   if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), F::LDS, lds_set)) return e;
   GemmDev g;

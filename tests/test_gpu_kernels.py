@@ -363,3 +363,30 @@ def test_attention_of_short_sequences(B, S, H, dh):
     """Up to 32 positions a wave owns a sequence and head: full and ragged workgroups of four, every head size; 33 is the first
     length of the tiled kernel."""
     test_attention_forward_backward(dp.BF16, B, S, H, dh, 1)
+
+
+@pytest.mark.parametrize("dtype,trans_a,trans_b,M,N,K", [
+    (dp.F32, False, False, 64, 8, 40_000_000),     # A: 31 rows of a 32-row tile are 4.96e9 bytes apart
+    (dp.F32, False, True, 8, 64, 40_000_000),      # B^T: 63 rows of 160 MB
+    (dp.BF16, True, False, 40_000_000, 8, 64),     # A: 63 K-rows of 80 MB
+    (dp.F32, True, False, 8, 9_000_000, 304),      # B: 127 K-rows of 36 MB
+])
+def test_gemm_operand_tiles_that_span_more_than_4_gib(dtype, trans_a, trans_b, M, N, K):
+    """Accepted sizes (fewer than 2^32 elements an operand, or 64 K-rows of it) whose byte offsets inside one tile pass 2^32.
+    Operands of small whole numbers, zero but for a few K (or a few rows of the long side): every product is exact."""
+    print(f"gemm far dtype={dtype} ta={trans_a} tb={trans_b} M={M} N={N} K={K}", flush=True)
+    g = torch.Generator().manual_seed(5)
+    A = torch.zeros((K, M) if trans_a else (M, K), dtype=TDT[dtype], device=DEV)
+    B = torch.zeros((N, K) if trans_b else (K, N), dtype=TDT[dtype], device=DEV)
+    pick = lambda n: torch.tensor(sorted({0, 1, n // 3, n // 2 + 1, n - 2, n - 1}) if n > 4096 else list(range(n)))
+    km, kn, kk = pick(M), pick(N), pick(K)
+    a = torch.randint(-3, 4, (len(km), len(kk)), generator=g).double()
+    b = torch.randint(-3, 4, (len(kk), len(kn)), generator=g).double()
+    put = lambda t, r, c, v: t.__setitem__((r.to(DEV)[:, None], c.to(DEV)[None, :]), v.to(TDT[dtype]).to(DEV))
+    put(A, *((kk, km, a.T) if trans_a else (km, kk, a)))
+    put(B, *((kn, kk, b.T) if trans_b else (kk, kn, b)))
+    C = torch.full((M, N), float("nan"), dtype=torch.float32 if trans_a else TDT[dtype], device=DEV)
+    dp.dipaco_k_gemm(dtype, trans_a, trans_b, trans_a, M, N, K, A, B, C)
+    got = C[km.to(DEV)][:, kn.to(DEV)].double().cpu()
+    assert torch.equal(got, a @ b)
+    assert float(C.double().abs().sum()) == float((a @ b).abs().sum())   # and zero everywhere else
