@@ -32,8 +32,9 @@
 // Head sizes.  A tile is kept as panels of 64 rows x 64 columns (128-byte rows), so one swizzle and one set of
 // fragment offsets serve every head size: head size 128 is two panels side by side, head size 32 uses the first half
 // of one panel's columns (the lanes whose 16 bytes fall into the other half fetch a valid chunk again, so that no
-// load is conditional).  Measured on 8 sequences x 8 heads x 512 positions, head size 128: forward 17 us, dQ 29, dK / dV 38
-// (one-thread-per-row kernels: 1470, 1990 and 20970 us).
+// load is conditional).  Head sizes 32 and 128 keep 16 bits of the probabilities and of dS in the second products and sum
+// rows in fp32 (split_p below); head size 64 rounds them to bf16.  Measured on 8 sequences x 8 heads x 512 positions, head
+// size 128: forward 19 us, backward 67 (with operands rounded to bf16 16 and 55, one-thread-per-row kernels 1470 and 22960).
 #include <type_traits>
 
 #include "kernels.h"
@@ -67,6 +68,31 @@ template <int E0> __device__ __forceinline__ uint4 pack8(const f32x16& v) {
   bf16x8 o = {(bf16)v[E0 + 0], (bf16)v[E0 + 1], (bf16)v[E0 + 2], (bf16)v[E0 + 3],
               (bf16)v[E0 + 4], (bf16)v[E0 + 5], (bf16)v[E0 + 6], (bf16)v[E0 + 7]};
   return __builtin_bit_cast(uint4, o);
+}
+
+// Probabilities (and dS) as the operand of a second product.  Head size 64: rounded to bf16.  Head sizes 32 and 128 (SPLIT): as the
+// sum of two bf16 numbers, the value rounded and what the rounding left over, one product each, 16 significant bits in all.  The
+// rounding of the bf16 output (2^-9) then hides the operand's (2^-18): over 17 .. 2048 positions the errors against 64 bits are
+// those of fp32 operands (o 1.3e-3 .. 1.6e-3, dq, dk, dv 1.6e-3 .. 1.7e-3, lse below 1e-5; operands rounded to bf16: 1.3e-3 ..
+// 2.1e-3, 2.0e-3 .. 2.6e-3, 1e-3 .. 4e-3).
+template <int DH> constexpr bool split_p() { return DH != 64; }
+template <bool SPLIT> struct PFrag { uint4 hi; };
+template <> struct PFrag<true> { uint4 hi, lo; };
+template <bool SPLIT, int E0> __device__ __forceinline__ PFrag<SPLIT> p_frag(const f32x16& v) {
+  PFrag<SPLIT> p;
+  p.hi = pack8<E0>(v);
+  if constexpr (SPLIT) {
+    const bf16x8 hi = __builtin_bit_cast(bf16x8, p.hi);
+    bf16x8 lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lo[e] = (bf16)(v[E0 + e] - (float)hi[e]);
+    p.lo = __builtin_bit_cast(uint4, lo);
+  }
+  return p;
+}
+template <bool SPLIT> __device__ __forceinline__ f32x16 mfma_p(const uint4& a, const PFrag<SPLIT>& p, f32x16 c) {
+  if constexpr (SPLIT) c = mfma16(a, p.lo, c);
+  return mfma16(a, p.hi, c);
 }
 
 __device__ __forceinline__ int swz64(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
@@ -198,25 +224,34 @@ template <int DT, int NT>
 __device__ __forceinline__ void mma_transposed(f32x16 (&acc)[DT], const char* tile, const TrOff& to, const f32x16 (&src)[NT], int t0) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const uint4 p0 = pack8<0>(src[t]), p1 = pack8<8>(src[t]);
+    if constexpr (split_p<32 * DT>()) {   // half a fragment at a time: a packed half takes the registers of the values it came from
+      const auto p0 = p_frag<true, 0>(src[t]);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * (t0 + t)), p0, acc[dt]);
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * (t0 + t) + 1), p1, acc[dt]);
+      for (int dt = 0; dt < DT; ++dt) acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * (t0 + t)), p0, acc[dt]);
+      const auto p1 = p_frag<true, 8>(src[t]);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * (t0 + t) + 1), p1, acc[dt]);
+    } else {
+      const auto p0 = p_frag<false, 0>(src[t]), p1 = p_frag<false, 8>(src[t]);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * (t0 + t)), p0, acc[dt]);
+        acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * (t0 + t) + 1), p1, acc[dt]);
+      }
     }
   }
 }
 
-// The same with the probabilities already packed to bf16: pk[t][0 / 1] = pack8<0 / 8>(src[t]).
+// The same with the probabilities already packed: pk[t][0 / 1] = p_frag<.., 0 / 8>(src[t]).
 template <int DT>
 __device__ __forceinline__ void mma_transposed_packed(f32x16 (&acc)[DT], const char* tile, const TrOff& to,
-                                                      const uint4 (&pk)[2][2]) {
+                                                      const PFrag<split_p<32 * DT>()> (&pk)[2][2]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t), pk[t][0], acc[dt]);
-      acc[dt] = mfma16(tr_read(tile, to, dt, 2 * t + 1), pk[t][1], acc[dt]);
+      acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * t), pk[t][0], acc[dt]);
+      acc[dt] = mfma_p(tr_read(tile, to, dt, 2 * t + 1), pk[t][1], acc[dt]);
     }
 }
 // acc + the eight bf16 values of v, two per instruction (v_dot2c_f32_bf16 with a vector of ones: products with 1 and
@@ -229,6 +264,19 @@ __device__ __forceinline__ float add8_bf16(float acc, const uint4& v) {
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v.z), ones, acc, false);
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v.w), ones, acc, false);
   return acc;
+}
+
+// l + this lane's sixteen probabilities: what the second product multiplies with
+template <bool SPLIT>
+__device__ __forceinline__ float add_row_sum(float l, const f32x16& p, const PFrag<SPLIT>& p0, const PFrag<SPLIT>& p1) {
+  if constexpr (SPLIT) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s += p[e];
+    return l + s;
+  } else {
+    return add8_bf16(add8_bf16(l, p0.hi), p1.hi);
+  }
 }
 
 // store 4 consecutive head columns (accumulator elements 4g..4g+3 of a transposed-output tile) as bf16
@@ -372,17 +420,17 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(c
           for (int e = 0; e < 16; ++e) ot[dt][e] *= corr;
         m = mn;
       }
-      // probabilities, rounded to bf16 once: the rounded values are both what the matrix core multiplies with V and
-      // what the row sum adds up (two per instruction), so numerator and denominator of the softmax agree exactly.
+      // probabilities.  Head size 64: rounded to bf16 once: the rounded values are both what the matrix core multiplies with V
+      // and what the row sum adds up (two per instruction), so numerator and denominator of the softmax agree exactly.
       // l is this lane's half of the row (keys 4h + 0..3 of every eight); the halves meet after the last tile.
-      uint4 pk[2][2];
+      PFrag<split_p<DH>()> pk[2][2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) st[t][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[t][e], sc, -m));
-        pk[t][0] = pack8<0>(st[t]);
-        pk[t][1] = pack8<8>(st[t]);
-        l = add8_bf16(add8_bf16(l, pk[t][0]), pk[t][1]);
+        pk[t][0] = p_frag<split_p<DH>(), 0>(st[t]);
+        pk[t][1] = p_frag<split_p<DH>(), 8>(st[t]);
+        l = add_row_sum(l, st[t], pk[t][0], pk[t][1]);
       }
       mma_transposed_packed(ot, v_, to, pk);
     }
@@ -463,14 +511,14 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 1 : 3) attn_fwd_short_
   const float sc = score_scale<DH>() * LOG2E, m = mx * sc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) st[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], sc, -m));
-  const uint4 p0 = pack8<0>(st), p1 = pack8<8>(st);
-  float l = add8_bf16(add8_bf16(0.f, p0), p1);
+  const auto p0 = p_frag<split_p<DH>(), 0>(st), p1 = p_frag<split_p<DH>(), 8>(st);
+  float l = add_row_sum(0.f, st, p0, p1);
   f32x16 ot[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     zero(ot[dt]);
-    ot[dt] = mfma16(tr_read(v_, to, dt, 0), p0, ot[dt]);
-    ot[dt] = mfma16(tr_read(v_, to, dt, 1), p1, ot[dt]);
+    ot[dt] = mfma_p(tr_read(v_, to, dt, 0), p0, ot[dt]);
+    ot[dt] = mfma_p(tr_read(v_, to, dt, 1), p1, ot[dt]);
   }
   l += __shfl_xor(l, 32, WAVE);
   // O^T to LDS as rows of O, in K's place (its reads are done: the scores above needed them), under the tiles' swizzle
@@ -612,7 +660,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
 template <int DH> constexpr int dkv_stage() { return 2 * tile_bytes<DH>() + 2 * 64 * (int)sizeof(float); }   // Q | dO | -lse2 | D
 
 template <int DH>
-__global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
+__global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
                                                                    const bf16* __restrict__ d_o,
                                                                    const float* __restrict__ dsum,
                                                                    bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H, int single) {

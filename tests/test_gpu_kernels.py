@@ -390,3 +390,33 @@ def test_gemm_operand_tiles_that_span_more_than_4_gib(dtype, trans_a, trans_b, M
     got = C[km.to(DEV)][:, kn.to(DEV)].double().cpu()
     assert torch.equal(got, a @ b)
     assert float(C.double().abs().sum()) == float((a @ b).abs().sum())   # and zero everywhere else
+
+
+@pytest.mark.parametrize("dh", [32, 128])
+@pytest.mark.parametrize("B,S,H", [(4, 17, 4), (3, 32, 4), (3, 33, 4), (2, 200, 3), (1, 1000, 2)])
+def test_bf16_attention_is_as_exact_as_its_outputs_are_rounded(B, S, H, dh):
+    """Head sizes 32 and 128 carry probabilities and dS with at least 16 bits into their products and sum rows in fp32: all that is
+    left of the error is the rounding of the bf16 outputs, plus 2 % for operands (2^-17 against 2^-9) and single roundings that
+    fall the other way; lse is fp32: 2^-24 of |lse| + |score| < 40 in a few roundings."""
+    print(f"attention exact B={B} S={S} H={H} dh={dh}", flush=True)
+    A, scale = H * dh, 1.0 / math.sqrt(dh)
+    qkv, x = _rand((B * S, 3 * A), 31, dp.BF16)
+    d_o, g = _rand((B * S, A), 32, dp.BF16)
+    o, dqkv = torch.empty_like(d_o), torch.empty_like(qkv)
+    lse = torch.empty((B, H, S), device=DEV)
+    dp.dipaco_k_attention_fwd(dp.BF16, qkv, o, lse, B, S, H, dh)
+    dsum = torch.empty(2 * B * H * ((S + 127) // 128 * 128), device=DEV)
+    dp.dipaco_k_attention_bwd(dp.BF16, qkv, o, d_o, lse, dqkv, dsum, B, S, H, dh)
+    q, k, v = np.moveaxis(x.reshape(B, S, 3, H, dh), (2, 3), (0, 2))            # [B, H, S, dh] each
+    g, stored = (np.moveaxis(t.reshape(B, S, H, dh), 1, 2) for t in (g, host(o).astype(np.float64)))
+    s = np.where(np.tril(np.ones((S, S), bool)), q @ np.swapaxes(k, -1, -2) * scale, -np.inf)
+    top = s.max(-1, keepdims=True)
+    L = top + np.log(np.exp(s - top).sum(-1, keepdims=True))
+    P = np.exp(s - L)
+    dS = P * (g @ np.swapaxes(v, -1, -2) - (stored * g).sum(-1, keepdims=True))
+    got = np.moveaxis(host(dqkv).astype(np.float64).reshape(B, S, 3, H, dh), (2, 3), (0, 2))
+    want = {"o": P @ v, "dq": dS @ k * scale, "dk": np.swapaxes(dS, -1, -2) @ q * scale, "dv": np.swapaxes(P, -1, -2) @ g}
+    for name, have in zip(want, (stored, *got)):
+        rounded = torch.from_numpy(want[name]).to(torch.bfloat16).double().numpy()
+        assert rel_l2(have, want[name]) <= 1.02 * rel_l2(rounded, want[name]), name
+    assert np.abs(host(lse) - L[..., 0]).max() <= 1e-5
