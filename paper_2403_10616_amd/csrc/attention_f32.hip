@@ -23,6 +23,7 @@
 // No atomics: every output element has exactly one writer and a fixed summation order.
 #include <type_traits>
 
+#include "attention_plain.h"
 #include "kernels.h"
 #include "mma_tile.h"
 
@@ -213,6 +214,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_f32(const float* __restri
     if (more) next.store(f_smem + ((kt + 1) & 1) * STAGE);
   }
   l = sum_groups(l);
+  if (__any(q < S && plain::not_finite(ot)) && q < S)
+    plain::attend<DH>(ot, base, ld, A, q, g, [&](float s) { return expf(s * head_scale<DH>() - mx); });
   if (q < S) {
     store_row<DH>(o + ((long)b * S + q) * A + hd * DH, ot, g, 1.0f / l);
     if (g == 0) lse[(long)bh * S + q] = mx + logf(l);
@@ -273,6 +276,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __res
     }
     if (more) next.store(f_smem + ((kt + 1) & 1) * STAGE);
   }
+  if (__any(q < S && plain::not_finite(dqt)) && q < S)
+    plain::query_grad<DH>(dqt, base, d_o + orow, D, ld, A, q, g, [&](float s) { return expf(s * head_scale<DH>() - L); });
   if (q < S) store_row<DH>(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, g, head_scale<DH>());
   // one row of partial column sums per (document, query block), this head's DH columns of dQ
   if (colsum)
@@ -347,6 +352,10 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
     }
     if (more) store(qt + 1);
   }
+  if (__any(key < S && (plain::not_finite(dkt) || plain::not_finite(dvt))) && key < S)
+    plain::key_grads<DH>(dkt, dvt, base, gbase, ld, A, key, S, g,
+                         [&](float s, int i) { return expf(s * head_scale<DH>() - lse[(long)bh * S + i]); },
+                         [&](int i) { return dsum[(long)bh * S + i]; });
   if (key < S) {
     float* out = dqkv + ((long)b * S + key) * ld + hd * DH;
     store_row<DH>(out + A, dkt, g, head_scale<DH>());

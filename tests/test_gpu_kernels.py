@@ -420,3 +420,55 @@ def test_bf16_attention_is_as_exact_as_its_outputs_are_rounded(B, S, H, dh):
         rounded = torch.from_numpy(want[name]).to(torch.bfloat16).double().numpy()
         assert rel_l2(have, want[name]) <= 1.02 * rel_l2(rounded, want[name]), name
     assert np.abs(host(lse) - L[..., 0]).max() <= 1e-5
+
+
+def _attention_over_visible_pairs(q, k, v, g, o, scale):
+    """One head in fp64, every sum over the pairs (query i, key j <= i) alone; o: the stored output, for D."""
+    S, n = len(q), q.shape[1]
+    lse, out, dq, dk, dv = np.zeros(S), np.zeros((S, n)), np.zeros((S, n)), np.zeros((S, n)), np.zeros((S, n))
+    with np.errstate(all="ignore"):
+        for i in range(S):
+            s = k[:i + 1] @ q[i] * scale
+            top = s.max()
+            lse[i] = top + np.log(np.exp(s - top).sum())
+            p = np.exp(s - lse[i])
+            ds = p * (v[:i + 1] @ g[i] - o[i] @ g[i])
+            out[i], dq[i] = p @ v[:i + 1], ds @ k[:i + 1] * scale
+            dv[:i + 1] += p[:, None] * g[i]
+            dk[:i + 1] += ds[:, None] * q[i] * scale
+    return lse, out, dq, dk, dv
+
+
+@pytest.mark.parametrize("dtype,dh", [(dp.F32, 32), (dp.F32, 64), (dp.F32, 128)])
+@pytest.mark.parametrize("B,S,H,at", [(2, 9, 2, 4), (2, 100, 2, 70), (1, 100, 2, 99), (1, 300, 1, 131), (260, 130, 2, 129)])
+@pytest.mark.parametrize("where,value", [("q", math.nan), ("k", math.nan), ("v", math.nan), ("v", math.inf), ("d_o", math.nan),
+                                         ("d_o", -math.inf)])
+def test_attention_keeps_non_finite_values_from_rows_that_do_not_see_them(dtype, dh, B, S, H, at, where, value):
+    """One non-finite row: what is finite over the visible pairs is finite and right, what is not is not.  S - 1 is the row that
+    rows past the end re-read; 260 x 2 heads of 130 positions run eight waves a workgroup in fp32."""
+    print(f"attention non-finite dtype={dtype} dh={dh} B={B} S={S} H={H} {where}[{at}]={value}", flush=True)
+    A = H * dh
+    qkv, _ = _rand((B * S, 3 * A), 41, dtype)
+    d_o, _ = _rand((B * S, A), 42, dtype)
+    third = {"q": 0, "k": 1, "v": 2}
+    if where == "d_o":
+        d_o[at, :dh] = value
+    else:
+        qkv[at, third[where] * A:third[where] * A + dh] = value
+    o, dqkv = torch.full_like(d_o, 7.0), torch.full_like(qkv, 7.0)
+    lse = torch.empty((B, H, S), device=DEV)
+    dp.dipaco_k_attention_fwd(dtype, qkv, o, lse, B, S, H, dh)
+    dsum = torch.empty(2 * B * H * ((S + 127) // 128 * 128), device=DEV)
+    dp.dipaco_k_attention_bwd(dtype, qkv, o, d_o, lse, dqkv, dsum, B, S, H, dh)
+    head = lambda t, n: host(t[:S]).astype(np.float64)[:, n * A:n * A + dh]
+    q, k, v = (head(qkv, n) for n in range(3))
+    want = _attention_over_visible_pairs(q, k, v, head(d_o, 0), head(o, 0), 1.0 / math.sqrt(dh))
+    have = (host(lse)[0, 0].astype(np.float64), head(o, 0), *(head(dqkv, n) for n in range(3)))
+    tol = 2e-5 if dtype == dp.F32 else 6e-3
+    for name, a, b in zip(("lse", "o", "dq", "dk", "dv"), have, want):
+        ok = np.isfinite(b)
+        assert np.array_equal(np.isfinite(a), ok), name
+        assert rel_l2(a[ok], b[ok]) <= tol, name
+    if B * H > 1:   # other heads and sequences
+        assert bool(torch.isfinite(o[:, dh:]).all()) and bool(torch.isfinite(dqkv.view(B * S, 3, A)[:, :, dh:]).all())
+        assert bool(torch.isfinite(o[S:]).all()) and bool(torch.isfinite(dqkv[S:]).all()) and bool(torch.isfinite(lse[1:]).all())

@@ -263,3 +263,29 @@ def test_embedding_gradient_on_both_sides_of_its_row_limit(B, S):
     _, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
     worst, where = per_tensor_rel(orc.param_layout(a), host(st.grads).astype(np.float64), o_grad)
     assert worst <= 1e-4, (worst, where)
+
+
+@pytest.mark.parametrize("compute,d_head", [(dp.F32, 32), (dp.F32, 64)])
+def test_scores_before_a_broken_embedding_row_stay_finite(compute, d_head):
+    """A causal path's token scores before a position do not depend on it, also when the embedding of the token there is NaN."""
+    cfg = dict(layers_per_level=(1, 1), d_model=64, n_heads=2, d_head=d_head, d_mlp=128, vocab=64, max_seq=96)
+    B, S, at = 3, 90, 41
+    a, ctx = make_arch(cfg, compute)
+    theta = gen.random_params(orc.param_count(a), seed=12, scale=0.08).astype(np.float32)
+    tok, tgt = _batch(cfg, B, S, 4)
+    tok, tgt = tok % 63, tgt % 63
+    tok[1, at] = 63
+    scores = []
+    for bad in (False, True):
+        if bad:
+            off, (_, width), _ = orc.param_layout(a)["tok_emb"]
+            theta[off + 63 * width:off + 64 * width] = np.nan
+        master = dev(theta)
+        lowp = master.to(torch.bfloat16) if compute == dp.BF16 else None
+        doc, nll = torch.empty(B, device=DEV), torch.empty((B, S), device=DEV)
+        ws = torch.empty(dp.dipaco_score_workspace_bytes(ctx, B, S), dtype=torch.uint8, device=DEV)
+        dp.dipaco_path_score(ctx, master, lowp, dev(tok.astype(np.int32)), dev(tgt.astype(np.int32)), B, S, doc, nll, ws)
+        scores.append(host(nll).astype(np.float64))
+    clean, got = scores
+    assert np.all(np.isnan(got[1, at:])) and np.array_equal(got[[0, 2]], clean[[0, 2]])
+    assert np.abs(got[1, :at] - clean[1, :at]).max() <= (1e-5 if compute == dp.F32 else 3e-2)
