@@ -155,7 +155,9 @@ dipaco_status dipaco_path_prefix_features_static(dipaco_ctx* ctx, const float* p
  * (device fp32 [batch]); token_nll_out: device fp32 [batch, seq] or NULL, the per-position negative log-likelihoods
  * (0 at ignored positions).  Call once per path on the same documents and take the argmax on the host; the same call
  * at seq = 2048 is the forward-only evaluation of Section 4.  tokens / targets / parameters as in
- * dipaco_path_fwd_bwd; workspace >= dipaco_score_workspace_bytes(ctx, batch, seq). */
+ * dipaco_path_fwd_bwd; workspace >= dipaco_score_workspace_bytes(ctx, batch, seq).
+ * Per-position results do not depend on later positions, also where those are not finite (a NaN embedding row, say);
+ * in bf16 with d_head = 64 a value that is not finite may reach earlier positions of its block of 64. */
 size_t dipaco_score_workspace_bytes(const dipaco_ctx* ctx, int32_t batch, int32_t seq);
 dipaco_status dipaco_path_score(dipaco_ctx* ctx, const float* path_master, const void* path_lowp, const int32_t* tokens,
                                 const int32_t* targets, int32_t batch, int32_t seq, float* doc_loglik_out,

@@ -63,7 +63,9 @@ dipaco_status dipaco_k_gemm_split_plan(int32_t M, int32_t N, int32_t K, int32_t 
 dipaco_status dipaco_k_set_attention_blocks(int32_t single_block);
 
 /* Causal softmax attention.  qkv: [B*S, 3*H*dh], row = q | k | v, head h at columns h*dh of each third;
- * o: [B*S, H*dh];  lse: fp32 [B, H, S] = log sum_j exp(q_i.k_j / sqrt(dh)), j <= i.  dh in {32, 64, 128}. */
+ * o: [B*S, H*dh];  lse: fp32 [B, H, S] = log sum_j exp(q_i.k_j / sqrt(dh)), j <= i.  dh in {32, 64, 128}.
+ * Here and in the gradient a value that is not finite reaches exactly the rows that see it; bf16 with dh = 64: any row of
+ * its block of 64 positions as well. */
 dipaco_status dipaco_k_attention_fwd(int32_t dtype, const void* qkv, void* o, float* lse, int32_t B, int32_t S,
                                      int32_t H, int32_t dh, void* stream);
 

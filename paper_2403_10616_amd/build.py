@@ -22,8 +22,9 @@ FLAGS = [
 ]
 
 
-# per-file additions.  attention_mfma.hip never forms a NaN (masked scores are -inf and every row keeps a finite
-# maximum); saying so removes the canonicalising self-maxima the compiler otherwise puts in front of every v_max.
+# per-file additions.  attention_mfma.hip (bf16, head size 64) forms no NaN of finite inputs (masked scores are -inf and every
+# row keeps a finite maximum); saying so removes the canonicalising self-maxima the compiler otherwise puts in front of every
+# v_max.  The kernels for the other head sizes and for fp32 honour NaN.
 EXTRA_FLAGS = {"attention_mfma.hip": ["-fno-honor-nans"]}
 
 

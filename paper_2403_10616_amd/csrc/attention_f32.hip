@@ -1,7 +1,7 @@
 // Causal attention in fp32 on the matrix cores, forward and backward, head sizes 32, 64 and 128.
 //
 // v_mfma_f32_16x16x4_f32 throughout: operand lane l supplies row (column) l % 16 and contraction index l / 16, and lane
-// l of a result holds column l % 16, rows 4 (l / 16) + e, e = 0..3.  As in the bf16 kernels (attention_mfma.hip) whatever
+// l of a result holds column l % 16, rows 4 (l / 16) + e, e = 0..3.  As in the bf16 kernels (attention_mfma.h) whatever
 // has to be contracted next is made the ROW index of the score tile, so that probabilities go from accumulator
 // registers straight into the next product: element e of a 16-row score tile IS the B operand of a product over the four
 // rows 4 (l / 16) + e.

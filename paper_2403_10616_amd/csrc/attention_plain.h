@@ -20,6 +20,20 @@ template <int N> __device__ __forceinline__ bool not_finite(const f32x4 (&acc)[N
     for (int e = 0; e < 4; ++e) z = __builtin_fmaf(acc[i][e], 0.f, z);
   return z != z;
 }
+template <int N> __device__ __forceinline__ bool not_finite(const f32x16 (&acc)[N]) {
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z = __builtin_fmaf(acc[i][e], 0.f, z);
+  return z != z;
+}
+template <int N> __device__ __forceinline__ void clear(f32x16 (&acc)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+}
 template <int N> __device__ __forceinline__ void clear(f32x4 (&acc)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -28,14 +42,29 @@ __device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
   const float4 t = *reinterpret_cast<const float4*>(p);
   v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
 }
-// acc += w * row, this lane's columns
-template <int DH, int N> __device__ __forceinline__ void add_row(f32x4 (&acc)[N], float w, const float* row, int sub) {
+__device__ __forceinline__ void load4(const bf16* p, float (&v)[4]) {
+  const bf16x4 t = *reinterpret_cast<const bf16x4*>(p);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = to_f32(t[e]);
+}
+// acc += w * row, this lane's columns: four lanes a row hold f32x4 tiles of 16 columns, two lanes f32x16 tiles of 32
+template <int N> __device__ __forceinline__ void add_row(f32x4 (&acc)[N], float w, const float* row, int sub) {
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     float v[4];
     load4(row + 16 * i + 4 * sub, v);
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[i][e] += w * v[e];
+  }
+}
+
+template <int N> __device__ __forceinline__ void add_row(f32x16 (&acc)[N], float w, const bf16* row, int sub) {
+#pragma unroll
+  for (int i = 0; i < 4 * N; ++i) {
+    float v[4];
+    load4(row + 8 * i + 4 * sub, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[i >> 2][4 * (i & 3) + e] += w * v[e];
   }
 }
 
@@ -60,7 +89,7 @@ __device__ __forceinline__ void attend(ACC& o, const T* base, long ld, int A, in
 #pragma unroll 1
   for (int j = 0; j <= q; ++j) {
     const T* k = base + (long)j * ld + A;
-    add_row<DH>(o, prob(dot<DH>(base + (long)q * ld, k)), k + A, sub);
+    add_row(o, prob(dot<DH>(base + (long)q * ld, k)), k + A, sub);
   }
 }
 // dQ of query q without the score scale: sum over j <= q of prob(q.k_j) (dO.v_j - D) k_j
@@ -70,7 +99,7 @@ __device__ __forceinline__ void query_grad(ACC& dq, const T* base, const T* d_o,
 #pragma unroll 1
   for (int j = 0; j <= q; ++j) {
     const T* k = base + (long)j * ld + A;
-    add_row<DH>(dq, prob(dot<DH>(base + (long)q * ld, k)) * (dot<DH>(d_o, k + A) - D), k, sub);
+    add_row(dq, prob(dot<DH>(base + (long)q * ld, k)) * (dot<DH>(d_o, k + A) - D), k, sub);
   }
 }
 // dK (without the score scale) and dV of a key: sums over i >= key of p_i (dO_i.v - D_i) q_i and p_i dO_i, p_i = prob(q_i.k, i).
@@ -86,8 +115,8 @@ __device__ __forceinline__ void key_grads(ACC& dk, ACC& dv, const T* base, const
     const T* q = base + (long)i * ld;
     const T* g = gbase + (long)i * A;
     const float p = prob(dot<DH>(q, k), i);
-    add_row<DH>(dv, p, g, sub);
-    add_row<DH>(dk, p * (dot<DH>(g, k + A) - D(i)), q, sub);
+    add_row(dv, p, g, sub);
+    add_row(dk, p * (dot<DH>(g, k + A) - D(i)), q, sub);
   }
 }
 

@@ -228,12 +228,14 @@ constexpr int ISSUE_PROBE_BLOCKS = 256;   // one workgroup per compute unit
 // out: ISSUE_PROBE_BLOCKS * 256 * waves_per_simd floats
 dipaco_status launch_issue_probe(int mode, int waves_per_simd, int iters, float* out, hipStream_t s);
 
-// ---- attention_mfma.hip: bf16, matrix cores ------------------------------------------------------------
-dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, int dh, hipStream_t s);
+// ---- attention_mfma.h: bf16, matrix cores, head sizes 32, 64 and 128 -------------------------------------
+template <int DH>
+dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, int B, int S, int H, hipStream_t s);
 // colsum_out (nullable): fp32 [3 H dh], the column sums of dqkv (the bias gradient of the QKV projection), from the
 // kernels' epilogues; colsum_partial: attention_bwd_colsum_floats(B, S, H, dh) floats of scratch
+template <int DH>
 dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv,
-                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,
+                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H,
                                         hipStream_t s, SumBatch* batch = nullptr);
 // ---- attention_f32.hip: fp32, matrix cores; arguments as above -------------------------------------------
 dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, int B, int S, int H, int dh, hipStream_t s);
@@ -242,5 +244,6 @@ dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const f
                                        hipStream_t s, SumBatch* batch, bool coarse);
 // bf16 kernels: 0: a workgroup takes a long and a short block of the causal triangle; 1: one block per workgroup, longest first
 void set_attention_single_block(int on);
+int attention_single_block();
 
 }  // namespace dipaco

@@ -439,7 +439,7 @@ def _attention_over_visible_pairs(q, k, v, g, o, scale):
     return lse, out, dq, dk, dv
 
 
-@pytest.mark.parametrize("dtype,dh", [(dp.F32, 32), (dp.F32, 64), (dp.F32, 128)])
+@pytest.mark.parametrize("dtype,dh", [(dp.F32, 32), (dp.F32, 64), (dp.F32, 128), (dp.BF16, 32), (dp.BF16, 128)])
 @pytest.mark.parametrize("B,S,H,at", [(2, 9, 2, 4), (2, 100, 2, 70), (1, 100, 2, 99), (1, 300, 1, 131), (260, 130, 2, 129)])
 @pytest.mark.parametrize("where,value", [("q", math.nan), ("k", math.nan), ("v", math.nan), ("v", math.inf), ("d_o", math.nan),
                                          ("d_o", -math.inf)])

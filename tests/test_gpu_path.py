@@ -265,7 +265,7 @@ def test_embedding_gradient_on_both_sides_of_its_row_limit(B, S):
     assert worst <= 1e-4, (worst, where)
 
 
-@pytest.mark.parametrize("compute,d_head", [(dp.F32, 32), (dp.F32, 64)])
+@pytest.mark.parametrize("compute,d_head", [(dp.F32, 32), (dp.F32, 64), (dp.BF16, 32), (dp.BF16, 128)])
 def test_scores_before_a_broken_embedding_row_stay_finite(compute, d_head):
     """A causal path's token scores before a position do not depend on it, also when the embedding of the token there is NaN."""
     cfg = dict(layers_per_level=(1, 1), d_model=64, n_heads=2, d_head=d_head, d_mlp=128, vocab=64, max_seq=96)
