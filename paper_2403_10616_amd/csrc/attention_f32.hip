@@ -375,8 +375,14 @@ template <int DH, int NW>
 dipaco_status fwd_rows(const float* qkv, float* o, float* lse, int B, int S, int H, hipStream_t s) {
   static std::atomic<unsigned long long> lds{0};
   if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_f32<DH, NW>), fwd_lds<DH>(), lds)) return st;
-  attn_fwd_f32<DH, NW><<<dim3(B * H, (S + 16 * NW - 1) / (16 * NW)), 64 * NW, fwd_lds<DH>(), s>>>(qkv, o, lse, S, H);
-  DIPACO_LAUNCH_CHECK();
+  const size_t A = (size_t)H * DH;
+  const int step = attention_launch_batch(B, H);
+  for (int b = 0; b < B; b += step) {
+    const size_t row = (size_t)b * S;
+    attn_fwd_f32<DH, NW><<<dim3(std::min(step, B - b) * H, (S + 16 * NW - 1) / (16 * NW)), 64 * NW, fwd_lds<DH>(), s>>>(
+        qkv + row * 3 * A, o + row * A, lse + row * H, S, H);
+    DIPACO_LAUNCH_CHECK();
+  }
   return DIPACO_OK;
 }
 template <int DH>
@@ -390,11 +396,19 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
   static std::atomic<unsigned long long> dq{0}, dkv{0};
   if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>), fwd_lds<DH>(), dq)) return st;
   if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>), dkv_lds<DH>(), dkv)) return st;
-  const dim3 grid(B * H, (S + 16 * NW - 1) / (16 * NW));
-  attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H);
-  DIPACO_LAUNCH_CHECK();
-  attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv, d_o, lse, dsum, dqkv, colsum, S, H);
-  DIPACO_LAUNCH_CHECK();
+  const size_t A = (size_t)H * DH;
+  const int step = attention_launch_batch(B, H), blocks = (S + 16 * NW - 1) / (16 * NW);
+  for (int b = 0; b < B; b += step) {
+    const size_t row = (size_t)b * S;
+    const dim3 grid(std::min(step, B - b) * H, blocks);
+    float* const cs = colsum ? colsum + (size_t)b * blocks * 3 * A : nullptr;
+    attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
+                                                                 dqkv + row * 3 * A, dsum + row * H, cs, S, H);
+    DIPACO_LAUNCH_CHECK();
+    attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv + row * 3 * A, d_o + row * A, lse + row * H, dsum + row * H,
+                                                                  dqkv + row * 3 * A, cs, S, H);
+    DIPACO_LAUNCH_CHECK();
+  }
   return DIPACO_OK;
 }
 

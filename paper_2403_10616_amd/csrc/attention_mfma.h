@@ -827,7 +827,7 @@ dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, in
     return DIPACO_OK;
   }
   const int single = attention_single_block();
-  const int nqb = (S + 127) / 128;
+  const int nqb = (S + 127) / 128;   // more than 32 positions: at most 2^32 / (33 * 3 * 32) sequences x heads, one launch
   dim3 grid = single ? dim3(B * H, nqb) : dim3((nqb + 1) / 2, B * H);   // one or two query blocks per workgroup
   attn_fwd_mfma<DH><<<grid, AT_THREADS, 0, s>>>(qkv, o, lse, S, H, single);
   DIPACO_LAUNCH_CHECK();
@@ -841,14 +841,22 @@ dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf
   constexpr int DQ_LDS = DQ_STAGES * 2 * tile_bytes<DH>(), DKV_LDS = DKV_STAGES * dkv_stage<DH>();
   const int single = attention_single_block();
   const int nqb = (S + 127) / 128;
-  dim3 grid = single ? dim3(B * H, nqb) : dim3((nqb + 1) / 2, B * H);   // one or two query (key) blocks per workgroup
   static std::atomic<unsigned long long> dq_lds{0}, dkv_lds{0};
   if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH>), DQ_LDS, dq_lds)) return st;
   if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH>), DKV_LDS, dkv_lds)) return st;
-  attn_bwd_dq_mfma<DH><<<grid, AT_THREADS, DQ_LDS, s>>>(qkv, o, d_o, lse, dqkv, dsum, colsum_out ? colsum_partial : nullptr, S, H, single);
-  DIPACO_LAUNCH_CHECK();
-  attn_bwd_dkv_mfma<DH><<<grid, AT_THREADS, DKV_LDS, s>>>(qkv, d_o, dsum, dqkv, colsum_out ? colsum_partial : nullptr, S, H, single);
-  DIPACO_LAUNCH_CHECK();
+  const size_t A = (size_t)H * DH;
+  const int step = attention_launch_batch(B, H);
+  for (int b = 0; b < B; b += step) {
+    const size_t row = (size_t)b * S;
+    const int n_bh = std::min(step, B - b) * H;
+    dim3 grid = single ? dim3(n_bh, nqb) : dim3((nqb + 1) / 2, n_bh);   // one or two query (key) blocks per workgroup
+    float* const cs = colsum_out ? colsum_partial + (size_t)b * nqb * 3 * A : nullptr;
+    attn_bwd_dq_mfma<DH><<<grid, AT_THREADS, DQ_LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
+                                                          dqkv + row * 3 * A, dsum, cs, S, H, single);
+    DIPACO_LAUNCH_CHECK();
+    attn_bwd_dkv_mfma<DH><<<grid, AT_THREADS, DKV_LDS, s>>>(qkv + row * 3 * A, d_o + row * A, dsum, dqkv + row * 3 * A, cs, S, H, single);
+    DIPACO_LAUNCH_CHECK();
+  }
   if (colsum_out) return launch_sum_rows(colsum_partial, colsum_out, B * nqb, 3 * H * DH, s, batch);
   return DIPACO_OK;
 }

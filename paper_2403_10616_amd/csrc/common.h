@@ -28,6 +28,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
     dipaco_status _st = ::dipaco::check_hip((call), #call);           \
     if (_st != DIPACO_OK) return _st;                                 \
   } while (0)
+// A launch holds fewer than 2^32 threads; the runtime does not refuse more, it runs a part of them.
+inline bool launch_fits(long long blocks, int threads) { return blocks * threads < (1LL << 32); }
+
 #define DIPACO_LAUNCH_CHECK() DIPACO_HIP(hipGetLastError())
 
 // Raises a kernel's dynamic-LDS limit to `bytes`, once per device: `done` is a call site's own bit mask of the

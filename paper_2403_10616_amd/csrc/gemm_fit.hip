@@ -442,7 +442,7 @@ dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
   g.k_per_split = (steps + want - 1) / want * F::BK;
   g.splits = (a.K + g.k_per_split - 1) / g.k_per_split;
   const long blocks = (long)g.tiles_m * g.tiles_n * g.splits;
-  if (blocks > 0x7fffffffL) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
+  if (!launch_fits(blocks, 64 * FIT_WAVES)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
   g.colsum_partial = a.colsum ? a.colsum_partial : nullptr;
   kern<<<(unsigned)blocks, 64 * FIT_WAVES, F::LDS, s>>>(g);
   DIPACO_LAUNCH_CHECK();

@@ -1,5 +1,7 @@
 // Host-side launchers of every kernel in libdipaco (one per .hip file group).  All enqueue on `s` and return.
 #pragma once
+#include <algorithm>
+
 #include "common.h"
 
 namespace dipaco {
@@ -222,6 +224,9 @@ dipaco_status launch_attention_bwd(const T* qkv, const T* o, const T* d_o, const
 // coarse: colsum_partial holds only B * ceil(S / 128) rows (the kernel-level entry point's documented scratch)
 size_t attention_bwd_colsum_rows_f32(int B, int S, int H);
 size_t attention_bwd_colsum_floats(int B, int S, int H, int dh);
+// Sequences per launch (launch_fits with up to 512 threads for each of them and each head): calls of more than 2^22
+// sequences x heads run as several
+inline int attention_launch_batch(int B, int H) { return std::min(B, std::max(1, (1 << 22) / H)); }
 
 // ---- probe.hip: register-only instruction-issue loops (measurement aid) --------------------------------
 constexpr int ISSUE_PROBE_BLOCKS = 256;   // one workgroup per compute unit

@@ -609,6 +609,7 @@ static int route_small_wc(int K) { return K > 128 ? 8 : K > 64 ? 4 : K > 32 ? 2 
 static int route_pick(int64_t N, int K) {
   const int64_t wc = route_small_wc(K), sweeps = (K + 32 * wc - 1) / (32 * wc), tasks = 256 * RS_WAVES;
   if ((N + 15) / 16 * wc <= tasks) return 1;
+  if (!launch_fits((N + 31) / 32 * wc / RS_WAVES + 1, RS_WAVES * WAVE)) return 0;
   const int64_t small = 43 * (((N + 31) / 32 * wc + tasks - 1) / tasks) * sweeps;
   const int64_t big = 230 * ((N + 256 * RBM - 1) / (256 * RBM)) * ((K + RBN - 1) / RBN);
   return small < big ? 2 : 0;
@@ -627,7 +628,6 @@ dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const fl
     if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_small_kernel<false, PT>), LDS, set_one)) return e;
     if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_small_kernel<true, PT>), LDS, set_two)) return e;
     const int64_t pts = 16 * PT * (RS_WAVES / wc), nb = (N + pts - 1) / pts;
-    if (nb > 0x7fffffffLL) return fail(DIPACO_ESHAPE, "route: N too large");
     if (n_best == 2) route_small_kernel<true, PT><<<(unsigned)nb, RS_WAVES * WAVE, LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, wc, idx, h, margin);
     else route_small_kernel<false, PT><<<(unsigned)nb, RS_WAVES * WAVE, LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, wc, idx, h, margin);
     DIPACO_LAUNCH_CHECK();
@@ -641,7 +641,7 @@ dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const fl
   if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<false>), (int)smem, lds_one)) return e;
   if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<true>), (int)smem, lds_two)) return e;
   const int64_t blocks = (N + RBM - 1) / RBM;
-  if (blocks > 0x7fffffffLL) return fail(DIPACO_ESHAPE, "route: N too large");
+  if (!launch_fits(blocks, R_THREADS)) return fail(DIPACO_ESHAPE, "route: N too large");
   if (n_best == 2) route_kernel<true><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
   else route_kernel<false><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
   DIPACO_LAUNCH_CHECK();

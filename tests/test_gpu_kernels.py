@@ -472,3 +472,32 @@ def test_attention_keeps_non_finite_values_from_rows_that_do_not_see_them(dtype,
     if B * H > 1:   # other heads and sequences
         assert bool(torch.isfinite(o[:, dh:]).all()) and bool(torch.isfinite(dqkv.view(B * S, 3, A)[:, :, dh:]).all())
         assert bool(torch.isfinite(o[S:]).all()) and bool(torch.isfinite(dqkv[S:]).all()) and bool(torch.isfinite(lse[1:]).all())
+
+
+@pytest.mark.parametrize("dtype,S,B,H,dh", [(dp.F32, 1, 3_000_000, 3, 32), (dp.F32, 2, 9_000_000, 1, 32), (dp.BF16, 1, 17_000_000, 1, 32)])
+def test_attention_of_more_heads_than_one_launch_holds(dtype, S, B, H, dh):
+    """Sequences x heads x threads of a workgroup reach 2^32.  One position: o = v, dv = d_o and their column sums (dS = p (dO.v - dO.o)
+    is a rounding difference of the two); two: the second row of the last sequence too."""
+    print(f"attention many dtype={dtype} S={S} B={B} H={H} dh={dh}", flush=True)
+    A, T = H * dh, B * S
+    qkv, d_o = (torch.randn((T, w), dtype=TDT[dtype], device=DEV, generator=torch.Generator(DEV).manual_seed(w)) for w in (3 * A, A))
+    o, dqkv = torch.full_like(d_o, 7.0), torch.full_like(qkv, 7.0)
+    lse = torch.full((B, H, S), float("nan"), device=DEV)
+    dp.dipaco_k_attention_fwd(dtype, qkv, o, lse, B, S, H, dh)
+    first = torch.arange(0, T, S, device=DEV) if S > 1 else slice(None)
+    assert torch.equal(o[first], qkv[first, 2 * A:]) and bool(torch.isfinite(o).all()) and bool(torch.isfinite(lse).all())
+    dsum, cs = torch.empty(2 * B * H * 128, device=DEV), torch.zeros(3 * A, device=DEV)
+    scratch = torch.full((B * 3 * A,), float("nan"), device=DEV)
+    dp.dipaco_k_attention_bwd(dtype, qkv, o, d_o, lse, dqkv, dsum, B, S, H, dh, colsum_out=cs, colsum_scratch=scratch)
+    assert bool(torch.isfinite(dqkv).all())
+    want = dqkv[:, 2 * A:].double().sum(0)
+    # stored bf16 values against the sums of the unrounded ones: 2^-9 of sqrt(T) values of about one each
+    assert float((cs[2 * A:].double() - want).abs().max()) <= (2e-3 if dtype == dp.F32 else 2.0 ** -8) * math.sqrt(T)
+    if S == 1:
+        # p = exp(score - lse) = 1 within 2^-24 of |score| < 12, times |d_o| < 7; in bf16 rounding gives d_o back
+        assert float((dqkv[:, 2 * A:] - d_o).abs().max()) <= (1e-5 if dtype == dp.F32 else 0.0)
+    else:
+        q, k, v = (t.double() for t in qkv[-2:].split(A, 1))
+        w = torch.softmax(q[1] @ k.T / math.sqrt(dh), 0)
+        assert rel_l2(host(o[-1]), (w @ v).cpu().numpy()) <= 1e-5
+        assert rel_l2(host(dqkv[-1, 2 * A:]), (w[1] * d_o[-1].double()).cpu().numpy()) <= 1e-5

@@ -423,3 +423,19 @@ def test_route_kernels_agree_with_fp64_on_both_sides_of_every_size_rule(N, D, K,
         assert torch.equal(idx.long(), want)
         assert torch.equal(hist, torch.bincount(want, minlength=K))
         assert torch.equal(margin.double(), order.values[:, 1] - order.values[:, 0])
+
+
+def test_more_points_than_one_launch_of_small_workgroups_holds():
+    """600,000,000 points and 100 centroids: 64 points a workgroup of 512 threads would pass 2^32 threads in a launch."""
+    N, D, K = 600_000_000, 4, 100
+    g = torch.Generator(DEV).manual_seed(3)
+    c = torch.randint(-9, 10, (K, D), generator=g, device=DEV).float()
+    z = torch.empty((N, D), device=DEV).normal_(generator=g).mul_(4.0).round_()
+    idx = torch.full((N,), -9, dtype=torch.int32, device=DEV)
+    hist = torch.full((K,), -7, dtype=torch.int64, device=DEV)
+    dp.dipaco_route_prefix(z, c, N, D, K, idx, hist, None)
+    assert int(hist.sum()) == N
+    for at in (0, N // 2, N - 4096):     # whole numbers: scores and ties are exact
+        part = z[at:at + 4096].double()
+        score = (c.double() ** 2).sum(1) - 2 * part @ c.double().T
+        assert torch.equal(idx[at:at + 4096].long(), torch.sort(score, dim=1, stable=True).indices[:, 0])
