@@ -90,7 +90,8 @@ dipaco_status dipaco_tensor_info(const dipaco_ctx* ctx, int32_t i, char* name_ou
 int64_t dipaco_path_index(const int32_t* modules, const int32_t* K, int32_t L);
 dipaco_status dipaco_path_modules(int64_t j, const int32_t* K, int32_t L, int32_t* modules_out);
 
-/* Bytes of device workspace dipaco_path_fwd_bwd needs for a [batch, seq] input. */
+/* Bytes of device workspace dipaco_path_fwd_bwd needs for a [batch, seq] input.  This and the other *_workspace_bytes are
+ * non-decreasing in their sizes: a workspace made for the largest call serves the smaller ones. */
 size_t dipaco_workspace_bytes(const dipaco_ctx* ctx, int32_t batch, int32_t seq);
 
 /* Start-of-round copy of the global modules into one path's local parameters (Algorithm 1: theta_i^t =

@@ -49,6 +49,8 @@ struct dipaco_ctx {
   std::vector<size_t> seg_off, seg_size;
   size_t n_params = 0;
   AdamLayout adam;
+  // most K slices of the five weight gradients (WeightKind) of up to 2^i tokens: gemm_slice_limits
+  int slice_limit[5][25];
 };
 
 namespace dipaco {
@@ -66,8 +68,17 @@ struct Plan {
   size_t total;
 };
 
-template <typename T> static int dw_splits(int M, int N, int K) { return gemm_plan_splits(M, N, K, sizeof(T) == 2); }
+enum WeightKind { W_QKV, W_O, W_UP, W_DOWN, W_HEAD };
+static void weight_shape(const dipaco_ctx* c, int kind, int& rows, int& cols) {
+  const int d = c->arch.d_model, A = c->A, F = c->arch.d_mlp;
+  rows = kind == W_O ? A : kind == W_DOWN ? F : d;
+  cols = kind == W_QKV ? 3 * A : kind == W_UP ? F : kind == W_HEAD ? c->arch.vocab : d;
+}
+static int slice_limit(const dipaco_ctx* c, int kind, int tokens) {
+  return c->slice_limit[kind][gemm_limit_index(tokens)];
+}
 
+// Every buffer, and so the total, is non-decreasing in B and in S: a workspace made for the largest batch serves the others.
 static Plan make_plan(const dipaco_ctx* c, int B, int S) {
   const dipaco_arch& a = c->arch;
   const size_t T = (size_t)B * S, d = a.d_model, A = c->A, F = a.d_mlp, V = a.vocab;
@@ -99,8 +110,11 @@ static Plan make_plan(const dipaco_ctx* c, int B, int S) {
                                   attention_bwd_colsum_floats((int)B, (int)S, a.n_heads, a.d_head)) * 4 + 255) & ~(size_t)255;
   p.cs_partial = take(p.cs_partial_stride * std::max<size_t>(1, 2 * (size_t)c->n_layers));
   size_t sk = 0;
-  auto need = [&](size_t M, size_t N) { sk = std::max(sk, (size_t)gemm_max_splits((int)M, (int)N, (int)T) * M * N); };
-  need(d, 3 * A); need(A, d); need(d, F); need(F, d); need(d, V);
+  for (int kind = W_QKV; kind <= W_HEAD; ++kind) {
+    int rows, cols;
+    weight_shape(c, kind, rows, cols);
+    sk = std::max(sk, (size_t)slice_limit(c, kind, (int)T) * rows * cols);
+  }
   p.splitk_partial = take(sk * 4);
   p.embed_ints = take(embed_bwd_scratch_ints((int)T, (int)V) * 4);
   p.total = pos;
@@ -145,9 +159,11 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
   const int NL = c->n_layers;
 
   // weight gradient dW[K_in, N_out] = X^T . dY (contraction over the tokens), fp32 into the gradient buffer
-  auto dweight = [&](const T* X, const T* dY, size_t w_off, int K_in, int N_out) {
+  auto dweight = [&](const T* X, const T* dY, size_t w_off, WeightKind kind) {
+    int K_in, N_out;
+    weight_shape(c, kind, K_in, N_out);
     return gemm<T>(X, dY, G + w_off, K_in, N_out, T_, K_in, N_out, N_out, true, false, nullptr, nullptr, nullptr, nullptr,
-                   0, true, dw_splits<T>(K_in, N_out, T_), skp, st);
+                   0, true, gemm_plan_splits(K_in, N_out, T_, sizeof(T) == 2, slice_limit(c, kind, T_)), skp, st);
   };
 
   // ---------------- forward ----------------
@@ -182,7 +198,7 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
 
   // ---------------- backward ----------------
   T* dlogits = buf(p.logits);
-  TRY(dweight(buf(p.y), dlogits, c->w_head, d, V));
+  TRY(dweight(buf(p.y), dlogits, c->w_head, W_HEAD));
   TRY(gemm<T>(dlogits, W + c->w_head, buf(p.dh), T_, d, V, V, V, d, false, true, nullptr, nullptr, nullptr, nullptr, 0,
               false, 1, nullptr, st));
   T* dx = buf(p.dxa);
@@ -196,23 +212,23 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
     const LayerBufs& L = p.layers[l];
     const BlockOff& o = c->blocks[l];
     // x_next = x_mid + gelu(u) W_down + b_down
-    TRY(dweight(buf(L.act), dx, o.w_down, F, d));
+    TRY(dweight(buf(L.act), dx, o.w_down, W_DOWN));
     // du = (dx W_down^T) * GELU'(u); its column sums, the gradient of b_up, come out of the same product
     TRY(gemm<T>(dx, W + o.w_down, buf(p.du), T_, F, d, d, d, F, false, true, nullptr, nullptr, nullptr, buf(L.u), 4,
                 false, 1, nullptr, st, G + o.b_up, next_csp(), &sums));
-    TRY(dweight(buf(L.h2), buf(p.du), o.w_up, d, F));
+    TRY(dweight(buf(L.h2), buf(p.du), o.w_up, W_UP));
     TRY(gemm<T>(buf(p.du), W + o.w_up, buf(p.dh), T_, d, F, F, F, d, false, true, nullptr, nullptr, nullptr, nullptr, 0,
                 false, 1, nullptr, st));
     TRY(launch_layernorm_bwd<T>(buf(p.dh), buf(L.x_mid), W + o.ln2_g, fbuf(L.mean2), fbuf(L.rstd2), dx, dx_other,
                                 G + o.ln2_g, G + o.ln2_b, G + o.b_o, next_lnp(), T_, d, st, &sums));
     // x_mid = x_in + attn(...) W_o + b_o          (dx_other = gradient at x_mid)
-    TRY(dweight(buf(L.o), dx_other, o.w_o, A, d));
+    TRY(dweight(buf(L.o), dx_other, o.w_o, W_O));
     TRY(gemm<T>(dx_other, W + o.w_o, buf(p.d_o), T_, A, d, d, d, A, false, true, nullptr, nullptr, nullptr, nullptr, 0,
                 false, 1, nullptr, st));
     // dqkv and its column sums, the gradient of b_qkv
     TRY(launch_attention_bwd<T>(buf(L.qkv), buf(L.o), buf(p.d_o), fbuf(L.lse), buf(p.dqkv), fbuf(p.dsum), G + o.b_qkv,
                                 next_csp(), B, S, H, dh, st, &sums));
-    TRY(dweight(buf(L.h1), buf(p.dqkv), o.w_qkv, d, 3 * A));
+    TRY(dweight(buf(L.h1), buf(p.dqkv), o.w_qkv, W_QKV));
     TRY(gemm<T>(buf(p.dqkv), W + o.w_qkv, buf(p.dh), T_, d, 3 * A, 3 * A, 3 * A, d, false, true, nullptr, nullptr,
                 nullptr, nullptr, 0, false, 1, nullptr, st));
     TRY(launch_layernorm_bwd<T>(buf(p.dh), buf(L.x_in), W + o.ln1_g, fbuf(L.mean1), fbuf(L.rstd1), dx_other, dx,
@@ -246,11 +262,12 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   if (with_head) { p.logits = take(T * (size_t)a.vocab * es); p.nll = take(T * 4); p.n_valid = take(256); }
   p.splits_o = gemm_raw_splits((int)T, (int)d, (int)A, es == 2);
   p.splits_down = gemm_raw_splits((int)T, (int)d, (int)F, es == 2);
-  if (std::max(p.splits_o, p.splits_down) > 1) {
-    const size_t before = pos;
-    p.planes = take(std::max(p.splits_o, p.splits_down) * T * d * 4);
-    // what fits the static scratch without the planes keeps fitting it
-    if (before <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) { pos = before; p.splits_o = p.splits_down = 1; }
+  // room for the planes of any smaller batch too; what fits the static scratch without them keeps fitting it
+  p.planes = pos;
+  take(std::max(gemm_raw_plane_floats((int)T, (int)d, (int)A, es == 2), gemm_raw_plane_floats((int)T, (int)d, (int)F, es == 2)) * 4);
+  if (p.planes <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) {
+    pos = DIPACO_STATIC_SCRATCH_BYTES;
+    if (p.planes + std::max(p.splits_o, p.splits_down) * T * d * 4 > pos) p.splits_o = p.splits_down = 1;
   }
   p.total = pos;
   return p;
@@ -410,6 +427,11 @@ dipaco_status dipaco_create(dipaco_ctx** out, const dipaco_arch* arch) {
       delete c;
       return fail(DIPACO_ESHAPE, "decoder blocks above 2^32 elements in total");
     }
+  }
+  for (int kind = W_QKV; kind <= W_HEAD; ++kind) {
+    int rows, cols;
+    weight_shape(c, kind, rows, cols);
+    gemm_slice_limits(rows, cols, a.compute == DIPACO_BF16, c->slice_limit[kind], 25);
   }
   *out = c;
   return DIPACO_OK;
@@ -793,7 +815,7 @@ dipaco_status dipaco_route_linear(const float* z, int64_t ldz, const float* weig
 }
 
 namespace {
-struct RouterPlan { size_t logits, nll, n_valid, cs_partial, sk_partial, total; };
+struct RouterPlan { size_t logits, nll, n_valid, cs_partial, sk_partial, total; int slice_limit; };
 RouterPlan make_router_plan(int64_t N, int D, int K) {
   RouterPlan p;
   size_t off = 0;
@@ -802,7 +824,11 @@ RouterPlan make_router_plan(int64_t N, int D, int K) {
   p.nll = take((size_t)N * 4);
   p.n_valid = take(256);
   p.cs_partial = take(dipaco::colsum_partial_floats((int)N, K) * 4);
-  p.sk_partial = take((size_t)dipaco::gemm_max_splits(K, D, (int)N) * K * D * 4);
+  int limit[32];
+  const int at = dipaco::gemm_limit_index(N);
+  dipaco::gemm_slice_limits(K, D, false, limit, at + 1);
+  p.slice_limit = limit[at];
+  p.sk_partial = take((size_t)p.slice_limit * K * D * 4);
   p.total = off;
   return p;
 }
@@ -851,7 +877,7 @@ dipaco_status dipaco_router_logistic_grad(const float* z, const int32_t* labels,
   TRY(launch_colsum(logits, dbias_out, reinterpret_cast<float*>(ws + p.cs_partial), (int)N, K, st));
   if (dweights_out)
     TRY(gemm<float>(logits, z, dweights_out, K, D, (int)N, K, D, D, true, false, nullptr, nullptr, nullptr, nullptr, 0,
-                    true, gemm_plan_splits(K, D, (int)N, false), reinterpret_cast<float*>(ws + p.sk_partial), st));
+                    true, gemm_plan_splits(K, D, (int)N, false, p.slice_limit), reinterpret_cast<float*>(ws + p.sk_partial), st));
   return DIPACO_OK;
 }
 

@@ -421,7 +421,10 @@ dipaco_status launch_attention_fwd_f32(const float* qkv, float* o, float* lse, i
   return fail(DIPACO_ESHAPE, "attention: d_head must be 32, 64 or 128");
 }
 
-size_t attention_bwd_colsum_rows_f32(int B, int S, int H) { return (size_t)B * ((S + (few_waves(B, S, H) ? 63 : 127)) / (few_waves(B, S, H) ? 64 : 128)); }
+// for any B and S up to these: four waves write a row per 64 positions, where B H ceil(S / 128) <= 512
+size_t attention_bwd_colsum_rows_f32(int B, int S, int H) {
+  return std::max<size_t>((size_t)B * ((S + 127) / 128), std::min<size_t>((size_t)B * ((S + 63) / 64), 2 * (512 / H)));
+}
 
 dipaco_status launch_attention_bwd_f32(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv,
                                        float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H, int dh,

@@ -88,8 +88,8 @@ struct SplitPlan { int splits; bool dlds; };
 // over 4096 tokens 38 us unsplit here against 42 + 15 there, 896 x 896 over 8192 24 + 5 / 27 + 9; over 32768 tokens
 // 896 x 2688 171 + 12 / 155 + 10, 1024 x 4096 294 / 212 + 14: beyond 16384 tokens the tiles of a one-round launch drift
 // apart and re-read their panels, and the direct-to-LDS plan is taken wherever there is one.
-static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_allowed) {
-  const int cap = std::max(1, std::min(bf16_operands ? GEMM_SLICE_CAP : GEMM_SLICE_CAP_F32, K / 256));
+static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_allowed, int limit = GEMM_SLICE_CAP_F32) {
+  const int cap = std::max(1, std::min({bf16_operands ? GEMM_SLICE_CAP : GEMM_SLICE_CAP_F32, K / 256, limit}));
   SplitPlan best{1, false};
   double cost = 1e30;
   for (int s = 1; s <= cap; ++s) {
@@ -110,19 +110,27 @@ static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_
   return best;
 }
 
-int gemm_plan_splits(int M, int N, int K, bool bf16_operands) {
+int gemm_plan_splits(int M, int N, int K, bool bf16_operands, int limit) {
   if (bf16_operands && g_forced_kernel == FORCED_DLDS) {
-    const int s = gemm_dlds_plan_slices(M, N, K, std::min(GEMM_SLICE_CAP, std::max(1, K / 256)), false, nullptr);
+    const int s = gemm_dlds_plan_slices(M, N, K, std::max(1, std::min({GEMM_SLICE_CAP, K / 256, limit})), false, nullptr);
     if (s) return s;
   }
-  return plan_splits(M, N, K, bf16_operands, g_forced_kernel != FORCED_FIT).splits;
+  return plan_splits(M, N, K, bf16_operands, g_forced_kernel != FORCED_FIT, limit).splits;
 }
 
-// Upper bound of gemm_plan_splits over types and tile settings: sizes the partial-product workspace.
-int gemm_max_splits(int M, int N, int K) {
-  const int cap = std::min(GEMM_SLICE_CAP, std::max(1, K / 256));
-  return std::max(std::max(plan_splits(M, N, K, true, false).splits, plan_splits(M, N, K, false, false).splits),
-                  gemm_dlds_plan_slices(M, N, K, cap, true, nullptr));
+// The plan's slices go up and down with K, but a workspace that serves K tokens has to serve fewer as well.  So the limit is the
+// largest plan, over all tile settings, at the powers of two from 512 (below, nothing is cut) to the one at or above K, and at
+// three quarters of each.  A plan between them that would take more is held to it (one in 10000 sizes drawn, by a slice or two).
+void gemm_slice_limits(int M, int N, bool bf16_operands, int* limit, int count) {
+  int most = 1;
+  for (int i = 0; i < count; ++i) {
+    for (int quarters = 3; i >= 9 && quarters <= 4; ++quarters) {
+      const int K = (int)std::min((1LL << i) / 4 * quarters, 0x7fffffffLL);
+      most = std::max(most, plan_splits(M, N, K, bf16_operands, false).splits);
+      if (bf16_operands) most = std::max(most, gemm_dlds_plan_slices(M, N, K, std::min(GEMM_SLICE_CAP, K / 256), true, nullptr));
+    }
+    limit[i] = most;
+  }
 }
 
 // bf16 products that fill most of the chip's 256 compute units with 256 x 256 tiles go to the direct-to-LDS kernel: measured

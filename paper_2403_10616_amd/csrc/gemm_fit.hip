@@ -515,6 +515,17 @@ int gemm_raw_splits(int M, int N, int K, bool bf16_operands) {
   return (steps + per - 1) / per;
 }
 
+size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands) {
+  size_t most = 0;
+  for (int m = std::min(M, 32);; m = std::min(M, m + 32)) {   // the split count depends on the rows in steps of 32
+    if (256 / (((m + 31) / 32) * ((N + 63) / 64)) < 2) break;
+    const int s = gemm_raw_splits(m, N, K, bf16_operands);
+    if (s > 1) most = std::max(most, (size_t)s * m * N);
+    if (m == M) break;
+  }
+  return most;
+}
+
 double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous) {
   double best = 1e30;
   for (int t = 1; t <= 5; ++t)

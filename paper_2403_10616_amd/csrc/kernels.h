@@ -128,6 +128,7 @@ void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64
 dipaco_status launch_splitk_reduce(const float* partial, float* C, int M, int N, long ldc, int splits, hipStream_t s);
 // K splits of a small forward product whose planes are summed by the next kernel: 1 = not worth it
 int gemm_raw_splits(int M, int N, int K, bool bf16_operands);
+size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands);   // their planes for any M up to this one
 // microseconds of a product of `splits` slices of K each with the best tile shape
 double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous);
 // 0 = automatic; 1 .. 4, 14 = gemm_fit.hip with 32x64, 64x128, 96x128, 128x128, 160x128 tiles, 5 = the direct-to-LDS kernel
@@ -143,9 +144,16 @@ dipaco_status launch_splitk_reduce_classes(const float* partial, float* C, int M
 int gemm_dlds_plan_slices(int M, int N, int K, int max_slices, bool any_shape, double* length);
 void gemm_dlds_plan_info(int M, int N, int K, int max_slices, int* out);   // host-only, for tests: see gemm_dlds.hip
 constexpr int GEMM_SLICE_CAP = 32;
-// split count the weight-gradient products are launched with
-int gemm_plan_splits(int M, int N, int K, bool bf16_operands);
-int gemm_max_splits(int M, int N, int K);    // its upper bound over tile settings (workspace sizing)
+// Split count a weight gradient is launched with: at most `limit`, for which the caller's workspace has planes
+int gemm_plan_splits(int M, int N, int K, bool bf16_operands, int limit);
+// What workspaces are sized for, by their K rounded up to a power of two: non-decreasing, and no less than what the plan would take
+// (but for bumps between the powers).  limit[i]: up to K = 2^i
+void gemm_slice_limits(int M, int N, bool bf16_operands, int* limit, int count);
+inline int gemm_limit_index(int64_t K) {   // of the power of two at or above K
+  int i = 0;
+  while ((1LL << i) < K) ++i;
+  return i;
+}
 
 // ---- transformer.hip ---------------------------------------------------------------------------------
 template <typename T>

@@ -748,9 +748,10 @@ dipaco_status launch_sum_layernorm(const float* planes, int n_planes, const T* b
   return DIPACO_OK;
 }
 
+// for any number of rows up to this one: eight rows a workgroup where few are launched with them
 size_t ln_bwd_partial_floats(int rows, int d) {
-  const int per = ln_bwd_rows(rows);
-  return (size_t)((rows + per - 1) / per) * 3 * d;
+  const int few = std::min(rows, 1024 * LN_BWD_FEW_ROWS);
+  return (size_t)std::max((few + LN_BWD_FEW_ROWS - 1) / LN_BWD_FEW_ROWS, (rows + LN_BWD_ROWS - 1) / LN_BWD_ROWS) * 3 * d;
 }
 
 template <typename T>

@@ -163,3 +163,29 @@ def test_uneven_split_plan_of_the_step_shapes():
     assert p["tiles"] == [49, 0, 0, 0] and p["slices"][0] == 5
     with pytest.raises(dp.DipacoError):
         dp.dipaco_k_gemm_split_plan(896, 3584, 1000, 32)
+
+
+@pytest.mark.parametrize("compute", [dp.F32, dp.BF16])
+@pytest.mark.parametrize("arch", [([6, 6], 896, 14, 64, 3584, 32000), ([1, 1], 64, 2, 32, 256, 256), ([3, 3], 1024, 8, 128, 4096, 16000),
+                                  ([1], 736, 3, 64, 3000, 1000), ([1], 32, 1, 32, 32, 40)])
+def test_workspaces_do_not_shrink_with_the_batch(compute, arch):
+    """A workspace made for the largest batch serves every smaller one, on both sides of the sizes where kernels change their split:
+    8192 rows (LayerNorm gradient), 512 blocks of 128 rows (fp32 attention), a few hundred tokens (residual products cut over K),
+    anything for the weight gradients' slices."""
+    ctx = dp.Context(*arch, 4096, 1e-5, compute)
+    for size in (dp.dipaco_workspace_bytes, dp.dipaco_features_workspace_bytes, dp.dipaco_score_workspace_bytes):
+        for S in (1, 16, 32, 33, 100, 256, 1000, 4096):
+            have = [size(ctx, B, S) for B in range(1, 1 + min(300, 130_000 // S))]
+            assert all(a <= b for a, b in zip(have, have[1:])) and have[0] > 0, (size.__name__, S)
+        for B in (1, 3, 8, 33):
+            have = [size(ctx, B, S) for S in range(1, 4097, 5)]
+            assert all(a <= b for a, b in zip(have, have[1:])), (size.__name__, B)
+
+
+@pytest.mark.parametrize("D,K", [(768, 64), (768, 256), (64, 8), (1024, 512)])
+def test_router_workspace_does_not_shrink_with_the_documents(D, K):
+    sizes, N = [], 1
+    while N < 1 << 21:
+        sizes.append(dp.dipaco_router_workspace_bytes(N, D, K))
+        N = max(N + 1, N * 1003 // 1000)
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
