@@ -463,7 +463,9 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || (bf16_op
 // Microseconds of `tiles` tiles over K: rounds of 256 workgroups x (fixed + per 1000 of K).  Fitted to launches of 256 .. 8192
 // rows, K 64 .. 8192 (rel. error 15 %): 3000 x 896 x 3584 bf16 34.8 / 26.0 / 28.8 / 33.7 us for shapes 2 .. 5, 5700 x 896 x 3584
 // 51 / 49 / 53 / 38, 1000 x 896 x 3584 20 (shape 1) / 21 / 24 / 28, 256 x 896 x 3584 10.5 / 19.
-// The 64 x 128 shape runs two workgroups on a compute unit.  In a weight gradient, whose workgroups all end together, 257 .. 512
+// The 64 x 128 shape runs two workgroups on a compute unit, so that over several rounds one loads and stores while the other
+// multiplies: bf16, outputs in many rounds, K = 48 / 200 / 520: 111 / 25.7 / 38.7 us, the next best shape 145 / 31.2 / 42.7
+// (9780 x 13336, 2540 x 7248, 9000 x 2000).  In a weight gradient, whose workgroups all end together, 257 .. 512
 // of them are one round of twice the length, and a third 256 behind them lands two to a unit again: 256 x 768 over 2^20 rows in
 // fp32 2930 us in 504 workgroups, 3500 - 3900 in 768, 2980 in 1536.
 double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
@@ -472,6 +474,7 @@ double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bo
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
   const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
   const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
+  if (t == 2 && a_kc && bf16_operands) return 4.9 + (double)rounds * (1.6 + k * K * 1e-3);
   return 3.0 + (double)rounds * (f + k * K * 1e-3);
 }
 
