@@ -289,3 +289,26 @@ def test_scores_before_a_broken_embedding_row_stay_finite(compute, d_head):
     clean, got = scores
     assert np.all(np.isnan(got[1, at:])) and np.array_equal(got[[0, 2]], clean[[0, 2]])
     assert np.abs(got[1, :at] - clean[1, :at]).max() <= (1e-5 if compute == dp.F32 else 3e-2)
+
+
+@pytest.mark.parametrize("B,S", [(128, 33), (129, 33)])
+def test_qkv_bias_gradient_on_both_sides_of_512_attention_blocks(B, S):
+    """fp32: up to 512 blocks four waves a workgroup leave a row of partial column sums per 64 positions, above eight waves one per
+    128; the bias gradient of the QKV projection is their sum (rel 1e-4 to the oracle, as every gradient)."""
+    cfg = dict(layers_per_level=(1,), d_model=32, n_heads=4, d_head=32, d_mlp=32, vocab=40, max_seq=40)
+    a, ctx = make_arch(cfg, dp.F32)
+    theta = gen.random_params(orc.param_count(a), seed=8, scale=0.08)
+    tok, tgt = _batch(cfg, B, S, 3)
+    st = PathState(ctx, theta, B, S)
+    st.fwd_bwd(tok, tgt)
+    _, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
+    layout = {k: v for k, v in orc.param_layout(a).items() if k.endswith(("b_qkv", "w_qkv"))}
+    got, want = host(st.grads).astype(np.float64), np.asarray(o_grad, dtype=np.float64)
+    for name, (off, shape, _) in layout.items():
+        n = int(np.prod(shape))
+        if name.endswith("b_qkv"):   # the key bias has no gradient (softmax is invariant to it): rounding alone
+            for third in (0, 2):
+                part = slice(off + third * n // 3, off + (third + 1) * n // 3)
+                assert rel_l2(got[part], want[part]) <= 1e-4, (name, third)
+        else:
+            assert rel_l2(got[off:off + n], want[off:off + n]) <= 1e-4, name
