@@ -32,7 +32,10 @@ namespace dipaco {
 namespace {
 
 // NW waves of 16 queries (keys) make a workgroup: 8, or 4 where the launch would otherwise be about one workgroup per
-// compute unit and as long as the causal triangle's longest block
+// compute unit and as long as the causal triangle's longest block.  Forward / backward in us with 4 | 8 waves, 8 heads of 500
+// positions: 256 blocks of 128 rows, head size 32: 26 / 69 | 31 / 82, 64: 41 / 114 | 49 / 139, 128: 68 / 206 | 85 / 247; 512
+// blocks 36 / 95 | 39 / 104, 57 / 171 | 63 / 180, 104 / 320 | 107 / 315; 1024 blocks 60 / 163 | 60 / 166, 100 / 294 | 101 / 294,
+// 195 / 591 | 176 / 652.
 constexpr int F_MANY = 8, F_FEW = 4;
 inline bool few_waves(int B, int S, int H) { return (long)B * H * ((S + 127) / 128) <= 512; }
 constexpr int F_TILE = 32;             // keys (queries) per tile

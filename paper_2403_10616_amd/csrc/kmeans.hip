@@ -14,7 +14,9 @@ namespace {
 constexpr int SORT_BLOCK = 2048;   // keys per workgroup
 constexpr int KM_CHUNK = 512;      // rows per partial sum
 constexpr int KM_COLS = 1024;      // columns per workgroup (4 float4 per lane)
-constexpr int KM_AHEAD = 4;        // rows in flight per wave: 2^20 x 768 points 718 us with one, 572 (5.6 TB/s) with four
+// Rows a wave takes per turn of its loop, their loads in front of their additions: 2^20 x 768 points 718 us with one, 572 (5.6 TB/s)
+// with four.  (Every lane loads the row's index, and the wait for it is also one for the row before: no two rows are in flight.)
+constexpr int KM_AHEAD = 4;
 
 __device__ __forceinline__ int clamp_key(int k, int n_keys) { return k < 0 ? 0 : (k >= n_keys ? n_keys - 1 : k); }
 

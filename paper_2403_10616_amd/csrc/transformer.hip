@@ -132,7 +132,8 @@ __global__ void __launch_bounds__(ROW_THREADS) ln_fwd_reg_kernel(const T* __rest
 
 // The sum of a split product's planes, its bias and residual, and the LayerNorm behind it, one wave per row: what the
 // product's epilogue and ln_fwd_reg_kernel do, in their order and on the value rounded to T, so that a small product may be
-// split over K without a pass of its own for the sum.
+// split over K without a pass of its own for the sum.  Bound by latency (4.3 us for 32 x 896): a chunk's bias, residual, gain
+// and shift arrive before its planes are asked for, and a row's second chunk follows the sum of its first.
 template <typename T, int NIT>
 __global__ void __launch_bounds__(WAVE) sum_layernorm_kernel(const float* __restrict__ planes, int n_planes,
                                                              const T* __restrict__ bias, const T* __restrict__ resid,
@@ -916,7 +917,9 @@ dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, flo
 }
 
 // out[b, :] = mean over the S positions of x[b*S + p, :]  (fp32, positions added in order).  A thread owns one 16-byte
-// column chunk and has eight positions' loads in flight (one element and one load at a time: 30 us for a single document).
+// column chunk: 10 us for a single document of 32 x 896 and 100 us for 8192 (one element a thread: 30 and 243).  Bound by the
+// latency of one load after another: the early exit of the adding loop lets the compiler put each position's load behind the
+// addition of the one before, whatever the eight loads written in front of it say.
 constexpr int POOL_THREADS = 128, POOL_AHEAD = 8;
 template <typename T>
 __global__ void __launch_bounds__(POOL_THREADS) mean_pool_kernel(const T* __restrict__ x, float* __restrict__ out, int S, int d) {
