@@ -30,6 +30,11 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
   } while (0)
 // A launch holds fewer than 2^32 threads; the runtime does not refuse more, it runs a part of them.
 inline bool launch_fits(long long blocks, int threads) { return blocks * threads < (1LL << 32); }
+// launch(first, count) over n blocks of up to 1024 threads, in as many launches as that takes: one up to 2^21 blocks
+template <typename F> void launch_parts(long long n, F launch) {
+  constexpr long long most = 1 << 21;
+  for (long long first = 0; first < n; first += most) launch(first, (unsigned)(n - first < most ? n - first : most));
+}
 
 #define DIPACO_LAUNCH_CHECK() DIPACO_HIP(hipGetLastError())
 

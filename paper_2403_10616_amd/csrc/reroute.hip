@@ -38,8 +38,8 @@ __global__ void __launch_bounds__(SCAN_THREADS) nll_prefix_kernel(const float* _
 
 // targets[b][j] = argmin_p (prefix[p][b][min(S, j + L)] - prefix[p][b][j]), lowest p on ties
 __global__ void __launch_bounds__(256) window_targets_kernel(const double* __restrict__ prefix, int* __restrict__ targets,
-                                                             int P, int B, int S, int L) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+                                                             int P, int B, int S, int L, long first_block) {
+  const long i = (first_block + blockIdx.x) * 256 + threadIdx.x;
   if (i >= (long)B * S) return;
   const int b = (int)(i / S), j = (int)(i - (long)b * S);
   const int e = (int)min((long)S, (long)j + L);
@@ -71,21 +71,29 @@ __global__ void __launch_bounds__(256) chunk_score_kernel(const double* __restri
 
 }  // namespace
 
+static void launch_prefixes(const float* nll, double* prefix, long long rows, int S, hipStream_t s) {
+  launch_parts(rows, [&](long long r, unsigned n) {
+    nll_prefix_kernel<<<n, SCAN_THREADS, 0, s>>>(nll + (size_t)r * S, prefix + (size_t)r * (S + 1), S);
+  });
+}
+
 size_t reroute_prefix_doubles(int P, int B, int S) { return (size_t)P * B * (size_t)(S + 1); }
 
 dipaco_status launch_window_targets(const float* nll, int P, int B, int S, int L, int* targets, double* prefix,
                                     hipStream_t s) {
-  nll_prefix_kernel<<<(unsigned)(P * B), SCAN_THREADS, 0, s>>>(nll, prefix, S);
+  launch_prefixes(nll, prefix, (long long)P * B, S, s);
   DIPACO_LAUNCH_CHECK();
   const long n = (long)B * S;
-  window_targets_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(prefix, targets, P, B, S, L);
+  launch_parts((n + 255) / 256, [&](long long first, unsigned blocks) {
+    window_targets_kernel<<<blocks, 256, 0, s>>>(prefix, targets, P, B, S, L, (long)first);
+  });
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
 
 dipaco_status launch_chunk_score(const float* nll, const int* choice, int P, int B, int S, int W, float* out,
                                  double* prefix, hipStream_t s) {
-  nll_prefix_kernel<<<(unsigned)(P * B), SCAN_THREADS, 0, s>>>(nll, prefix, S);
+  launch_prefixes(nll, prefix, (long long)P * B, S, s);
   DIPACO_LAUNCH_CHECK();
   chunk_score_kernel<<<(unsigned)((B + 255) / 256), 256, 0, s>>>(prefix, choice, out, P, B, S, W);
   DIPACO_LAUNCH_CHECK();

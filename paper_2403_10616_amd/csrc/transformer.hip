@@ -861,9 +861,12 @@ dipaco_status launch_softmax_xent(T* logits, const int* targets, const int* n_va
   const size_t vectors = ((size_t)V * sizeof(T) + 15) / 16;
   auto go = [&](auto grad) {
     constexpr bool G = decltype(grad)::value;
-    if (vectors <= 4 * (size_t)XENT_THREADS) softmax_xent_kernel<T, 4, G><<<rows, XENT_THREADS, 0, s>>>(logits, targets, n_valid, nll, V);
-    else if (vectors <= 8 * (size_t)XENT_THREADS) softmax_xent_kernel<T, 8, G><<<rows, XENT_THREADS, 0, s>>>(logits, targets, n_valid, nll, V);
-    else softmax_xent_kernel<T, 0, G><<<rows, ROW_THREADS, 0, s>>>(logits, targets, n_valid, nll, V);
+    launch_parts(rows, [&](long long r, unsigned n) {
+      T* const at = logits + (size_t)r * V;
+      if (vectors <= 4 * (size_t)XENT_THREADS) softmax_xent_kernel<T, 4, G><<<n, XENT_THREADS, 0, s>>>(at, targets + r, n_valid, nll + r, V);
+      else if (vectors <= 8 * (size_t)XENT_THREADS) softmax_xent_kernel<T, 8, G><<<n, XENT_THREADS, 0, s>>>(at, targets + r, n_valid, nll + r, V);
+      else softmax_xent_kernel<T, 0, G><<<n, ROW_THREADS, 0, s>>>(at, targets + r, n_valid, nll + r, V);
+    });
   };
   if (want_grad) go(std::true_type{});
   else go(std::false_type{});
@@ -961,7 +964,7 @@ __global__ void __launch_bounds__(256) doc_score_kernel(const float* __restrict_
 }
 
 dipaco_status launch_doc_score(const float* nll, float* out, int B, int S, hipStream_t s) {
-  doc_score_kernel<<<B, 256, 0, s>>>(nll, out, S);
+  launch_parts(B, [&](long long b, unsigned n) { doc_score_kernel<<<n, 256, 0, s>>>(nll + (size_t)b * S, out + b, S); });
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }

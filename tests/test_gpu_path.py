@@ -312,3 +312,26 @@ def test_qkv_bias_gradient_on_both_sides_of_512_attention_blocks(B, S):
                 assert rel_l2(got[part], want[part]) <= 1e-4, (name, third)
         else:
             assert rel_l2(got[off:off + n], want[off:off + n]) <= 1e-4, name
+
+
+def test_scores_and_loss_of_more_rows_than_one_launch_of_workgroups_holds():
+    """5,000,000 one-token documents: a workgroup of 1024 threads per row passes 2^32 threads in a launch.  A row's score depends on
+    its token and target alone, so every row is checked against the 32 x 32 pairs."""
+    cfg = dict(layers_per_level=(1,), d_model=32, n_heads=1, d_head=32, d_mlp=32, vocab=32, max_seq=1)
+    a, ctx = make_arch(cfg, dp.F32)
+    theta = gen.random_params(orc.param_count(a), seed=14, scale=0.3).astype(np.float32)
+    pairs = np.arange(1024)
+    few = PathState(ctx, theta, 1024, 1)
+    few.fwd_bwd((pairs // 32)[:, None], (pairs % 32)[:, None])
+    B = 5_000_000
+    st = PathState(ctx, theta, B, 1)
+    pick = torch.randint(0, 1024, (B,), device=DEV, generator=torch.Generator(DEV).manual_seed(2))
+    tok, tgt = (x.to(torch.int32).view(B, 1).contiguous() for x in (pick // 32, pick % 32))
+    dp.dipaco_path_fwd_bwd(ctx, st.master, None, tok, tgt, B, 1, st.loss, st.nll, st.grads, st.ws)
+    want = few.nll[pick]
+    assert float((st.nll - want).abs().max()) <= 1e-5
+    assert abs(float(st.loss) - float(want.double().mean())) <= 1e-5
+    doc, nll = torch.full((B,), 7.0, device=DEV), torch.full((B, 1), 7.0, device=DEV)
+    ws = torch.empty(dp.dipaco_score_workspace_bytes(ctx, B, 1), dtype=torch.uint8, device=DEV)
+    dp.dipaco_path_score(ctx, st.master, None, tok, tgt, B, 1, doc, nll, ws)
+    assert float((nll.view(-1) - want).abs().max()) <= 1e-5 and torch.equal(doc, -nll.view(-1))

@@ -439,3 +439,18 @@ def test_more_points_than_one_launch_of_small_workgroups_holds():
         part = z[at:at + 4096].double()
         score = (c.double() ** 2).sum(1) - 2 * part @ c.double().T
         assert torch.equal(idx[at:at + 4096].long(), torch.sort(score, dim=1, stable=True).indices[:, 0])
+
+
+def test_window_labels_of_more_documents_than_one_launch_holds():
+    """17,000,000 documents x 1 position: a workgroup of threads per document and path passes 2^32 threads in a launch."""
+    P, B = 2, 17_000_000
+    nll = torch.rand((P, B, 1), device=DEV, generator=torch.Generator(DEV).manual_seed(4))
+    nbytes = dp.dipaco_reroute_workspace_bytes(P, B, 1)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    labels = torch.full((B, 1), -3, dtype=torch.int32, device=DEV)
+    dp.dipaco_window_targets(nll, P, B, 1, 1, labels, ws, nbytes)
+    want = (nll[1, :, 0] < nll[0, :, 0]).long()
+    assert torch.equal(labels[:, 0].long(), want)
+    out = torch.full((B,), 9.0, device=DEV)
+    dp.dipaco_chunk_routed_score(nll, labels, P, B, 1, 1, out, ws, nbytes)
+    assert torch.equal(out, -nll[:, :, 0].amin(0))
