@@ -735,7 +735,7 @@ def bench_router(args):
                        "route_linear_ms": times["route"],
                        "route_linear_tflops": 2.0 * N * D * K / (times["route"] * 1e-3) / 1e12,
                        "loss": float(loss[0].item())},
-            "roofline": {"bound": "mfma", "kernel": "gemm_kernel<float> (logits, weight gradient) + logistic_rows_kernel",
+            "roofline": {"bound": "mfma", "kernel": "gemm_fit_kernel<float> (logits, weight gradient) + logistic_rows_small_kernel",
                          "achieved": ach, "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_F32_TFLOPS,
                          "traffic": None}}
 
@@ -801,7 +801,7 @@ def bench_gemm(args):
             "dtype": "bf16", "data": "synthetic",
             "config": {"workload": f"gemm {args.layout} M={M} N={N} K={K} epilogue={ep} splits={splits} operands={args.operands}",
                        "library_reference": library},
-            "roofline": {"bound": "mfma", "kernel": "gemm_kernel", "achieved": ach, "peak": PEAK_BF16_TFLOPS,
+            "roofline": {"bound": "mfma", "kernel": "gemm_dlds_kernel / gemm_fit_kernel", "achieved": ach, "peak": PEAK_BF16_TFLOPS,
                          "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS, "traffic": None, "flops_per_launch": flops}}
 
 

@@ -34,7 +34,7 @@
 // of one panel's columns (the lanes whose 16 bytes fall into the other half fetch a valid chunk again, so that no
 // load is conditional).  Head sizes 32 and 128 keep 16 bits of the probabilities and of dS in the second products and sum
 // rows in fp32 (split_p below); head size 64 rounds them to bf16.  Measured on 8 sequences x 8 heads x 512 positions, head
-// size 128: forward 19 us, backward 67 (with operands rounded to bf16 16 and 55, one-thread-per-row kernels 1470 and 22960).
+// size 128: forward 19 us, backward 69 (with operands rounded to bf16 16 and 55, one-thread-per-row kernels 1470 and 22960).
 //
 // The kernels for head size 64 are compiled in attention_mfma.hip, those for 32 and 128 in attention_mfma_exact.hip: the latter
 // honour NaN and keep non-finite values from rows that do not see them (attention_plain.h); with head size 64 such a value may
