@@ -74,8 +74,9 @@ static void weight_shape(const dipaco_ctx* c, int kind, int& rows, int& cols) {
   rows = kind == W_O ? A : kind == W_DOWN ? F : d;
   cols = kind == W_QKV ? 3 * A : kind == W_UP ? F : kind == W_HEAD ? c->arch.vocab : d;
 }
-static int slice_limit(const dipaco_ctx* c, int kind, int tokens) {
-  return c->slice_limit[kind][gemm_limit_index(tokens)];
+constexpr size_t MAX_TOKENS = 1 << 24;   // of a call (check_batch_shape); a size may be asked for more
+static int slice_limit(const dipaco_ctx* c, int kind, size_t tokens) {
+  return c->slice_limit[kind][gemm_limit_index(std::min(tokens, MAX_TOKENS))];
 }
 
 // Every buffer, and so the total, is non-decreasing in B and in S: a workspace made for the largest batch serves the others.
@@ -83,6 +84,7 @@ static Plan make_plan(const dipaco_ctx* c, int B, int S) {
   const dipaco_arch& a = c->arch;
   const size_t T = (size_t)B * S, d = a.d_model, A = c->A, F = a.d_mlp, V = a.vocab;
   const size_t es = a.compute == DIPACO_BF16 ? 2 : 4;
+  const int rows = (int)std::min(T, MAX_TOKENS);
   size_t pos = 0;
   auto take = [&](size_t bytes) {
     size_t at = pos;
@@ -104,19 +106,19 @@ static Plan make_plan(const dipaco_ctx* c, int B, int S) {
   // Partial rows of the backward pass's fixed-order sums.  Their final reductions run as one launch at the end of the
   // step, so every producer keeps a buffer of its own: one per LayerNorm, two per block (the column sums of dU and
   // of dqkv).
-  p.ln_partial_stride = (ln_bwd_partial_floats((int)T, (int)d) * 4 + 255) & ~(size_t)255;
+  p.ln_partial_stride = (ln_bwd_partial_floats(rows, (int)d) * 4 + 255) & ~(size_t)255;
   p.ln_partial = take(p.ln_partial_stride * (2 * (size_t)c->n_layers + 1));
-  p.cs_partial_stride = (std::max(gemm_colsum_partial_floats((int)T, (int)F),
+  p.cs_partial_stride = (std::max(gemm_colsum_partial_floats(rows, (int)F),
                                   attention_bwd_colsum_floats((int)B, (int)S, a.n_heads, a.d_head)) * 4 + 255) & ~(size_t)255;
   p.cs_partial = take(p.cs_partial_stride * std::max<size_t>(1, 2 * (size_t)c->n_layers));
   size_t sk = 0;
   for (int kind = W_QKV; kind <= W_HEAD; ++kind) {
-    int rows, cols;
-    weight_shape(c, kind, rows, cols);
-    sk = std::max(sk, (size_t)slice_limit(c, kind, (int)T) * rows * cols);
+    int M, N;
+    weight_shape(c, kind, M, N);
+    sk = std::max(sk, (size_t)slice_limit(c, kind, T) * M * N);
   }
   p.splitk_partial = take(sk * 4);
-  p.embed_ints = take(embed_bwd_scratch_ints((int)T, (int)V) * 4);
+  p.embed_ints = take(embed_bwd_scratch_ints(rows, (int)V) * 4);
   p.total = pos;
   return p;
 }
@@ -260,11 +262,12 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   p.x_mid = take(T * d * es); p.u = take(T * F * es); p.act = take(T * F * es);   // u: GELU', which only a step keeps; the plan's size is part of the interface
   p.logits = p.nll = p.n_valid = 0;
   if (with_head) { p.logits = take(T * (size_t)a.vocab * es); p.nll = take(T * 4); p.n_valid = take(256); }
-  p.splits_o = gemm_raw_splits((int)T, (int)d, (int)A, es == 2);
-  p.splits_down = gemm_raw_splits((int)T, (int)d, (int)F, es == 2);
+  const int rows = (int)std::min(T, MAX_TOKENS);
+  p.splits_o = gemm_raw_splits(rows, (int)d, (int)A, es == 2);
+  p.splits_down = gemm_raw_splits(rows, (int)d, (int)F, es == 2);
   // room for the planes of any smaller batch too; what fits the static scratch without them keeps fitting it
   p.planes = pos;
-  take(std::max(gemm_raw_plane_floats((int)T, (int)d, (int)A, es == 2), gemm_raw_plane_floats((int)T, (int)d, (int)F, es == 2)) * 4);
+  take(std::max(gemm_raw_plane_floats(rows, (int)d, (int)A, es == 2), gemm_raw_plane_floats(rows, (int)d, (int)F, es == 2)) * 4);
   if (p.planes <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) {
     pos = DIPACO_STATIC_SCRATCH_BYTES;
     if (p.planes + std::max(p.splits_o, p.splits_down) * T * d * 4 > pos) p.splits_o = p.splits_down = 1;
@@ -330,7 +333,7 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
 // kernels index their operands with 32-bit element offsets, so tokens x (widest activation row) stays below 2^32.
 static dipaco_status check_batch_shape(const dipaco_ctx* c, int B, int S, bool with_head) {
   if (B < 1 || S < 1 || S > c->arch.max_seq) return fail(DIPACO_ESHAPE, "batch >= 1 and 1 <= seq <= max_seq required");
-  if ((int64_t)B * S > (1 << 24)) return fail(DIPACO_ESHAPE, "batch*seq above 2^24 is not supported");
+  if ((int64_t)B * S > (int64_t)MAX_TOKENS) return fail(DIPACO_ESHAPE, "batch*seq above 2^24 is not supported");
   const int64_t widest = std::max<int64_t>(std::max<int64_t>(c->arch.d_mlp, 3 * (int64_t)c->A),
                                            std::max<int64_t>(c->arch.d_model, with_head ? c->arch.vocab : 0));
   if ((int64_t)S * 3 * c->A * 2 >= (1LL << 32))   // the attention kernels address one sequence's q | k | v rows with 32-bit byte offsets

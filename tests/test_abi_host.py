@@ -189,3 +189,12 @@ def test_router_workspace_does_not_shrink_with_the_documents(D, K):
         sizes.append(dp.dipaco_router_workspace_bytes(N, D, K))
         N = max(N + 1, N * 1003 // 1000)
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+@pytest.mark.parametrize("compute", [dp.F32, dp.BF16])
+@pytest.mark.parametrize("batch,seq", [(1 << 14, 1 << 10), ((1 << 24) + 1, 1), (1 << 16, 1 << 16), (1 << 20, 1 << 11), (3, 1 << 30)])
+def test_workspace_sizes_beyond_the_token_limit_are_numbers(compute, batch, seq):
+    """A size may be asked for where a call would be refused (2^24 tokens and more)."""
+    ctx = dp.Context([1, 1], 64, 2, 32, 256, 256, 2048, 1e-5, compute)
+    for size in (dp.dipaco_workspace_bytes, dp.dipaco_features_workspace_bytes, dp.dipaco_score_workspace_bytes):
+        assert size(ctx, batch, seq) > batch * seq * 64
