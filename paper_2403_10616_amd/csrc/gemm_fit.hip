@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "gemm_common.h"
+#include "gemm_fit_epilogue.h"
 #include "kernels.h"
 #include "mma_tile.h"
 
@@ -66,9 +67,8 @@ template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM,
   static constexpr int RA = BM * (int)sizeof(T), RB = BN * (int)sizeof(T);   // bytes of a K-row
   static constexpr int NLA = TILE_A / 1024, NL = STAGE / 1024;               // wave-level loads of a stage
   static constexpr int LPS = (NL + FIT_WAVES - 1) / FIT_WAVES;
-  static constexpr int LDW = BN + 4;                       // padded row of the epilogue region (floats)
   static constexpr int IC = TM <= 4 ? TM : 3;              // 16-row blocks per wave and epilogue pass
-  static constexpr int EPI = G * WM * 16 * IC * LDW * 4;
+  static constexpr int EPI = fit_epilogue_bytes(IC, TN, WM, WN, G);
   static constexpr int LDS = ST * STAGE > EPI ? ST * STAGE : EPI;
   // Workgroups on a compute unit, two waves a SIMD each: the register budget has to leave room for both (132 registers in the
   // 64 x 128 A.B^T kernel of fp32 left one: 36311 x 3488 x 104 435 us, 338 with both)
@@ -308,118 +308,8 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, (2 * Fit<T, TC, A_KC, B_KC, TM
   if (nkt & 1) multiply_last(C0{});
   else multiply_last(C1{});
 
-  // ---- epilogue: groups added in order, then bias / activation / residual on eight columns per item ----
-  constexpr int CG = BN / 8, IC = F::IC, LDW = F::LDW;
-  static_assert((64 * FIT_WAVES) % CG == 0, "a thread keeps its column group over the items");
-  float* const red = reinterpret_cast<float*>(smem);
-  const int cg = tid % CG, col = n0 + 8 * cg;
-  const bool col_ok = col < g.N, partial = g.splits > 1;
-  const T* const bias = static_cast<const T*>(g.bias);
-  const T* const resid = static_cast<const T*>(g.resid);
-  const T* const aux_in = static_cast<const T*>(g.aux_in);
-  const bool want_aux = g.act == 2 || g.act == 4;
-  const T* const ahead = want_aux ? aux_in : resid;
-  const long ldc = g.ldc;
-  float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (bias && col_ok) OutVec<T>::load(bias + col, bv);
-  auto pass = [&](auto I0, auto N16) {   // 16-row blocks I0 .. I0 + N16 - 1 of every wave
-    constexpr int i0 = decltype(I0)::value, n16 = decltype(N16)::value;
-    constexpr int ROWS = WM * 16 * n16, ITERS = (ROWS * CG + 64 * FIT_WAVES - 1) / (64 * FIT_WAVES);
-    auto row_of = [&](int rr) { return m0 + (rr / (16 * n16)) * 16 * TM + 16 * i0 + rr % (16 * n16); };
-    Raw8<T> rin[ITERS];
-    if (ahead) {
-#pragma unroll
-      for (int it = 0; it < ITERS; ++it) {
-        const int rr = (tid + 64 * FIT_WAVES * it) / CG, row = row_of(rr);
-        if (rr < ROWS && row < g.M && col_ok) rin[it] = raw8_load(ahead + (size_t)row * ldc + col);
-      }
-    }
-    __syncthreads();   // the ring (or the pass before) has been read
-#pragma unroll
-    for (int i = 0; i < n16; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          red[((grp * WM + wm) * 16 * n16 + 16 * i + 4 * kg + e) * LDW + (wn * TN + j) * 16 + r] = acc[i0 + i][j][e];
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-      const int rr = (tid + 64 * FIT_WAVES * it) / CG, row = row_of(rr);
-      if (rr >= ROWS || row >= g.M || !col_ok) continue;
-      float v[8];
-      OutVec<float>::load(red + rr * LDW + 8 * cg, v);
-#pragma unroll
-      for (int q = 1; q < G; ++q) {
-        float w[8];
-        OutVec<float>::load(red + (q * ROWS + rr) * LDW + 8 * cg, w);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] += w[c];
-      }
-      if (partial) {
-        OutVec<float>::store(g.partial + ((size_t)split * g.M + row) * g.N + col, v);
-        continue;
-      }
-      const size_t o = (size_t)row * ldc + col;
-      if constexpr (std::is_same<T, TC>::value) {
-        if (bias) {
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] += bv[c];
-        }
-        if (g.act == 1) {
-          OutVec<T>::store(static_cast<T*>(g.aux_out) + o, v);   // GELU is applied to the stored value
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] = gelu_t<T>(to_f32(from_f32<T>(v[c])));
-        } else if (g.act == 3) {
-          float dv[8];
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv[c]);
-          OutVec<T>::store(static_cast<T*>(g.aux_out) + o, dv);
-        } else if (g.act == 5) {
-          float dv;
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] = gelu_with_grad_t<T>(v[c], dv);
-        } else if (want_aux) {
-          float u[8];
-          raw8_unpack(rin[it], u);
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] *= g.act == 2 ? gelu_grad_t<T>(u[c]) : u[c];
-        }
-        if (resid) {
-          float rv[8];
-          raw8_unpack(want_aux ? raw8_load(resid + o) : rin[it], rv);
-#pragma unroll
-          for (int c = 0; c < 8; ++c) v[c] += rv[c];
-        }
-      }
-      OutVec<TC>::store(static_cast<TC*>(g.C) + o, v);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) cs[c] += v[c];
-    }
-  };
-  pass(C0{}, std::integral_constant<int, IC>{});
-  if constexpr (TM > IC) pass(std::integral_constant<int, IC>{}, std::integral_constant<int, TM - IC>{});
-  if (g.colsum_partial) {   // one row of column sums per tile: lanes with the same columns, then the waves in order
-#pragma unroll
-    for (int m = CG; m < WAVE; m <<= 1)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) cs[c] += __shfl_xor(cs[c], m, WAVE);
-    __syncthreads();
-    if (lane < CG) OutVec<float>::store(red + wave * BN + 8 * lane, cs);
-    __syncthreads();
-    if (tid < CG && col_ok) {
-      float s[8];
-      OutVec<float>::load(red + 8 * tid, s);
-#pragma unroll
-      for (int w = 1; w < FIT_WAVES; ++w) {
-        float x[8];
-        OutVec<float>::load(red + w * BN + 8 * tid, x);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s[c] += x[c];
-      }
-      OutVec<float>::store(g.colsum_partial + (size_t)tile_m * g.N + col, s);
-    }
-  }
+  fit_epilogue<T, TC, TM, TN, WM, WN, G, F::IC>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0, tile_m, split,
+                                                [](float (&)[8], int, int) {});
 }
 
 template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST, bool FAR = false>
@@ -455,10 +345,10 @@ dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
   return DIPACO_OK;
 }
 
-// Tile shapes: 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 rows x 128.  fp32 has 1 and 2 (its matrix-core steps are sixteen times as
-// long: 64 x 128 tiles, two workgroups per compute unit, were the fastest of the 128-column ones on every product measured);
-// row-contiguous A 1, 2 and 4.
-bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || (bf16_operands && (a_kc || t == 4)); }
+// Tile shapes: 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 rows x 128.  fp32 has 1, 2 (its matrix-core steps are sixteen times as
+// long: 64 x 128 tiles, two workgroups per compute unit, were the fastest of the 128-column ones on every product measured) and 4, which
+// runs on the bf16 matrix cores (gemm_split.hip); row-contiguous A 1, 2 and 4.
+bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 || (bf16_operands && a_kc); }
 
 // Microseconds of `tiles` tiles over K: rounds of 256 workgroups x (fixed + per 1000 of K).  Fitted to launches of 256 .. 8192
 // rows, K 64 .. 8192 (rel. error 15 %): 3000 x 896 x 3584 bf16 34.8 / 26.0 / 28.8 / 33.7 us for shapes 2 .. 5, 5700 x 896 x 3584
@@ -468,10 +358,17 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || (bf16_op
 // (9780 x 13336, 2540 x 7248, 9000 x 2000).  In a weight gradient, whose workgroups all end together, 257 .. 512
 // of them are one round of twice the length, and a third 256 behind them lands two to a unit again: 256 x 768 over 2^20 rows in
 // fp32 2930 us in 504 workgroups, 3500 - 3900 in 768, 2980 in 1536.
+// fp32 in 128 x 128 tiles, us against 64 x 128 ones, by tiles over K (K = 256 / 512 / 2048 / 8192): 256 tiles 28 / 42 / 124 / 452 against
+// 25 / 39 / 126 / 477, 384 35 / 53 / 160 / 620 against 34 / 55 / 188 / 726, 512 39 / 57 / 182 / 700 against 42 / 70 / 245 / 948, 2048
+// 132 / 206 / 708 against 150 / 262 / 968; at K = 64 512 tiles are level.  A round of 512 workgroups is two to a compute unit.
 double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
   const int bm = 32 * t, bn = t == 1 ? 64 : 128;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
+  if (t == 4 && !bf16_operands) {
+    const long full = (tiles + 255) / 512, rest = tiles - full * 512;   // rounds of two workgroups a unit, and of one behind them
+    return 3.0 + full * (18.0 + 88.0 * K * 1e-3) + (rest > 0 ? 10.5 + 60.0 * K * 1e-3 : 0.0);
+  }
   const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
   const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
   if (t == 2 && a_kc && bf16_operands) return 4.9 + (double)rounds * (1.6 + k * K * 1e-3);
@@ -496,7 +393,12 @@ template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_s
   const int splits = std::max(1, a.splits);
   const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
-  if constexpr (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 4) {
+    if (t == 4) {
+      constexpr uint64_t most = 1ull << 32;   // 32-bit offsets there too
+      if (fit_span(A_KC, 128, 32, a.M, a.K, a.lda, 4) < most && fit_span(B_KC, 128, 32, a.N, a.K, a.ldb, 4) < most) return launch_gemm_split(a, s);
+    }
+  } else {
     if constexpr (A_KC) {
       if (t == 3) return run_fit<T, TC, A_KC, B_KC, 3, 4, 2, 2, 2, 4>(a, s);
       if (t == 5) return run_fit<T, TC, A_KC, B_KC, 5, 4, 2, 2, 2, 4>(a, s);

@@ -362,6 +362,38 @@ def test_gemm_fitted_tiles_at_their_edges(dtype, tile, M, N, K):
         dp.dipaco_k_set_gemm_tile(0)
 
 
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+@pytest.mark.parametrize("M,N,K", [(128, 128, 32), (132, 136, 36), (256, 264, 500), (4, 8, 4), (260, 120, 2052)])
+def test_fp32_products_from_bf16_parts(ta, tb, M, N, K):
+    """The 128 x 128 fp32 tile multiplies three bf16 parts of every number.  The part products left out and the cut-off of a
+    matrix-core step stay below 2^-22 of a step of 32, and the steps are added in fp32; numbers whose first part is not finite take
+    the fp32 way."""
+    dp.dipaco_k_set_gemm_tile(4)
+    try:
+        A, Ar = _rand((K, M) if ta else (M, K), 21, dp.F32)
+        B, Br = _rand((N, K) if tb else (K, N), 22, dp.F32)
+        Br = Br.T if tb else Br
+        C = torch.empty((M, N), dtype=torch.float32, device=DEV)
+        run = lambda: dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C)
+        run()
+        ref = (Ar.T if ta else Ar) @ Br
+        assert rel_l2(host(C), ref) <= 2.0 ** -22 + 2.0 ** -25 * math.sqrt((K + 31) // 32)
+        before = host(C).copy()
+        row = lambda m: A[:, m] if ta else A[m]
+        row(1)[K - 1] = math.inf
+        row(2).zero_()
+        row(2)[0] = 3.4e38                       # finite, but its first bf16 part is not
+        B.mul_(0.125)
+        run()
+        got = host(C)
+        with np.errstate(over="ignore"):
+            assert np.array_equal(got[1], np.where(Br[K - 1] > 0, np.inf, -np.inf).astype(np.float32))
+        assert np.allclose(got[2], 3.4e38 * 0.125 * Br[0], rtol=1e-6)
+        assert np.array_equal(got[3:], before[3:] * np.float32(0.125)) and np.array_equal(got[0], before[0] * np.float32(0.125))
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
+
+
 @pytest.mark.parametrize("B,S,H,dh", [(260, 33, 2, 32), (260, 33, 2, 64), (260, 100, 2, 128), (60, 300, 3, 32), (171, 129, 2, 64)])
 def test_fp32_attention_above_512_blocks(B, S, H, dh):
     """More than 512 blocks of 128 rows run eight waves a workgroup, forward and backward."""
