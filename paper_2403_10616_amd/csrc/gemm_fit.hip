@@ -346,9 +346,9 @@ dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
 }
 
 // Tile shapes: 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 rows x 128.  fp32 has 1, 2 (its matrix-core steps are sixteen times as
-// long: 64 x 128 tiles, two workgroups per compute unit, were the fastest of the 128-column ones on every product measured) and 4, which
-// runs on the bf16 matrix cores (gemm_split.hip); row-contiguous A 1, 2 and 4.
-bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 || (bf16_operands && a_kc); }
+// long: 64 x 128 tiles, two workgroups per compute unit, were the fastest of the 128-column ones on every product measured) and, on the
+// bf16 matrix cores (gemm_split.hip), 4 and a 64 x 128 tile as number 3; row-contiguous A in bf16 1, 2 and 4.
+bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 || (t == 3 && !bf16_operands) || (bf16_operands && a_kc); }
 
 // Microseconds of `tiles` tiles over K: rounds of 256 workgroups x (fixed + per 1000 of K).  Fitted to launches of 256 .. 8192
 // rows, K 64 .. 8192 (rel. error 15 %): 3000 x 896 x 3584 bf16 34.8 / 26.0 / 28.8 / 33.7 us for shapes 2 .. 5, 5700 x 896 x 3584
@@ -361,10 +361,14 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 |
 // fp32 in 128 x 128 tiles, us against 64 x 128 ones, by tiles over K (K = 256 / 512 / 2048 / 8192): 256 tiles 28 / 42 / 124 / 452 against
 // 25 / 39 / 126 / 477, 384 35 / 53 / 160 / 620 against 34 / 55 / 188 / 726, 512 39 / 57 / 182 / 700 against 42 / 70 / 245 / 948, 2048
 // 132 / 206 / 708 against 150 / 262 / 968; at K = 64 512 tiles are level.  A round of 512 workgroups is two to a compute unit.
+// In 64 x 128 tiles of bf16 parts, one to a compute unit: 250 tiles 21.5 / 65 / 225 us (K = 512 / 2048 / 8192) against 22.5 / 71 - 80 /
+// 252 - 280 on the fp32 instruction, 750 tiles 58 against 55: taken for one round.
 double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
-  const int bm = 32 * t, bn = t == 1 ? 64 : 128;
+  const bool split_64 = t == 3 && !bf16_operands;
+  const int bm = split_64 ? 64 : 32 * t, bn = t == 1 ? 64 : 128;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
+  if (split_64) return tiles <= 256 ? 8.0 + 27.0 * K * 1e-3 : 1e30;
   if (t == 4 && !bf16_operands) {
     const long full = (tiles + 255) / 512, rest = tiles - full * 512;   // rounds of two workgroups a unit, and of one behind them
     return 3.0 + full * (18.0 + 88.0 * K * 1e-3) + (rest > 0 ? 10.5 + 60.0 * K * 1e-3 : 0.0);
@@ -394,9 +398,10 @@ template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_s
   const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
   if constexpr (sizeof(T) == 4) {
-    if (t == 4) {
+    if (t == 3 || t == 4) {
       constexpr uint64_t most = 1ull << 32;   // 32-bit offsets there too
-      if (fit_span(A_KC, 128, 32, a.M, a.K, a.lda, 4) < most && fit_span(B_KC, 128, 32, a.N, a.K, a.ldb, 4) < most) return launch_gemm_split(a, s);
+      if (fit_span(A_KC, 128, 32, a.M, a.K, a.lda, 4) < most && fit_span(B_KC, 128, 32, a.N, a.K, a.ldb, 4) < most)
+        return launch_gemm_split(a, t == 3 ? 64 : 128, s);
     }
   } else {
     if constexpr (A_KC) {

@@ -1,14 +1,16 @@
 // fp32 products on the bf16 matrix cores (three bf16 parts of every number, six part products: split_tile.h), all three operand
 // layouts of the path step, any M, N, K that launch_gemm accepts: the fp32 products of many tiles.
 //
-// A workgroup is four waves of 64 x 64 outputs on a 128 x 128 tile.  A wave loads its share of the next 32 of K into registers while it
+// A workgroup is four waves of 64 x 64 outputs on a 128 x 128 tile, or, for one round of smaller tiles, eight on a 64 x 128 tile: four groups
+// of two along K, whose sums meet in the epilogue (4000 x 512 x 2048 in 250 workgroups 71 - 80 us on the fp32 instruction, 65 here; the
+// groups split and multiply in step, and LDS serves 221 KB a stage).  A wave loads its share of the next 32 of K into registers while it
 // multiplies; then the shares are taken apart, each number once per workgroup, into one stage of LDS.  Two workgroups share a compute
 // unit: one splits and stores under the other's MFMAs, which go first (wave priority: 4096^3 678 -> 640 us).
 // Bound by the MFMAs and the power they draw: 4096^3 takes 504 us without loads and splitting, 640 with, 950 on the fp32 instruction
 // (16384 x 4096 x 1024 990 -> 690, 4000 x 8192 x 512 265 -> 185); error against 64 bits 2.2e-7 | 8.1e-7 there (K = 4096), 9e-8 | 2.9e-7 at 512.
 // Left out, measured: eight waves on 256 x 128 with two stages and the splitting dealt over the MFMAs (630 us, and a workgroup's ends uncovered:
-// 4000 x 2048 x 512 59 us against 55), tiles split by the waves that read them (VALU: 770), 64 x 64 and 64 x 128 tiles (level with the
-// fp32 instruction: 4000 x 512 x 2048 65 - 72 us against 75).
+// 4000 x 2048 x 512 59 us against 55), tiles split by the waves that read them (VALU: 770), 64 x 64 and 64 x 128 tiles on
+// four waves (level with the fp32 instruction: 4000 x 512 x 2048 65 - 72 us against 75).
 #include <algorithm>
 #include <type_traits>
 
@@ -21,16 +23,26 @@ namespace dipaco {
 
 namespace {
 
-constexpr int SP_TILE = 128, SP_T = 4;   // tile side; 16-row blocks of a wave's 64 rows and columns
-constexpr int SP_PLANE = SP_TILE * SPLIT_ROW;
-constexpr int SP_EPI_ROWS = 2;           // blocks of an epilogue pass
-constexpr int SP_LDS = 6 * SP_PLANE;     // planes of A, planes of B
-static_assert(fit_epilogue_bytes(SP_EPI_ROWS, SP_T, 2, 2, 1) <= SP_LDS && 2 * SP_LDS <= 160 * 1024, "two workgroups on a compute unit");
+constexpr int SP_T = 4;   // 16-row blocks of a wave's 64 rows and columns
 
-template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(256, 2) gemm_split_kernel(const GemmDev g) {
+// G groups of WM x WN waves; a group takes its own 32 of a stage's 32 G of K
+template <int WM, int WN, int G> struct SplitGemm {
+  static constexpr int BM = 64 * WM, BN = 64 * WN, BK = 32 * G, THREADS = 64 * WM * WN * G;
+  static constexpr int UA = 2 / WN, UB = 2 / WM;   // 32-row units of each operand that a wave stages
+  static constexpr int PLANE_A = BM * SPLIT_ROW, PLANE_B = BN * SPLIT_ROW;
+  static constexpr int GROUP = 3 * (PLANE_A + PLANE_B);   // planes of A, planes of B
+  static constexpr int EPI_ROWS = G == 1 ? 2 : 4;         // blocks of an epilogue pass
+  static constexpr int LDS = G * GROUP;
+  static_assert(fit_epilogue_bytes(EPI_ROWS, SP_T, WM, WN, G) <= LDS && LDS * (512 / THREADS) <= 160 * 1024, "two waves a SIMD");
+};
+
+template <bool A_KC, bool B_KC, int WM, int WN, int G>
+__global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const GemmDev g) {
+  using P = SplitGemm<WM, WN, G>;
+  constexpr int UA = P::UA, UB = P::UB, BK = P::BK;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave_all / (WM * WN), wave = wave_all % (WM * WN), wm = wave / WN, wn = wave % WN;
 
   int split, tile_m, tile_n;
   if (g.splits > 1) {   // each XCD gets a contiguous, slice-major range
@@ -41,60 +53,75 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(256, 2) gemm_s
   } else {
     gemm_tile_of_block(g, blockIdx.x, split, tile_m, tile_n);
   }
-  const int m0 = tile_m * SP_TILE, n0 = tile_n * SP_TILE;
+  const int m0 = tile_m * P::BM, n0 = tile_n * P::BN;
   const int k_begin = split * g.k_per_split, k_end = min(g.K, k_begin + g.k_per_split);
-  const int nkt = (k_end - k_begin + 31) / 32;
+  const int nkt = (k_end - k_begin + BK - 1) / BK;
+  const int k_grp = k_end - k_begin - 32 * grp;   // K left to the group at stage 0
 
-  // ---- staging: wave w loads and splits rows 32 w .. 32 w + 31 of both operand tiles ----
+  // ---- staging: a wave loads and splits UA and UB units of 32 rows of the group's operand tiles ----
   using UnitA = SplitUnit<A_KC>;
   using UnitB = SplitUnit<B_KC>;
-  const char* base_a = static_cast<const char*>(g.A) + (A_KC ? (long)m0 * g.lda + k_begin : (long)k_begin * g.lda + m0) * 4;
-  const char* base_b = static_cast<const char*>(g.B) + (B_KC ? (long)n0 * g.ldb + k_begin : (long)k_begin * g.ldb + n0) * 4;
-  const long adv_a = (A_KC ? 32L : 32 * g.lda) * 4, adv_b = (B_KC ? 32L : 32 * g.ldb) * 4;
-  UnitA sa;
-  UnitB sb;
-  uint32_t off_a[4], off_b[4];
-  // byte offsets relative to the operands' bases at the stage's first K; klim: K left there
+  const long kb = k_begin + 32 * grp;
+  const char* base_a = static_cast<const char*>(g.A) + (A_KC ? (long)m0 * g.lda + kb : kb * g.lda + m0) * 4;
+  const char* base_b = static_cast<const char*>(g.B) + (B_KC ? (long)n0 * g.ldb + kb : kb * g.ldb + n0) * 4;
+  const long adv_a = (A_KC ? (long)BK : BK * g.lda) * 4, adv_b = (B_KC ? (long)BK : BK * g.ldb) * 4;
+  UnitA sa[UA];
+  UnitB sb[UB];
+  uint32_t off_a[UA][4], off_b[UB][4];
+  // byte offsets relative to the operands' bases at the group's first K of a stage; klim: K left there
   auto offsets = [&](int klim) {
-    auto offset = [&](auto KCc, int j, long ld, int left) {
+    auto offset = [&](auto KCc, int unit, int j, long ld, int left) {
       using Unit = SplitUnit<decltype(KCc)::value>;
-      const int row = 32 * wave + Unit::row(lane, j), k = Unit::k(lane, j);
+      const int row = 32 * unit + Unit::row(lane, j), k = Unit::k(lane, j);
       if (decltype(KCc)::value) return (uint32_t)(((long)min(row, left - 1) * ld + min(k, klim - 4)) * 4);
       return (uint32_t)(((long)min(k, klim - 1) * ld + min(row, left - 4)) * 4);
     };
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      off_a[j] = offset(std::bool_constant<A_KC>{}, j, g.lda, g.M - m0);
-      off_b[j] = offset(std::bool_constant<B_KC>{}, j, g.ldb, g.N - n0);
+#pragma unroll
+      for (int u = 0; u < UA; ++u) off_a[u][j] = offset(std::bool_constant<A_KC>{}, UA * wave + u, j, g.lda, g.M - m0);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) off_b[u][j] = offset(std::bool_constant<B_KC>{}, UB * wave + u, j, g.ldb, g.N - n0);
     }
   };
-  auto load = [&](int kt) {   // stage kt, if it exists; stages are requested in order
-    const int klim = k_end - k_begin - kt * 32;
+  auto load = [&](int kt) {   // stage kt, if the group has one; stages are requested in order
+    const int klim = k_grp - kt * BK;
     if (klim <= 0) return;
     if (klim < 32) offsets(klim);   // the last one, where the range ends inside it
 #pragma unroll
-    for (int j = 0; j < 4; ++j) sa.load(base_a, off_a[j], j);
+    for (int u = 0; u < UA; ++u)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) sb.load(base_b, off_b[j], j);
+      for (int j = 0; j < 4; ++j) sa[u].load(base_a, off_a[u][j], j);
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sb[u].load(base_b, off_b[u][j], j);
     base_a += adv_a;
     base_b += adv_b;
   };
-  int store_a[4], store_b[4];
+  char* const stage = smem + grp * P::GROUP;
+  int store_a[4], store_b[4];   // of the wave's first units; the next ones lie 32 rows on
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    store_a[q] = 32 * SPLIT_ROW * wave + UnitA::store_offset(lane, q);
-    store_b[q] = 3 * SP_PLANE + 32 * SPLIT_ROW * wave + UnitB::store_offset(lane, q);
+    store_a[q] = 32 * SPLIT_ROW * UA * wave + UnitA::store_offset(lane, q);
+    store_b[q] = 3 * P::PLANE_A + 32 * SPLIT_ROW * UB * wave + UnitB::store_offset(lane, q);
   }
   auto store = [&](int kt) {
-    const int klim = k_end - k_begin - kt * 32;
+    const int klim = k_grp - kt * BK;
     if (klim < 32) {   // K beyond the range counts as zero
-      sa.cut(lane, klim);
-      sb.cut(lane, klim);
+#pragma unroll
+      for (int u = 0; u < UA; ++u) sa[u].cut(lane, klim);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) sb[u].cut(lane, klim);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sa.template store<SP_PLANE>(smem + store_a[q], q);
+    for (int u = 0; u < UA; ++u)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sb.template store<SP_PLANE>(smem + store_b[q], q);
+      for (int q = 0; q < 4; ++q) sa[u].template store<P::PLANE_A>(stage + store_a[q] + 32 * SPLIT_ROW * u, q);
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sb[u].template store<P::PLANE_B>(stage + store_b[q] + 32 * SPLIT_ROW * u, q);
   };
 
   f32x4 acc[SP_T][SP_T];
@@ -105,8 +132,8 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(256, 2) gemm_s
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
   const SplitFragments frag(lane);
-  const char* const pa = smem + wm * 64 * SPLIT_ROW;
-  const char* const pb = smem + 3 * SP_PLANE + wn * 64 * SPLIT_ROW;
+  const char* const pa = stage + wm * 64 * SPLIT_ROW;
+  const char* const pb = stage + 3 * P::PLANE_A + wn * 64 * SPLIT_ROW;
 
   offsets(1 << 30);
   load(0);
@@ -115,7 +142,7 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(256, 2) gemm_s
     load(kt + 1);
     __syncthreads();
     __builtin_amdgcn_s_setprio(1);
-    split_multiply<SP_T, SP_T, SP_PLANE, SP_PLANE>(acc, pa, pb, frag);
+    split_multiply<SP_T, SP_T, P::PLANE_A, P::PLANE_B>(acc, pa, pb, frag);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
   }
@@ -132,28 +159,29 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(256, 2) gemm_s
       v[c] = s;
     }
   };
-  fit_epilogue<float, float, SP_T, SP_T, 2, 2, 1, SP_EPI_ROWS>(g, acc, reinterpret_cast<float*>(smem), tid, 0, wm, wn, m0, n0, tile_m,
-                                                                split, fix);
+  fit_epilogue<float, float, SP_T, SP_T, WM, WN, G, P::EPI_ROWS>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0,
+                                                                  tile_m, split, fix);
 }
 
-template <bool A_KC, bool B_KC> dipaco_status run_split(const GemmArgs& a, hipStream_t s) {
-  auto kern = gemm_split_kernel<A_KC, B_KC>;
+template <bool A_KC, bool B_KC, int WM, int WN, int G> dipaco_status run_split(const GemmArgs& a, hipStream_t s) {
+  using P = SplitGemm<WM, WN, G>;
+  auto kern = gemm_split_kernel<A_KC, B_KC, WM, WN, G>;
   static std::atomic<unsigned long long> lds_set{0};   // per instantiation
-  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), SP_LDS, lds_set)) return e;
+  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), P::LDS, lds_set)) return e;
   GemmDev g;
   g.A = a.A; g.B = a.B; g.C = a.C; g.M = a.M; g.N = a.N; g.K = a.K;
   g.lda = a.lda; g.ldb = a.ldb; g.ldc = a.ldc;
   g.bias = a.bias; g.resid = a.resid; g.aux_out = a.aux_out; g.aux_in = a.aux_in; g.act = a.act;
   g.partial = a.partial;
-  g.tiles_m = (a.M + SP_TILE - 1) / SP_TILE;
-  g.tiles_n = (a.N + SP_TILE - 1) / SP_TILE;
-  const int steps = (a.K + 31) / 32, want = std::max(1, std::min(a.splits, steps));
-  g.k_per_split = (steps + want - 1) / want * 32;
+  g.tiles_m = (a.M + P::BM - 1) / P::BM;
+  g.tiles_n = (a.N + P::BN - 1) / P::BN;
+  const int steps = (a.K + P::BK - 1) / P::BK, want = std::max(1, std::min(a.splits, steps));
+  g.k_per_split = (steps + want - 1) / want * P::BK;
   g.splits = (a.K + g.k_per_split - 1) / g.k_per_split;
   const long blocks = (long)g.tiles_m * g.tiles_n * g.splits;
-  if (!launch_fits(blocks, 256)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
+  if (!launch_fits(blocks, P::THREADS)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
   g.colsum_partial = a.colsum ? a.colsum_partial : nullptr;
-  kern<<<(unsigned)blocks, 256, SP_LDS, s>>>(g);
+  kern<<<(unsigned)blocks, P::THREADS, P::LDS, s>>>(g);
   DIPACO_LAUNCH_CHECK();
   if (g.splits > 1) return launch_splitk_reduce(a.partial, static_cast<float*>(a.C), a.M, a.N, a.ldc, g.splits, s);
   if (a.colsum) return launch_sum_rows(a.colsum_partial, a.colsum, g.tiles_m, a.N, s, a.sum_batch);
@@ -162,10 +190,14 @@ template <bool A_KC, bool B_KC> dipaco_status run_split(const GemmArgs& a, hipSt
 
 }  // namespace
 
-dipaco_status launch_gemm_split(const GemmArgs& a, hipStream_t s) {
-  if (a.out_f32) return run_split<false, false>(a, s);
-  if (!a.trans_b) return run_split<true, false>(a, s);
-  return run_split<true, true>(a, s);
+template <bool A_KC, bool B_KC> dipaco_status run_split_shape(const GemmArgs& a, int rows, hipStream_t s) {
+  if (rows == 64) return run_split<A_KC, B_KC, 1, 2, 4>(a, s);
+  return run_split<A_KC, B_KC, 2, 2, 1>(a, s);
+}
+dipaco_status launch_gemm_split(const GemmArgs& a, int rows, hipStream_t s) {
+  if (a.out_f32) return run_split_shape<false, false>(a, rows, s);
+  if (!a.trans_b) return run_split_shape<true, false>(a, rows, s);
+  return run_split_shape<true, true>(a, rows, s);
 }
 
 }  // namespace dipaco

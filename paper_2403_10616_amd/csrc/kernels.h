@@ -123,8 +123,8 @@ dipaco_status launch_gemm_dlds(const GemmArgs& g, hipStream_t s);
 void set_gemm_dlds_shape(int shape);   // 0 = automatic, 1 = 256 x 256, 2 = 256 x 128, 3 / 4 = 128 x 512 / 512 x 128 for weight gradients, 5 = 224-column tiles where N % 224 == 0
 // gemm_fit.hip: any type, layout and size that launch_gemm accepts; tiles fitted to the grid
 template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& g, hipStream_t s);
-// gemm_split.hip: fp32 on the bf16 matrix cores, 64 x 128 or (tall) 128 x 128 tiles; rows less than 4 GiB apart within a tile
-dipaco_status launch_gemm_split(const GemmArgs& g, hipStream_t s);
+// gemm_split.hip: fp32 on the bf16 matrix cores, tiles of 64 or 128 rows x 128; rows less than 4 GiB apart within a tile
+dipaco_status launch_gemm_split(const GemmArgs& g, int rows, hipStream_t s);
 void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 x 128
 // C[m, n] = sum over z < splits of partial[z, m, n], in index order
 dipaco_status launch_splitk_reduce(const float* partial, float* C, int M, int N, long ldc, int splits, hipStream_t s);

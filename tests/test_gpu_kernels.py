@@ -363,12 +363,13 @@ def test_gemm_fitted_tiles_at_their_edges(dtype, tile, M, N, K):
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+@pytest.mark.parametrize("tile", [3, 4])
 @pytest.mark.parametrize("M,N,K", [(128, 128, 32), (132, 136, 36), (256, 264, 500), (4, 8, 4), (260, 120, 2052)])
-def test_fp32_products_from_bf16_parts(ta, tb, M, N, K):
-    """The 128 x 128 fp32 tile multiplies three bf16 parts of every number.  The part products left out and the cut-off of a
+def test_fp32_products_from_bf16_parts(ta, tb, M, N, K, tile):
+    """The 128 x 128 fp32 tile and the 64 x 128 one (four groups of waves along K) multiply three bf16 parts of every number.  The part products left out and the cut-off of a
     matrix-core step stay below 2^-22 of a step of 32, and the steps are added in fp32; numbers whose first part is not finite take
     the fp32 way."""
-    dp.dipaco_k_set_gemm_tile(4)
+    dp.dipaco_k_set_gemm_tile(tile)
     try:
         A, Ar = _rand((K, M) if ta else (M, K), 21, dp.F32)
         B, Br = _rand((N, K) if tb else (K, N), 22, dp.F32)
