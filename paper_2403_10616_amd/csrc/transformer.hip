@@ -583,37 +583,49 @@ __global__ void __launch_bounds__(1024) mean_loss_kernel(const float* __restrict
 // ---- embedding gradient ----------------------------------------------------------------------------------
 // d_tok[v] = sum of dx rows whose token is v, added in increasing position order (no float atomics): positions are
 // grouped by token with a stable sort (kmeans.hip), then one workgroup per vocabulary row adds its positions.
-// One workgroup (16 waves) per vocabulary row.  Wave w adds the row's positions w, w+16, ... in order (lanes over
-// 16-byte column chunks, eight row loads in flight), then the wave sums are added in wave order: a fixed tree, so the frequent tokens
-// of a Zipf batch (thousands of positions) are spread over the workgroup without any atomics.
+// A workgroup (16 waves) takes up to 16 vocabulary rows, `stride` apart (the frequent tokens of a corpus have low ids: neighbours go to
+// different workgroups).  Rows of no or one position are written by a wave each; for the others wave w adds the row's positions
+// w, w+16, ... in order (lanes over 16-byte column chunks, eight row loads in flight), then the wave sums are added in wave order: a
+// fixed tree, so the frequent tokens of a Zipf batch (thousands of positions) are spread over the workgroup without any atomics.
 constexpr int TG_WAVES = 16;
 constexpr int TG_UNROLL = 8;   // row loads in flight per wave
 constexpr int TG_MAX_D = 2048;   // widest model: 16 partial rows of 2048 floats = 128 KB of the 160 KB of LDS
-// SCAN: up to TG_SCAN_ROWS positions the workgroup finds its token's positions itself, by ballots over all of them (the
-// same increasing order), instead of the sort's seven launches of 4 - 12 us each in front of this one.
+// SCAN: up to TG_SCAN_ROWS positions the workgroup finds its tokens' positions itself, by ballots over all of them (the
+// same increasing order), instead of the sort's seven launches of 4 - 12 us each in front of this one.  The scan, not the 4 bytes a
+// gradient, bounds a workgroup with one row: 32000 of them over 3000 positions x 896 took 142 us.
 constexpr int TG_SCAN_ROWS = 4 * TG_WAVES * WAVE;
+// log2 of the rows' stride: a workgroup per row up to 1024 rows, else 1024 workgroups or 16 rows each
+inline int tok_grad_stride_log2(int vocab) {
+  int sh = 0;
+  while ((1LL << sh) < vocab && (sh < 10 || (vocab - 1) >> sh >= TG_WAVES)) ++sh;
+  return sh;
+}
 template <typename T, bool SCAN>
 __global__ void __launch_bounds__(TG_WAVES * WAVE) tok_grad_kernel(const T* __restrict__ dx,
                                                                    const int* __restrict__ offsets,
                                                                    const int* __restrict__ order,
                                                                    const int* __restrict__ tokens, int rows,
-                                                                   float* __restrict__ d_tok, int d) {
+                                                                   float* __restrict__ d_tok, int d, int vocab, int stride_log2) {
   constexpr int VEC = Vec16<T>::N;
-  extern __shared__ float tg_red[];   // [TG_WAVES][d], SCAN: then the positions
-  const int v = blockIdx.x;
+  extern __shared__ float tg_red[];   // [TG_WAVES][d]; SCAN: first the found positions, and the rows' lists behind them
+  __shared__ int from[TG_WAVES + 1];  // a row's positions in `order`: from[q] .. from[q + 1] - 1 (SCAN)
+  const int v0 = blockIdx.x, n_rows = v0 < vocab ? ((vocab - 1 - v0) >> stride_log2) + 1 : 0;   // at most 16
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int lo = 0, hi;
   if constexpr (SCAN) {
     __shared__ unsigned long long found[64];   // ballot of 64 positions at a time: chunk q of 1024, wave w at 16 q + w
-    int* const list = reinterpret_cast<int*>(tg_red + TG_WAVES * d);
+    int* const all = reinterpret_cast<int*>(tg_red);   // position | row << 12, by position
+    int* const list = all + max(TG_WAVES * d, rows);
     unsigned long long mine[4];
+    int entry[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int j = q * TG_WAVES * WAVE + threadIdx.x;
       bool is = false;
+      entry[q] = j;
       if (j < rows) {
-        const int t = tokens[j];
-        is = (t < 0 ? 0 : (t >= (int)gridDim.x ? (int)gridDim.x - 1 : t)) == v;
+        const int t = min(max(tokens[j], 0), vocab - 1);
+        is = (t & ((1 << stride_log2) - 1)) == v0;
+        entry[q] |= (t >> stride_log2) << 12;
       }
       mine[q] = __builtin_amdgcn_ballot_w64(is);
       if (lane == 0) found[q * TG_WAVES + wave] = mine[q];
@@ -626,61 +638,90 @@ __global__ void __launch_bounds__(TG_WAVES * WAVE) tok_grad_kernel(const T* __re
       const int below = __shfl_up(upto, s, WAVE);
       if (lane >= s) upto += below;
     }
-    hi = __shfl(upto, WAVE - 1, WAVE);
+    const int n = __shfl(upto, WAVE - 1, WAVE);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int before = __shfl(upto - cnt, q * TG_WAVES + wave, WAVE);
-      if ((mine[q] >> lane) & 1) list[before + __builtin_popcountll(mine[q] & ((1ull << lane) - 1ull))] = q * TG_WAVES * WAVE + threadIdx.x;
+      if ((mine[q] >> lane) & 1) all[before + __builtin_popcountll(mine[q] & ((1ull << lane) - 1ull))] = entry[q];
     }
     __syncthreads();
+    int own = 0;   // wave w: positions of row w
+    for (int i = lane; i - lane < n; i += WAVE) own += __builtin_popcountll(__builtin_amdgcn_ballot_w64(i < n && all[min(i, n - 1)] >> 12 == wave));
+    if (lane == 0) from[wave + 1] = own;
+    if (threadIdx.x == 0) from[0] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int q = 1; q <= TG_WAVES; ++q) from[q] += from[q - 1];
+    __syncthreads();
+    int at = from[wave];
+    if (own)
+      for (int i = lane; i - lane < n; i += WAVE) {
+        const int e = all[min(i, n - 1)];
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(i < n && e >> 12 == wave);
+        if ((hit >> lane) & 1) list[at + __builtin_popcountll(hit & ((1ull << lane) - 1ull))] = e & 4095;
+        at += __builtin_popcountll(hit);
+      }
+    __syncthreads();
     order = list;
-  } else {
-    lo = offsets[v];
-    hi = offsets[v + 1];
   }
-  float* o = d_tok + (size_t)v * d;
-  if (hi - lo <= 1) {   // most of the vocabulary: nothing to add
-    for (int c = threadIdx.x * VEC; c < d; c += TG_WAVES * WAVE * VEC) {
-      float a[VEC];
-      if (hi > lo) load_vec16(dx + (size_t)order[lo] * d + c, a);
-      else {
+  auto bounds = [&](int q, int& lo, int& hi) {
+    lo = SCAN ? from[q] : offsets[v0 + (q << stride_log2)];
+    hi = SCAN ? from[q + 1] : offsets[v0 + (q << stride_log2) + 1];
+  };
+  auto row = [&](int q) { return d_tok + ((size_t)v0 + ((size_t)q << stride_log2)) * d; };
+  int lo, hi;
+  if (wave < n_rows) {
+    bounds(wave, lo, hi);
+    if (hi - lo <= 1) {   // most of the vocabulary: nothing to add
+      float* const o = row(wave);
+      const T* const src = hi > lo ? dx + (size_t)order[lo] * d : nullptr;
+      for (int c = lane * VEC; c < d; c += WAVE * VEC) {
+        float a[VEC];
+        if (src) load_vec16(src + c, a);
+        else {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) a[i] = 0.f;
+          for (int i = 0; i < VEC; ++i) a[i] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) *reinterpret_cast<float4*>(o + c + i) = make_float4(a[i], a[i + 1], a[i + 2], a[i + 3]);
+      }
+    }
+  }
+  for (int q = 0; q < n_rows; ++q) {
+    bounds(q, lo, hi);
+    if (hi - lo <= 1) continue;   // uniform
+    for (int c = lane * VEC; c < d; c += WAVE * VEC) {
+      float acc[VEC];
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+      int j = lo + wave;
+      for (; j + (TG_UNROLL - 1) * TG_WAVES < hi; j += TG_UNROLL * TG_WAVES) {
+        float a[TG_UNROLL][VEC];
+#pragma unroll
+        for (int u = 0; u < TG_UNROLL; ++u) load_vec16(dx + (size_t)order[j + u * TG_WAVES] * d + c, a[u]);
+#pragma unroll
+        for (int u = 0; u < TG_UNROLL; ++u)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) acc[i] += a[u][i];
+      }
+      for (; j < hi; j += TG_WAVES) {
+        float a[VEC];
+        load_vec16(dx + (size_t)order[j] * d + c, a);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] += a[i];
       }
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) o[c + i] = a[i];
+      for (int i = 0; i < VEC; ++i) tg_red[wave * d + c + i] = acc[i];
     }
-    return;
-  }
-  for (int c = lane * VEC; c < d; c += WAVE * VEC) {
-    float acc[VEC];
+    __syncthreads();
+    float* const o = row(q);
+    for (int c = threadIdx.x; c < d; c += TG_WAVES * WAVE) {
+      float t = tg_red[c];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-    int j = lo + wave;
-    for (; j + (TG_UNROLL - 1) * TG_WAVES < hi; j += TG_UNROLL * TG_WAVES) {
-      float a[TG_UNROLL][VEC];
-#pragma unroll
-      for (int u = 0; u < TG_UNROLL; ++u) load_vec16(dx + (size_t)order[j + u * TG_WAVES] * d + c, a[u]);
-#pragma unroll
-      for (int u = 0; u < TG_UNROLL; ++u)
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] += a[u][i];
+      for (int w = 1; w < TG_WAVES; ++w) t += tg_red[w * d + c];
+      o[c] = t;
     }
-    for (; j < hi; j += TG_WAVES) {
-      float a[VEC];
-      load_vec16(dx + (size_t)order[j] * d + c, a);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] += a[i];
-    }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) tg_red[wave * d + c + i] = acc[i];
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < d; c += TG_WAVES * WAVE) {
-    float t = tg_red[c];
-#pragma unroll
-    for (int w = 1; w < TG_WAVES; ++w) t += tg_red[w * d + c];
-    o[c] = t;
+    __syncthreads();   // the sums are read: the next row may write its own
   }
 }
 
@@ -893,11 +934,13 @@ dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, flo
   const size_t lds = TG_WAVES * d * sizeof(float);
   static std::atomic<unsigned long long> tg_lds{0}, tg_scan_lds{0};   // per element type
   dipaco_status st;
+  const int sh = tok_grad_stride_log2(vocab);
   if (rows <= TG_SCAN_ROWS) {
     st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, true>),
                             TG_WAVES * TG_MAX_D * (int)sizeof(float) + TG_SCAN_ROWS * (int)sizeof(int), tg_scan_lds);
     if (st != DIPACO_OK) return st;
-    tok_grad_kernel<T, true><<<vocab, TG_WAVES * WAVE, lds + rows * sizeof(int), s>>>(dx, nullptr, nullptr, tokens, rows, d_tok, d);
+    const size_t scan_lds = (size_t)(std::max(TG_WAVES * d, rows) + rows) * sizeof(int);
+    tok_grad_kernel<T, true><<<std::min(vocab, 1 << sh), TG_WAVES * WAVE, scan_lds, s>>>(dx, nullptr, nullptr, tokens, rows, d_tok, d, vocab, sh);
   } else {
     int* count = scratch;
     int* offsets = scratch + vocab;
@@ -911,7 +954,7 @@ dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, flo
     if (st != DIPACO_OK) return st;
     st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, false>), TG_WAVES * TG_MAX_D * (int)sizeof(float), tg_lds);
     if (st != DIPACO_OK) return st;
-    tok_grad_kernel<T, false><<<vocab, TG_WAVES * WAVE, lds, s>>>(dx, offsets, order, nullptr, rows, d_tok, d);
+    tok_grad_kernel<T, false><<<std::min(vocab, 1 << sh), TG_WAVES * WAVE, lds, s>>>(dx, offsets, order, nullptr, rows, d_tok, d, vocab, sh);
   }
   DIPACO_LAUNCH_CHECK();
   pos_grad_kernel<T><<<max_seq, 128, 0, s>>>(dx, d_pos, B, S, d);

@@ -75,6 +75,40 @@ def test_fp32_loss_and_gradients_match_oracle(name, B, S, mask):
     assert loss2 == loss and np.array_equal(g0, host(st.grads))
 
 
+@pytest.mark.parametrize("vocab,B,S", [(1024, 4, 256), (1032, 4, 256), (5000, 2, 2000), (16392, 8, 512), (40000, 3, 700),
+                                       (1032, 9, 500), (40000, 9, 500)])
+def test_embedding_gradient_with_several_vocabulary_rows_a_workgroup(vocab, B, S):
+    """Up to 1024 rows a workgroup takes one, above that up to sixteen that lie a power of two apart; up to 4096 positions it finds
+    them itself.  The sum of the table's gradient over the vocabulary is that of the position table's over the positions; rows
+    no token names are zero."""
+    cfg = dict(layers_per_level=(1,), d_model=64, n_heads=2, d_head=32, d_mlp=64, vocab=vocab, max_seq=S)
+    print(f"embedding gradient vocab={vocab} B={B} S={S}", flush=True)
+    a, ctx = make_arch(cfg, dp.F32)
+    lay = orc.param_layout(a)
+    theta = gen.random_params(orc.param_count(a), seed=5, scale=0.05)
+    tok, tgt = _batch(cfg, B, S, seed=6, zipf=True)
+    tok[0, :8] = [0, vocab - 1, 0, 1, vocab - 2, vocab - 1, vocab // 2, 0]
+    st = PathState(ctx, theta, B, S)
+    st.fwd_bwd(tok, tgt)
+    g = host(st.grads).astype(np.float64)
+    (to, tshape, _), (po, pshape, _) = lay["tok_emb"], lay["pos_emb"]
+    dt, dpos = g[to:to + vocab * 64].reshape(vocab, 64), g[po:po + S * 64].reshape(S, 64)
+    seen = np.zeros(vocab, bool)
+    seen[tok.ravel()] = True
+    assert not dt[~seen].any()
+    # both are sums over all B S positions; rounding: 2^-24 of the absolute values a step, at most B S / 16 steps one after another
+    bound = 2.0 ** -24 * (B * S / 16 + 32) * np.abs(dt).sum(0)
+    assert np.all(np.abs(dt.sum(0) - dpos.sum(0)) <= bound + 1e-12)
+    g0 = host(st.grads).copy()
+    st.fwd_bwd(tok, tgt)
+    assert np.array_equal(g0, host(st.grads))
+    if vocab <= 5000:
+        _, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
+        od = o_grad[to:to + vocab * 64].reshape(vocab, 64)
+        assert rel_l2(dt, od) <= 1e-4
+        assert np.linalg.norm(dt - od, axis=1).max() <= 1e-4 * np.linalg.norm(od)
+
+
 def test_config1_full_round_matches_oracle():
     """Tiny 2x2 grid, fp32: compose -> 2 inner AdamW steps on each of the 4 paths -> outer Nesterov step of the
     4 block modules (2 paths each) and of the stem and head (shared by all 4 paths)."""
