@@ -142,6 +142,19 @@ static bool want_dlds(const GemmArgs& a) {
   return (long)((a.M + 255) / 256) * ((a.N + 255) / 256) >= 160;
 }
 
+// Rows of a direct-to-LDS product that its whole rounds of 256 workgroups hold, when the rows left over cost less in tiles fitted to
+// them than as the last, mostly empty round: 5700 x 3584 x 896 is 322 tiles of 256 x 256, two rounds, 53 us (77 with GELU and its derivative); the first 4352 rows
+// (238 tiles) and then 1348 rows in 252 tiles of 160 x 128 take 45 (59); 20000 x 896 x 3584 140 -> 116, 5000 x 3584 x 3584 159 -> 113.  Else, and where column sums are wanted (their partial rows are
+// numbered by one launch's tiles), all of them.
+static int dlds_rows(const GemmArgs& a) {
+  const long tn = (a.N + 255) / 256, tiles = (a.M + 255) / 256 * tn, rounds = (tiles + 255) / 256;
+  if (a.out_f32 || a.colsum || g_forced_kernel || rounds < 2) return a.M;
+  const long rows = (rounds - 1) * 256 / tn * 256;
+  if (rows < 256 || rows >= a.M) return a.M;
+  const double round = 8.0 + 0.023 * a.K;
+  return gemm_fit_cost((int)(a.M - rows), a.N, a.K, 1, true, true) + 4.0 < round ? (int)rows : a.M;
+}
+
 template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s) {
   constexpr int VEC = 16 / sizeof(T);
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return fail(DIPACO_ESHAPE, "gemm: empty operand");
@@ -171,7 +184,21 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   if (a.out_f32 && !(a.trans_a && !a.trans_b)) return fail(DIPACO_EUNSUPPORTED, "gemm: fp32 output only for A^T.B");
   if (!a.out_f32 && a.trans_a) return fail(DIPACO_EUNSUPPORTED, "gemm: operand layout not instantiated");
   if constexpr (std::is_same<T, bf16>::value) {
-    if (want_dlds(a) && gemm_dlds_eligible(a)) return launch_gemm_dlds(a, s);
+    if (want_dlds(a) && gemm_dlds_eligible(a)) {
+      const int rows = dlds_rows(a);
+      if (rows == a.M) return launch_gemm_dlds(a, s);
+      GemmArgs first = a, rest = a;
+      first.M = rows;
+      rest.M = a.M - rows;
+      auto below = [&](auto p, long ld) { return p ? (decltype(p))((uintptr_t)p + (size_t)rows * ld * sizeof(T)) : p; };
+      rest.A = below(a.A, a.lda);
+      rest.C = below(a.C, a.ldc);
+      rest.resid = below(a.resid, a.ldc);
+      rest.aux_in = below(a.aux_in, a.ldc);
+      rest.aux_out = below(a.aux_out, a.ldc);
+      if (dipaco_status st = launch_gemm_dlds(first, s)) return st;
+      return launch_gemm_fit<T>(rest, s);
+    }
   }
   return launch_gemm_fit<T>(a, s);
 }

@@ -362,6 +362,13 @@ def test_gemm_fitted_tiles_at_their_edges(dtype, tile, M, N, K):
         dp.dipaco_k_set_gemm_tile(0)
 
 
+@pytest.mark.parametrize("M,N,K", [(4097, 4096, 64), (4360, 4096, 32), (5700, 3584, 96), (1025, 16392, 64), (2800, 16384, 32)])
+def test_bf16_products_whose_last_round_is_taken_in_fitted_tiles(M, N, K):
+    """More than one round of 256 tiles of 256 x 256, the last one mostly empty: its rows are a second launch."""
+    test_gemm_forward_layout_with_epilogues(dp.BF16, M, N, K, 0)
+    test_gemm_input_gradient_layout(dp.BF16, M, N, K, 0)
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
 @pytest.mark.parametrize("tile", [3, 4])
 @pytest.mark.parametrize("M,N,K", [(128, 128, 32), (132, 136, 36), (256, 264, 500), (4, 8, 4), (260, 120, 2052)])
