@@ -125,16 +125,22 @@ static Plan make_plan(const dipaco_ctx* c, int B, int S) {
 
 // ---- the path step ---------------------------------------------------------------------------------------
 template <typename T>
-static dipaco_status gemm(const T* A, const T* B, void* C, int M, int N, int K, long lda, long ldb, long ldc,
+static GemmArgs gemm_args(const T* A, const T* B, void* C, int M, int N, int K, long lda, long ldb, long ldc,
                           bool ta, bool tb, const T* bias, const T* resid, T* aux_out, const T* aux_in, int act,
-                          bool out_f32, int splits, float* partial, hipStream_t s, float* colsum = nullptr,
-                          float* colsum_partial = nullptr, SumBatch* sum_batch = nullptr) {
+                          bool out_f32, int splits, float* partial, float* colsum = nullptr, float* colsum_partial = nullptr,
+                          SumBatch* sum_batch = nullptr) {
   GemmArgs g;
   g.colsum = colsum; g.colsum_partial = colsum_partial; g.sum_batch = sum_batch;
   g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
   g.bias = bias; g.resid = resid; g.aux_out = aux_out; g.aux_in = aux_in; g.act = act;
   g.trans_a = ta; g.trans_b = tb; g.out_f32 = out_f32; g.splits = splits; g.partial = partial;
-  return launch_gemm<T>(g, s);
+  return g;
+}
+template <typename T>
+static dipaco_status gemm(const T* A, const T* B, void* C, int M, int N, int K, long lda, long ldb, long ldc,
+                          bool ta, bool tb, const T* bias, const T* resid, T* aux_out, const T* aux_in, int act,
+                          bool out_f32, int splits, float* partial, hipStream_t s) {
+  return launch_gemm<T>(gemm_args<T>(A, B, C, M, N, K, lda, ldb, ldc, ta, tb, bias, resid, aux_out, aux_in, act, out_f32, splits, partial), s);
 }
 
 #define TRY(expr)                          \
@@ -160,12 +166,16 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
   float* nll = nll_out ? nll_out : fbuf(p.nll);
   const int NL = c->n_layers;
 
-  // weight gradient dW[K_in, N_out] = X^T . dY (contraction over the tokens), fp32 into the gradient buffer
-  auto dweight = [&](const T* X, const T* dY, size_t w_off, WeightKind kind) {
+  // The gradients of a linear layer Y = X W: dW[K_in, N_out] = X^T . dY (contraction over the tokens), fp32 into the gradient buffer,
+  // and dX = dY . W^T; with act_grad dX is multiplied by it, and its column sums go to col_sums
+  auto linear_grads = [&](const T* X, const T* dY, size_t w_off, WeightKind kind, T* dX, const T* act_grad, float* col_sums) {
     int K_in, N_out;
     weight_shape(c, kind, K_in, N_out);
-    return gemm<T>(X, dY, G + w_off, K_in, N_out, T_, K_in, N_out, N_out, true, false, nullptr, nullptr, nullptr, nullptr,
-                   0, true, gemm_plan_splits(K_in, N_out, T_, sizeof(T) == 2, slice_limit(c, kind, T_)), skp, st);
+    const GemmArgs dw = gemm_args<T>(X, dY, G + w_off, K_in, N_out, T_, K_in, N_out, N_out, true, false, nullptr, nullptr, nullptr,
+                                     nullptr, 0, true, gemm_plan_splits(K_in, N_out, T_, sizeof(T) == 2, slice_limit(c, kind, T_)), skp);
+    const GemmArgs dx = gemm_args<T>(dY, W + w_off, dX, T_, K_in, N_out, N_out, N_out, K_in, false, true, nullptr, nullptr, nullptr,
+                                     act_grad, act_grad ? 4 : 0, false, 1, nullptr, col_sums, col_sums ? next_csp() : nullptr, &sums);
+    return launch_gemm_pair<T>(dw, dx, st);
   };
 
   // ---------------- forward ----------------
@@ -200,9 +210,7 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
 
   // ---------------- backward ----------------
   T* dlogits = buf(p.logits);
-  TRY(dweight(buf(p.y), dlogits, c->w_head, W_HEAD));
-  TRY(gemm<T>(dlogits, W + c->w_head, buf(p.dh), T_, d, V, V, V, d, false, true, nullptr, nullptr, nullptr, nullptr, 0,
-              false, 1, nullptr, st));
+  TRY(linear_grads(buf(p.y), dlogits, c->w_head, W_HEAD, buf(p.dh), nullptr, nullptr));
   T* dx = buf(p.dxa);
   T* dx_other = buf(p.dxb);
   // every LayerNorm backward also leaves the column sums of the dx it writes: the bias gradient of the linear
@@ -214,25 +222,17 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
     const LayerBufs& L = p.layers[l];
     const BlockOff& o = c->blocks[l];
     // x_next = x_mid + gelu(u) W_down + b_down
-    TRY(dweight(buf(L.act), dx, o.w_down, W_DOWN));
     // du = (dx W_down^T) * GELU'(u); its column sums, the gradient of b_up, come out of the same product
-    TRY(gemm<T>(dx, W + o.w_down, buf(p.du), T_, F, d, d, d, F, false, true, nullptr, nullptr, nullptr, buf(L.u), 4,
-                false, 1, nullptr, st, G + o.b_up, next_csp(), &sums));
-    TRY(dweight(buf(L.h2), buf(p.du), o.w_up, W_UP));
-    TRY(gemm<T>(buf(p.du), W + o.w_up, buf(p.dh), T_, d, F, F, F, d, false, true, nullptr, nullptr, nullptr, nullptr, 0,
-                false, 1, nullptr, st));
+    TRY(linear_grads(buf(L.act), dx, o.w_down, W_DOWN, buf(p.du), buf(L.u), G + o.b_up));
+    TRY(linear_grads(buf(L.h2), buf(p.du), o.w_up, W_UP, buf(p.dh), nullptr, nullptr));
     TRY(launch_layernorm_bwd<T>(buf(p.dh), buf(L.x_mid), W + o.ln2_g, fbuf(L.mean2), fbuf(L.rstd2), dx, dx_other,
                                 G + o.ln2_g, G + o.ln2_b, G + o.b_o, next_lnp(), T_, d, st, &sums));
     // x_mid = x_in + attn(...) W_o + b_o          (dx_other = gradient at x_mid)
-    TRY(dweight(buf(L.o), dx_other, o.w_o, W_O));
-    TRY(gemm<T>(dx_other, W + o.w_o, buf(p.d_o), T_, A, d, d, d, A, false, true, nullptr, nullptr, nullptr, nullptr, 0,
-                false, 1, nullptr, st));
+    TRY(linear_grads(buf(L.o), dx_other, o.w_o, W_O, buf(p.d_o), nullptr, nullptr));
     // dqkv and its column sums, the gradient of b_qkv
     TRY(launch_attention_bwd<T>(buf(L.qkv), buf(L.o), buf(p.d_o), fbuf(L.lse), buf(p.dqkv), fbuf(p.dsum), G + o.b_qkv,
                                 next_csp(), B, S, H, dh, st, &sums));
-    TRY(dweight(buf(L.h1), buf(p.dqkv), o.w_qkv, W_QKV));
-    TRY(gemm<T>(buf(p.dqkv), W + o.w_qkv, buf(p.dh), T_, d, 3 * A, 3 * A, 3 * A, d, false, true, nullptr, nullptr,
-                nullptr, nullptr, 0, false, 1, nullptr, st));
+    TRY(linear_grads(buf(L.h1), buf(p.dqkv), o.w_qkv, W_QKV, buf(p.dh), nullptr, nullptr));
     TRY(launch_layernorm_bwd<T>(buf(p.dh), buf(L.x_in), W + o.ln1_g, fbuf(L.mean1), fbuf(L.rstd1), dx_other, dx,
                                 G + o.ln1_g, G + o.ln1_b, l > 0 ? G + c->blocks[l - 1].b_down : nullptr, next_lnp(), T_, d, st,
                                 &sums));

@@ -155,7 +155,7 @@ static int dlds_rows(const GemmArgs& a) {
   return gemm_fit_cost((int)(a.M - rows), a.N, a.K, 1, true, true) + 4.0 < round ? (int)rows : a.M;
 }
 
-template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s) {
+template <typename T> static dipaco_status check_gemm(const GemmArgs& a) {
   constexpr int VEC = 16 / sizeof(T);
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return fail(DIPACO_ESHAPE, "gemm: empty operand");
   // 16-byte vectors run along the contiguous index of each operand and along the rows of C
@@ -177,12 +177,18 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   if (a.raw_planes) {
     if (a.splits < 2 || a.out_f32 || a.trans_a || a.trans_b || a.bias || a.resid || a.act || a.colsum || !a.partial)
       return fail(DIPACO_EINVAL, "gemm: raw planes come from a split forward product without an epilogue");
-    return launch_gemm_fit<T>(a, s);
+    return DIPACO_OK;
   }
   if (a.splits > 1 && (!a.out_f32 || a.bias || a.resid || a.act || !a.partial))
     return fail(DIPACO_EINVAL, "gemm: split-K needs fp32 output, a partial buffer and no epilogue");
   if (a.out_f32 && !(a.trans_a && !a.trans_b)) return fail(DIPACO_EUNSUPPORTED, "gemm: fp32 output only for A^T.B");
   if (!a.out_f32 && a.trans_a) return fail(DIPACO_EUNSUPPORTED, "gemm: operand layout not instantiated");
+  return DIPACO_OK;
+}
+
+template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s) {
+  if (dipaco_status st = check_gemm<T>(a)) return st;
+  if (a.raw_planes) return launch_gemm_fit<T>(a, s);
   if constexpr (std::is_same<T, bf16>::value) {
     if (want_dlds(a) && gemm_dlds_eligible(a)) {
       const int rows = dlds_rows(a);
@@ -203,6 +209,16 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   return launch_gemm_fit<T>(a, s);
 }
 
+template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
+  if (dipaco_status st = check_gemm<T>(dw)) return st;
+  if (dipaco_status st = check_gemm<T>(dx)) return st;
+  if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32 && gemm_fit_pair_takes<T>(dw, dx)) return launch_gemm_fit_pair<T>(dw, dx, s);
+  if (dipaco_status st = launch_gemm<T>(dw, s)) return st;
+  return launch_gemm<T>(dx, s);
+}
+
+template dipaco_status launch_gemm_pair<float>(const GemmArgs&, const GemmArgs&, hipStream_t);
+template dipaco_status launch_gemm_pair<bf16>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template dipaco_status launch_gemm<float>(const GemmArgs&, hipStream_t);
 template dipaco_status launch_gemm<bf16>(const GemmArgs&, hipStream_t);
 

@@ -116,6 +116,8 @@ struct GemmArgs {
 };
 size_t gemm_colsum_partial_floats(int M, int N);
 template <typename T> dipaco_status launch_gemm(const GemmArgs& g, hipStream_t s);
+// X^T dY and dY W^T of a linear layer: neither reads what the other writes
+template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
 // gemm_dlds.hip: bf16, 256x256 tiles loaded from global memory straight into LDS; takes the shapes for which
 // gemm_dlds_eligible holds (whole K tiles of 32, 16-byte rows); launch_gemm routes to it by itself
 bool gemm_dlds_eligible(const GemmArgs& g);
@@ -123,6 +125,9 @@ dipaco_status launch_gemm_dlds(const GemmArgs& g, hipStream_t s);
 void set_gemm_dlds_shape(int shape);   // 0 = automatic, 1 = 256 x 256, 2 = 256 x 128, 3 / 4 = 128 x 512 / 512 x 128 for weight gradients, 5 = 224-column tiles where N % 224 == 0
 // gemm_fit.hip: any type, layout and size that launch_gemm accepts; tiles fitted to the grid
 template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& g, hipStream_t s);
+// X^T dY (fp32) and dY W^T of a linear layer in one launch, where both are small
+template <typename T> bool gemm_fit_pair_takes(const GemmArgs& dw, const GemmArgs& dx);
+template <typename T> dipaco_status launch_gemm_fit_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
 // gemm_split.hip: fp32 on the bf16 matrix cores, tiles of 64 or 128 rows x 128; rows less than 4 GiB apart within a tile
 dipaco_status launch_gemm_split(const GemmArgs& g, int rows, hipStream_t s);
 void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 x 128

@@ -109,6 +109,26 @@ def test_embedding_gradient_with_several_vocabulary_rows_a_workgroup(vocab, B, S
         assert np.linalg.norm(dt - od, axis=1).max() <= 1e-4 * np.linalg.norm(od)
 
 
+@pytest.mark.parametrize("dtype", [dp.F32, dp.BF16])
+@pytest.mark.parametrize("name,B,S", [("ragged", 3, 50), ("one_level", 5, 16), ("one_level", 1, 1), ("ragged", 1, 33)])
+def test_both_products_of_a_small_layers_backward_pass_in_one_launch(name, B, S, dtype):
+    """The same tiles in one launch as in two (which a forced tile takes): the same bits."""
+    cfg = SHAPES[name]
+    a, ctx = make_arch(cfg, dtype)
+    theta = gen.random_params(orc.param_count(a), seed=5, scale=0.05)
+    tok, tgt = _batch(cfg, B, S, seed=6)
+    grads = []
+    for tile in (0, 1):
+        dp.dipaco_k_set_gemm_tile(tile)
+        try:
+            st = PathState(ctx, theta, B, S)
+            st.fwd_bwd(tok, tgt)
+            grads.append(host(st.grads).copy())
+        finally:
+            dp.dipaco_k_set_gemm_tile(0)
+    assert np.array_equal(grads[0], grads[1]) and np.isfinite(grads[0]).all()
+
+
 def test_config1_full_round_matches_oracle():
     """Tiny 2x2 grid, fp32: compose -> 2 inner AdamW steps on each of the 4 paths -> outer Nesterov step of the
     4 block modules (2 paths each) and of the stem and head (shared by all 4 paths)."""
