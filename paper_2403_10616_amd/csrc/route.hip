@@ -1,29 +1,30 @@
 // k-means prefix routing: idx[n] = argmin_k ||z_n - c_k||^2, per-centroid histogram, and the gap between the
 // two best scores.  The argmin is taken over s(n,k) = ||c_k||^2 - 2 z_n.c_k (||z_n||^2 is common to all k), so
-// the work is one fp32 contraction z.C^T on the matrix cores (v_mfma_f32_32x32x2_f32) with the reduction over
-// centroids done in the epilogue: scores never reach memory.
+// the work is one fp32 contraction z.C^T on the matrix cores with the reduction over centroids done in the epilogue:
+// scores never reach memory.
 //
-// One workgroup (8 waves, 2 x 4: two per SIMD, so that one wave's staging, barriers and reductions run under the
-// other's matrix instructions) owns 256 points and walks the centroids in tiles of 256; every wave holds a 128 x 64
-// block of scores in accumulators.  ||c_k||^2 is accumulated by the threads that stage the centroid
-// tile, from the very values they put into LDS.
+// route_kernel: every number taken apart into three bf16 parts (split_tile.h).  A workgroup of four waves owns 128 points and walks
+// the centroids in tiles of 128; ||c_k||^2 is accumulated by the threads that stage the centroid tile, from the very values they load.
+// Two workgroups share a compute unit: one splits, stores and folds scores under the other's MFMAs, which go first (wave priority).
+// Bound by the MFMAs and the power they draw (six part products: 2^20 x 768 x 256 is 2.5 PFLOP of them), as gemm_split.hip.  On the
+// fp32 matrix instruction 256 x 256 tiles took 3230 us there, now 2460; 300000 x 768 x 1000 3970 -> 2870, 1000000 x 64 x 256 488 -> 349.
+// Error of the margins against 64 bits 3.6e-7 (1.9e-6 before) at D = 896, 2.2e-7 (6.2e-7) at 64.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
 #include "mma_tile.h"
+#include "split_tile.h"
 
 namespace dipaco {
 
 namespace {
 
-constexpr int RBM = 256;   // points per workgroup
-constexpr int RBN = 256;   // centroids per tile
-constexpr int RBK = 32;    // fp32 K tile
-constexpr int R_THREADS = 512;
-constexpr int R_WN = 4;    // waves along the centroids, 64 columns each
-constexpr int R_STAGE = (RBM + RBN) * TILE_ROW_BYTES;
-constexpr int R_MAX_K_LDS_HIST = 4096;
-constexpr int R_TM = RBM / 64;   // 32-row score tiles per wave (two waves along the points)
+constexpr int RB = 128;    // points of a workgroup; centroids of a tile
+constexpr int RBK = 32;    // K tile
+constexpr int R_PLANE = RB * SPLIT_ROW;
+constexpr int R_LDS = 6 * R_PLANE;   // planes of the centroids, planes of the points
+constexpr int R_MAX_K = 4096;
 
 // Best and second-best (score, index) of a row, ordered lexicographically: exact ties go to the lower index.
 // TOP2 = false: the second index is not tracked (only its score, for the margin).
@@ -64,190 +65,231 @@ template <bool TOP2> __device__ __forceinline__ Best best_merge(const Best& a, c
   return o;
 }
 
-// The value of lane l ^ MASK (MASK < 32): quad permutes on the vector ALU for 1 and 2, the LDS crossbar (no LDS
-// memory) for 4, 8, 16.
-template <int MASK> __device__ __forceinline__ int lane_xor(int v) {
-  if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(v, v, 0xb1, 0xf, 0xf, false);        // quad_perm [1,0,3,2]
-  else if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(v, v, 0x4e, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
-  else return __builtin_amdgcn_ds_swizzle(v, (MASK << 10) | 0x1f);   // bit mode: and 0x1f, or 0, xor MASK
+// Near-ties of route_kernel.  A chain of fp32 multiply-adds errs by a few 2^-24 of its sums, the part products by less: what the two
+// order differently lies closer together than NEAR_TIE of the scores, a point in 10^4, and is decided by the chain in the order of
+// v_mfma_f32_32x32x2_f32 over chunks of four K (0, 4, 1, 5, 2, 6, 3, 7 of every eight), so that assignments do not turn with the
+// unit that multiplies.  A wave takes 32 points, lanes 0 .. 31 their best candidates, lanes 32 .. 63 the second ones.
+constexpr float NEAR_TIE = 1.0f / 131072.0f;
+__device__ __forceinline__ bool near_tie(const Best& b) {
+  return b.i2 != NO_INDEX && b.s2 - b.s1 < NEAR_TIE * (fabsf(b.s1) + fabsf(b.s2));
 }
-template <int MASK> __device__ __forceinline__ float lane_xor(float v) {
-  return __builtin_bit_cast(float, lane_xor<MASK>(__builtin_bit_cast(int, v)));
-}
-
-// Reduction over the 32 lanes that share rows: the entries of 2^LEVEL rows (BASE .. BASE + 2^LEVEL - 1 of the lane's
-// 32), reduced over lane bits 0 .. LEVEL-1, as ONE entry per lane.  Two halves are reduced first; then the lane whose
-// bit LEVEL-1 is clear keeps the entry of the lower half and hands the other to its partner lane ^ 2^(LEVEL-1), the
-// partner the other way round, and each merges what it keeps with what it receives.  At LEVEL 5 every lane holds one
-// row (number l & 31) reduced over all 32 lanes: 31 merges per lane instead of the 160 of a butterfly on every row,
-// and, walked depth-first, never more than LEVEL + 1 entries alive (leaf(r) builds row r's entry when it is needed).
-template <bool TOP2, int LEVEL, int BASE, typename Leaf>
-__device__ __forceinline__ Best best_reduce_rows(const Leaf& leaf, int lane) {
-  if constexpr (LEVEL == 0) {
-    return leaf(std::integral_constant<int, BASE>{});
-  } else {
-    constexpr int MASK = 1 << (LEVEL - 1);
-    const Best lo = best_reduce_rows<TOP2, LEVEL - 1, BASE>(leaf, lane);
-    const Best hi = best_reduce_rows<TOP2, LEVEL - 1, BASE + MASK>(leaf, lane);
-    const bool up = (lane & MASK) != 0;
-    Best mine, theirs, got;
-    mine.s1 = up ? hi.s1 : lo.s1; mine.i1 = up ? hi.i1 : lo.i1; mine.s2 = up ? hi.s2 : lo.s2;
-    theirs.s1 = up ? lo.s1 : hi.s1; theirs.i1 = up ? lo.i1 : hi.i1; theirs.s2 = up ? lo.s2 : hi.s2;
-    mine.i2 = TOP2 ? (up ? hi.i2 : lo.i2) : NO_INDEX;
-    theirs.i2 = TOP2 ? (up ? lo.i2 : hi.i2) : NO_INDEX;
-    got.s1 = lane_xor<MASK>(theirs.s1); got.i1 = lane_xor<MASK>(theirs.i1); got.s2 = lane_xor<MASK>(theirs.s2);
-    got.i2 = TOP2 ? lane_xor<MASK>(theirs.i2) : NO_INDEX;
-    return best_merge<TOP2>(mine, got);
+__device__ __forceinline__ void decide_near_tie(Best& b, const float* __restrict__ z_row, const float* __restrict__ c,
+                                                const float* __restrict__ lin_bias, int D, float dot_mul, int lane) {
+  const bool near = near_tie(b);
+  const int k = near ? (lane < 32 ? b.i1 : b.i2) : 0;
+  const float* const c_row = c + (long)k * D;
+  float dot = 0.f, n[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float4 x[8], y[8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {   // K beyond the row counts as zero
+      const bool in = k0 + 4 * q < D;
+      const int at = min(k0 + 4 * q, D - 4);
+      x[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(z_row + at), in));
+      y[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(c_row + at), in));
+    }
+  };
+  load(0);
+#pragma unroll 1
+  for (int k0 = 0; k0 < D; k0 += RBK) {
+    float4 u[8], v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { u[q] = x[q]; v[q] = y[q]; }
+    if (k0 + RBK < D) load(k0 + RBK);
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {
+      dot = __builtin_fmaf(u[q].x, v[q].x, dot); dot = __builtin_fmaf(u[q + 1].x, v[q + 1].x, dot);
+      dot = __builtin_fmaf(u[q].y, v[q].y, dot); dot = __builtin_fmaf(u[q + 1].y, v[q + 1].y, dot);
+      dot = __builtin_fmaf(u[q].z, v[q].z, dot); dot = __builtin_fmaf(u[q + 1].z, v[q + 1].z, dot);
+      dot = __builtin_fmaf(u[q].w, v[q].w, dot); dot = __builtin_fmaf(u[q + 1].w, v[q + 1].w, dot);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) n[q] += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
   }
+  const float cn = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
+  const float s = __builtin_fmaf(-dot_mul, dot, lin_bias ? -lin_bias[k] : cn), other = __shfl_xor(s, 32, WAVE);
+  if (!near) return;
+  const float s1 = lane < 32 ? s : other, s2 = lane < 32 ? other : s;
+  const int k1 = b.i1, k2 = b.i2;
+  const bool swap = lex_less(s2, k2, s1, k1);
+  b.s1 = swap ? s2 : s1; b.i1 = swap ? k2 : k1;
+  b.s2 = swap ? s1 : s2; b.i2 = swap ? k1 : k2;
 }
 
 // z: row n at z + n * ldz.  TOP2: idx is [N, 2] (second entry -1 when K = 1) and hist counts both memberships.
+// The product is computed transposed (centroids are the rows of the accumulator), so a lane holds scores of one point of
+// each of its four blocks for ascending centroids and folds them into that point's running entry without a merge.
 template <bool TOP2>
-__global__ void __launch_bounds__(R_THREADS) route_kernel(const float* __restrict__ z, long ldz,
-                                                             const float* __restrict__ c,
-                                                             const float* __restrict__ lin_bias, long N, int D, int K,
-                                                             int* __restrict__ idx,
-                                                             unsigned long long* __restrict__ hist,
-                                                             float* __restrict__ margin) {
+__global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__ z, long ldz, const float* __restrict__ c,
+                                                       const float* __restrict__ lin_bias, long N, int D, int K,
+                                                       int* __restrict__ idx, unsigned long long* __restrict__ hist,
+                                                       float* __restrict__ margin) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ float cnorm[RBN];
-  __shared__ unsigned int lhist[R_MAX_K_LDS_HIST];
+  __shared__ __attribute__((aligned(16))) float cnorm[RB];
+  __shared__ unsigned int lhist[R_MAX_K];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / R_WN, wn = wave % R_WN;
-  const long m0 = (long)blockIdx.x * RBM;
-  const int rows_left = (int)min((long)RBM, N - m0);
-  const float* zb = z + m0 * ldz;
-  const bool use_lhist = K <= R_MAX_K_LDS_HIST;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kg = lane >> 4;
+  const int wc = wave >> 1, wp = wave & 1;   // the wave's 64 centroids of a tile, its 64 points
+  const long m0 = (long)blockIdx.x * RB;
+  const int rows_left = (int)min((long)RB, N - m0);
+  const float* const zb = z + m0 * ldz;
   const float dot_mul = lin_bias ? 1.0f : 2.0f;
-  if (use_lhist) for (int k = tid; k < K; k += R_THREADS) lhist[k] = 0;
-
-  using LZ = TileLoader<float, RBM, R_THREADS>;
-  using LC = TileLoader<float, RBN, R_THREADS>;
+  for (int k = tid; k < K; k += 256) lhist[k] = 0;
   const int nkt = (D + RBK - 1) / RBK;
 
-  // Running best / second best of one row per lane and pair of row tiles: after the reduction at the end of a
-  // centroid tile lane l holds, of pair hb, row tile 2 hb + ((l & 31) >> 4), accumulator element e = l & 15.
-  Best run[R_TM / 2];
+  // staging: wave w loads and splits rows 32 w .. 32 w + 31 of both tiles.  Rows beyond the last point or centroid read that one
+  // (their scores are dropped, or +inf)
+  using Unit = SplitUnit<true>;
+  Unit sc, sz;
+  uint32_t off_c[4], off_z[4];
+  auto load = [&](int n0, int kt) {
+    const int klim = D - kt * RBK;
+    if (kt == 0 || klim < RBK) {
 #pragma unroll
-  for (int hb = 0; hb < R_TM / 2; ++hb) { run[hb].s1 = INFINITY; run[hb].i1 = NO_INDEX; run[hb].s2 = INFINITY; run[hb].i2 = NO_INDEX; }
-
-  for (int n0 = 0; n0 < K; n0 += RBN) {
-    f32x16 acc[R_TM][2];
-#pragma unroll
-    for (int i = 0; i < R_TM; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    float nrm[LC::NLD];
-#pragma unroll
-    for (int i = 0; i < LC::NLD; ++i) nrm[i] = 0.f;
-
-    uint4 rz[LZ::NLD], rc[LC::NLD];
-    const float* cb = c + (long)n0 * D;
-    const int crow_left = min(RBN, K - n0);
-    LZ::load_tail(rz, zb, ldz, 0, rows_left, 0, D, tid);
-    LC::load_tail(rc, cb, D, 0, crow_left, 0, D, tid);
-    __syncthreads();   // previous centroid tile's readers of LDS and of cnorm are done
-    LZ::store(rz, smem, tid, 0, D);
-    LC::store(rc, smem + RBM * TILE_ROW_BYTES, tid, 0, D);
-    const bool keep0 = (tid & 7) * 4 < D;
-#pragma unroll
-    for (int i = 0; i < LC::NLD; ++i) {
-      float4 v = *reinterpret_cast<float4*>(&rc[i]);
-      if (keep0) nrm[i] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+      for (int j = 0; j < 4; ++j) {
+        const int row = 32 * wave + Unit::row(lane, j), k = min(Unit::k(lane, j), klim - 4);
+        off_c[j] = (uint32_t)(((long)min(row, K - n0 - 1) * D + k) * 4);
+        off_z[j] = (uint32_t)(((long)min(row, rows_left - 1) * ldz + k) * 4);
+      }
     }
-    __syncthreads();
-    for (int kt = 0; kt < nkt; ++kt) {
-      char* cur = smem + (kt & 1) * R_STAGE;
-      char* nxt = smem + ((kt + 1) & 1) * R_STAGE;
-      const bool more = kt + 1 < nkt;
-      if (more) {
-        LZ::load_tail(rz, zb, ldz, 0, rows_left, (kt + 1) * RBK, D, tid);
-        LC::load_tail(rc, cb, D, 0, crow_left, (kt + 1) * RBK, D, tid);
-      }
-      mma_ktile<float, R_TM, 2>(acc, cur, cur + RBM * TILE_ROW_BYTES, wm * (RBM / 2), wn * 64, lane);
-      if (more) {
-        const int k0n = (kt + 1) * RBK;
-        LZ::store(rz, nxt, tid, k0n, D);
-        LC::store(rc, nxt + RBM * TILE_ROW_BYTES, tid, k0n, D);
-        const bool keep = k0n + (tid & 7) * 4 < D;
+    const char* const cb = reinterpret_cast<const char*>(c + (long)n0 * D + kt * RBK);
+    const char* const pb = reinterpret_cast<const char*>(zb + kt * RBK);
 #pragma unroll
-        for (int i = 0; i < LC::NLD; ++i) {
-          float4 v = *reinterpret_cast<float4*>(&rc[i]);
-          if (keep) nrm[i] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        }
+    for (int j = 0; j < 4; ++j) sc.load(cb, off_c[j], j);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sz.load(pb, off_z[j], j);
+  };
+  int store_at[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) store_at[q] = 32 * SPLIT_ROW * wave + Unit::store_offset(lane, q);
+  const SplitFragments frag(lane);
+  const char* const pc = smem + wc * 64 * SPLIT_ROW;
+  const char* const pz = smem + 3 * R_PLANE + wp * 64 * SPLIT_ROW;
+
+  Best run[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { run[j].s1 = INFINITY; run[j].i1 = NO_INDEX; run[j].s2 = INFINITY; run[j].i2 = NO_INDEX; }
+
+  load(0, 0);
+  for (int n0 = 0; n0 < K; n0 += RB) {
+    f32x4 acc[4][4];
+    float nrm[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+    for (int kt = 0; kt < nkt; ++kt) {
+      const int klim = D - kt * RBK;
+      if (klim < RBK) {   // K beyond the range counts as zero
+        sc.cut(lane, klim);
+        sz.cut(lane, klim);
       }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        nrm[q] += sc.v[q][0] * sc.v[q][0] + sc.v[q][1] * sc.v[q][1] + sc.v[q][2] * sc.v[q][2] + sc.v[q][3] * sc.v[q][3];
+        sc.template store<R_PLANE>(smem + store_at[q], q);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sz.template store<R_PLANE>(smem + 3 * R_PLANE + store_at[q], q);
+      if (kt + 1 < nkt) load(n0, kt + 1);
+      else if (n0 + RB < K) load(n0 + RB, 0);
+      __syncthreads();
+      __builtin_amdgcn_s_setprio(1);
+      split_multiply<4, 4, R_PLANE, R_PLANE>(acc, pc, pz, frag);
+      __builtin_amdgcn_s_setprio(0);
       __syncthreads();
     }
-    // ||c||^2: thread tid staged chunk (tid & 7) of centroid rows (tid >> 3) + 64 i
+    // ||c||^2: lane l staged piece l % 8 of the wave's centroid rows l / 8 + 8 q.  The barriers of the next tile's first stage stand
+    // between these reads of cnorm and its next writes
 #pragma unroll
-    for (int i = 0; i < LC::NLD; ++i) {
-      float v = nrm[i];
+    for (int q = 0; q < 4; ++q) {
+      float v = nrm[q];
       v += __shfl_xor(v, 1, WAVE);
       v += __shfl_xor(v, 2, WAVE);
       v += __shfl_xor(v, 4, WAVE);
-      if ((tid & 7) == 0) {
-        const int col = (tid >> 3) + (R_THREADS / 8) * i;
+      if ((lane & 7) == 0) {
+        const int col = 32 * wave + (lane >> 3) + 8 * q;
         // linear router: the score to minimise is -(w_k.z + b_k), so -b_k takes the place of ||c_k||^2
-        // a column beyond K scores +inf: it never enters a best entry
+        // a centroid beyond K scores +inf: it never enters a best entry
         cnorm[col] = n0 + col < K ? (lin_bias ? -lin_bias[n0 + col] : v) : INFINITY;
       }
     }
     __syncthreads();
-    // this centroid tile: for each pair of row tiles (32 rows of the lane) the best entries over the lane's 2 columns
-    // (ascending index), reduced over the 32 lanes of the half (they hold the other columns of the same rows) to one
-    // row per lane, and folded into the running entry of that row
-    float cn[2];
-    int kk[2];
+    const int k0 = 64 * wc + 4 * kg;   // the lane's rows of block i: k0 + 16 i + e
+    float sum = 0.f;                   // not finite where an accumulator is not
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = wn * 64 + 32 * j + (lane & 31);
-      kk[j] = n0 + col;
-      cn[j] = cnorm[col];
-    }
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int hb = 0; hb < R_TM / 2; ++hb) {
-      auto leaf = [&](auto R) {
-        constexpr int r = decltype(R)::value;
-        Best b;
-        b.s1 = INFINITY; b.i1 = NO_INDEX; b.s2 = INFINITY; b.i2 = NO_INDEX;
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          best_push_ascending<TOP2>(b, __builtin_fmaf(-dot_mul, acc[2 * hb + r / 16][j][r % 16], cn[j]), kk[j]);
-        return b;
-      };
-      run[hb] = best_merge<TOP2>(run[hb], best_reduce_rows<TOP2, 5, 0>(leaf, lane));
+        for (int e = 0; e < 4; ++e) sum = __builtin_fmaf(acc[i][j][e], 0.f, sum);
+    if (__any(sum != 0.f)) {
+      // An infinity among the operands leaves NaN where fp32 has an infinity: the wave's scores are taken again in fp32
+      const float* zr[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) zr[j] = zb + (long)min(64 * wp + 16 * j + r, rows_left - 1) * ldz;
+#pragma unroll 1
+      for (int t = 0; t < 16; ++t) {
+        const int col = k0 + 16 * (t >> 2) + (t & 3);
+        const float* const cr = c + (long)min(n0 + col, K - 1) * D;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int k = 0; k < D; ++k) {
+          const float x = cr[k];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) s[j] = __builtin_fmaf(x, zr[j][k], s[j]);
+        }
+        const float cn = cnorm[col];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) best_push_ascending<true>(run[j], __builtin_fmaf(-dot_mul, s[j], cn), n0 + col);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 cn4 = *reinterpret_cast<const float4*>(cnorm + k0 + 16 * i);
+        const float cn[4] = {cn4.x, cn4.y, cn4.z, cn4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            best_push_ascending<true>(run[j], __builtin_fmaf(-dot_mul, acc[i][j][e], cn[e]), n0 + k0 + 16 * i + e);
+      }
     }
   }
 
-  // Row of a lane's entry: step t of the reduction kept the entries whose bit t equals lane bit t, so the entry left
-  // is number l & 31 = 16 i + e of its pair.  Then the four waves along N are merged through LDS (the operand stages
-  // are free: every wave has passed the barriers that end the last centroid tile).
+  // the four lane groups of a point, then the two waves that share its points, through LDS (the planes are free: every wave has passed
+  // the barriers that end the last stage)
   float* const red_s1 = reinterpret_cast<float*>(smem);
-  float* const red_s2 = red_s1 + R_WN * RBM;
-  int* const red_i1 = reinterpret_cast<int*>(red_s2 + R_WN * RBM);
-  int* const red_i2 = red_i1 + R_WN * RBM;
-  static_assert(4 * R_WN * RBM * sizeof(float) <= 2 * (size_t)R_STAGE, "the merge arrays fit in the operand stages");
+  float* const red_s2 = red_s1 + 2 * RB;
+  int* const red_i1 = reinterpret_cast<int*>(red_s2 + 2 * RB);
+  int* const red_i2 = red_i1 + 2 * RB;
+  static_assert(8 * RB * sizeof(float) <= R_LDS, "the merge arrays fit in the planes");
 #pragma unroll
-  for (int hb = 0; hb < R_TM / 2; ++hb) {
-    const int r = lane & 31;
-    const int row = wm * (RBM / 2) + 64 * hb + 32 * (r >> 4) + acc_row(r & 15, lane);
-    red_s1[wn * RBM + row] = run[hb].s1; red_i1[wn * RBM + row] = run[hb].i1; red_s2[wn * RBM + row] = run[hb].s2;
-    if (TOP2) red_i2[wn * RBM + row] = run[hb].i2;
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int m = 16; m < WAVE; m <<= 1) {
+      Best o;
+      o.s1 = __shfl_xor(run[j].s1, m, WAVE); o.i1 = __shfl_xor(run[j].i1, m, WAVE); o.s2 = __shfl_xor(run[j].s2, m, WAVE);
+      o.i2 = __shfl_xor(run[j].i2, m, WAVE);
+      run[j] = best_merge<true>(run[j], o);
+    }
+    if (kg == 0) {
+      const int at = wc * RB + 64 * wp + 16 * j + r;
+      red_s1[at] = run[j].s1; red_i1[at] = run[j].i1; red_s2[at] = run[j].s2; red_i2[at] = run[j].i2;
+    }
   }
   __syncthreads();
-  if (tid < RBM && tid < rows_left) {
-    Best b;
-    b.s1 = red_s1[tid]; b.i1 = red_i1[tid]; b.s2 = red_s2[tid]; b.i2 = TOP2 ? red_i2[tid] : NO_INDEX;
-#pragma unroll
-    for (int w = 1; w < R_WN; ++w) {
-      Best o;
-      o.s1 = red_s1[w * RBM + tid]; o.i1 = red_i1[w * RBM + tid]; o.s2 = red_s2[w * RBM + tid];
-      o.i2 = TOP2 ? red_i2[w * RBM + tid] : NO_INDEX;
-      b = best_merge<TOP2>(b, o);
-    }
+  const int point = 32 * wave + (lane & 31);   // both halves of the wave hold its 32 points
+  Best b, o;
+  b.s1 = red_s1[point]; b.i1 = red_i1[point]; b.s2 = red_s2[point]; b.i2 = red_i2[point];
+  o.s1 = red_s1[RB + point]; o.i1 = red_i1[RB + point]; o.s2 = red_s2[RB + point]; o.i2 = red_i2[RB + point];
+  b = best_merge<true>(b, o);
+  if (__any(point < rows_left && near_tie(b)))
+    decide_near_tie(b, zb + (long)min(point, rows_left - 1) * ldz, c, lin_bias, D, dot_mul, lane);
+  if (lane < 32 && point < rows_left) {
     // A row none of whose scores compares below +inf (NaN or infinite features: a diverged path) never entered an
     // entry.  It is given the first centroid (the first two with TOP2) and a NaN margin, which is what the plain
     // definition's argmin over a row of NaN distances yields; it must not reach the histogram with an unset index.
@@ -258,32 +300,26 @@ __global__ void __launch_bounds__(R_THREADS) route_kernel(const float* __restric
     }
     if (TOP2) {
       const bool has2 = b.i2 != NO_INDEX;
-      idx[2 * (m0 + tid)] = b.i1;
-      idx[2 * (m0 + tid) + 1] = has2 ? b.i2 : -1;
-      if (has2) {
-        if (use_lhist) atomicAdd(&lhist[b.i2], 1u);
-        else atomicAdd(&hist[b.i2], 1ull);
-      }
+      idx[2 * (m0 + point)] = b.i1;
+      idx[2 * (m0 + point) + 1] = has2 ? b.i2 : -1;
+      if (has2) atomicAdd(&lhist[b.i2], 1u);
     } else {
-      idx[m0 + tid] = b.i1;
+      idx[m0 + point] = b.i1;
     }
-    if (margin) margin[m0 + tid] = b.s2 - b.s1;
-    if (use_lhist) atomicAdd(&lhist[b.i1], 1u);
-    else atomicAdd(&hist[b.i1], 1ull);
+    if (margin) margin[m0 + point] = b.s2 - b.s1;
+    atomicAdd(&lhist[b.i1], 1u);
   }
-  if (use_lhist) {
-    __syncthreads();
-    for (int k = tid; k < K; k += R_THREADS) {
-      unsigned int v = lhist[k];
-      if (v) atomicAdd(&hist[k], (unsigned long long)v);
-    }
+  __syncthreads();
+  for (int k = tid; k < K; k += 256) {
+    const unsigned int v = lhist[k];
+    if (v) atomicAdd(&hist[k], (unsigned long long)v);
   }
 }
 
 // ---- few points, or few centroids ----------------------------------------------------------------------------
-// A workgroup of route_kernel owns 256 points and multiplies them with 256 centroids at a time: a batch of N points runs
-// on N / 256 compute units and takes the time of one workgroup, a serial walk over 256 D, however small it is, and fewer
-// than 256 centroids are padded.  Here a wave owns 16 PT points and 32 centroids of a sweep (v_mfma_f32_16x16x4_f32): wc
+// A workgroup of route_kernel owns 128 points and multiplies them with 128 centroids at a time: a batch of N points runs
+// on N / 128 compute units and takes the time of one workgroup, a serial walk over 128 D, however small it is, and fewer
+// than 128 centroids are padded.  Here a wave owns 16 PT points and 32 centroids of a sweep (v_mfma_f32_16x16x4_f32): wc
 // waves of a workgroup take different centroids, 8 / wc different points.  A wave stages its own operand rows, K tiles of
 // 32 in a ring of ST stages, straight into LDS: a lane-to-row assignment in which eight adjacent lanes read one 128-byte
 // line (fragments fetched directly would touch 16 lines per 16 lanes: measured 44 us against 25 at 100 x 896 x 256).
@@ -601,17 +637,20 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
 // Waves of a small-kernel workgroup along the centroids: as many as there are groups of 32, so that none is idle.
 static int route_small_wc(int K) { return K > 128 ? 8 : K > 64 ? 4 : K > 32 ? 2 : 1; }
 
-// 1 / 2: route_small_kernel with 16 / 32 points per wave, 0: route_kernel.  All take time in whole rounds over the 256
-// compute units, one workgroup each, proportional to D.  Measured at D = 896: a round of route_kernel (65536 points x 256
-// centroids) 230 us, of the small kernel with 32 points per wave (2048 wave tasks) 43 us, with 16 points 28 us.  So the 16-point form
-// is taken where one round of it holds everything (100 x 256: 228 -> 25 us), else the cheaper of the other two (32768 x 896 x 256:
-// 239 -> 176; 65536: 252 against 337, kept; 300000 x 768 x 16: 1001 -> 202; x 100: 1001 -> 663).
-static int route_pick(int64_t N, int K) {
+// 1 / 2: route_small_kernel with 16 / 32 points per wave, 0: route_kernel.  All take time in whole rounds over the compute units,
+// proportional to D.  Measured at D = 896: 512 workgroups of route_kernel (65536 points) with 256 centroids 169 us, up to 256 of them 125; a
+// round of the small kernel with 32 points per wave (2048 wave tasks) 43 us, with 16 points 28 us.  The 16-point form is taken where one round
+// of it holds everything (100 x 256: 25 us, 45 with 32 points, 120 in route_kernel).  Else route_kernel where 230 us for a round of 65536
+// points x 256 centroids would be the cheaper: at 16384 x 256 91 | 125 us, 65536 x 256 328 | 169, 300000 x 768 x 256 1300 | 720, x 16 202 | 371.
+// The line lies where it did when route_kernel took those 230 us: nearer to it the two err differently (the small kernel's chain takes K
+// in another order than decide_near_tie), and a program's assignments would turn at near-ties.
+static int route_pick(int64_t N, int64_t ldz, int D, int K) {
   const int64_t wc = route_small_wc(K), sweeps = (K + 32 * wc - 1) / (32 * wc), tasks = 256 * RS_WAVES;
   if ((N + 15) / 16 * wc <= tasks) return 1;
   if (!launch_fits((N + 31) / 32 * wc / RS_WAVES + 1, RS_WAVES * WAVE)) return 0;
+  if (std::max<int64_t>(ldz, D) * 4 * RB >= 1LL << 32) return 2;   // route_kernel's byte offsets within a tile are 32-bit
   const int64_t small = 43 * (((N + 31) / 32 * wc + tasks - 1) / tasks) * sweeps;
-  const int64_t big = 230 * ((N + 256 * RBM - 1) / (256 * RBM)) * ((K + RBN - 1) / RBN);
+  const int64_t big = 230 * ((N + 65535) / 65536) * ((K + 255) / 256);
   return small < big ? 2 : 0;
 }
 
@@ -633,17 +672,16 @@ dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const fl
     DIPACO_LAUNCH_CHECK();
     return DIPACO_OK;
   };
-  const int pick = route_pick(N, K);
+  const int pick = route_pick(N, ldz, D, K);
   if (pick == 1) return small(std::integral_constant<int, 1>{});
   if (pick == 2) return small(std::integral_constant<int, 2>{});
-  constexpr size_t smem = 2 * (size_t)R_STAGE;
   static std::atomic<unsigned long long> lds_one{0}, lds_two{0};
-  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<false>), (int)smem, lds_one)) return e;
-  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<true>), (int)smem, lds_two)) return e;
-  const int64_t blocks = (N + RBM - 1) / RBM;
-  if (!launch_fits(blocks, R_THREADS)) return fail(DIPACO_ESHAPE, "route: N too large");
-  if (n_best == 2) route_kernel<true><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
-  else route_kernel<false><<<(unsigned)blocks, R_THREADS, smem, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
+  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<false>), R_LDS, lds_one)) return e;
+  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_kernel<true>), R_LDS, lds_two)) return e;
+  const int64_t blocks = (N + RB - 1) / RB;
+  if (!launch_fits(blocks, 256)) return fail(DIPACO_ESHAPE, "route: N too large");
+  if (n_best == 2) route_kernel<true><<<(unsigned)blocks, 256, R_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
+  else route_kernel<false><<<(unsigned)blocks, 256, R_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, idx, h, margin);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }

@@ -1,4 +1,6 @@
 """GPU parity of prefix routing against the oracle's fp64 argmin."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -423,6 +425,63 @@ def test_route_kernels_agree_with_fp64_on_both_sides_of_every_size_rule(N, D, K,
         assert torch.equal(idx.long(), want)
         assert torch.equal(hist, torch.bincount(want, minlength=K))
         assert torch.equal(margin.double(), order.values[:, 1] - order.values[:, 0])
+
+
+@pytest.mark.parametrize("N,D,K,bias", [(45000, 64, 129, False), (45057, 36, 256, True), (50001, 100, 257, False), (41500, 896, 200, False),
+                                        (45056, 4, 130, True), (45000, 16, 4096, False)])
+def test_tiles_of_bf16_parts_route_as_fp64_does(N, D, K, bias):
+    """128 points x 128 centroids a tile, whole ones and remainders in points, centroids and features.  Whole numbers are one bf16
+    part each, so every score is exact, and so are those of the ties, which are taken again in fp32."""
+    test_route_kernels_agree_with_fp64_on_both_sides_of_every_size_rule(N, D, K, bias)
+
+
+def test_tiles_of_bf16_parts_with_values_that_are_not_finite():
+    """An infinity has no bf16 parts that multiply as it does: such tiles are taken again in fp32.  Expected: the smallest score that is
+    not NaN, the lowest index among equals; rows without one go to centroid 0 with a NaN margin."""
+    N, D, K = 45000, 68, 130
+    g = torch.Generator().manual_seed(5)
+    z = torch.randint(-3, 4, (N, D), generator=g).float()
+    c = torch.randint(1, 4, (K, D), generator=g).float()
+    z[5, 3], z[700, 67], z[701, 0] = math.inf, -math.inf, math.nan
+    z[900, 1], z[900, 2] = math.inf, -math.inf
+    z[1234, 7] = 3.4e38              # finite, but its first bf16 part is not
+    c[129, 5] = math.inf             # never the nearest
+    z[0:N:97, 5] = 0.0               # 0 x inf
+    score = (c.double() ** 2).sum(1) - 2 * z.double() @ c.double().T
+    score = torch.where(score.isnan(), math.inf, score)
+    order = torch.sort(score, dim=1, stable=True)
+    idx, hist, margin = (torch.empty(N, dtype=torch.int32, device=DEV), torch.empty(K, dtype=torch.int64, device=DEV),
+                         torch.empty(N, device=DEV))
+    dp.dipaco_route_prefix(z.to(DEV), c.to(DEV), N, D, K, idx, hist, margin)
+    idx, margin = idx.cpu().long(), margin.cpu()
+    none = order.values[:, 0] == math.inf
+    assert none.nonzero().flatten().tolist() == [700, 701, 900] and bool((idx[none] == 0).all()) and bool(margin[none].isnan().all())
+    plain = ~none & order.values[:, 0].isfinite()
+    plain[1234] = False              # every score beyond fp32: -inf
+    assert torch.equal(idx[plain], order.indices[plain, 0])
+    assert torch.equal(margin[plain].double(), (order.values[:, 1] - order.values[:, 0])[plain])
+    assert idx[5] == 0 and idx[1234] == 0
+    assert torch.equal(hist.cpu(), torch.bincount(idx, minlength=K))
+
+
+def test_near_ties_of_bf16_parts_are_decided_by_the_fp32_chain():
+    """Pairs of centroids 2^-18 apart: every point is a near-tie of its pair.  Taken in fp32 the choice errs by at most the chain's
+    rounding, D 2^-24 of the sum of absolute products; what is further apart than that has to be decided rightly."""
+    N, D, K = 45000, 64, 256
+    g = torch.Generator().manual_seed(8)
+    z = torch.randn((N, D), generator=g)
+    c = torch.randn((K, D), generator=g)
+    c[1::2] = c[::2] * (1 + torch.randn((K // 2, D), generator=g) * 2.0 ** -18)
+    score = (c.double() ** 2).sum(1) - 2 * z.double() @ c.double().T
+    idx, hist, margin = (torch.empty(N, dtype=torch.int32, device=DEV), torch.empty(K, dtype=torch.int64, device=DEV),
+                         torch.empty(N, device=DEV))
+    dp.dipaco_route_prefix(z.to(DEV), c.to(DEV), N, D, K, idx, hist, margin)
+    idx = idx.cpu().long()
+    best = score.min(1).values
+    taken = score.gather(1, idx[:, None])[:, 0]
+    bound = D * 2.0 ** -24 * ((c[idx].double() ** 2).sum(1) + 2 * (z.double() * c[idx].double()).abs().sum(1)) * 2
+    assert bool((taken - best <= bound).all())
+    assert bool((margin.cpu() >= 0).all()) and torch.equal(hist.cpu(), torch.bincount(idx, minlength=K))
 
 
 def test_more_points_than_one_launch_of_small_workgroups_holds():
