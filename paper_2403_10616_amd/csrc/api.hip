@@ -180,7 +180,7 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
 
   // ---------------- forward ----------------
   T* x0 = NL > 0 ? buf(p.layers[0].x_in) : buf(p.x_final);
-  TRY(launch_embed<T>(W + c->tok_emb, W + c->pos_emb, tokens, x0, B, S, d, V, st));
+  TRY(launch_embed<T>(W + c->tok_emb, W + c->pos_emb, tokens, x0, B, S, d, V, targets, n_valid, st));
   for (int l = 0; l < NL; ++l) {
     const LayerBufs& L = p.layers[l];
     const BlockOff& o = c->blocks[l];
@@ -204,9 +204,7 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
                               a.ln_eps, st));
   TRY(gemm<T>(buf(p.y), W + c->w_head, buf(p.logits), T_, V, d, d, V, V, false, false, nullptr, nullptr, nullptr,
               nullptr, 0, false, 1, nullptr, st));
-  TRY(launch_count_valid(targets, T_, n_valid, st));
   TRY(launch_softmax_xent<T>(buf(p.logits), targets, n_valid, nll, T_, V, true, st));
-  TRY(launch_mean_loss(nll, n_valid, loss_out, T_, st));
 
   // ---------------- backward ----------------
   T* dlogits = buf(p.logits);
@@ -238,9 +236,8 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
                                 &sums));
   }
   TRY(flush_sum_batch(sums, st));
-  TRY(launch_embed_bwd<T>(dx, tokens, G + c->tok_emb, G + c->pos_emb, reinterpret_cast<int*>(ws + p.embed_ints), B, S,
-                          d, V, a.max_seq, st));
-  return DIPACO_OK;
+  return launch_step_tail<T>(dx, tokens, G + c->tok_emb, G + c->pos_emb, reinterpret_cast<int*>(ws + p.embed_ints), B, S, d, V,
+                             a.max_seq, nll, n_valid, loss_out, st);
 }
 
 // ---- prefix features: forward through the blocks only, one set of layer buffers reused by every block -------
@@ -287,7 +284,7 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
   auto fbuf = [&](size_t off) { return reinterpret_cast<float*>(ws + off); };
   T* x = buf(p.x_a);
   T* x_other = buf(p.x_b);
-  TRY(launch_embed<T>(W + c->tok_emb, W + c->pos_emb, tokens, x, B, S, d, V, st));
+  TRY(launch_embed<T>(W + c->tok_emb, W + c->pos_emb, tokens, x, B, S, d, V, nullptr, nullptr, st));
   // x_new = resid + X Wt + bias, and h = LayerNorm(x_new) under ln_g / ln_b (null: none follows)
   auto residual = [&](const T* X, size_t w_off, size_t b_off, int K, int splits, const T* resid, T* x_new, const T* ln_g,
                       const T* ln_b) -> dipaco_status {

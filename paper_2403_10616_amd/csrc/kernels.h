@@ -164,8 +164,8 @@ inline int gemm_limit_index(int64_t K) {   // of the power of two at or above K
 
 // ---- transformer.hip ---------------------------------------------------------------------------------
 template <typename T>
-dipaco_status launch_embed(const T* tok_emb, const T* pos_emb, const int* tokens, T* x, int B, int S, int d,
-                           int vocab, hipStream_t s);
+dipaco_status launch_embed(const T* tok_emb, const T* pos_emb, const int* tokens, T* x, int B, int S, int d, int vocab,
+                           const int* targets, int* n_valid, hipStream_t s);   // targets (16-byte aligned) or null: n_valid[0] = #targets >= 0
 template <typename T>
 dipaco_status launch_layernorm_fwd(const T* x, const T* g, const T* b, T* y, float* mean, float* rstd, int rows,
                                    int d, float eps, hipStream_t s);
@@ -210,8 +210,6 @@ size_t colsum_partial_floats(int rows, int cols);
 template <typename T> dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipStream_t s);
 // out[b] = -sum_p nll[b*S + p]
 dipaco_status launch_doc_score(const float* nll, float* out, int B, int S, hipStream_t s);
-// n_valid[0] = #targets >= 0
-dipaco_status launch_count_valid(const int* targets, int n, int* n_valid, hipStream_t s);
 // logits [rows, V] (T) -> nll[rows] fp32 and, when want_grad, in place dlogits = (softmax - onehot)/n_valid (0 on
 // ignored rows); without want_grad the logits are only read (n_valid is then not used)
 template <typename T>
@@ -221,8 +219,8 @@ dipaco_status launch_softmax_xent(T* logits, const int* targets, const int* n_va
 dipaco_status launch_mean_loss(const float* nll, const int* n_valid, float* loss, int rows, hipStream_t s);
 // token/position embedding gradients (deterministic).  ints: embed_bwd_scratch_ints(rows, vocab) scratch.
 template <typename T>
-dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, float* d_pos, int* scratch, int B,
-                               int S, int d, int vocab, int max_seq, hipStream_t s);
+dipaco_status launch_step_tail(const T* dx, const int* tokens, float* d_tok, float* d_pos, int* scratch, int B, int S, int d, int vocab,
+                               int max_seq, const float* nll, const int* n_valid, float* loss, hipStream_t s);
 size_t embed_bwd_scratch_ints(int rows, int vocab);
 
 // ---- attention.hip -----------------------------------------------------------------------------------

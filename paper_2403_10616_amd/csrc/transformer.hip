@@ -15,12 +15,39 @@ constexpr int ROW_THREADS = 256;
 constexpr int ROWS_PER_BLOCK = ROW_THREADS / WAVE;  // one wave per row
 
 // ---- embedding -------------------------------------------------------------------------------------------
+// n_valid[0] = targets that are not negative, by a workgroup of ROW_THREADS; targets are 16-byte aligned
+__device__ __forceinline__ void count_valid(const int* __restrict__ targets, int n, int* __restrict__ n_valid) {
+  __shared__ int red[ROWS_PER_BLOCK];
+  int c = 0;
+  const int4* const t4 = reinterpret_cast<const int4*>(targets);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n >> 2; i += ROW_THREADS) {
+    const int4 t = t4[i];
+    c += (t.x >= 0) + (t.y >= 0) + (t.z >= 0) + (t.w >= 0);
+  }
+  for (int i = (n & ~3) + threadIdx.x; i < n; i += ROW_THREADS) c += targets[i] >= 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, WAVE);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int s = 0;
+    for (int i = 0; i < ROWS_PER_BLOCK; ++i) s += red[i];
+    n_valid[0] = s;
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(ROW_THREADS) embed_kernel(const T* __restrict__ E, const T* __restrict__ P,
                                                             const int* __restrict__ tok, T* __restrict__ x, int rows,
-                                                            int S, int d, int vocab) {
+                                                            int S, int d, int vocab, const int* __restrict__ targets,
+                                                            int* __restrict__ n_valid) {
   constexpr int VEC = Vec16<T>::N;
-  const int row = blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+  if (targets && blockIdx.x == 0) {   // a step's first workgroup counts its targets: one launch less
+    count_valid(targets, rows, n_valid);
+    return;
+  }
+  const int row = (blockIdx.x - (targets ? 1 : 0)) * ROWS_PER_BLOCK + (threadIdx.x >> 6);
   if (row >= rows) return;
   const int lane = threadIdx.x & 63;
   int t = tok[row];
@@ -431,22 +458,6 @@ __global__ void __launch_bounds__(ROW_THREADS) colsum_kernel(const float* __rest
 }
 
 // ---- loss ------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) count_valid_kernel(const int* __restrict__ targets, int n,
-                                                           int* __restrict__ n_valid) {
-  __shared__ int red[16];
-  int c = 0;
-  for (int i = threadIdx.x; i < n; i += 1024) c += targets[i] >= 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, WAVE);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int s = 0;
-    for (int i = 0; i < 16; ++i) s += red[i];
-    n_valid[0] = s;
-  }
-}
-
 __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) {
   v = is_max ? wave_max(v) : wave_sum(v);
   __syncthreads();
@@ -548,8 +559,8 @@ softmax_xent_kernel(T* __restrict__ logits, const int* __restrict__ targets, con
 }
 
 // loss = (sum of nll in a fixed tree order) / n_valid; one workgroup
-__global__ void __launch_bounds__(1024) mean_loss_kernel(const float* __restrict__ nll, const int* __restrict__ n_valid,
-                                                         float* __restrict__ loss, int rows) {
+__device__ __forceinline__ void mean_loss(const float* __restrict__ nll, const int* __restrict__ n_valid, float* __restrict__ loss,
+                                          int rows) {   // a workgroup of 1024
   __shared__ float red[16];
   // 16-byte loads, four in flight per thread (one workgroup has to pull a million values for the router's loss);
   // the order of the additions is fixed by the indices alone
@@ -580,6 +591,11 @@ __global__ void __launch_bounds__(1024) mean_loss_kernel(const float* __restrict
   }
 }
 
+__global__ void __launch_bounds__(1024) mean_loss_kernel(const float* __restrict__ nll, const int* __restrict__ n_valid,
+                                                         float* __restrict__ loss, int rows) {
+  mean_loss(nll, n_valid, loss, rows);
+}
+
 // ---- embedding gradient ----------------------------------------------------------------------------------
 // d_tok[v] = sum of dx rows whose token is v, added in increasing position order (no float atomics): positions are
 // grouped by token with a stable sort (kmeans.hip), then one workgroup per vocabulary row adds its positions.
@@ -600,17 +616,60 @@ inline int tok_grad_stride_log2(int vocab) {
   while ((1LL << sh) < vocab && (sh < 10 || (vocab - 1) >> sh >= TG_WAVES)) ++sh;
   return sh;
 }
-template <typename T, bool SCAN>
-__global__ void __launch_bounds__(TG_WAVES * WAVE) tok_grad_kernel(const T* __restrict__ dx,
-                                                                   const int* __restrict__ offsets,
-                                                                   const int* __restrict__ order,
-                                                                   const int* __restrict__ tokens, int rows,
-                                                                   float* __restrict__ d_tok, int d, int vocab, int stride_log2) {
+// d_pos[p] = sum_b dx[b*S + p] for p < S, 0 for S <= p < max_seq: a wave per position, eight rows in flight, added in order
+template <typename T>
+__device__ __forceinline__ void pos_grad(const T* __restrict__ dx, float* __restrict__ d_pos, int p, int B, int S, int d, int lane) {
+  constexpr int VEC = Vec16<T>::N, AHEAD = 8;
+  for (int c = lane * VEC; c < d; c += WAVE * VEC) {
+    float acc[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    for (int b0 = 0; p < S && b0 < B; b0 += AHEAD) {
+      float a[AHEAD][VEC];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) load_vec16(dx + ((size_t)min(b0 + u, B - 1) * S + p) * d + c, a[u]);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const bool on = b0 + u < B;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = on ? acc[i] + a[u][i] : acc[i];
+      }
+    }
+    float* const o = d_pos + (size_t)p * d + c;
+#pragma unroll
+    for (int i = 0; i < VEC; i += 4) *reinterpret_cast<float4*>(o + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+  }
+}
+
+// What closes a step, in one launch: workgroups 0 .. n_tok - 1 the token table's gradient, then sixteen positions of the position
+// table's each, the last one the mean loss.
+template <typename T> struct StepTail {
+  const T* dx;
+  const int *offsets, *order, *tokens;   // SCAN: tokens, else the sorted positions
+  float *d_tok, *d_pos;
+  int rows, B, S, d, vocab, max_seq, stride_log2, n_tok;
+  const float* nll;
+  const int* n_valid;
+  float* loss;
+};
+template <typename T, bool SCAN> __global__ void __launch_bounds__(TG_WAVES * WAVE) step_tail_kernel(const StepTail<T> a) {
   constexpr int VEC = Vec16<T>::N;
   extern __shared__ float tg_red[];   // [TG_WAVES][d]; SCAN: first the found positions, and the rows' lists behind them
   __shared__ int from[TG_WAVES + 1];  // a row's positions in `order`: from[q] .. from[q + 1] - 1 (SCAN)
-  const int v0 = blockIdx.x, n_rows = v0 < vocab ? ((vocab - 1 - v0) >> stride_log2) + 1 : 0;   // at most 16
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)blockIdx.x >= a.n_tok) {
+    const int p = ((int)blockIdx.x - a.n_tok) * TG_WAVES + wave;
+    if (blockIdx.x + 1 == gridDim.x) mean_loss(a.nll, a.n_valid, a.loss, a.rows);
+    else if (p < a.max_seq) pos_grad(a.dx, a.d_pos, p, a.B, a.S, a.d, lane);
+    return;
+  }
+  const T* const dx = a.dx;
+  const int* const tokens = a.tokens;
+  const int* const offsets = a.offsets;
+  const int* order = a.order;
+  float* const d_tok = a.d_tok;
+  const int rows = a.rows, d = a.d, vocab = a.vocab, stride_log2 = a.stride_log2;
+  const int v0 = blockIdx.x, n_rows = v0 < vocab ? ((vocab - 1 - v0) >> stride_log2) + 1 : 0;   // at most 16
   if constexpr (SCAN) {
     __shared__ unsigned long long found[64];   // ballot of 64 positions at a time: chunk q of 1024, wave w at 16 q + w
     int* const all = reinterpret_cast<int*>(tg_red);   // position | row << 12, by position
@@ -725,39 +784,15 @@ __global__ void __launch_bounds__(TG_WAVES * WAVE) tok_grad_kernel(const T* __re
   }
 }
 
-// d_pos[s] = sum_b dx[b*S + s] for s < S, 0 for S <= s < max_seq
-template <typename T>
-__global__ void __launch_bounds__(128) pos_grad_kernel(const T* __restrict__ dx, float* __restrict__ d_pos, int B, int S,
-                                                       int d) {
-  constexpr int VEC = Vec16<T>::N;
-  const int s = blockIdx.x;
-  for (int c = threadIdx.x * VEC; c < d; c += 128 * VEC) {
-    float acc[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-    if (s < S) {
-      for (int b = 0; b < B; ++b) {
-        float a[VEC];
-        load_vec16(dx + ((size_t)b * S + s) * d + c, a);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] += a[i];
-      }
-    }
-    float* o = d_pos + (size_t)s * d + c;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) o[i] = acc[i];
-  }
-}
-
 inline int row_blocks(int rows) { return (rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK; }
 
 }  // namespace
 
 template <typename T>
-dipaco_status launch_embed(const T* E, const T* P, const int* tokens, T* x, int B, int S, int d, int vocab,
-                           hipStream_t s) {
+dipaco_status launch_embed(const T* E, const T* P, const int* tokens, T* x, int B, int S, int d, int vocab, const int* targets,
+                           int* n_valid, hipStream_t s) {
   const int rows = B * S;
-  embed_kernel<T><<<row_blocks(rows), ROW_THREADS, 0, s>>>(E, P, tokens, x, rows, S, d, vocab);
+  embed_kernel<T><<<row_blocks(rows) + (targets ? 1 : 0), ROW_THREADS, 0, s>>>(E, P, tokens, x, rows, S, d, vocab, targets, n_valid);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
@@ -890,12 +925,6 @@ dipaco_status launch_sum_rows(const float* partial, float* out, int n_partials, 
   return sum_partials(partial, out, out, nullptr, n_partials, cols, cols, batch, s);
 }
 
-dipaco_status launch_count_valid(const int* targets, int n, int* n_valid, hipStream_t s) {
-  count_valid_kernel<<<1, 1024, 0, s>>>(targets, n, n_valid);
-  DIPACO_LAUNCH_CHECK();
-  return DIPACO_OK;
-}
-
 template <typename T>
 dipaco_status launch_softmax_xent(T* logits, const int* targets, const int* n_valid, float* nll, int rows, int V,
                                   bool want_grad, hipStream_t s) {
@@ -926,38 +955,43 @@ size_t embed_bwd_scratch_ints(int rows, int vocab) {
 }
 
 template <typename T>
-dipaco_status launch_embed_bwd(const T* dx, const int* tokens, float* d_tok, float* d_pos, int* scratch, int B,
-                               int S, int d, int vocab, int max_seq, hipStream_t s) {
-  const int rows = B * S;
+dipaco_status launch_step_tail(const T* dx, const int* tokens, float* d_tok, float* d_pos, int* scratch, int B, int S, int d, int vocab,
+                               int max_seq, const float* nll, const int* n_valid, float* loss, hipStream_t s) {
   // 16 partial rows of d floats: above 64 KB (d_model > 1024) the kernel's dynamic-LDS limit has to be raised
   if (d > TG_MAX_D) return fail(DIPACO_ESHAPE, "embedding gradient: d_model above 2048");
-  const size_t lds = TG_WAVES * d * sizeof(float);
   static std::atomic<unsigned long long> tg_lds{0}, tg_scan_lds{0};   // per element type
+  StepTail<T> a;
+  a.dx = dx; a.tokens = tokens; a.offsets = a.order = nullptr; a.d_tok = d_tok; a.d_pos = d_pos;
+  a.rows = B * S; a.B = B; a.S = S; a.d = d; a.vocab = vocab; a.max_seq = max_seq;
+  a.stride_log2 = tok_grad_stride_log2(vocab);
+  a.n_tok = std::min(vocab, 1 << a.stride_log2);
+  a.nll = nll; a.n_valid = n_valid; a.loss = loss;
+  const long blocks = a.n_tok + (max_seq + (long)TG_WAVES - 1) / TG_WAVES + 1;
+  if (!launch_fits(blocks, TG_WAVES * WAVE)) return fail(DIPACO_ESHAPE, "embedding gradient: max_seq above 2^26");
   dipaco_status st;
-  const int sh = tok_grad_stride_log2(vocab);
-  if (rows <= TG_SCAN_ROWS) {
-    st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, true>),
+  if (a.rows <= TG_SCAN_ROWS) {
+    st = ensure_dynamic_lds(reinterpret_cast<const void*>(step_tail_kernel<T, true>),
                             TG_WAVES * TG_MAX_D * (int)sizeof(float) + TG_SCAN_ROWS * (int)sizeof(int), tg_scan_lds);
     if (st != DIPACO_OK) return st;
-    const size_t scan_lds = (size_t)(std::max(TG_WAVES * d, rows) + rows) * sizeof(int);
-    tok_grad_kernel<T, true><<<std::min(vocab, 1 << sh), TG_WAVES * WAVE, scan_lds, s>>>(dx, nullptr, nullptr, tokens, rows, d_tok, d, vocab, sh);
+    const size_t scan_lds = (size_t)(std::max(TG_WAVES * d, a.rows) + a.rows) * sizeof(int);
+    step_tail_kernel<T, true><<<(unsigned)blocks, TG_WAVES * WAVE, scan_lds, s>>>(a);
   } else {
     int* count = scratch;
     int* offsets = scratch + vocab;
     int* order = offsets + vocab + 1;
-    int* sort_scratch = order + rows;
+    int* sort_scratch = order + a.rows;
     // positions grouped by token id, earlier positions first (stable sort: integer work only), so that every
     // vocabulary row is summed in a fixed order
-    st = launch_key_offsets(tokens, rows, vocab, count, offsets, nullptr, s);
+    st = launch_key_offsets(tokens, a.rows, vocab, count, offsets, nullptr, s);
     if (st != DIPACO_OK) return st;
-    st = launch_stable_sort_indices(tokens, rows, vocab, order, sort_scratch, s);
+    st = launch_stable_sort_indices(tokens, a.rows, vocab, order, sort_scratch, s);
     if (st != DIPACO_OK) return st;
-    st = ensure_dynamic_lds(reinterpret_cast<const void*>(tok_grad_kernel<T, false>), TG_WAVES * TG_MAX_D * (int)sizeof(float), tg_lds);
+    st = ensure_dynamic_lds(reinterpret_cast<const void*>(step_tail_kernel<T, false>), TG_WAVES * TG_MAX_D * (int)sizeof(float), tg_lds);
     if (st != DIPACO_OK) return st;
-    tok_grad_kernel<T, false><<<std::min(vocab, 1 << sh), TG_WAVES * WAVE, lds, s>>>(dx, offsets, order, nullptr, rows, d_tok, d, vocab, sh);
+    a.offsets = offsets;
+    a.order = order;
+    step_tail_kernel<T, false><<<(unsigned)blocks, TG_WAVES * WAVE, TG_WAVES * d * sizeof(float), s>>>(a);
   }
-  DIPACO_LAUNCH_CHECK();
-  pos_grad_kernel<T><<<max_seq, 128, 0, s>>>(dx, d_pos, B, S, d);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
@@ -1022,7 +1056,7 @@ dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipS
 }
 
 #define INSTANTIATE(T)                                                                                              \
-  template dipaco_status launch_embed<T>(const T*, const T*, const int*, T*, int, int, int, int, hipStream_t);       \
+  template dipaco_status launch_embed<T>(const T*, const T*, const int*, T*, int, int, int, int, const int*, int*, hipStream_t); \
   template dipaco_status launch_layernorm_fwd<T>(const T*, const T*, const T*, T*, float*, float*, int, int, float,  \
                                                  hipStream_t);                                                      \
   template dipaco_status launch_layernorm_bwd<T>(const T*, const T*, const T*, const float*, const float*, const T*, \
@@ -1032,8 +1066,8 @@ dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipS
                                                  float, hipStream_t);                                               \
   template dipaco_status launch_mean_pool<T>(const T*, float*, int, int, int, hipStream_t);                          \
   template dipaco_status launch_softmax_xent<T>(T*, const int*, const int*, float*, int, int, bool, hipStream_t);          \
-  template dipaco_status launch_embed_bwd<T>(const T*, const int*, float*, float*, int*, int, int, int, int, int,    \
-                                             hipStream_t);
+  template dipaco_status launch_step_tail<T>(const T*, const int*, float*, float*, int*, int, int, int, int, int,     \
+                                             const float*, const int*, float*, hipStream_t);
 INSTANTIATE(float)
 INSTANTIATE(bf16)
 
