@@ -13,7 +13,7 @@
 // inner loops is paid in full: the forward kernel adds its row sums two bf16 values per instruction on the packed
 // probabilities, walks its two stages with compile-time LDS offsets, and leaves the sum over a lane pair to the end.
 //
-// One workgroup = 4 waves, each wave owns 32 queries (or 32 keys).  K / V (or Q / dO) tiles of 64 rows x 64
+// One workgroup = 4 waves (or two groups of 4: below), each wave owns 32 queries (or 32 keys).  K / V (or Q / dO) tiles of 64 rows x 64
 // columns go from global memory straight into LDS (16-byte global_load_lds: lane l of a wave-level load writes
 // LDS bytes [16 l, 16 l + 16), so the swizzle is applied by choosing which 16 bytes a lane fetches) into a ring
 // of stages that runs two or three tiles ahead of the arithmetic, one barrier per tile.  A tile is stored once,
@@ -317,12 +317,12 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 // Column sums of a block's 128 rows of a transposed-output tile pair (the bias gradient of the projection whose
 // output gradient the block is): every lane adds scale * its values over the 32 rows of its wave, the four waves'
 // sums are added in wave order, and the 32 DT sums go to out.
-// red: LDS [4][32 DT].  All four waves call it; rows with valid = false count as zero.
+// red: LDS [4][32 DT].  All waves of the workgroup call it; rows with valid = false count as zero.
 template <int DT> __device__ __forceinline__ void block_column_sums(const f32x16 (&ot)[DT], float scale, bool valid, float (*red)[32 * DT],
-                                                  float* __restrict__ out, int wave, int lane) {
+                                                  float* __restrict__ out, int grp, int wave, int lane) {
   const int h = lane >> 5;
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
+  for (int dt = 0; grp == 0 && dt < DT; ++dt)   // the second group has handed its sums over
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const float v = half_wave_sum(valid ? ot[dt][k] * scale : 0.f);
@@ -336,15 +336,51 @@ template <int DT> __device__ __forceinline__ void block_column_sums(const f32x16
   __syncthreads();   // red is reused by the workgroup's next block
 }
 
+// ---- two groups of waves -----------------------------------------------------------------------------------------
+// Where a launch has few blocks, the causal triangle's longest one is its length, on four waves of a compute unit that holds
+// little else.  There a block gets two groups of four waves (NG = 2), each with a ring of its own, that take its tiles in turn;
+// at the end the second group hands its sums over through LDS.  A workgroup then fills its compute unit, so the blocks' tiles
+// (nqb + 1 on the mean, 2 nqb in the longest) have to be fewer than 0.9 of the chip's in that time, and four blocks long or more to repay the
+// hand-over.  Us forward | backward with one -> two groups, head size 64: 42 heads x 1000 (336 blocks) 21.0 -> 18.5 | 57.9 -> 52.7, 28 x 1900
+// (420) 39.0 -> 29.6 | 95.7 -> 81.0, 4 x 2048 30.0 -> 22.9 | 81 -> 63, 64 x 512 (256) 11.3 -> 10.7 | 31.5 -> 30.1; head size 128: 42 x 1000
+// 34.6 -> 32.1 | 136 -> 109, 64 x 512 18.7 -> 18.3 | 70 -> 63, 14 x 2048 55 -> 46 | 226 -> 159.  Beyond the rule: 112 x 512 (448) 13.4 -> 15.8 |
+// 38.8 -> 45.0, 42 x 1900 (630) 37.3 -> 43.9 | 114 -> 125, 56 x 256 8.0 -> 8.1 | 20.0 -> 20.4.
+inline bool two_groups(int B, int H, int S) {
+  const long nqb = (S + 127) / 128, blocks = (long)B * H * nqb;
+  return nqb >= 4 && 10 * blocks * (nqb + 1) <= 9 * 512 * nqb;
+}
+template <int N> __device__ __forceinline__ void hand_over(const f32x16 (&v)[N], float* at, int lane) {   // at: this wave's 16 N x 64 floats
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(at + ((n * 4 + g) * WAVE + lane) * 4) = make_float4(v[n][4 * g], v[n][4 * g + 1], v[n][4 * g + 2], v[n][4 * g + 3]);
+}
+// v = a v + b (what was handed over)
+template <int N> __device__ __forceinline__ void take_over(f32x16 (&v)[N], const float* at, float a, float b, int lane) {
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 w = *reinterpret_cast<const float4*>(at + ((n * 4 + g) * WAVE + lane) * 4);
+      v[n][4 * g] = v[n][4 * g] * a + w.x * b;
+      v[n][4 * g + 1] = v[n][4 * g + 1] * a + w.y * b;
+      v[n][4 * g + 2] = v[n][4 * g + 2] * a + w.z * b;
+      v[n][4 * g + 3] = v[n][4 * g + 3] * a + w.w * b;
+    }
+}
+
 // ---- forward ---------------------------------------------------------------------------------------------------
 constexpr int FWD_STAGES = 2, DQ_STAGES = 2, DKV_STAGES = 2;   // three stages measured: forward level, backward 4 % slower
 
-template <int DH>
-__global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(const bf16* __restrict__ qkv, bf16* __restrict__ o,
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, NG == 2 || DH == 128 ? 2 : 3) attn_fwd_mfma(const bf16* __restrict__ qkv, bf16* __restrict__ o,
                                                                float* __restrict__ lse, int S, int H, int single) {
   constexpr int NS = FWD_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
-  __shared__ __attribute__((aligned(16))) char smem[NS][2][TILE_BYTES];   // [stage][K | V]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  extern __shared__ __attribute__((aligned(16))) char fwd_smem[];   // [group][stage][K | V]
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = NG == 1 ? 0 : wave_all >> 2, wave = NG == 1 ? wave_all : wave_all & 3;
+  char (*smem)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(fwd_smem) + grp * NS;
   const int r = lane & 31, h = lane >> 5;
   const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
   const int bx = single ? (int)blockIdx.y : (int)blockIdx.x;   // single: one block per workgroup, longest first
@@ -353,7 +389,7 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(c
   const bf16* base = qkv + (long)b * S * ld + hd * DH;
   const FragOff fo = frag_offsets(lane);
   const TrOff to = tr_offsets(lane);
-  const uint32_t smem_addr = (uint32_t)(uintptr_t)&smem[0][0][0];
+  const uint32_t smem_addr = (uint32_t)(uintptr_t)fwd_smem + grp * NS * 2 * TILE_BYTES;
   const StageLoader<DH> L = make_loader<DH>(ld, ld, wave, lane);
   const bf16* const ktile = base + A;
   const bf16* const vtile = base + 2 * A;
@@ -383,17 +419,17 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(c
 
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
-    if (s < ntiles) issue_stage(L, ktile, vtile, s * 64, S, ld, ld, wave, lane, smem_addr + s * 2 * TILE_BYTES);
+    if (grp + NG * s < ntiles) issue_stage(L, ktile, vtile, (grp + NG * s) * 64, S, ld, ld, wave, lane, smem_addr + s * 2 * TILE_BYTES);
   static_assert(NS == 2 || NS == 3, "the tile loop below is unrolled over the stages, so that every LDS offset is a constant");
   // one key / value tile; CUR: the stage it sits in
   auto tile = [&](auto CUR, int kt) {
     constexpr int cur = decltype(CUR)::value;
-    wait_stages_but<LPW>(min(NS - 2, ntiles - 1 - kt));
+    wait_stages_but<LPW>(min(NS - 2, (ntiles - 1 - kt) / NG));
     __syncthreads();   // tile kt is in LDS; nobody still reads the stage of tile kt - 1, which is refilled now
-    if (kt + NS - 1 < ntiles)
-      issue_stage(L, ktile, vtile, (kt + NS - 1) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
+    if (kt + NG * (NS - 1) < ntiles)
+      issue_stage(L, ktile, vtile, (kt + NG * (NS - 1)) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
     const int kv0 = kt * 64;
-    if (kv0 <= qw0 + 31) {   // wave-uniform: at least one query of this wave sees this tile
+    if (kv0 <= qw0 + 31 && (NG == 1 || kt < ntiles)) {   // wave-uniform: at least one query of this wave sees this tile
       const char* k_ = smem[cur][0];
       const char* v_ = smem[cur][1];
       f32x16 st[2];
@@ -441,10 +477,28 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 2 : 3) attn_fwd_mfma(c
       mma_transposed_packed(ot, v_, to, pk);
     }
   };
-  for (int kt = 0; kt < ntiles; kt += NS) {
-    tile(std::integral_constant<int, 0>{}, kt);
-    if (kt + 1 < ntiles) tile(std::integral_constant<int, 1>{}, kt + 1);
-    if (NS > 2 && kt + 2 < ntiles) tile(std::integral_constant<int, NS - 1>{}, kt + 2);
+  for (int kt = 0; kt < ntiles; kt += NG * NS) {   // both groups walk as often as the first: the barriers are the workgroup's
+    tile(std::integral_constant<int, 0>{}, kt + grp);
+    if (kt + NG < ntiles) tile(std::integral_constant<int, 1>{}, kt + NG + grp);
+    if (NS > 2 && kt + 2 * NG < ntiles) tile(std::integral_constant<int, NS - 1>{}, kt + 2 * NG + grp);
+  }
+  if constexpr (NG == 2) {
+    constexpr int PER = (16 * DT + 2) * WAVE;   // floats a wave hands over: O^T, the reference exponent, the half row sum
+    static_assert(4 * PER * 4 <= NG * NS * 2 * TILE_BYTES, "the sums fit in the rings");
+    float* const at = reinterpret_cast<float*>(fwd_smem) + wave * PER;
+    __syncthreads();   // the rings have been read
+    if (grp == 1) {
+      hand_over(ot, at, lane);
+      at[16 * DT * WAVE + lane] = m;
+      at[(16 * DT + 1) * WAVE + lane] = l;
+    }
+    __syncthreads();
+    if (grp == 1) continue;
+    const float m1 = at[16 * DT * WAVE + lane], mn = fmaxf(m, m1);   // m is finite: key 0 is the first group's
+    const float c0 = __builtin_amdgcn_exp2f(m - mn), c1 = __builtin_amdgcn_exp2f(m1 - mn);
+    l = l * c0 + at[(16 * DT + 1) * WAVE + lane] * c1;
+    take_over(ot, at, c0, c1, lane);
+    m = mn;
   }
   l += __shfl_xor(l, 32, WAVE);
   if constexpr (split_p<DH>()) {
@@ -559,16 +613,17 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 1 : 3) attn_fwd_short_
 }
 
 // ---- backward, dQ (also writes D = rowsum(dO * O)) --------------------------------------------------------------
-template <int DH>
-__global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                                   const bf16* __restrict__ d_o,
                                                                   const float* __restrict__ lse, bf16* __restrict__ dqkv,
                                                                   float* __restrict__ dsum, float* __restrict__ colsum, int S, int H, int single) {
   constexpr int NS = DQ_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   __shared__ float cs_red[4][DH];
-  extern __shared__ __attribute__((aligned(16))) char dq_smem[];   // [stage][K | V]
-  char (*smem)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(dq_smem);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  extern __shared__ __attribute__((aligned(16))) char dq_smem[];   // [group][stage][K | V]
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = NG == 1 ? 0 : wave_all >> 2, wave = NG == 1 ? wave_all : wave_all & 3;
+  char (*smem)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(dq_smem) + grp * NS;
   const int r = lane & 31, h = lane >> 5;
   const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
   const int n_bh = single ? gridDim.x : gridDim.y;
@@ -578,7 +633,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
   const bf16* base = qkv + (long)b * S * ld + hd * DH;
   const FragOff fo = frag_offsets(lane);
   const TrOff to = tr_offsets(lane);
-  const uint32_t smem_addr = (uint32_t)(uintptr_t)dq_smem;
+  const uint32_t smem_addr = (uint32_t)(uintptr_t)dq_smem + grp * NS * 2 * TILE_BYTES;
   const StageLoader<DH> L = make_loader<DH>(ld, ld, wave, lane);
   const bf16* const ktile = base + A;
   const bf16* const vtile = base + 2 * A;
@@ -613,7 +668,7 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
   const float nlse2 = q < S ? -lse[(long)bh * S + q] * LOG2E : -INFINITY;
   // per-query statistics for the dK / dV kernel, in rows padded to whole query blocks: D (0 beyond S) and
   // -lse * log2(e) (-inf beyond S: probability 0), so that kernel needs neither a bounds check nor a rescale
-  if (h == 0) {
+  if (h == 0 && grp == 0) {
     const long Sp = (long)nqb * 128;
     dsum[bh * Sp + q] = q < S ? D : 0.f;
     dsum[(long)n_bh * Sp + bh * Sp + q] = nlse2;
@@ -628,15 +683,15 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
 
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
-    if (s < ntiles) issue_stage(L, ktile, vtile, s * 64, S, ld, ld, wave, lane, smem_addr + s * 2 * TILE_BYTES);
+    if (grp + NG * s < ntiles) issue_stage(L, ktile, vtile, (grp + NG * s) * 64, S, ld, ld, wave, lane, smem_addr + s * 2 * TILE_BYTES);
   int cur = 0;
-  for (int kt = 0; kt < ntiles; ++kt, cur = cur + 1 == NS ? 0 : cur + 1) {
-    wait_stages_but<LPW>(min(NS - 2, ntiles - 1 - kt));
+  for (int kt = grp; kt - grp < ntiles; kt += NG, cur = cur + 1 == NS ? 0 : cur + 1) {
+    wait_stages_but<LPW>(min(NS - 2, (ntiles - 1 - kt) / NG));
     __syncthreads();   // tile kt is in LDS; nobody still reads the stage of tile kt - 1, which is refilled now
-    if (kt + NS - 1 < ntiles)
-      issue_stage(L, ktile, vtile, (kt + NS - 1) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
+    if (kt + NG * (NS - 1) < ntiles)
+      issue_stage(L, ktile, vtile, (kt + NG * (NS - 1)) * 64, S, ld, ld, wave, lane, smem_addr + (cur == 0 ? NS - 1 : cur - 1) * 2 * TILE_BYTES);
     const int kv0 = kt * 64;
-    if (kv0 <= qw0 + 31) {
+    if (kv0 <= qw0 + 31 && (NG == 1 || kt < ntiles)) {
       const char* k_ = smem[cur][0];
       const char* v_ = smem[cur][1];
       f32x16 st[2], dp[2];
@@ -664,30 +719,40 @@ __global__ void __launch_bounds__(AT_THREADS, 2) attn_bwd_dq_mfma(const bf16* __
       mma_transposed<DT, 2>(dqt, k_, to, st, 0);
     }
   }
+  if constexpr (NG == 2) {
+    static_assert(4 * 16 * DT * WAVE * 4 <= NG * NS * 2 * TILE_BYTES, "the sums fit in the rings");
+    float* const at = reinterpret_cast<float*>(dq_smem) + wave * 16 * DT * WAVE;
+    __syncthreads();   // the rings have been read
+    if (grp == 1) hand_over(dqt, at, lane);
+    __syncthreads();
+    if (grp == 0) take_over(dqt, at, 1.0f, 1.0f, lane);
+  }
   if constexpr (split_p<DH>()) {
-    if (__any(q < S && plain::not_finite(dqt)) && q < S)
+    if (grp == 0 && __any(q < S && plain::not_finite(dqt)) && q < S)
       plain::query_grad<DH>(dqt, base, d_o + ((long)b * S + q) * A + hd * DH, D, ld, A, q, h,
                             [&](float s) { return __builtin_amdgcn_exp2f(__builtin_fmaf(s, sc, nlse2)); });
   }
-  if (q < S) store_transposed_out(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, h, score_scale<DH>());
+  if (grp == 0 && q < S) store_transposed_out(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, h, score_scale<DH>());
   // one row of partial column sums per (document, query block): [b * nqb + qb][3 A], this head's 64 dQ columns
-  if (colsum) block_column_sums(dqt, score_scale<DH>(), q < S, cs_red, colsum + ((long)b * nqb + qb) * ld + hd * DH, wave, lane);
+  if (colsum) block_column_sums(dqt, score_scale<DH>(), q < S, cs_red, colsum + ((long)b * nqb + qb) * ld + hd * DH, grp, wave, lane);
   }
 }
 
 // ---- backward, dK and dV ------------------------------------------------------------------------------------------
 template <int DH> constexpr int dkv_stage() { return 2 * tile_bytes<DH>() + 2 * 64 * (int)sizeof(float); }   // Q | dO | -lse2 | D
 
-template <int DH>
-__global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
                                                                    const bf16* __restrict__ d_o,
                                                                    const float* __restrict__ dsum,
                                                                    bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H, int single) {
   constexpr int NS = DKV_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   constexpr int DKV_STAGE = dkv_stage<DH>();
   __shared__ float cs_red[4][DH];
-  extern __shared__ __attribute__((aligned(16))) char dkv_smem[];   // NS stages of DKV_STAGE bytes
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  extern __shared__ __attribute__((aligned(16))) char dkv_rings[];   // NS stages of DKV_STAGE bytes per group
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = NG == 1 ? 0 : wave_all >> 2, wave = NG == 1 ? wave_all : wave_all & 3;
+  char* const dkv_smem = dkv_rings + grp * NS * DKV_STAGE;
   const int r = lane & 31, h = lane >> 5;
   const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
   const int n_bh = single ? gridDim.x : gridDim.y;
@@ -698,7 +763,7 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfm
   const bf16* gbase = d_o + (long)b * S * A + hd * DH;
   FragOff fo = frag_offsets(lane);
   TrOff to = tr_offsets(lane);
-  const uint32_t smem_addr = (uint32_t)(uintptr_t)dkv_smem;
+  const uint32_t smem_addr = (uint32_t)(uintptr_t)dkv_rings + grp * NS * DKV_STAGE;
   const int nkb = (S + 127) / 128;
   const int ntiles = (S + 63) / 64;
   // Statistics of a tile's 64 queries (written by the dQ kernel into rows padded to whole query blocks): waves 0
@@ -735,14 +800,14 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfm
   const int first = k0 / 64;               // first query tile that can see a key of this block
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
-    if (first + s < ntiles) issue(first + s, s);
+    if (first + grp + NG * s < ntiles) issue(first + grp + NG * s, s);
   int cur = 0;
-  for (int qt = first; qt < ntiles; ++qt, cur = cur + 1 == NS ? 0 : cur + 1) {
-    wait_stages_but<LPW + 1>(min(NS - 2, ntiles - 1 - qt));
+  for (int qt = first + grp; qt - grp < ntiles; qt += NG, cur = cur + 1 == NS ? 0 : cur + 1) {
+    wait_stages_but<LPW + 1>(min(NS - 2, (ntiles - 1 - qt) / NG));
     __syncthreads();
-    if (qt + NS - 1 < ntiles) issue(qt + NS - 1, cur == 0 ? NS - 1 : cur - 1);
+    if (qt + NG * (NS - 1) < ntiles) issue(qt + NG * (NS - 1), cur == 0 ? NS - 1 : cur - 1);
     const int q0 = qt * 64;
-    if (q0 + 63 >= kw0) {   // wave-uniform: some query of this tile sees a key of this wave
+    if (q0 + 63 >= kw0 && (NG == 1 || qt < ntiles)) {   // wave-uniform: some query of this tile sees a key of this wave
       const char* q_ = dkv_smem + cur * DKV_STAGE;
       const char* g_ = q_ + TILE_BYTES;
       const float* nlse2s = reinterpret_cast<const float*>(q_ + 2 * TILE_BYTES);
@@ -791,7 +856,22 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfm
       }
     }
   }
-  int key_out = key;   // as in the forward kernel: output addresses are formed behind the loop
+  if constexpr (NG == 2) {
+    constexpr int PER = 2 * 16 * DT * WAVE;
+    static_assert(4 * PER * 4 <= NG * NS * DKV_STAGE, "the sums fit in the rings");
+    float* const at = reinterpret_cast<float*>(dkv_rings) + wave * PER;
+    __syncthreads();   // the rings have been read
+    if (grp == 1) {
+      hand_over(dkt, at, lane);
+      hand_over(dvt, at + PER / 2, lane);
+    }
+    __syncthreads();
+    if (grp == 0) {
+      take_over(dkt, at, 1.0f, 1.0f, lane);
+      take_over(dvt, at + PER / 2, 1.0f, 1.0f, lane);
+    }
+  }
+  int key_out = grp == 0 ? key : S;   // as in the forward kernel: output addresses are formed behind the loop
   asm volatile("" : "+v"(key_out));
   if constexpr (split_p<DH>()) {
     const float* const D = dsum + bh * Sp;
@@ -807,8 +887,8 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 32 ? 3 : 2) attn_bwd_dkv_mfm
   }
   if (colsum) {
     float* cs = colsum + ((long)b * nkb + kb) * ld + hd * DH;
-    block_column_sums(dkt, score_scale<DH>(), key < S, cs_red, cs + A, wave, lane);
-    block_column_sums(dvt, 1.0f, key < S, cs_red, cs + 2 * A, wave, lane);
+    block_column_sums(dkt, score_scale<DH>(), key < S, cs_red, cs + A, grp, wave, lane);
+    block_column_sums(dvt, 1.0f, key < S, cs_red, cs + 2 * A, grp, wave, lane);
   }
   }
 }
@@ -829,34 +909,44 @@ dipaco_status launch_attention_fwd_mfma(const bf16* qkv, bf16* o, float* lse, in
   const int single = attention_single_block();
   const int nqb = (S + 127) / 128;   // more than 32 positions: at most 2^32 / (33 * 3 * 32) sequences x heads, one launch
   dim3 grid = single ? dim3(B * H, nqb) : dim3((nqb + 1) / 2, B * H);   // one or two query blocks per workgroup
-  attn_fwd_mfma<DH><<<grid, AT_THREADS, 0, s>>>(qkv, o, lse, S, H, single);
-  DIPACO_LAUNCH_CHECK();
-  return DIPACO_OK;
+  auto run = [&](auto NGc) -> dipaco_status {
+    constexpr int NG = decltype(NGc)::value, LDS = NG * FWD_STAGES * 2 * tile_bytes<DH>();
+    static std::atomic<unsigned long long> lds_set{0};
+    if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_mfma<DH, NG>), LDS, lds_set)) return st;
+    attn_fwd_mfma<DH, NG><<<grid, AT_THREADS * NG, LDS, s>>>(qkv, o, lse, S, H, single);
+    DIPACO_LAUNCH_CHECK();
+    return DIPACO_OK;
+  };
+  return two_groups(B, H, S) ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 1>{});
 }
 
 template <int DH>
 dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf16* d_o, const float* lse, bf16* dqkv,
                                         float* dsum, float* colsum_out, float* colsum_partial, int B, int S, int H,
                                         hipStream_t s, SumBatch* batch) {
-  constexpr int DQ_LDS = DQ_STAGES * 2 * tile_bytes<DH>(), DKV_LDS = DKV_STAGES * dkv_stage<DH>();
   const int single = attention_single_block();
   const int nqb = (S + 127) / 128;
-  static std::atomic<unsigned long long> dq_lds{0}, dkv_lds{0};
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH>), DQ_LDS, dq_lds)) return st;
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH>), DKV_LDS, dkv_lds)) return st;
   const size_t A = (size_t)H * DH;
   const int step = attention_launch_batch(B, H);
-  for (int b = 0; b < B; b += step) {
-    const size_t row = (size_t)b * S;
-    const int n_bh = std::min(step, B - b) * H;
-    dim3 grid = single ? dim3(n_bh, nqb) : dim3((nqb + 1) / 2, n_bh);   // one or two query (key) blocks per workgroup
-    float* const cs = colsum_out ? colsum_partial + (size_t)b * nqb * 3 * A : nullptr;
-    attn_bwd_dq_mfma<DH><<<grid, AT_THREADS, DQ_LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
-                                                          dqkv + row * 3 * A, dsum, cs, S, H, single);
-    DIPACO_LAUNCH_CHECK();
-    attn_bwd_dkv_mfma<DH><<<grid, AT_THREADS, DKV_LDS, s>>>(qkv + row * 3 * A, d_o + row * A, dsum, dqkv + row * 3 * A, cs, S, H, single);
-    DIPACO_LAUNCH_CHECK();
-  }
+  auto run = [&](auto NGc) -> dipaco_status {
+    constexpr int NG = decltype(NGc)::value, DQ_LDS = NG * DQ_STAGES * 2 * tile_bytes<DH>(), DKV_LDS = NG * DKV_STAGES * dkv_stage<DH>();
+    static std::atomic<unsigned long long> dq_lds{0}, dkv_lds{0};
+    if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH, NG>), DQ_LDS, dq_lds)) return st;
+    if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, NG>), DKV_LDS, dkv_lds)) return st;
+    for (int b = 0; b < B; b += step) {
+      const size_t row = (size_t)b * S;
+      const int n_bh = std::min(step, B - b) * H;
+      dim3 grid = single ? dim3(n_bh, nqb) : dim3((nqb + 1) / 2, n_bh);   // one or two query (key) blocks per workgroup
+      float* const cs = colsum_out ? colsum_partial + (size_t)b * nqb * 3 * A : nullptr;
+      attn_bwd_dq_mfma<DH, NG><<<grid, AT_THREADS * NG, DQ_LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
+                                                                     dqkv + row * 3 * A, dsum, cs, S, H, single);
+      DIPACO_LAUNCH_CHECK();
+      attn_bwd_dkv_mfma<DH, NG><<<grid, AT_THREADS * NG, DKV_LDS, s>>>(qkv + row * 3 * A, d_o + row * A, dsum, dqkv + row * 3 * A, cs, S, H, single);
+      DIPACO_LAUNCH_CHECK();
+    }
+    return DIPACO_OK;
+  };
+  if (dipaco_status st = two_groups(B, H, S) ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 1>{})) return st;
   if (colsum_out) return launch_sum_rows(colsum_partial, colsum_out, B * nqb, 3 * H * DH, s, batch);
   return DIPACO_OK;
 }

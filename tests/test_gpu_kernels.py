@@ -223,6 +223,14 @@ def test_attention_head_sizes_at_tile_edges(dtype, B, S, H, dh):
     test_attention_forward_backward(dtype, B, S, H, dh, 1)
 
 
+@pytest.mark.parametrize("B,S,H,dh", [(1, 385, 1, 32), (1, 385, 2, 64), (1, 385, 1, 128), (2, 640, 3, 32), (2, 641, 3, 64), (1, 700, 2, 128),
+                                      (8, 400, 11, 64), (8, 400, 12, 64), (8, 400, 12, 32), (8, 400, 12, 128)])
+def test_attention_with_two_groups_of_waves_a_block(B, S, H, dh, attn_blocks):
+    """Four blocks long or longer and few of them: two groups take a block's tiles in turn; 352 and 384 blocks of 128 rows lie on the two
+    sides of that rule.  Odd and even numbers of tiles, the last one ragged."""
+    test_attention_forward_backward(dp.BF16, B, S, H, dh, attn_blocks)
+
+
 # ---- the benchmarked kernels at the step's own shapes, element by element ---------------------------------------
 def _bf16_ulp(x):
     """Spacing of bf16 numbers at |x| (8 significant bits)."""
