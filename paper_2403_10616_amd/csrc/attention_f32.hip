@@ -21,6 +21,7 @@
 // with eight (256 workgroups on 256 compute units, the causal triangle's longest block setting the length of each launch);
 // one thread per row on the vector ALU: 375, 911, 1517.
 // No atomics: every output element has exactly one writer and a fixed summation order.
+#include <algorithm>
 #include <type_traits>
 
 #include "attention_plain.h"
@@ -225,31 +226,30 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_f32(const float* __restri
   }
 }
 
+template <int DH> __device__ __forceinline__ float row_dot(const RowFrag<DH>& a, const RowFrag<DH>& b) {
+  float d = 0.f;
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c) d += (a.c[c].x * b.c[c].x + a.c[c].y * b.c[c].y) + (a.c[c].z * b.c[c].z + a.c[c].w * b.c[c].w);
+  return sum_groups(d);
+}
+
 // dQ_i = scale * sum_{j<=i} p_ij (dO_i.v_j - D_i) k_j, with D_i = dO_i.o_i (also stored for the dK/dV kernel)
 template <int DH, int NW>
-__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
-                                                                const float* __restrict__ d_o, const float* __restrict__ lse,
-                                                                float* __restrict__ dqkv, float* __restrict__ dsum,
-                                                                float* __restrict__ colsum, int S, int H) {
+__device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                         const float* __restrict__ lse, float* __restrict__ dqkv, float* __restrict__ dsum,
+                                         float* __restrict__ colsum, int S, int H, int qb, int n_blocks) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
   constexpr int STAGE = 2 * tile_floats<DH>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
   const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
-  const int qb = gridDim.y - 1 - blockIdx.y, q0 = qb * (16 * NW);
+  const int q0 = qb * (16 * NW);
   const int qw0 = q0 + 16 * wave, q = qw0 + m;
   const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
   const long orow = ((long)b * S + q) * A + hd * DH;
   const RowFrag<DH> gf = load_row<DH>(d_o + orow, g, q < S);
-  float D = 0.f;
-  {
-    const RowFrag<DH> of = load_row<DH>(o + orow, g, q < S);
-#pragma unroll
-    for (int c = 0; c < DH / 16; ++c)
-      D += (gf.c[c].x * of.c[c].x + gf.c[c].y * of.c[c].y) + (gf.c[c].z * of.c[c].z + gf.c[c].w * of.c[c].w);
-    D = sum_groups(D);
-  }
+  const float D = row_dot<DH>(gf, load_row<DH>(o + orow, g, q < S));
   const float L = q < S ? lse[(long)bh * S + q] : INFINITY;   // +inf beyond the sequence: probability 0
   if (g == 0 && q < S) dsum[(long)bh * S + q] = D;
   const int ntiles = (min(S, q0 + (16 * NW)) + F_TILE - 1) / F_TILE;
@@ -284,15 +284,15 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __res
   if (q < S) store_row<DH>(dqkv + ((long)b * S + q) * ld + hd * DH, dqt, g, head_scale<DH>());
   // one row of partial column sums per (document, query block), this head's DH columns of dQ
   if (colsum)
-    block_column_sums<DH, NW>(dqt, head_scale<DH>(), q < S, f_smem, colsum + ((long)b * gridDim.y + qb) * ld + hd * DH, wave, m, g);
+    block_column_sums<DH, NW>(dqt, head_scale<DH>(), q < S, f_smem, colsum + ((long)b * n_blocks + qb) * ld + hd * DH, wave, m, g);
 }
 
 // dV_j = sum_{i>=j} p_ij dO_i;  dK_j = scale * sum_{i>=j} p_ij (dO_i.v_j - D_i) q_i
-template <int DH, int NW>
-__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
-                                                                 const float* __restrict__ lse, const float* __restrict__ dsum,
-                                                                 float* __restrict__ dqkv, float* __restrict__ colsum, int S,
-                                                                 int H) {
+// OWN_D: one block holds the sequence, and D is taken here, from o, by the arithmetic of dq_block; else from dsum
+template <int DH, int NW, bool OWN_D>
+__device__ __forceinline__ void dkv_block(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                          const float* __restrict__ lse, const float* __restrict__ dsum, float* __restrict__ dqkv,
+                                          float* __restrict__ colsum, int S, int H, int kb, int n_blocks) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][Q | dO | lse | D]
   constexpr int STAGE = 2 * tile_floats<DH>() + 2 * F_TILE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
   const float* gbase = d_o + (long)b * S * A + hd * DH;
-  const int kb = blockIdx.y, k0 = kb * (16 * NW);            // early key blocks are the long ones
+  const int k0 = kb * (16 * NW);            // early key blocks are the long ones
   const int kw0 = k0 + 16 * wave, key = kw0 + m;
   const RowFrag<DH> kf = load_row<DH>(base + (long)key * ld + A, g, key < S);
   const RowFrag<DH> vf = load_row<DH>(base + (long)key * ld + 2 * A, g, key < S);
@@ -308,6 +308,13 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
   zero_acc<DH>(dkt);
   zero_acc<DH>(dvt);
   const int first = k0 / F_TILE, ntiles = (S + F_TILE - 1) / F_TILE;
+  __shared__ float own_d[OWN_D ? 16 * NW : 1];
+  if constexpr (OWN_D) {
+    const long orow = ((long)b * S + key) * A + hd * DH;
+    const float D = row_dot<DH>(load_row<DH>(d_o + orow, g, key < S), load_row<DH>(o + orow, g, key < S));
+    if (g == 0) own_d[key] = D;
+    __syncthreads();
+  }
   TilePair<DH, NW> next;
   float next_stat = 0.f;
   // statistics of a tile's queries: threads 0..31 move lse (+inf beyond the sequence: probability 0), 32..63 D
@@ -316,7 +323,8 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
     if (threadIdx.x < 2 * F_TILE) {
       const int q = qt * F_TILE + (threadIdx.x & (F_TILE - 1));
       const bool is_lse = threadIdx.x < F_TILE;
-      next_stat = q < S ? (is_lse ? lse : dsum)[(long)bh * S + q] : (is_lse ? INFINITY : 0.f);
+      if (OWN_D && !is_lse) next_stat = q < S ? own_d[q] : 0.f;
+      else next_stat = q < S ? (is_lse ? lse : dsum)[(long)bh * S + q] : (is_lse ? INFINITY : 0.f);
     }
   };
   auto store = [&](int qt) {
@@ -358,17 +366,42 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
   if (__any(key < S && (plain::not_finite(dkt) || plain::not_finite(dvt))) && key < S)
     plain::key_grads<DH>(dkt, dvt, base, gbase, ld, A, key, S, g,
                          [&](float s, int i) { return expf(s * head_scale<DH>() - lse[(long)bh * S + i]); },
-                         [&](int i) { return dsum[(long)bh * S + i]; });
+                         [&](int i) { return OWN_D ? own_d[i] : dsum[(long)bh * S + i]; });
   if (key < S) {
     float* out = dqkv + ((long)b * S + key) * ld + hd * DH;
     store_row<DH>(out + A, dkt, g, head_scale<DH>());
     store_row<DH>(out + 2 * A, dvt, g, 1.0f);
   }
   if (colsum) {
-    float* cs = colsum + ((long)b * gridDim.y + kb) * ld + hd * DH;
+    float* cs = colsum + ((long)b * n_blocks + kb) * ld + hd * DH;
     block_column_sums<DH, NW>(dkt, head_scale<DH>(), key < S, f_smem, cs + A, wave, m, g);
     block_column_sums<DH, NW>(dvt, 1.0f, key < S, f_smem, cs + 2 * A, wave, m, g);
   }
+}
+
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                float* __restrict__ dqkv, float* __restrict__ dsum,
+                                                                float* __restrict__ colsum, int S, int H) {
+  dq_block<DH, NW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, gridDim.y - 1 - blockIdx.y, gridDim.y);
+}
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
+                                                                 const float* __restrict__ lse, const float* __restrict__ dsum,
+                                                                 float* __restrict__ dqkv, float* __restrict__ colsum, int S,
+                                                                 int H) {
+  dkv_block<DH, NW, false>(qkv, nullptr, d_o, lse, dsum, dqkv, colsum, S, H, blockIdx.y, gridDim.y);
+}
+// Sequences of one block (up to 64 positions on four waves): dQ and dK / dV in one launch, one workgroup each (blockIdx.y), as
+// such launches take as long as any launch: 4 x 2 heads x 64 x 32 6.6 + 7.0 us and a gap, 8.2 in one.
+template <int DH>
+__global__ void __launch_bounds__(64 * F_FEW, 2) attn_bwd_short_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                      const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                      float* __restrict__ dqkv, float* __restrict__ dsum,
+                                                                      float* __restrict__ colsum, int S, int H) {
+  if (blockIdx.y == 0) dkv_block<DH, F_FEW, true>(qkv, o, d_o, lse, nullptr, dqkv, colsum, S, H, 0, 1);
+  else dq_block<DH, F_FEW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, 0, 1);
 }
 
 template <int DH> constexpr int fwd_lds() { return 2 * 2 * tile_floats<DH>() * (int)sizeof(float); }
@@ -405,6 +438,17 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
     const size_t row = (size_t)b * S;
     const dim3 grid(std::min(step, B - b) * H, blocks);
     float* const cs = colsum ? colsum + (size_t)b * blocks * 3 * A : nullptr;
+    if constexpr (NW == F_FEW) {
+      if (blocks == 1) {
+        static std::atomic<unsigned long long> both{0};
+        constexpr int LDS = std::max(fwd_lds<DH>(), dkv_lds<DH>());
+        if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_short_f32<DH>), LDS, both)) return st;
+        attn_bwd_short_f32<DH><<<dim3(grid.x, 2), 64 * NW, LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
+                                                                     dqkv + row * 3 * A, dsum + row * H, cs, S, H);
+        DIPACO_LAUNCH_CHECK();
+        continue;
+      }
+    }
     attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
                                                                  dqkv + row * 3 * A, dsum + row * H, cs, S, H);
     DIPACO_LAUNCH_CHECK();
