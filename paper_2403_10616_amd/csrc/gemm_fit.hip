@@ -389,8 +389,9 @@ double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bo
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
   if (split_64) return tiles <= 256 ? 8.0 + 27.0 * K * 1e-3 : 1e30;
   if (t == 4 && !bf16_operands) {
-    const long full = (tiles + 255) / 512, rest = tiles - full * 512;   // rounds of two workgroups a unit, and of one behind them
-    return 3.0 + full * (18.0 + 88.0 * K * 1e-3) + (rest > 0 ? 10.5 + 60.0 * K * 1e-3 : 0.0);
+    const long full = tiles / 512, rest = tiles % 512;   // rounds of two workgroups a unit; behind them up to one a unit, or on the way to two
+    const double round = 18.0 + 88.0 * K * 1e-3, single = 10.5 + 60.0 * K * 1e-3;
+    return 3.0 + full * round + (rest == 0 ? 0.0 : single + std::max(0L, rest - 256) / 256.0 * (round - single));
   }
   const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
   const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
