@@ -823,7 +823,7 @@ RouterPlan make_router_plan(int64_t N, int D, int K) {
   p.logits = take((size_t)N * K * 4);
   p.nll = take((size_t)N * 4);
   p.n_valid = take(256);
-  p.cs_partial = take(dipaco::colsum_partial_floats((int)N, K) * 4);
+  p.cs_partial = take(dipaco::logistic_partial_floats(N, K) * 4);
   int limit[32];
   const int at = dipaco::gemm_limit_index(N);
   dipaco::gemm_slice_limits(K, D, false, limit, at + 1);
@@ -870,11 +870,9 @@ dipaco_status dipaco_router_logistic_grad(const float* z, const int32_t* labels,
   // logits = z W^T + b;  then per row the loss and (softmax - onehot) / N in place
   TRY(gemm<float>(z, weights, logits, (int)N, K, D, D, D, K, false, true, bias, nullptr, nullptr, nullptr, 0, false, 1,
                   nullptr, st));
-  TRY(launch_logistic_rows(logits, labels, N, K, (float)(1.0 / (double)N), nll, st));
-  TRY(launch_fill_i32(n_valid, (int)N, 1, st));
-  TRY(launch_mean_loss(nll, n_valid, loss_out, (int)N, st));
-  // db = column sums;  dW = dlogits^T z (contraction over the documents)
-  TRY(launch_colsum(logits, dbias_out, reinterpret_cast<float*>(ws + p.cs_partial), (int)N, K, st));
+  // and over them the mean loss and db = column sums
+  TRY(launch_logistic_rows(logits, labels, N, K, nll, n_valid, reinterpret_cast<float*>(ws + p.cs_partial), loss_out, dbias_out, st));
+  // dW = dlogits^T z (contraction over the documents)
   if (dweights_out)
     TRY(gemm<float>(logits, z, dweights_out, K, D, (int)N, K, D, D, true, false, nullptr, nullptr, nullptr, nullptr, 0,
                     true, gemm_plan_splits(K, D, (int)N, false, p.slice_limit), reinterpret_cast<float*>(ws + p.sk_partial), st));

@@ -51,9 +51,11 @@ dipaco_status launch_fill_i64(long long* p, long long value, size_t n, hipStream
 // lin_bias (nullable): linear router -- c holds the K weight rows and the score minimised is -(c_k.z_n + lin_bias[k])
 dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const float* lin_bias, int64_t N, int D, int K,
                            int n_best, int* idx, long long* hist, float* margin, hipStream_t s);
-// logits [rows, K] fp32 -> nll[rows] and, in place, (softmax - onehot(label)) * inv_n; labels outside [0, K): zeros
-dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t rows, int K, float inv_n, float* nll,
-                                   hipStream_t s);
+// logits [rows, K] fp32: in place (softmax - onehot(label)) / rows, zeros where the label lies outside [0, K); loss = mean negative
+// log-likelihood, db[K] = column sums of what is written.  nll [rows] and n_valid: scratch; partial: logistic_partial_floats
+dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t rows, int K, float* nll, int* n_valid, float* partial, float* loss,
+                                   float* db, hipStream_t s);
+size_t logistic_partial_floats(int64_t rows, int K);
 
 // ---- reroute.hip -------------------------------------------------------------------------------------
 // nll: [P, B, S] per-position negative log-likelihoods of B documents under P paths; prefix: scratch of

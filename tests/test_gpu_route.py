@@ -259,6 +259,12 @@ def test_logistic_loss_and_gradients_match_oracle(N, D, K):
     assert none_dW is None and np.array_equal(db2, db)
 
 
+@pytest.mark.parametrize("N,D,K", [(31, 8, 256), (33, 16, 200), (32768, 16, 256), (32769, 16, 256), (70001, 8, 120), (65568, 8, 8)])
+def test_logistic_sums_over_several_rounds_of_rows(N, D, K):
+    """A workgroup takes 32 rows up to 32768 rows, above that 32 several times: the sums of whole and ragged rounds."""
+    test_logistic_loss_and_gradients_match_oracle(N, D, K)
+
+
 def test_bias_fit_on_gpu_gradients_matches_label_distribution_and_refills_empty_paths():
     """Weights frozen, bias descended with the GPU's dbias: the mean predicted distribution reaches the labels',
     and classes the unfitted classifier never picked get documents again."""
