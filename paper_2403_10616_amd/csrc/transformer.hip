@@ -332,26 +332,36 @@ __global__ void __launch_bounds__(ROW_THREADS) ln_bwd_kernel(const T* __restrict
       }
     }
   }
-  // combine the four waves' column sums in wave order: each wave in turn adds into a [3][d] LDS row
-  extern __shared__ float cols[];
+  // combine the four waves' column sums in wave order: each wave in turn adds into a [3][d] LDS row, four columns at a time (one at a
+  // time the lanes, VEC columns apart, met on an eighth of the banks: 3000 rows of 896 13.3 us, 9.8 here)
+  extern __shared__ __attribute__((aligned(16))) float cols[];
   for (int w = 0; w < ROWS_PER_BLOCK; ++w) {
     if (wave == w) {
+      auto add = [&](float* at, const float (&v)[VEC]) {
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) {
+          float4 t = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+          if (w != 0) {
+            const float4 u = *reinterpret_cast<const float4*>(at + i);
+            t = make_float4(u.x + t.x, u.y + t.y, u.z + t.z, u.w + t.w);
+          }
+          *reinterpret_cast<float4*>(at + i) = t;
+        }
+      };
 #pragma unroll
       for (int it = 0; it < NIT; ++it) {
         const int c = (lane + WAVE * it) * VEC;
         if (c < d) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) {
-            if (w == 0) { cols[c + i] = ag[it][i]; cols[d + c + i] = ab[it][i]; cols[2 * d + c + i] = ac[it][i]; }
-            else { cols[c + i] += ag[it][i]; cols[d + c + i] += ab[it][i]; cols[2 * d + c + i] += ac[it][i]; }
-          }
+          add(cols + c, ag[it]);
+          add(cols + d + c, ab[it]);
+          add(cols + 2 * d + c, ac[it]);
         }
       }
     }
     __syncthreads();
   }
   float* out = partial + (size_t)blockIdx.x * 3 * d;
-  for (int c = threadIdx.x; c < 3 * d; c += ROW_THREADS) out[c] = cols[c];
+  for (int c = 4 * threadIdx.x; c < 3 * d; c += 4 * ROW_THREADS) *reinterpret_cast<float4*>(out + c) = *reinterpret_cast<const float4*>(cols + c);
 }
 
 // out[c] = sum over p of partial[p * stride + c].  32 columns x 32 partial phases per workgroup: phase y adds
