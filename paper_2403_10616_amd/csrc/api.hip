@@ -246,6 +246,7 @@ struct FeaturePlan {
   // small batches: planes of the two products that write the residual stream, cut over K (1: not cut)
   size_t planes = 0;
   int splits_o = 1, splits_down = 1;
+  int attn_planes = 0;   // planes of attention and output projection in one launch (0: two launches)
 };
 static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool with_head = false) {
   const dipaco_arch& a = c->arch;
@@ -264,10 +265,15 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   p.splits_down = gemm_raw_splits(rows, (int)d, (int)F, es == 2);
   // room for the planes of any smaller batch too; what fits the static scratch without them keeps fitting it
   p.planes = pos;
-  take(std::max(gemm_raw_plane_floats(rows, (int)d, (int)A, es == 2), gemm_raw_plane_floats(rows, (int)d, (int)F, es == 2)) * 4);
+  size_t plane_floats = std::max(gemm_raw_plane_floats(rows, (int)d, (int)A, es == 2), gemm_raw_plane_floats(rows, (int)d, (int)F, es == 2));
+  if (es == 2) {
+    p.attn_planes = attn_out_planes(B, S, a.n_heads, a.d_head);
+    plane_floats = std::max(plane_floats, (size_t)attn_out_planes(1, 1, a.n_heads, a.d_head) * std::min(rows, SMALL_FORWARD_ROWS) * d);
+  }
+  take(plane_floats * 4);
   if (p.planes <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) {
     pos = DIPACO_STATIC_SCRATCH_BYTES;
-    if (p.planes + std::max(p.splits_o, p.splits_down) * T * d * 4 > pos) p.splits_o = p.splits_down = 1;
+    if (p.planes + std::max({p.splits_o, p.splits_down, p.attn_planes}) * T * d * 4 > pos) { p.splits_o = p.splits_down = 1; p.attn_planes = 0; }
   }
   p.total = pos;
   return p;
@@ -301,19 +307,29 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
     if (!ln_g) return DIPACO_OK;
     return launch_layernorm_fwd<T>(x_new, ln_g, ln_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st);
   };
+  // X W + b of a block's input, then GELU; no backward pass: GELU' is neither kept nor written (act 5)
+  auto linear = [&](const T* X, size_t w_off, size_t b_off, T* Y, int N, bool gelu) -> dipaco_status {
+    if constexpr (std::is_same<T, bf16>::value) {
+      if (small_product_takes(T_, N, d)) return launch_small_product(X, W + w_off, W + b_off, Y, T_, N, d, gelu, st);
+    }
+    return gemm<T>(X, W + w_off, Y, T_, N, d, d, N, N, false, false, W + b_off, nullptr, nullptr, nullptr, gelu ? 5 : 0, false, 1, nullptr, st);
+  };
   // the LayerNorm in front of block l; behind the last block the final one, which only scoring needs
   auto ln_g = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_g : targets ? W + c->lnf_g : nullptr; };
   auto ln_b = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_b : targets ? W + c->lnf_b : nullptr; };
   if (ln_g(0)) TRY(launch_layernorm_fwd<T>(x, ln_g(0), ln_b(0), buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st));
   for (int l = 0; l < c->n_layers; ++l) {
     const BlockOff& o = c->blocks[l];
-    TRY(gemm<T>(buf(p.h), W + o.w_qkv, buf(p.qkv), T_, 3 * A, d, d, 3 * A, 3 * A, false, false, W + o.b_qkv, nullptr,
-                nullptr, nullptr, 0, false, 1, nullptr, st));
-    TRY(launch_attention_fwd<T>(buf(p.qkv), buf(p.o), fbuf(p.lse), B, S, H, dh, st));
-    TRY(residual(buf(p.o), o.w_o, o.b_o, A, p.splits_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b));
-    // no backward pass: GELU' is neither kept nor written (act 5)
-    TRY(gemm<T>(buf(p.h), W + o.w_up, buf(p.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, nullptr, nullptr,
-                5, false, 1, nullptr, st));
+    TRY(linear(buf(p.h), o.w_qkv, o.b_qkv, buf(p.qkv), 3 * A, false));
+    if (p.attn_planes) {
+      if constexpr (std::is_same<T, bf16>::value) TRY(launch_attn_out(buf(p.qkv), W + o.w_o, fbuf(p.planes), B, S, H, d, st));
+      TRY(launch_sum_layernorm<T>(fbuf(p.planes), p.attn_planes, W + o.b_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b, buf(p.h), T_, d,
+                                  a.ln_eps, st));
+    } else {
+      TRY(launch_attention_fwd<T>(buf(p.qkv), buf(p.o), fbuf(p.lse), B, S, H, dh, st));
+      TRY(residual(buf(p.o), o.w_o, o.b_o, A, p.splits_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b));
+    }
+    TRY(linear(buf(p.h), o.w_up, o.b_up, buf(p.act), F, true));
     TRY(residual(buf(p.act), o.w_down, o.b_down, F, p.splits_down, buf(p.x_mid), x_other, ln_g(l + 1), ln_b(l + 1)));
     std::swap(x, x_other);
   }

@@ -208,6 +208,14 @@ dipaco_status launch_sum_rows(const float* partial, float* out, int n_partials, 
 // out[n] = sum_m x[m,n] (fp32, fixed order);  partial: colsum_partial_floats scratch
 dipaco_status launch_colsum(const float* x, float* out, float* partial, int rows, int cols, hipStream_t s);
 size_t colsum_partial_floats(int rows, int cols);
+// small_forward.hip: a bf16 block's forward pass over a few rows
+constexpr int SMALL_FORWARD_ROWS = 256;
+// out = x W + bias (then GELU): x [rows, K], W [K, N]
+bool small_product_takes(int rows, int N, int K);
+dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, hipStream_t s);
+// attention and output projection, without bias and residual: the planes [n][B S, d] of launch_sum_layernorm.  0: does not take them
+int attn_out_planes(int B, int S, int H, int d_head);
+dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, hipStream_t s);
 // out[b, :] (fp32) = mean over positions of x[b*S + p, :]
 template <typename T> dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipStream_t s);
 // out[b] = -sum_p nll[b*S + p]

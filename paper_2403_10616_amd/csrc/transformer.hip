@@ -157,73 +157,71 @@ __global__ void __launch_bounds__(ROW_THREADS) ln_fwd_reg_kernel(const T* __rest
   }
 }
 
-// The sum of a split product's planes, its bias and residual, and the LayerNorm behind it, one wave per row: what the
-// product's epilogue and ln_fwd_reg_kernel do, in their order and on the value rounded to T, so that a small product may be
-// split over K without a pass of its own for the sum.  Bound by latency (4.3 us for 32 x 896): a chunk's bias, residual, gain
-// and shift arrive before its planes are asked for, and a row's second chunk follows the sum of its first.
-template <typename T, int NIT>
-__global__ void __launch_bounds__(WAVE) sum_layernorm_kernel(const float* __restrict__ planes, int n_planes,
-                                                             const T* __restrict__ bias, const T* __restrict__ resid,
-                                                             T* __restrict__ x, const T* __restrict__ g, const T* __restrict__ b,
-                                                             T* __restrict__ y, int rows, int d, float eps) {
+// x = sum of the planes (in index order) + bias + resid, y = LayerNorm(x) (null y: none): what stands behind a small product cut over
+// K.  A workgroup of NW waves per row, one 16-byte chunk a thread, so that every load of a row is in flight at once (one wave a row with
+// two chunks a lane: 4.4 us for 32 rows of 896 and seven planes, 3.6 here; the launch alone takes 2 - 3).
+template <typename T, int NW>
+__global__ void __launch_bounds__(WAVE * NW) sum_layernorm_kernel(const float* __restrict__ planes, int n_planes,
+                                                                  const T* __restrict__ bias, const T* __restrict__ resid,
+                                                                  T* __restrict__ x, const T* __restrict__ g, const T* __restrict__ b,
+                                                                  T* __restrict__ y, int rows, int d, float eps) {
   constexpr int VEC = Vec16<T>::N;
-  const int row = blockIdx.x, lane = threadIdx.x;
-  const size_t at = (size_t)row * d, plane = (size_t)rows * d;
-  float a[NIT][VEC], gg[NIT][VEC], bb[NIT][VEC];
+  __shared__ float red[2][NW];
+  const int row = blockIdx.x, c = threadIdx.x * VEC, wave = threadIdx.x >> 6;
+  const size_t at = (size_t)row * d + c, plane = (size_t)rows * d;
+  const bool on = c < d;
+  float a[VEC], gg[VEC], bb[VEC];
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int c = (lane + WAVE * it) * VEC;
-    if (c < d) {
-      float bi[VEC], re[VEC];
-      load_vec16(bias + c, bi);
-      load_vec16(resid + at + c, re);
-      if (y) { load_vec16(g + c, gg[it]); load_vec16(b + c, bb[it]); }
-      float4 v[8][VEC / 4];
+  for (int i = 0; i < VEC; ++i) a[i] = gg[i] = bb[i] = 0.f;
+  if (on) {
+    float bi[VEC], re[VEC];
+    load_vec16(bias + c, bi);
+    load_vec16(resid + at, re);
+    if (y) { load_vec16(g + c, gg); load_vec16(b + c, bb); }
+    float4 v[8][VEC / 4];
 #pragma unroll
-      for (int z = 0; z < 8; ++z)
-        if (z < n_planes) {
+    for (int z = 0; z < 8; ++z)
+      if (z < n_planes) {
 #pragma unroll
-          for (int q = 0; q < VEC / 4; ++q) v[z][q] = *reinterpret_cast<const float4*>(planes + z * plane + at + c + 4 * q);
-        }
-#pragma unroll
-      for (int q = 0; q < VEC / 4; ++q) {
-        float4 s = v[0][q];
-#pragma unroll
-        for (int z = 1; z < 8; ++z)
-          if (z < n_planes) { s.x += v[z][q].x; s.y += v[z][q].y; s.z += v[z][q].z; s.w += v[z][q].w; }
-        a[it][4 * q] = s.x; a[it][4 * q + 1] = s.y; a[it][4 * q + 2] = s.z; a[it][4 * q + 3] = s.w;
+        for (int q = 0; q < VEC / 4; ++q) v[z][q] = *reinterpret_cast<const float4*>(planes + z * plane + at + 4 * q);
       }
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) a[it][i] = to_f32(from_f32<T>((a[it][i] + bi[i]) + re[i]));
-      store_vec16(x + at + c, a[it]);
+    for (int q = 0; q < VEC / 4; ++q) {
+      float4 s = v[0][q];
+#pragma unroll
+      for (int z = 1; z < 8; ++z)
+        if (z < n_planes) { s.x += v[z][q].x; s.y += v[z][q].y; s.z += v[z][q].z; s.w += v[z][q].w; }
+      a[4 * q] = s.x; a[4 * q + 1] = s.y; a[4 * q + 2] = s.z; a[4 * q + 3] = s.w;
     }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) a[i] = to_f32(from_f32<T>((a[i] + bi[i]) + re[i]));
+    store_vec16(x + at, a);
   }
   if (!y) return;
+  auto row_sum = [&](float v, int which) {   // over the row's waves, in order
+    v = wave_sum(v);
+    if constexpr (NW == 1) return v;
+    if ((threadIdx.x & 63) == 0) red[which][wave] = v;
+    __syncthreads();
+    float s = red[which][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[which][w];
+    return s;
+  };
   float s = 0.f;
 #pragma unroll
-  for (int it = 0; it < NIT; ++it)
-    if ((lane + WAVE * it) * VEC < d) {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) s += a[it][i];
-    }
-  const float mu = wave_sum(s) / d;
+  for (int i = 0; i < VEC; ++i) s += a[i];
+  const float mu = row_sum(s, 0) / d;
   float q = 0.f;
+  if (on) {
 #pragma unroll
-  for (int it = 0; it < NIT; ++it)
-    if ((lane + WAVE * it) * VEC < d) {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) { float t = a[it][i] - mu; q += t * t; }
-    }
-  const float rs = 1.0f / sqrtf(wave_sum(q) / d + eps);
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int c = (lane + WAVE * it) * VEC;
-    if (c < d) {
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) a[it][i] = (a[it][i] - mu) * rs * gg[it][i] + bb[it][i];
-      store_vec16(y + at + c, a[it]);
-    }
+    for (int i = 0; i < VEC; ++i) { const float t = a[i] - mu; q += t * t; }
   }
+  const float rs = 1.0f / sqrtf(row_sum(q, 1) / d + eps);
+  if (!on) return;
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) a[i] = (a[i] - mu) * rs * gg[i] + bb[i];
+  store_vec16(y + at, a);
 }
 
 // ---- LayerNorm backward -----------------------------------------------------------------------------------
@@ -824,13 +822,16 @@ template <typename T>
 dipaco_status launch_sum_layernorm(const float* planes, int n_planes, const T* bias, const T* resid, T* x, const T* g, const T* b,
                                    T* y, int rows, int d, float eps, hipStream_t s) {
   constexpr int VEC = Vec16<T>::N;
-  const int chunks = (d + WAVE * VEC - 1) / (WAVE * VEC);
+  const int waves = (d + WAVE * VEC - 1) / (WAVE * VEC);
   if (n_planes < 2 || n_planes > 8 || d > 2048) return fail(DIPACO_ESHAPE, "plane sum: 2 to 8 planes, d_model up to 2048");
-  auto run = [&](auto kern) { kern<<<rows, WAVE, 0, s>>>(planes, n_planes, bias, resid, x, g, b, y, rows, d, eps); };
-  if (chunks <= 1) run(sum_layernorm_kernel<T, 1>);
-  else if (chunks <= 2) run(sum_layernorm_kernel<T, 2>);
-  else if (chunks <= 4) run(sum_layernorm_kernel<T, 4>);
-  else if constexpr (VEC == 4) run(sum_layernorm_kernel<T, 8>);   // bf16 rows of up to 2048 are four chunks a lane
+  auto run = [&](auto NWc) {
+    constexpr int NW = decltype(NWc)::value;
+    sum_layernorm_kernel<T, NW><<<rows, WAVE * NW, 0, s>>>(planes, n_planes, bias, resid, x, g, b, y, rows, d, eps);
+  };
+  if (waves <= 1) run(std::integral_constant<int, 1>{});
+  else if (waves <= 2) run(std::integral_constant<int, 2>{});
+  else if (waves <= 4) run(std::integral_constant<int, 4>{});
+  else if constexpr (VEC == 4) run(std::integral_constant<int, 8>{});   // bf16 rows of up to 2048 are four waves
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
@@ -1007,10 +1008,9 @@ dipaco_status launch_step_tail(const T* dx, const int* tokens, float* d_tok, flo
 }
 
 // out[b, :] = mean over the S positions of x[b*S + p, :]  (fp32, positions added in order).  A thread owns one 16-byte
-// column chunk: 10 us for a single document of 32 x 896 and 100 us for 8192 (one element a thread: 30 and 243).  Bound by the
-// latency of one load after another: the early exit of the adding loop lets the compiler put each position's load behind the
-// addition of the one before, whatever the eight loads written in front of it say.
-constexpr int POOL_THREADS = 128, POOL_AHEAD = 8;
+// column chunk.  Bound by the latency of its loads: sixteen in flight, whose additions are selects (with an early exit the compiler puts
+// each position's load behind the addition of the one before: one document of 32 x 896 10.5 us, 3.5 here).
+constexpr int POOL_THREADS = 128, POOL_AHEAD = 16;
 template <typename T>
 __global__ void __launch_bounds__(POOL_THREADS) mean_pool_kernel(const T* __restrict__ x, float* __restrict__ out, int S, int d) {
   constexpr int VEC = Vec16<T>::N;
@@ -1026,10 +1026,10 @@ __global__ void __launch_bounds__(POOL_THREADS) mean_pool_kernel(const T* __rest
     for (int u = 0; u < POOL_AHEAD; ++u) raw[u] = *reinterpret_cast<const uint4*>(src + (size_t)min(p0 + u, S - 1) * d);
 #pragma unroll
     for (int u = 0; u < POOL_AHEAD; ++u) {
-      if (p0 + u >= S) break;
+      const bool on = p0 + u < S;
       const T* e = reinterpret_cast<const T*>(&raw[u]);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) s[i] += to_f32(e[i]);
+      for (int i = 0; i < VEC; ++i) s[i] = on ? s[i] + to_f32(e[i]) : s[i];
     }
   }
   float* o = out + (size_t)b * d + c;

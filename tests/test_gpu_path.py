@@ -273,6 +273,17 @@ def test_prefix_features_match_oracle(name, B, S, compute, tol):
                                        torch.empty(16, dtype=torch.uint8, device=DEV))
 
 
+SHAPES.update({f"heads{h}": dict(layers_per_level=(1, 1), d_model=d, n_heads=h, d_head=64, d_mlp=d_mlp, vocab=264, max_seq=40)
+               for h, d, d_mlp in ((3, 72, 200), (4, 256, 520), (5, 200, 264), (15, 136, 64), (16, 328, 128))})
+
+
+@pytest.mark.parametrize("name,B,S", [("heads3", 1, 32), ("heads3", 2, 17), ("heads4", 1, 1), ("heads4", 2, 32), ("heads5", 3, 31),
+                                      ("heads5", 1, 33), ("heads15", 1, 16), ("heads16", 1, 32), ("heads16", 9, 15)])
+def test_prefix_features_of_a_few_rows_match_oracle(name, B, S):
+    """Attention and output projection of two heads a workgroup: odd numbers of heads, ragged widths, one position to a whole block."""
+    test_prefix_features_match_oracle(name, B, S, dp.BF16, 2e-2)
+
+
 @pytest.mark.parametrize("name,B,S,compute,mask", [("ragged", 3, 50, dp.F32, 5), ("wide", 4, 160, dp.F32, 32),
                                                    ("wide", 4, 160, dp.BF16, 32), ("one_level", 2, 16, dp.F32, 0)])
 def test_path_scores_match_oracle_and_training_loss(name, B, S, compute, mask):
