@@ -112,7 +112,9 @@ def test_embedding_gradient_with_several_vocabulary_rows_a_workgroup(vocab, B, S
 @pytest.mark.parametrize("dtype", [dp.F32, dp.BF16])
 @pytest.mark.parametrize("name,B,S", [("ragged", 3, 50), ("one_level", 5, 16), ("one_level", 1, 1), ("ragged", 1, 33)])
 def test_both_products_of_a_small_layers_backward_pass_in_one_launch(name, B, S, dtype):
-    """The same tiles in one launch as in two (which a forced tile takes): the same bits."""
+    """The same tiles in one launch as in two: the same bits in bf16.  A forced tile takes two launches; in fp32 those of a contraction of
+    up to 128 add in another order: eight sums of 16 against four of 32, a few 2^-24 each, and the oracle's bound of 1e-4 holds for
+    either; 1e-5 between them."""
     cfg = SHAPES[name]
     a, ctx = make_arch(cfg, dtype)
     theta = gen.random_params(orc.param_count(a), seed=5, scale=0.05)
@@ -126,7 +128,10 @@ def test_both_products_of_a_small_layers_backward_pass_in_one_launch(name, B, S,
             grads.append(host(st.grads).copy())
         finally:
             dp.dipaco_k_set_gemm_tile(0)
-    assert np.array_equal(grads[0], grads[1]) and np.isfinite(grads[0]).all()
+    assert np.isfinite(grads[0]).all()
+    if dtype == dp.BF16:
+        assert np.array_equal(grads[0], grads[1])
+    assert rel_l2(grads[0], grads[1]) <= 1e-5
 
 
 def test_config1_full_round_matches_oracle():
