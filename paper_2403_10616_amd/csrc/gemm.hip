@@ -92,10 +92,11 @@ static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_
   const int cap = std::max(1, std::min({bf16_operands ? GEMM_SLICE_CAP : GEMM_SLICE_CAP_F32, K / 256, limit}));
   SplitPlan best{1, false};
   double cost = 1e30;
+  const GemmFitTiles tiles = gemm_fit_tiles(M, N, bf16_operands, false);
   for (int s = 1; s <= cap; ++s) {
     const double planes = plane_cost(M, N, s) + reduce_cost(M, N, s);
     if (planes > cost) break;   // grows with s
-    const double c = gemm_fit_cost(M, N, (K + s - 1) / s, s, bf16_operands, false) + planes;
+    const double c = gemm_fit_cost(tiles, (K + s - 1) / s, s) + planes;
     if (c < cost) { cost = c; best.splits = s; }
   }
   if (bf16_operands && dlds_allowed && K % 32 == 0) {
@@ -152,7 +153,7 @@ static int dlds_rows(const GemmArgs& a) {
   const long rows = (rounds - 1) * 256 / tn * 256;
   if (rows < 256 || rows >= a.M) return a.M;
   const double round = 8.0 + 0.023 * a.K;
-  return gemm_fit_cost((int)(a.M - rows), a.N, a.K, 1, true, true) + 4.0 < round ? (int)rows : a.M;
+  return gemm_fit_cost(gemm_fit_tiles((int)(a.M - rows), a.N, true, true), a.K, 1) + 4.0 < round ? (int)rows : a.M;
 }
 
 template <typename T> static dipaco_status check_gemm(const GemmArgs& a) {

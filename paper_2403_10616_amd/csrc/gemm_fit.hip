@@ -465,16 +465,17 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 |
 // 132 / 206 / 708 against 150 / 262 / 968; at K = 64 512 tiles are level.  A round of 512 workgroups is two to a compute unit.
 // In 64 x 128 tiles of bf16 parts, one to a compute unit: 250 tiles 21.5 / 65 / 225 us (K = 512 / 2048 / 8192) against 22.5 / 71 - 80 /
 // 252 - 280 on the fp32 instruction, 750 tiles 58 against 55: taken for one round.
-double shape_cost(int t, int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
+long shape_tiles(int t, int M, int N, bool bf16_operands) {
+  const int bm = t == 3 && !bf16_operands ? 64 : 32 * t, bn = t == 1 ? 64 : 128;
+  return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+}
+inline __attribute__((always_inline)) double shape_cost(int t, long tiles, int K, bool bf16_operands, bool a_kc) {
   static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
-  const bool split_64 = t == 3 && !bf16_operands;
-  const int bm = split_64 ? 64 : 32 * t, bn = t == 1 ? 64 : 128;
-  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
-  if (split_64) return tiles <= 256 ? 8.0 + 27.0 * K * 1e-3 : 1e30;
+  if (t == 3 && !bf16_operands) return tiles <= 256 ? 8.0 + 27.0 * K * 1e-3 : 1e30;
   if (t == 4 && !bf16_operands) {
     const long full = tiles / 512, rest = tiles % 512;   // rounds of two workgroups a unit; behind them up to one a unit, or on the way to two
     const double round = 18.0 + 88.0 * K * 1e-3, single = 10.5 + 60.0 * K * 1e-3;
-    return 3.0 + full * round + (rest == 0 ? 0.0 : single + std::max(0L, rest - 256) / 256.0 * (round - single));
+    return 3.0 + (double)full * round + (rest == 0 ? 0.0 : single + std::max(0L, rest - 256) / 256.0 * (round - single));
   }
   const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
   const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
@@ -489,10 +490,10 @@ int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
     while (!fit_built(t, bf16_operands, a_kc)) --t;
     return t;
   }
+  auto cost = [&](int t) { return shape_cost(t, shape_tiles(t, M, N, bf16_operands) * splits, K, bf16_operands, a_kc); };
   int best = 1;
   for (int t = 2; t <= 5; ++t)
-    if (fit_built(t, bf16_operands, a_kc) &&
-        shape_cost(t, M, N, K, splits, bf16_operands, a_kc) < shape_cost(best, M, N, K, splits, bf16_operands, a_kc)) best = t;
+    if (fit_built(t, bf16_operands, a_kc) && cost(t) < cost(best)) best = t;
   return best;
 }
 
@@ -576,10 +577,16 @@ size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands) {
   return most;
 }
 
-double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous) {
+GemmFitTiles gemm_fit_tiles(int M, int N, bool bf16_operands, bool a_k_contiguous) {
+  GemmFitTiles f{{}, bf16_operands, a_k_contiguous};
+  for (int t = 1; t <= 5; ++t) f.tiles[t] = fit_built(t, bf16_operands, a_k_contiguous) ? shape_tiles(t, M, N, bf16_operands) : 0;
+  return f;
+}
+double gemm_fit_cost(const GemmFitTiles& f, int K, int splits) {
   double best = 1e30;
+#pragma unroll
   for (int t = 1; t <= 5; ++t)
-    if (fit_built(t, bf16_operands, a_k_contiguous)) best = std::min(best, shape_cost(t, M, N, K, splits, bf16_operands, a_k_contiguous));
+    if (f.tiles[t]) best = std::min(best, shape_cost(t, f.tiles[t] * splits, K, f.bf16_operands, f.a_k_contiguous));
   return best;
 }
 

@@ -138,8 +138,10 @@ dipaco_status launch_splitk_reduce(const float* partial, float* C, int M, int N,
 // K splits of a small forward product whose planes are summed by the next kernel: 1 = not worth it
 int gemm_raw_splits(int M, int N, int K, bool bf16_operands);
 size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands);   // their planes for any M up to this one
-// microseconds of a product of `splits` slices of K each with the best tile shape
-double gemm_fit_cost(int M, int N, int K, int splits, bool bf16_operands, bool a_k_contiguous);
+// microseconds of a product of `splits` slices of K each with the best tile shape; the tiles of each shape are counted once for all K
+struct GemmFitTiles { long tiles[6]; bool bf16_operands, a_k_contiguous; };
+GemmFitTiles gemm_fit_tiles(int M, int N, bool bf16_operands, bool a_k_contiguous);
+double gemm_fit_cost(const GemmFitTiles& f, int K, int splits);
 // 0 = automatic; 1 .. 4, 14 = gemm_fit.hip with 32x64, 64x128, 96x128, 128x128, 160x128 tiles, 5 = the direct-to-LDS kernel
 // wherever the shape allows, 6 .. 13 = the same with the shapes of set_gemm_dlds_shape (tuning and tests)
 void set_gemm_tile(int t);
