@@ -735,7 +735,7 @@ def bench_router(args):
                        "route_linear_ms": times["route"],
                        "route_linear_tflops": 2.0 * N * D * K / (times["route"] * 1e-3) / 1e12,
                        "loss": float(loss[0].item())},
-            "roofline": {"bound": "mfma", "kernel": "gemm_fit_kernel<float> (logits, weight gradient) + logistic_rows_small_kernel",
+            "roofline": {"bound": "mfma", "kernel": "gemm_split_kernel (logits, weight gradient) + logistic_rows_small_kernel",
                          "achieved": ach, "peak": PEAK_F32_PARTS_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_F32_PARTS_TFLOPS,
                          "traffic": None}}
 
