@@ -384,10 +384,10 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(64 * DIRECT_G,
 // The two products of a linear layer's backward pass, X^T dY (blocks 0 .. first - 1) and dY W^T, in one launch of 32 x 64 tiles.
 // Bound by launches: a step on 256 tokens is fifty of 5 us each, and neither product reads what the other writes (260 -> 209 us).  For
 // products whose tiles are on the compute units at once; larger ones gain nothing from company (their tiles fill the same rounds).
-template <typename T> __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_pair_kernel(const GemmDev dw, const GemmDev dx, int first) {
+template <typename T, int TN> __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_pair_kernel(const GemmDev dw, const GemmDev dx, int first) {
   const int block = blockIdx.x;
-  if (block < first) fit_product<T, float, false, false, 2, 4, 1, 1, 8, 3, false>(dw, block);
-  else fit_product<T, T, true, true, 2, 4, 1, 1, 8, 3, false>(dx, block - first);
+  if (block < first) fit_product<T, float, false, false, 2, TN, 1, 1, 8, 3, false>(dw, block);
+  else fit_product<T, T, true, true, 2, TN, 1, 1, 8, 3, false>(dx, block - first);
 }
 
 template <typename F> GemmDev fit_dev(const GemmArgs& a) {
@@ -497,11 +497,16 @@ int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   return best;
 }
 
+// fp32 tiles of 32 x 32: the eight waves' matrix instructions over a few hundred of K are 1.7 us of a launch of 7 in a 32 x 64 tile, and
+// such launches leave most compute units idle.  The same sums, bit for bit.
+long narrow_tiles(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32); }
+
 template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_shape(const GemmArgs& a, hipStream_t s) {
   const int splits = std::max(1, a.splits);
   const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
   if constexpr (sizeof(T) == 4) {
     if (t == 1 && direct_takes(a, A_KC, B_KC)) return run_direct<A_KC, B_KC>(a, s);
+    if (t == 1 && narrow_tiles(a.M, a.N) * splits <= 128) return run_fit<T, TC, A_KC, B_KC, 2, 2, 1, 1, 8, 3>(a, s);
   }
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
   if constexpr (sizeof(T) == 4) {
@@ -535,18 +540,25 @@ template <typename T> bool pair_fits(const GemmArgs& dw, const GemmArgs& dx) {
 
 template <typename T> bool gemm_fit_pair_takes(const GemmArgs& dw, const GemmArgs& dx) { return pair_fits<T>(dw, dx); }
 template <typename T> dipaco_status launch_gemm_fit_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
-  using W = Fit<T, float, false, false, 2, 4, 1, 1, 8, 3>;
-  using X = Fit<T, T, true, true, 2, 4, 1, 1, 8, 3>;
-  constexpr int LDS = W::LDS > X::LDS ? W::LDS : X::LDS;
-  auto kern = gemm_fit_pair_kernel<T>;
-  static std::atomic<unsigned long long> lds_set{0};   // per instantiation
-  if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_set)) return e;
-  const GemmDev w = fit_dev<W>(dw), x = fit_dev<X>(dx);
-  const int first = w.tiles_m * w.tiles_n;
-  kern<<<first + x.tiles_m * x.tiles_n, 64 * FIT_WAVES, LDS, s>>>(w, x, first);
-  DIPACO_LAUNCH_CHECK();
-  if (dx.colsum) return launch_sum_rows(dx.colsum_partial, dx.colsum, x.tiles_m, dx.N, s, dx.sum_batch);
-  return DIPACO_OK;
+  auto run = [&](auto TNc) -> dipaco_status {
+    constexpr int TN = decltype(TNc)::value;
+    using W = Fit<T, float, false, false, 2, TN, 1, 1, 8, 3>;
+    using X = Fit<T, T, true, true, 2, TN, 1, 1, 8, 3>;
+    constexpr int LDS = W::LDS > X::LDS ? W::LDS : X::LDS;
+    auto kern = gemm_fit_pair_kernel<T, TN>;
+    static std::atomic<unsigned long long> lds_set{0};   // per instantiation
+    if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_set)) return e;
+    const GemmDev w = fit_dev<W>(dw), x = fit_dev<X>(dx);
+    const int first = w.tiles_m * w.tiles_n;
+    kern<<<first + x.tiles_m * x.tiles_n, 64 * FIT_WAVES, LDS, s>>>(w, x, first);
+    DIPACO_LAUNCH_CHECK();
+    if (dx.colsum) return launch_sum_rows(dx.colsum_partial, dx.colsum, x.tiles_m, dx.N, s, dx.sum_batch);
+    return DIPACO_OK;
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (narrow_tiles(dw.M, dw.N) + narrow_tiles(dx.M, dx.N) <= 256) return run(std::integral_constant<int, 2>{});
+  }
+  return run(std::integral_constant<int, 4>{});
 }
 template bool gemm_fit_pair_takes<float>(const GemmArgs&, const GemmArgs&);
 template bool gemm_fit_pair_takes<bf16>(const GemmArgs&, const GemmArgs&);
