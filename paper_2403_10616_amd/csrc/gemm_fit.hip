@@ -317,25 +317,25 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, (2 * Fit<T, TC, A_KC, B_KC, TM
   fit_product<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST, FAR>(g, blockIdx.x);
 }
 
-// fp32 over a short K (up to DIRECT_K): 32 x 64 tiles whose operands go from memory straight into the lanes that multiply them.  Four waves
-// take 16 of K each at a time, two such steps in flight; their sums meet in the epilogue.  Such a product is bound by its launch, one
-// trip to memory and the instructions in front of and behind it: the ring above costs a second trip through LDS, a barrier and the
-// arithmetic of its addresses (256 x 192 x 64 6.0 us there, 4.9 here; 256 x 64 x 64 6.5 | 4.7; at K = 256 eight waves are level with it).
+// fp32 over a short K (up to DIRECT_K): 32 x 64 tiles, or 32 x 32 as below, whose operands go from memory straight into the lanes that
+// multiply them.  Four waves take 16 of K each at a time, two such steps in flight; their sums meet in the epilogue.  Such a product is
+// bound by its launch, one trip to memory and the instructions in front of and behind it: the ring above costs a second trip through LDS,
+// a barrier and the arithmetic of its addresses (256 x 192 x 64 6.0 us there, 4.9 here; 256 x 64 x 64 6.5 | 4.7).
 constexpr int DIRECT_K = 128, DIRECT_G = 4;
-template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(64 * DIRECT_G, 2) gemm_direct_kernel(const GemmDev g) {
+template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * DIRECT_G, 2) gemm_direct_kernel(const GemmDev g) {
   constexpr int G = DIRECT_G;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, kg = lane >> 4;
   const int tile_n = (int)blockIdx.x / g.tiles_m, tile_m = (int)blockIdx.x - tile_n * g.tiles_m;
-  const int m0 = tile_m * 32, n0 = tile_n * 64;
+  const int m0 = tile_m * 32, n0 = tile_n * 16 * TN;
   const float* const A = static_cast<const float*>(g.A);
   const float* const B = static_cast<const float*>(g.B);
   // rows and columns beyond the matrix re-read the last ones (their results are not stored); K beyond it counts as zero
-  uint32_t ra[2], rb[4];
+  uint32_t ra[2], rb[TN];
 #pragma unroll
   for (int i = 0; i < 2; ++i) ra[i] = (uint32_t)min(m0 + 16 * i + r, g.M - 1);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) rb[j] = (uint32_t)min(n0 + 16 * j + r, g.N - 1);
+  for (int j = 0; j < TN; ++j) rb[j] = (uint32_t)min(n0 + 16 * j + r, g.N - 1);
   const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
   auto load = [&](auto KCc, const float* p, uint32_t ld, uint32_t row, int k, float (&v)[4]) {   // K k .. k + 3 of a row
     if constexpr (decltype(KCc)::value) {   // K is a multiple of 4
@@ -350,21 +350,21 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(64 * DIRECT_G,
       }
     }
   };
-  f32x4 acc[2][4];
+  f32x4 acc[2][TN];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int AHEAD = 2;
   for (int k0 = 16 * wave; k0 < g.K; k0 += 16 * G * AHEAD) {   // uniform
-    float a[AHEAD][2][4], b[AHEAD][4][4];
+    float a[AHEAD][2][4], b[AHEAD][TN][4];
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) {
       const int k = k0 + 16 * G * s + 4 * kg;
 #pragma unroll
       for (int i = 0; i < 2; ++i) load(std::bool_constant<A_KC>{}, A, lda, ra[i], k, a[s][i]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) load(std::bool_constant<B_KC>{}, B, ldb, rb[j], k, b[s][j]);
+      for (int j = 0; j < TN; ++j) load(std::bool_constant<B_KC>{}, B, ldb, rb[j], k, b[s][j]);
     }
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) {
@@ -374,10 +374,10 @@ template <bool A_KC, bool B_KC> __global__ void __launch_bounds__(64 * DIRECT_G,
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][q], b[s][j][q], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][q], b[s][j][q], acc[i][j], 0, 0, 0);
     }
   }
-  fit_epilogue<float, float, 2, 4, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0,
+  fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0,
                                                [](float (&)[8], int, int) {});
 }
 
@@ -434,14 +434,14 @@ bool direct_takes(const GemmArgs& a, bool a_kc, bool b_kc) {
   return a.K <= DIRECT_K && std::max(1, a.splits) == 1 && !a.raw_planes && (uint64_t)(a_kc ? a.M : a.K) * a.lda < most &&
          (uint64_t)(b_kc ? a.N : a.K) * a.ldb < most;
 }
-struct DirectTile { static constexpr int BM = 32, BN = 64, BK = 16; };
-template <bool A_KC, bool B_KC> dipaco_status run_direct(const GemmArgs& a, hipStream_t s) {
-  const GemmDev g = fit_dev<DirectTile>(a);
+template <int TN> struct DirectTile { static constexpr int BM = 32, BN = 16 * TN, BK = 16; };
+template <bool A_KC, bool B_KC, int TN> dipaco_status run_direct(const GemmArgs& a, hipStream_t s) {
+  const GemmDev g = fit_dev<DirectTile<TN>>(a);
   const long blocks = (long)g.tiles_m * g.tiles_n;
   if (!launch_fits(blocks, 64 * DIRECT_G)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
-  constexpr int LDS = fit_epilogue_bytes(2, 4, 1, 1, DIRECT_G);
+  constexpr int LDS = fit_epilogue_bytes(2, TN, 1, 1, DIRECT_G);
   static_assert(LDS <= 64 * 1024, "no limit to raise");
-  gemm_direct_kernel<A_KC, B_KC><<<(unsigned)blocks, 64 * DIRECT_G, LDS, s>>>(g);
+  gemm_direct_kernel<A_KC, B_KC, TN><<<(unsigned)blocks, 64 * DIRECT_G, LDS, s>>>(g);
   DIPACO_LAUNCH_CHECK();
   if (a.colsum) return launch_sum_rows(a.colsum_partial, a.colsum, g.tiles_m, a.N, s, a.sum_batch);
   return DIPACO_OK;
@@ -497,16 +497,18 @@ int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
   return best;
 }
 
-// fp32 tiles of 32 x 32: the eight waves' matrix instructions over a few hundred of K are 1.7 us of a launch of 7 in a 32 x 64 tile, and
-// such launches leave most compute units idle.  The same sums, bit for bit.
+// fp32 tiles of 32 x 32 while one round of 256 compute units holds them: the eight waves' matrix instructions over 256 of K are 1.7 us of a
+// launch of 7 in a 32 x 64 tile, while compute units idle.  500 x 256 x 768 10.7 -> 8.1 us, 1000 x 256 x 768 11.5 -> 8.4, 500 x 512 x 2048
+// 21.7 -> 13.9, 512 x 512 x 4096 36.8 -> 22.7; the same sums, bit for bit.
 long narrow_tiles(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32); }
 
 template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_shape(const GemmArgs& a, hipStream_t s) {
   const int splits = std::max(1, a.splits);
   const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
   if constexpr (sizeof(T) == 4) {
-    if (t == 1 && direct_takes(a, A_KC, B_KC)) return run_direct<A_KC, B_KC>(a, s);
-    if (t == 1 && narrow_tiles(a.M, a.N) * splits <= 128) return run_fit<T, TC, A_KC, B_KC, 2, 2, 1, 1, 8, 3>(a, s);
+    const bool narrow = narrow_tiles(a.M, a.N) * splits <= 256;
+    if (t == 1 && direct_takes(a, A_KC, B_KC)) return narrow ? run_direct<A_KC, B_KC, 2>(a, s) : run_direct<A_KC, B_KC, 4>(a, s);
+    if (t == 1 && narrow) return run_fit<T, TC, A_KC, B_KC, 2, 2, 1, 1, 8, 3>(a, s);
   }
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
   if constexpr (sizeof(T) == 4) {
