@@ -308,8 +308,7 @@ __device__ __forceinline__ void fit_product(const GemmDev& g, int block) {
   if (nkt & 1) multiply_last(C0{});
   else multiply_last(C1{});
 
-  fit_epilogue<T, TC, TM, TN, WM, WN, G, F::IC>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0, tile_m, split,
-                                                [](float (&)[8], int, int) {});
+  fit_epilogue<T, TC, TM, TN, WM, WN, G, F::IC>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0, tile_m, split);
 }
 
 template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST, bool FAR>
@@ -377,8 +376,7 @@ template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * D
           for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i][q], b[s][j][q], acc[i][j], 0, 0, 0);
     }
   }
-  fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0,
-                                               [](float (&)[8], int, int) {});
+  fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0);
 }
 
 // The two products of a linear layer's backward pass, X^T dY (blocks 0 .. first - 1) and dY W^T, in one launch of 32 x 64 tiles.

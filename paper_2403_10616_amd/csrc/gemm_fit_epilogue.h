@@ -13,10 +13,10 @@ constexpr int FIT_PAD = 4;   // floats between rows of the staging region
 constexpr int fit_epilogue_bytes(int n16, int TN, int WM, int WN, int G) { return G * WM * 16 * n16 * (16 * TN * WN + FIT_PAD) * 4; }
 
 // acc: the wave's TM x TN tiles of 16 x 16 (lane l: column l % 16, rows 4 (l / 16) + e), taken in two passes of IC and TM - IC
-// tile rows.  red: LDS, free once every wave has reached this call.  fix(v, row, col) may replace the eight sums v.
-template <typename T, typename TC, int TM, int TN, int WM, int WN, int G, int IC, typename FIX>
+// tile rows.  red: LDS, free once every wave has reached this call.
+template <typename T, typename TC, int TM, int TN, int WM, int WN, int G, int IC>
 __device__ __forceinline__ void fit_epilogue(const GemmDev& g, const f32x4 (&acc)[TM][TN], float* red, int tid, int grp, int wm, int wn,
-                                             int m0, int n0, int tile_m, int split, FIX fix) {
+                                             int m0, int n0, int tile_m, int split) {
   static_assert(TM <= 2 * IC, "two passes");
   constexpr int NW = WM * WN * G, BN = 16 * TN * WN, LDW = BN + FIT_PAD, CG = BN / 8;
   const int lane = tid & 63, wave = tid >> 6, r = lane & 15, kg = lane >> 4;
@@ -65,7 +65,6 @@ __device__ __forceinline__ void fit_epilogue(const GemmDev& g, const f32x4 (&acc
 #pragma unroll
         for (int c = 0; c < 8; ++c) v[c] += w[c];
       }
-      fix(v, row, col);
       if (partial) {
         OutVec<float>::store(g.partial + ((size_t)split * g.M + row) * g.N + col, v);
         continue;

@@ -36,6 +36,82 @@ template <int WM, int WN, int G> struct SplitGemm {
   static_assert(fit_epilogue_bytes(EPI_ROWS, SP_T, WM, WN, G) <= LDS && LDS * (512 / THREADS) <= 160 * 1024, "two waves a SIMD");
 };
 
+// The workgroup's sums that the parts cannot give, on v_mfma_f32_16x16x4_f32.  Where the operands' largest number (NaN aside) is small enough
+// for every product and sum to be finite, a sum that is not comes of a NaN operand and stays.
+// 2048^3 146 us: 175 with all sums NaN, 430 - 550 with an infinity in every tile (a serial chain for each sum: 17 - 33 ms).
+// red: LDS of as many floats as waves
+template <bool A_KC, bool B_KC, int WM, int WN, int G>
+__device__ __forceinline__ void split_again(const GemmDev& g, f32x4 (&acc)[SP_T][SP_T], float* red, int tid, int grp, int wm, int wn, int m0, int n0,
+                                            int k_begin, int k_end) {
+  using P = SplitGemm<WM, WN, G>;
+  constexpr int NW = WM * WN * G;
+  const int lane = tid & 63, r = lane & 15, kg = lane >> 4, depth = k_end - k_begin;
+  const float* const A = static_cast<const float*>(g.A);
+  const float* const B = static_cast<const float*>(g.B);
+  float top = 0.f;
+  auto scan = [&](auto KCc, const float* p, long ld, int row0, int rows) {   // rows and depth are multiples of 4 along the contiguous index
+    constexpr bool KC = decltype(KCc)::value;
+    const int inner = (KC ? depth : rows) / 4, outer = KC ? rows : depth;
+    const float* const base = p + (KC ? row0 * ld + k_begin : k_begin * ld + row0);
+    constexpr int STEP = 64 * NW / 32, AHEAD = 8;
+    for (int i0 = 0; i0 < inner; i0 += 32)
+      for (int o0 = 0; o0 < outer; o0 += AHEAD * STEP) {
+        float4 x[AHEAD];   // what lies beyond the operand reads its last numbers
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+          x[u] = *reinterpret_cast<const float4*>(base + min(o0 + STEP * u + tid / 32, outer - 1) * ld + 4 * min(i0 + tid % 32, inner - 1));
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) top = fmaxf(fmaxf(fmaxf(top, fabsf(x[u].x)), fmaxf(fabsf(x[u].y), fabsf(x[u].z))), fabsf(x[u].w));
+      }
+  };
+  scan(std::bool_constant<A_KC>{}, A, g.lda, m0, min(P::BM, g.M - m0));
+  scan(std::bool_constant<B_KC>{}, B, g.ldb, n0, min(P::BN, g.N - n0));
+  top = wave_max(top);
+  if (lane == 0) red[tid >> 6] = top;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) top = fmaxf(top, red[w]);
+  if (top < 281474976710656.f) return;   // 2^48: products below 2^96, sums of 2^31 of them below 2^127
+  auto load = [&](auto KCc, const float* p, long ld, int row, int k, float (&v)[4]) {   // K k .. k + 3 of a row; beyond k_end: zero
+    if constexpr (decltype(KCc)::value) {
+      const float4 x = *reinterpret_cast<const float4*>(p + row * ld + min(k, k_end - 4));
+      const bool in = k < k_end;
+      v[0] = in ? x.x : 0.f; v[1] = in ? x.y : 0.f; v[2] = in ? x.z : 0.f; v[3] = in ? x.w : 0.f;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float x = p[min(k + q, k_end - 1) * ld + row];
+        v[q] = k + q < k_end ? x : 0.f;
+      }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < SP_T; ++i) {
+    f32x4 t[SP_T];
+#pragma unroll
+    for (int j = 0; j < SP_T; ++j) t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int row = min(m0 + 64 * wm + 16 * i + r, g.M - 1);
+#pragma unroll 1
+    for (int k0 = k_begin + 32 * grp; k0 < k_end; k0 += P::BK)   // the group's 32 of every stage
+#pragma unroll
+      for (int h = 0; h < 32; h += 16) {
+        float a[4], b[SP_T][4];
+        load(std::bool_constant<A_KC>{}, A, g.lda, row, k0 + h + 4 * kg, a);
+#pragma unroll
+        for (int j = 0; j < SP_T; ++j) load(std::bool_constant<B_KC>{}, B, g.ldb, min(n0 + 64 * wn + 16 * j + r, g.N - 1), k0 + h + 4 * kg, b[j]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int j = 0; j < SP_T; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[j][q], t[j], 0, 0, 0);
+      }
+#pragma unroll
+    for (int j = 0; j < SP_T; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!(fabsf(acc[i][j][e]) < INFINITY)) acc[i][j][e] = t[j][e];
+  }
+}
+
 template <bool A_KC, bool B_KC, int WM, int WN, int G>
 __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const GemmDev g) {
   using P = SplitGemm<WM, WN, G>;
@@ -147,20 +223,26 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
     __syncthreads();
   }
 
-  // An infinity among the operands leaves NaN here where fp32 has an infinity: sums that are not finite are taken again
-  auto fix = [&](float (&v)[8], int row, int col) {
-    const float *a = static_cast<const float*>(g.A), *b = static_cast<const float*>(g.B);
-#pragma unroll 1
-    for (int c = 0; c < 8; ++c) {
-      if (__builtin_isfinite(v[c])) continue;
-      float s = 0.f;
-      for (long k = k_begin; k < k_end; ++k)
-        s = __builtin_fmaf(A_KC ? a[row * g.lda + k] : a[k * g.lda + row], B_KC ? b[(col + c) * g.ldb + k] : b[k * g.ldb + col + c], s);
-      v[c] = s;
-    }
-  };
-  fit_epilogue<float, float, SP_T, SP_T, WM, WN, G, P::EPI_ROWS>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0,
-                                                                  tile_m, split, fix);
+  // An infinity among the operands leaves NaN here where fp32 has an infinity: sums that are not finite are looked at again
+  float* const red = reinterpret_cast<float*>(smem);
+  {
+    float finite = 0.f;   // NaN where a sum is not
+#pragma unroll
+    for (int i = 0; i < SP_T; ++i)
+#pragma unroll
+      for (int j = 0; j < SP_T; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) finite = __builtin_fmaf(acc[i][j][e], 0.f, finite);
+    const bool any = __any(finite != 0.f);
+    if (lane == 0) red[wave_all] = any ? 1.f : 0.f;
+    __syncthreads();
+    float seen = 0.f;
+#pragma unroll
+    for (int w = 0; w < WM * WN * G; ++w) seen = fmaxf(seen, red[w]);
+    if (seen != 0.f)   // uniform
+      split_again<A_KC, B_KC, WM, WN, G>(g, acc, red + WM * WN * G, tid, grp, wm, wn, m0, n0, k_begin, k_end);
+  }
+  fit_epilogue<float, float, SP_T, SP_T, WM, WN, G, P::EPI_ROWS>(g, acc, red, tid, grp, wm, wn, m0, n0, tile_m, split);
 }
 
 template <bool A_KC, bool B_KC, int WM, int WN, int G> dipaco_status run_split(const GemmArgs& a, hipStream_t s) {

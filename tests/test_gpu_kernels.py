@@ -8,7 +8,7 @@ from scipy.special import erf
 
 import paper_2403_10616_amd as dp
 from oracle import dipaco_oracle as orc
-from gpu_util import DEV, dev, host, rel_l2
+from gpu_util import DEV, dev, host, median_us, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -406,6 +406,35 @@ def test_fp32_products_from_bf16_parts(ta, tb, M, N, K, tile):
             assert np.array_equal(got[1], np.where(Br[K - 1] > 0, np.inf, -np.inf).astype(np.float32))
         assert np.allclose(got[2], 3.4e38 * 0.125 * Br[0], rtol=1e-6)
         assert np.array_equal(got[3:], before[3:] * np.float32(0.125)) and np.array_equal(got[0], before[0] * np.float32(0.125))
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
+
+
+@pytest.mark.parametrize("tile", [3, 4])
+def test_fp32_products_of_values_that_are_not_finite_take_no_second_walk_per_sum(tile):
+    """NaN operands: their sums are NaN already.  Infinities: the tiles they reach are multiplied once more."""
+    M, N, K = 2048, 2048, 2048
+    A, B = torch.randn((M, K), device=DEV), torch.randn((K, N), device=DEV)
+    C = torch.empty((M, N), device=DEV)
+    dp.dipaco_k_set_gemm_tile(tile)
+    try:
+        run = lambda: dp.dipaco_k_gemm(dp.F32, False, False, False, M, N, K, A, B, C)
+        finite = median_us(run)
+        A[5, 7] = math.nan
+        B[:, 11] = math.nan
+        run()
+        nan = torch.isnan(C)
+        assert bool(nan[5].all()) and bool(nan[:, 11].all()) and int(nan.sum()) == M + N - 1
+        A[:, 9] = math.nan
+        times = [median_us(run)]
+        assert bool(torch.isnan(C).all())
+        A[:, 7:10] = 1.0
+        A[:, 9] = math.inf
+        times.append(median_us(run))
+        C[:, 11] = 0.0
+        assert bool(torch.isinf(C).sum() == M * (N - 1))
+        print(f"tile {tile}: us finite {finite:.0f} NaN {times[0]:.0f} infinite {times[1]:.0f}", flush=True)
+        assert times[0] <= 2 * finite and times[1] <= 6 * finite
     finally:
         dp.dipaco_k_set_gemm_tile(0)
 
