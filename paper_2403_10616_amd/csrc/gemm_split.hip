@@ -37,12 +37,14 @@ template <int WM, int WN, int G> struct SplitGemm {
 };
 
 // The workgroup's sums that the parts cannot give, on v_mfma_f32_16x16x4_f32.  Where the operands' largest number (NaN aside) is small enough
-// for every product and sum to be finite, a sum that is not comes of a NaN operand and stays.
-// 2048^3 146 us: 175 with all sums NaN, 430 - 550 with an infinity in every tile (a serial chain for each sum: 17 - 33 ms).
+// for every product and sum to be finite, a sum that is not comes of a NaN operand and stays.  tiny: numbers below SPLIT_LEAST, each of
+// which errs by up to 2^-134 in its parts; sums of up to `floor` could show that in their 24 bits.
+// 2048^3 146 us: 175 with all sums NaN or small numbers that no sum depends on, 430 - 550 with an infinity in every tile (a serial chain
+// for each sum: 17 - 33 ms).
 // red: LDS of as many floats as waves
 template <bool A_KC, bool B_KC, int WM, int WN, int G>
 __device__ __forceinline__ void split_again(const GemmDev& g, f32x4 (&acc)[SP_T][SP_T], float* red, int tid, int grp, int wm, int wn, int m0, int n0,
-                                            int k_begin, int k_end) {
+                                            int k_begin, int k_end, bool tiny) {
   using P = SplitGemm<WM, WN, G>;
   constexpr int NW = WM * WN * G;
   const int lane = tid & 63, r = lane & 15, kg = lane >> 4, depth = k_end - k_begin;
@@ -71,7 +73,17 @@ __device__ __forceinline__ void split_again(const GemmDev& g, f32x4 (&acc)[SP_T]
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < NW; ++w) top = fmaxf(top, red[w]);
-  if (top < 281474976710656.f) return;   // 2^48: products below 2^96, sums of 2^31 of them below 2^127
+  if (!tiny && top < 281474976710656.f) return;   // 2^48: products below 2^96, sums of 2^31 of them below 2^127
+  const float floor = tiny ? top * (float)depth * 0x1p-109f : 0.f;
+  auto holds = [&](float v) { return fabsf(v) >= floor && fabsf(v) < INFINITY; };
+  bool all_hold = true;
+#pragma unroll
+  for (int i = 0; i < SP_T; ++i)
+#pragma unroll
+    for (int j = 0; j < SP_T; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) all_hold &= holds(acc[i][j][e]);
+  if (__all(all_hold)) return;   // the wave's own sums: no barrier follows here
   auto load = [&](auto KCc, const float* p, long ld, int row, int k, float (&v)[4]) {   // K k .. k + 3 of a row; beyond k_end: zero
     if constexpr (decltype(KCc)::value) {
       const float4 x = *reinterpret_cast<const float4*>(p + row * ld + min(k, k_end - 4));
@@ -108,7 +120,7 @@ __device__ __forceinline__ void split_again(const GemmDev& g, f32x4 (&acc)[SP_T]
     for (int j = 0; j < SP_T; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (!(fabsf(acc[i][j][e]) < INFINITY)) acc[i][j][e] = t[j][e];
+        if (!holds(acc[i][j][e])) acc[i][j][e] = t[j][e];
   }
 }
 
@@ -182,6 +194,8 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
     store_a[q] = 32 * SPLIT_ROW * UA * wave + UnitA::store_offset(lane, q);
     store_b[q] = 3 * P::PLANE_A + 32 * SPLIT_ROW * UB * wave + UnitB::store_offset(lane, q);
   }
+  float least = INFINITY;   // |x| of a stage's numbers
+  bool tiny = false;        // some lie below SPLIT_LEAST and are not zero
   auto store = [&](int kt) {
     const int klim = k_grp - kt * BK;
     if (klim < 32) {   // K beyond the range counts as zero
@@ -189,6 +203,23 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
       for (int u = 0; u < UA; ++u) sa[u].cut(lane, klim);
 #pragma unroll
       for (int u = 0; u < UB; ++u) sb[u].cut(lane, klim);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+      for (int u = 0; u < UA; ++u) sa[u].least(least, q);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) sb[u].least(least, q);
+    }
+    if (__any(least < SPLIT_LEAST)) {
+      least = INFINITY;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int u = 0; u < UA; ++u) tiny |= sa[u].tiny(q);
+#pragma unroll
+        for (int u = 0; u < UB; ++u) tiny |= sb[u].tiny(q);
+      }
     }
 #pragma unroll
     for (int u = 0; u < UA; ++u)
@@ -223,7 +254,8 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
     __syncthreads();
   }
 
-  // An infinity among the operands leaves NaN here where fp32 has an infinity: sums that are not finite are looked at again
+  // What the parts do not carry (split_tile.h) is looked for once the sums are there: infinities and overflow where a sum is not
+  // finite, and numbers below SPLIT_LEAST.  Such sums are taken again on the fp32 instruction.
   float* const red = reinterpret_cast<float*>(smem);
   {
     float finite = 0.f;   // NaN where a sum is not
@@ -233,14 +265,14 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
       for (int j = 0; j < SP_T; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) finite = __builtin_fmaf(acc[i][j][e], 0.f, finite);
-    const bool any = __any(finite != 0.f);
-    if (lane == 0) red[wave_all] = any ? 1.f : 0.f;
+    const bool any_tiny = __any(tiny);
+    if (lane == 0) red[wave_all] = any_tiny ? 2.f : __any(finite != 0.f) ? 1.f : 0.f;
     __syncthreads();
     float seen = 0.f;
 #pragma unroll
     for (int w = 0; w < WM * WN * G; ++w) seen = fmaxf(seen, red[w]);
     if (seen != 0.f)   // uniform
-      split_again<A_KC, B_KC, WM, WN, G>(g, acc, red + WM * WN * G, tid, grp, wm, wn, m0, n0, k_begin, k_end);
+      split_again<A_KC, B_KC, WM, WN, G>(g, acc, red + WM * WN * G, tid, grp, wm, wn, m0, n0, k_begin, k_end, seen == 2.f);
   }
   fit_epilogue<float, float, SP_T, SP_T, WM, WN, G, P::EPI_ROWS>(g, acc, red, tid, grp, wm, wn, m0, n0, tile_m, split);
 }

@@ -3,8 +3,11 @@
 // m m, h l, l h in fp32 accumulators.  The three left out are below 2^-25 of it.  v_mfma_f32_16x16x32_bf16 contracts 32 of K in the time
 // v_mfma_f32_16x16x4_f32 takes for two, so six of them do 2.7 times the work of the fp32 instruction.  The instruction cuts what falls
 // below its accumulator's last bit: the six are chained from zero over 32 of K and added to the running sum on the vector ALU, which rounds.
-// Limits: parts of numbers below 2^-110 fall under the smallest bf16; infinities (and numbers that round to one) make a part NaN, so
-// callers look at their sums and take those that are not finite again in fp32.
+// Limits: a third part ends at 2^-133, the smallest bf16 (conversions and products keep subnormal numbers), so a number below
+// SPLIT_LEAST errs by up to 2^-134, more than 2^-24 of it; infinities and numbers that round to one make a part NaN.  Callers look
+// for both and take what depends on them again in fp32.
+// The split and the sum of part products are those of G. Henry, P. T. P. Tang, A. Heinecke, Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations, ARITH 2019.
 //
 // Operand tiles in LDS: three planes (h, m, l) of rows of 32 K = 64 bytes.  Within a plane, row R lies at row slot
 // 4 (R / 4) + ((R ^ (R / 4)) & 3), and its 16-byte chunk c (K 8 c .. 8 c + 7) at chunk c ^ 2 (R / 8 & 1) ^ (R / 16 & 1): what the LDS
@@ -16,6 +19,7 @@
 namespace dipaco {
 
 constexpr int SPLIT_ROW = 64;    // bytes of a plane's row: 32 of K
+constexpr float SPLIT_LEAST = 0x1p-110f;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -63,6 +67,14 @@ template <bool KC> struct SplitUnit {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (4 * piece(lane) + j >= left) v[0][j] = v[1][j] = v[2][j] = v[3][j] = 0.f;
+  }
+  __device__ __forceinline__ void least(float& m, int q) const {   // m = min(m, |row q|); by hand: fminf would first quiet its operands
+    asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(v[q][0]), "v"(v[q][1]));
+    asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(v[q][2]), "v"(v[q][3]));
+  }
+  __device__ __forceinline__ bool tiny(int q) const {
+    auto is = [](float x) { return fabsf(x) < SPLIT_LEAST && x != 0.f; };
+    return is(v[q][0]) || is(v[q][1]) || is(v[q][2]) || is(v[q][3]);
   }
   // row q, taken apart, into the planes at p, p + PLANE, p + 2 PLANE
   template <int PLANE> __device__ __forceinline__ void store(char* p, int q) const {

@@ -410,9 +410,44 @@ def test_fp32_products_from_bf16_parts(ta, tb, M, N, K, tile):
         dp.dipaco_k_set_gemm_tile(0)
 
 
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+@pytest.mark.parametrize("tile", [3, 4])
+@pytest.mark.parametrize("M,N,K", [(132, 136, 36), (256, 264, 500), (260, 120, 2052)])
+def test_fp32_products_from_bf16_parts_keep_the_bits_of_small_numbers(ta, tb, M, N, K, tile):
+    """Below 2^-110 three bf16 parts hold fewer than 24 bits.  Sums that consist of such numbers alone are taken on the fp32 instruction: its
+    error is a few 2^-24 of the terms and their partial sums; sums that normal numbers decide keep their bits."""
+    dp.dipaco_k_set_gemm_tile(tile)
+    try:
+        A, Ar = _rand((K, M) if ta else (M, K), 31, dp.F32)
+        B, Br = _rand((N, K) if tb else (K, N), 32, dp.F32)
+        Br = Br.T if tb else Br
+        C = torch.empty((M, N), dtype=torch.float32, device=DEV)
+        run = lambda: dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C)
+        run()
+        ref = (Ar.T if ta else Ar) @ Br
+        before = host(C).copy()
+        bound = 2.0 ** -24 * (4 + math.sqrt(K))
+        row = lambda m: A[:, m] if ta else A[m]
+        row(1).mul_(2.0 ** -120)
+        row(2).zero_()
+        row(3)[::2] = 0.0                        # zeros lack nothing
+        run()
+        got = host(C)
+        assert rel_l2(got[1] * 2.0 ** 120, ref[1]) <= bound
+        assert not got[2].any()
+        assert np.array_equal(got[4:], before[4:]) and np.array_equal(got[0], before[0])
+        A.copy_(torch.from_numpy((Ar * 2.0 ** -120).astype(np.float32)))
+        B.mul_(2.0 ** 100)
+        run()
+        assert rel_l2(host(C) * 2.0 ** 20, ref) <= bound
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
+
+
 @pytest.mark.parametrize("tile", [3, 4])
 def test_fp32_products_of_values_that_are_not_finite_take_no_second_walk_per_sum(tile):
-    """NaN operands: their sums are NaN already.  Infinities: the tiles they reach are multiplied once more."""
+    """NaN operands: their sums are NaN already.  Numbers below 2^-110 that no sum depends on: they are.  Infinities: the tiles they reach
+    are multiplied once more."""
     M, N, K = 2048, 2048, 2048
     A, B = torch.randn((M, K), device=DEV), torch.randn((K, N), device=DEV)
     C = torch.empty((M, N), device=DEV)
@@ -428,13 +463,15 @@ def test_fp32_products_of_values_that_are_not_finite_take_no_second_walk_per_sum
         A[:, 9] = math.nan
         times = [median_us(run)]
         assert bool(torch.isnan(C).all())
-        A[:, 7:10] = 1.0
-        A[:, 9] = math.inf
+        A[:, 7:10], B[:, 11] = 1.0, 1.0
+        A[:, 9] = 2.0 ** -120
+        times.append(median_us(run))
+        A[:, 9], B[:, 11] = math.inf, math.nan
         times.append(median_us(run))
         C[:, 11] = 0.0
         assert bool(torch.isinf(C).sum() == M * (N - 1))
-        print(f"tile {tile}: us finite {finite:.0f} NaN {times[0]:.0f} infinite {times[1]:.0f}", flush=True)
-        assert times[0] <= 2 * finite and times[1] <= 6 * finite
+        print(f"tile {tile}: us finite {finite:.0f} NaN {times[0]:.0f} small {times[1]:.0f} infinite {times[2]:.0f}", flush=True)
+        assert max(times[:2]) <= 2 * finite and times[2] <= 6 * finite
     finally:
         dp.dipaco_k_set_gemm_tile(0)
 
