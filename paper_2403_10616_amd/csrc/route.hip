@@ -69,13 +69,15 @@ template <bool TOP2> __device__ __forceinline__ Best best_merge(const Best& a, c
 // order differently lies closer together than NEAR_TIE of the scores, a point in 10^4, and is decided by the chain in the order of
 // v_mfma_f32_32x32x2_f32 over chunks of four K (0, 4, 1, 5, 2, 6, 3, 7 of every eight), so that assignments do not turn with the
 // unit that multiplies.  A wave takes 32 points, lanes 0 .. 31 their best candidates, lanes 32 .. 63 the second ones.
+// Points whose norm, or a centroid's, is so large that part products may overflow (infinities among them) are taken again by their wave
+// against all centroids (again_in_fp32).
+constexpr float LARGE_NORM2 = 8.507059e37f;   // 2^126
 constexpr float NEAR_TIE = 1.0f / 131072.0f;
 __device__ __forceinline__ bool near_tie(const Best& b) {
   return b.i2 != NO_INDEX && b.s2 - b.s1 < NEAR_TIE * (fabsf(b.s1) + fabsf(b.s2));
 }
-__device__ __forceinline__ void decide_near_tie(Best& b, const float* __restrict__ z_row, const float* __restrict__ c,
+__device__ __forceinline__ void decide_near_tie(Best& b, bool near, const float* __restrict__ z_row, const float* __restrict__ c,
                                                 const float* __restrict__ lin_bias, int D, float dot_mul, int lane) {
-  const bool near = near_tie(b);
   const int k = near ? (lane < 32 ? b.i1 : b.i2) : 0;
   const float* const c_row = c + (long)k * D;
   float dot = 0.f, n[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -114,6 +116,58 @@ __device__ __forceinline__ void decide_near_tie(Best& b, const float* __restrict
   const bool swap = lex_less(s2, k2, s1, k1);
   b.s1 = swap ? s2 : s1; b.i1 = swap ? k2 : k1;
   b.s2 = swap ? s1 : s2; b.i2 = swap ? k1 : k2;
+}
+
+// A wave's 32 points (lane l: point l % 32, z_row) against all centroids on the fp32 matrix instruction, K in the order above
+__device__ __forceinline__ Best again_in_fp32(const float* __restrict__ z_row, const float* __restrict__ c, const float* __restrict__ lin_bias,
+                                              int D, int K, float dot_mul, int lane) {
+  const int r = lane & 31, h = lane >> 5;
+  Best b;
+  b.s1 = INFINITY; b.i1 = NO_INDEX; b.s2 = INFINITY; b.i2 = NO_INDEX;
+#pragma unroll 1
+  for (int n0 = 0; n0 < K; n0 += 32) {
+    const float* const c_row = c + (long)min(n0 + r, K - 1) * D;
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    float n[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 x[4], y[4];
+    auto load = [&](int k0) {   // chunk 2 q + h of 32 K; K beyond the row counts as zero
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = k0 + 8 * q + 4 * h, at = min(k, D - 4);
+        x[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(z_row + at), k < D));
+        y[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(c_row + at), k < D));
+      }
+    };
+    load(0);
+#pragma unroll 1
+    for (int k0 = 0; k0 < D; k0 += RBK) {
+      float4 u[4], v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { u[q] = x[q]; v[q] = y[q]; }
+      if (k0 + RBK < D) load(k0 + RBK);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].x, u[q].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].y, u[q].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].z, u[q].z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].w, u[q].w, acc, 0, 0, 0);
+        n[q] += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) n[q] += __shfl_xor(n[q], 32, WAVE);
+    const float cn = n0 + r < K ? (lin_bias ? -lin_bias[n0 + r] : (n[0] + n[1]) + (n[2] + n[3])) : INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int row = acc_row(e, lane);
+      best_push_ascending<true>(b, __builtin_fmaf(-dot_mul, acc[e], __shfl(cn, row, WAVE)), n0 + row);
+    }
+  }
+  Best o;
+  o.s1 = __shfl_xor(b.s1, 32, WAVE); o.i1 = __shfl_xor(b.i1, 32, WAVE); o.s2 = __shfl_xor(b.s2, 32, WAVE); o.i2 = __shfl_xor(b.i2, 32, WAVE);
+  return best_merge<true>(b, o);
 }
 
 // z: row n at z + n * ldz.  TOP2: idx is [N, 2] (second entry -1 when K = 1) and hist counts both memberships.
@@ -170,6 +224,8 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   Best run[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) { run[j].s1 = INFINITY; run[j].i1 = NO_INDEX; run[j].s2 = INFINITY; run[j].i2 = NO_INDEX; }
+  float zn[4] = {0.f, 0.f, 0.f, 0.f};   // |z|^2 of the pieces the lane stages, of their first parts, times the tiles of centroids
+  float c2 = 0.f;   // the largest |c|^2 the lane has seen
 
   load(0, 0);
   for (int n0 = 0; n0 < K; n0 += RB) {
@@ -193,7 +249,10 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
         sc.template store<R_PLANE>(smem + store_at[q], q);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sz.template store<R_PLANE>(smem + 3 * R_PLANE + store_at[q], q);
+      for (int q = 0; q < 4; ++q) {
+        const uint2 first = sz.template store<R_PLANE>(smem + 3 * R_PLANE + store_at[q], q);
+        zn[q] = add_squares(first.x, add_squares(first.y, zn[q]));   // for every tile of centroids: a branch for the first one costs more
+      }
       if (kt + 1 < nkt) load(n0, kt + 1);
       else if (n0 + RB < K) load(n0 + RB, 0);
       __syncthreads();
@@ -210,6 +269,7 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
       v += __shfl_xor(v, 1, WAVE);
       v += __shfl_xor(v, 2, WAVE);
       v += __shfl_xor(v, 4, WAVE);
+      c2 = fmaxf(c2, v);   // a NaN passes by: such a centroid is nobody's
       if ((lane & 7) == 0) {
         const int col = 32 * wave + (lane >> 3) + 8 * q;
         // linear router: the score to minimise is -(w_k.z + b_k), so -b_k takes the place of ||c_k||^2
@@ -219,44 +279,17 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
     }
     __syncthreads();
     const int k0 = 64 * wc + 4 * kg;   // the lane's rows of block i: k0 + 16 i + e
-    float sum = 0.f;                   // not finite where an accumulator is not
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+      const float4 cn4 = *reinterpret_cast<const float4*>(cnorm + k0 + 16 * i);
+      const float cn[4] = {cn4.x, cn4.y, cn4.z, cn4.w};
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum = __builtin_fmaf(acc[i][j][e], 0.f, sum);
-    if (__any(sum != 0.f)) {
-      // An infinity among the operands leaves NaN where fp32 has an infinity: the wave's scores are taken again in fp32
-      const float* zr[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) zr[j] = zb + (long)min(64 * wp + 16 * j + r, rows_left - 1) * ldz;
-#pragma unroll 1
-      for (int t = 0; t < 16; ++t) {
-        const int col = k0 + 16 * (t >> 2) + (t & 3);
-        const float* const cr = c + (long)min(n0 + col, K - 1) * D;
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-        for (int k = 0; k < D; ++k) {
-          const float x = cr[k];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) s[j] = __builtin_fmaf(x, zr[j][k], s[j]);
+        for (int j = 0; j < 4; ++j) {
+          const float s = __builtin_fmaf(-dot_mul, acc[i][j][e], cn[e]);
+          best_push_ascending<true>(run[j], s, n0 + k0 + 16 * i + e);
         }
-        const float cn = cnorm[col];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) best_push_ascending<true>(run[j], __builtin_fmaf(-dot_mul, s[j], cn), n0 + col);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 cn4 = *reinterpret_cast<const float4*>(cnorm + k0 + 16 * i);
-        const float cn[4] = {cn4.x, cn4.y, cn4.z, cn4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            best_push_ascending<true>(run[j], __builtin_fmaf(-dot_mul, acc[i][j][e], cn[e]), n0 + k0 + 16 * i + e);
-      }
     }
   }
 
@@ -266,7 +299,11 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   float* const red_s2 = red_s1 + 2 * RB;
   int* const red_i1 = reinterpret_cast<int*>(red_s2 + 2 * RB);
   int* const red_i2 = red_i1 + 2 * RB;
-  static_assert(8 * RB * sizeof(float) <= R_LDS, "the merge arrays fit in the planes");
+  float* const red_z2 = reinterpret_cast<float*>(red_i2 + 2 * RB);   // [4][256]
+  float* const red_c2 = red_z2 + 4 * 256;
+  static_assert((16 * RB + 4) * sizeof(float) <= R_LDS, "the merge arrays fit in the planes");
+#pragma unroll
+  for (int q = 0; q < 4; ++q) red_z2[256 * q + tid] = zn[q];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
 #pragma unroll
@@ -281,14 +318,29 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
       red_s1[at] = run[j].s1; red_i1[at] = run[j].i1; red_s2[at] = run[j].s2; red_i2[at] = run[j].i2;
     }
   }
+  c2 = wave_max(c2);
+  if (lane == 0) red_c2[wave] = c2;
   __syncthreads();
   const int point = 32 * wave + (lane & 31);   // both halves of the wave hold its 32 points
   Best b, o;
   b.s1 = red_s1[point]; b.i1 = red_i1[point]; b.s2 = red_s2[point]; b.i2 = red_i2[point];
   o.s1 = red_s1[RB + point]; o.i1 = red_i1[RB + point]; o.s2 = red_s2[RB + point]; o.i2 = red_i2[RB + point];
   b = best_merge<true>(b, o);
-  if (__any(point < rows_left && near_tie(b)))
-    decide_near_tie(b, zb + (long)min(point, rows_left - 1) * ldz, c, lin_bias, D, dot_mul, lane);
+  c2 = fmaxf(fmaxf(red_c2[0], red_c2[1]), fmaxf(red_c2[2], red_c2[3]));
+  float z2 = 0.f;   // point p of the wave: the eight lanes 8 (p % 8) + t staged its pieces as their row p / 8
+#pragma unroll
+  for (int t = 0; t < 8; ++t) z2 += red_z2[256 * ((lane & 31) >> 3) + 64 * wave + 8 * (lane & 7) + t];
+  z2 *= __builtin_amdgcn_rcpf((float)((K + RB - 1) / RB));
+  const bool on = point < rows_left;
+  // what is not finite compares false: rows of NaN have no scores, those of infinities are told by their norm
+  const bool again = on && fmaxf(z2, c2) >= LARGE_NORM2;
+  const bool near = on && !again && near_tie(b);
+  const float* const z_row = zb + (long)min(point, rows_left - 1) * ldz;
+  if (__any(near)) decide_near_tie(b, near, z_row, c, lin_bias, D, dot_mul, lane);
+  if (__any(again)) {
+    const Best f = again_in_fp32(z_row, c, lin_bias, D, K, dot_mul, lane);
+    if (again) b = f;
+  }
   if (lane < 32 && point < rows_left) {
     // A row none of whose scores compares below +inf (NaN or infinite features: a diverged path) never entered an
     // entry.  It is given the first centroid (the first two with TOP2) and a NaN margin, which is what the plain

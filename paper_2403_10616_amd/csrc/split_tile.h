@@ -39,6 +39,11 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& h, uint32
   l = pack(x, y);
 }
 
+// s + the squares of a word's two bf16 numbers
+__device__ __forceinline__ float add_squares(uint32_t p, float s) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), __builtin_bit_cast(bf16x2, p), s, false);
+}
+
 // byte offset of 8-byte piece p (K 4 p .. 4 p + 3) of row R in a plane
 __device__ __forceinline__ int split_offset(int R, int p) {
   return ((R & ~3) | ((R ^ (R >> 2)) & 3)) * SPLIT_ROW + (((p >> 1) ^ ((R >> 2) & 2) ^ ((R >> 4) & 1)) << 4) + ((p & 1) << 3);
@@ -76,14 +81,15 @@ template <bool KC> struct SplitUnit {
     auto is = [](float x) { return fabsf(x) < SPLIT_LEAST && x != 0.f; };
     return is(v[q][0]) || is(v[q][1]) || is(v[q][2]) || is(v[q][3]);
   }
-  // row q, taken apart, into the planes at p, p + PLANE, p + 2 PLANE
-  template <int PLANE> __device__ __forceinline__ void store(char* p, int q) const {
+  // row q, taken apart, into the planes at p, p + PLANE, p + 2 PLANE; returns the first parts
+  template <int PLANE> __device__ __forceinline__ uint2 store(char* p, int q) const {
     uint2 h, m, l;
     split_pair(v[q][0], v[q][1], h.x, m.x, l.x);
     split_pair(v[q][2], v[q][3], h.y, m.y, l.y);
     *reinterpret_cast<uint2*>(p) = h;
     *reinterpret_cast<uint2*>(p + PLANE) = m;
     *reinterpret_cast<uint2*>(p + 2 * PLANE) = l;
+    return h;
   }
 };
 

@@ -8,7 +8,7 @@ import torch
 import dipaco_inputs as gen
 import paper_2403_10616_amd as dp
 from oracle import dipaco_oracle as orc
-from gpu_util import DEV, dev, host, rel_l2
+from gpu_util import DEV, dev, host, median_us, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -488,6 +488,26 @@ def test_near_ties_of_bf16_parts_are_decided_by_the_fp32_chain():
     bound = D * 2.0 ** -24 * ((c[idx].double() ** 2).sum(1) + 2 * (z.double() * c[idx].double()).abs().sum(1)) * 2
     assert bool((taken - best <= bound).all())
     assert bool((margin.cpu() >= 0).all()) and torch.equal(hist.cpu(), torch.bincount(idx, minlength=K))
+
+
+def test_rows_that_are_not_finite_do_not_hold_the_others_up():
+    """Rows of NaN have no scores and are not multiplied again; infinite ones are, by their wave alone."""
+    N, D, K = 65536, 256, 256
+    g = torch.Generator().manual_seed(5)
+    z, c = torch.randn((N, D), generator=g).to(DEV), torch.randn((K, D), generator=g).to(DEV)
+    idx, hist = torch.empty(N, dtype=torch.int32, device=DEV), torch.empty(K, dtype=torch.int64, device=DEV)
+    run = lambda: dp.dipaco_route_prefix(z, c, N, D, K, idx, hist, None)
+    finite = median_us(run)
+    want = idx.clone()
+    z[::64, 3] = math.nan
+    times = [median_us(run)]
+    keep = torch.arange(N, device=DEV) % 64 != 0
+    assert torch.equal(idx[keep], want[keep]) and not bool(idx[~keep].any())
+    z[::64, 3] = math.inf
+    times.append(median_us(run))
+    assert torch.equal(idx[keep], want[keep])
+    print(f"route us finite {finite:.0f} NaN {times[0]:.0f} infinite {times[1]:.0f}", flush=True)
+    assert times[0] <= 1.5 * finite and times[1] <= 6 * finite
 
 
 def test_more_points_than_one_launch_of_small_workgroups_holds():
