@@ -462,7 +462,7 @@ bool fit_built(int t, bool bf16_operands, bool a_kc) { return t <= 2 || t == 4 |
 // 25 / 39 / 126 / 477, 384 35 / 53 / 160 / 620 against 34 / 55 / 188 / 726, 512 39 / 57 / 182 / 700 against 42 / 70 / 245 / 948, 2048
 // 132 / 206 / 708 against 150 / 262 / 968; at K = 64 512 tiles are level.  A round of 512 workgroups is two to a compute unit.
 // In 64 x 128 tiles of bf16 parts, one to a compute unit: 250 tiles 21.5 / 65 / 225 us (K = 512 / 2048 / 8192) against 22.5 / 71 - 80 /
-// 252 - 280 on the fp32 instruction, 750 tiles 58 against 55: taken for one round.
+// 252 - 280 on the fp32 instruction, 750 tiles 58 against 55: here taken for one round.
 long shape_tiles(int t, int M, int N, bool bf16_operands) {
   const int bm = t == 3 && !bf16_operands ? 64 : 32 * t, bn = t == 1 ? 64 : 128;
   return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -481,17 +481,48 @@ inline __attribute__((always_inline)) double shape_cost(int t, long tiles, int K
   return 3.0 + (double)rounds * (f + k * K * 1e-3);
 }
 
+// The same for one fp32 product that is not cut over K, close enough (rel. error 5 %) to tell the two ways of multiplying apart where they
+// lie near each other: 1, 2 on the fp32 instruction, 3, 4 in bf16 parts.  Fitted to 3144 products of 16 - 1280 tiles of 128 x 128, K 32 -
+// 8192, of all three layouts.  Up to 128 of K tile 1 is gemm_direct_kernel; its stages are 256 of K, tile 3's 128; two workgroups of 2
+// and 4 share a unit, so that a second round costs less than the first; A.B^T is the slowest layout in parts of 128 x 128.  Tile 4, and
+// 3 in more than one round, have to be ahead by 3 and 7 %: then 5 of the 3144 are more than 3 % behind what the fp32 instruction took with
+// its rule above (with the prices above for all four, 375: 4036 x 512 x 264 14.8 us in tile 2, 18.0 in 3; 2564 x 2056 x 136 23.4, 26.6 in
+// 4; 1476 x 2048 x 896 A.B^T 56.7, 61.8 in 4), and all together take 0.95 of its time.
+double f32_cost(int t, long tiles, int K, bool a_kc, bool b_kc) {
+  const double rounds = (double)((tiles + 255) / 256);
+  auto up = [&](int stage) { return (double)((K + stage - 1) / stage * stage); };
+  if (t == 1) {
+    if (K <= DIRECT_K) return std::max(7.5, 5.5 + rounds * (0.6 + 7.8e-3 * K));
+    return 1.04 * (2.5 + rounds * (3.2 + (!a_kc ? 7.7e-3 : b_kc ? 6.9e-3 : 7.3e-3) * 0.5 * (K + up(256))));
+  }
+  if (t == 2) return std::max(7.7, 2.8 + rounds * (2.7 + 28.8e-3 * K));
+  if (t == 3) return (rounds > 1.0 ? 1.07 : 1.0) * (3.0 + rounds * (4.5 + 24.7e-3 * up(128)) + 2.0 * ((double)tiles / 256.0 - (rounds - 1.0)));
+  const long full = tiles / 512, rest = tiles % 512;
+  const double single = (!a_kc ? 52.2e-3 : b_kc ? 54.5e-3 : 50.5e-3) * K;
+  double c = 4.0 + (double)full * (12.8 + 75.6e-3 * K);
+  if (rest > 256) c += 12.4 + 61.8e-3 * K + (double)(rest - 256) / 256.0 * (0.4 + 13.8e-3 * K);
+  else if (rest) c += 7.5 + single + 2.0 * (double)rest / 256.0;
+  return 1.03 * c;
+}
+
 std::atomic<int> g_forced_fit{0};
-int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc) {
+int pick_fit(int M, int N, int K, int splits, bool bf16_operands, bool a_kc, bool b_kc) {
   if (g_forced_fit) {
     int t = g_forced_fit;
     while (!fit_built(t, bf16_operands, a_kc)) --t;
     return t;
   }
   auto cost = [&](int t) { return shape_cost(t, shape_tiles(t, M, N, bf16_operands) * splits, K, bf16_operands, a_kc); };
+  const bool by_parts = !bf16_operands && splits == 1;   // 3 and 4 against the better of 1 and 2
   int best = 1;
-  for (int t = 2; t <= 5; ++t)
+  for (int t = 2; t <= (by_parts ? 2 : 5); ++t)
     if (fit_built(t, bf16_operands, a_kc) && cost(t) < cost(best)) best = t;
+  if (by_parts) {
+    auto f32 = [&](int t) { return f32_cost(t, shape_tiles(t, M, N, false), K, a_kc, b_kc); };
+    double least = f32(best);
+    for (int t = 3; t <= 4; ++t)
+      if (f32(t) < least) { least = f32(t); best = t; }
+  }
   return best;
 }
 
@@ -502,7 +533,7 @@ long narrow_tiles(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32)
 
 template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_shape(const GemmArgs& a, hipStream_t s) {
   const int splits = std::max(1, a.splits);
-  const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC);
+  const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC, B_KC);
   if constexpr (sizeof(T) == 4) {
     const bool narrow = narrow_tiles(a.M, a.N) * splits <= 256;
     if (t == 1 && direct_takes(a, A_KC, B_KC)) return narrow ? run_direct<A_KC, B_KC, 2>(a, s) : run_direct<A_KC, B_KC, 4>(a, s);
@@ -530,8 +561,8 @@ template <typename T> bool pair_fits(const GemmArgs& dw, const GemmArgs& dx) {
   using F = Fit<T, T, true, true, 2, 4, 1, 1, 8, 3>;
   constexpr uint64_t most = 1ull << 32;
   auto tiles = [](const GemmArgs& a) { return (long)((a.M + 31) / 32) * ((a.N + 63) / 64); };
-  return dw.splits <= 1 && dx.splits <= 1 && pick_fit(dw.M, dw.N, dw.K, 1, sizeof(T) == 2, false) == 1 &&
-         pick_fit(dx.M, dx.N, dx.K, 1, sizeof(T) == 2, true) == 1 && tiles(dw) + tiles(dx) <= 256 &&
+  return dw.splits <= 1 && dx.splits <= 1 && pick_fit(dw.M, dw.N, dw.K, 1, sizeof(T) == 2, false, false) == 1 &&
+         pick_fit(dx.M, dx.N, dx.K, 1, sizeof(T) == 2, true, true) == 1 && tiles(dw) + tiles(dx) <= 256 &&
          fit_span(false, F::BM, F::BK, dw.M, dw.K, dw.lda, sizeof(T)) < most && fit_span(false, F::BN, F::BK, dw.N, dw.K, dw.ldb, sizeof(T)) < most &&
          fit_span(true, F::BM, F::BK, dx.M, dx.K, dx.lda, sizeof(T)) < most && fit_span(true, F::BN, F::BK, dx.N, dx.K, dx.ldb, sizeof(T)) < most;
 }

@@ -444,6 +444,24 @@ def test_fp32_products_from_bf16_parts_keep_the_bits_of_small_numbers(ta, tb, M,
         dp.dipaco_k_set_gemm_tile(0)
 
 
+@pytest.mark.parametrize("M,N,K,ta,tb,tile", [
+    (4036, 512, 264, False, False, 2), (4036, 512, 264, False, True, 2), (1920, 512, 264, True, False, 2), (768, 2048, 520, False, True, 2),
+    (2564, 2056, 136, False, False, 2), (1476, 2048, 896, False, True, 2), (9540, 512, 136, True, False, 2), (5756, 1024, 264, False, True, 2),
+    (4000, 512, 2048, False, False, 3), (768, 2048, 1024, True, False, 3), (4000, 8192, 512, False, True, 4), (4096, 2048, 1024, True, False, 4)])
+def test_fp32_products_take_parts_only_where_they_are_ahead(M, N, K, ta, tb, tile):
+    """64 x 128 tiles of the fp32 instruction (2) against 64 x 128 (3) and 128 x 128 (4) in bf16 parts, told by their bits: sizes where one of
+    them measured at least 5 % ahead of the others."""
+    A, B = torch.randn((K, M) if ta else (M, K), device=DEV), torch.randn((N, K) if tb else (K, N), device=DEV)
+    C = {t: torch.empty((M, N), device=DEV) for t in (0, 2, 3, 4)}
+    try:
+        for t in C:
+            dp.dipaco_k_set_gemm_tile(t)
+            dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C[t])
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
+    assert [t for t in (2, 3, 4) if torch.equal(C[0], C[t])] == [tile]
+
+
 @pytest.mark.parametrize("tile", [3, 4])
 def test_fp32_products_of_values_that_are_not_finite_take_no_second_walk_per_sum(tile):
     """NaN operands: their sums are NaN already.  Numbers below 2^-110 that no sum depends on: they are.  Infinities: the tiles they reach
