@@ -143,17 +143,19 @@ static bool want_dlds(const GemmArgs& a) {
   return (long)((a.M + 255) / 256) * ((a.N + 255) / 256) >= 160;
 }
 
-// Rows of a direct-to-LDS product that its whole rounds of 256 workgroups hold, when the rows left over cost less in tiles fitted to
-// them than as the last, mostly empty round: 5700 x 3584 x 896 is 322 tiles of 256 x 256, two rounds, 53 us (77 with GELU and its derivative); the first 4352 rows
-// (238 tiles) and then 1348 rows in 252 tiles of 160 x 128 take 45 (59); 20000 x 896 x 3584 140 -> 116, 5000 x 3584 x 3584 159 -> 113.  Else, and where column sums are wanted (their partial rows are
-// numbered by one launch's tiles), all of them.
+// Rows of a direct-to-LDS product that its whole rounds of 256 workgroups hold, when the rows left over cost clearly less in tiles fitted
+// to them than as the last, mostly empty round: 5700 x 3584 x 896 is 322 tiles of 256 x 256, two rounds, 55 us (70 with GELU and its
+// derivative); the first 4608 rows (252 tiles) and then 1092 rows in 196 tiles of 160 x 128 take 49 (58); 20000 x 896 x 3584 137 -> 116,
+// 5000 x 3584 x 3584 156 -> 110, 12000 x 3584 x 3584 (modelled 77 against 90) 246 -> 242.  The second launch has to be modelled a tenth below
+// the round: at 118 against 123 5000 x 5000 x 4992 is level to 5 % slower (233 -> 244 with GELU), at 28.5 against 28.6 32768 x 2688 x 896 147
+// -> 151.  Else, and where column sums are wanted (their partial rows are numbered by one launch's tiles), all of them.
 static int dlds_rows(const GemmArgs& a) {
   const long tn = (a.N + 255) / 256, tiles = (a.M + 255) / 256 * tn, rounds = (tiles + 255) / 256;
   if (a.out_f32 || a.colsum || g_forced_kernel || rounds < 2) return a.M;
   const long rows = (rounds - 1) * 256 / tn * 256;
   if (rows < 256 || rows >= a.M) return a.M;
   const double round = 8.0 + 0.023 * a.K;
-  return gemm_fit_cost(gemm_fit_tiles((int)(a.M - rows), a.N, true, true), a.K, 1) + 4.0 < round ? (int)rows : a.M;
+  return gemm_fit_cost(gemm_fit_tiles((int)(a.M - rows), a.N, true, true), a.K, 1) + 4.0 < 0.9 * round ? (int)rows : a.M;
 }
 
 template <typename T> static dipaco_status check_gemm(const GemmArgs& a) {

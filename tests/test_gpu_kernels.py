@@ -377,6 +377,20 @@ def test_bf16_products_whose_last_round_is_taken_in_fitted_tiles(M, N, K):
     test_gemm_input_gradient_layout(dp.BF16, M, N, K, 0)
 
 
+@pytest.mark.parametrize("M,N,K,split", [(5700, 3584, 896, True), (5000, 3584, 3584, True), (5000, 5000, 4992, False), (32768, 2688, 896, False)])
+def test_last_round_is_taken_in_fitted_tiles_only_where_that_is_ahead(M, N, K, split):
+    """Told by the bits: forced, the direct-to-LDS kernel takes all rows."""
+    A, B = torch.randn((M, K), device=DEV).to(torch.bfloat16), torch.randn((K, N), device=DEV).to(torch.bfloat16)
+    C = {t: torch.empty((M, N), dtype=torch.bfloat16, device=DEV) for t in (0, 5)}
+    try:
+        for t in C:
+            dp.dipaco_k_set_gemm_tile(t)
+            dp.dipaco_k_gemm(dp.BF16, False, False, False, M, N, K, A, B, C[t])
+    finally:
+        dp.dipaco_k_set_gemm_tile(0)
+    assert torch.equal(C[0], C[5]) != split
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
 @pytest.mark.parametrize("tile", [3, 4])
 @pytest.mark.parametrize("M,N,K", [(128, 128, 32), (132, 136, 36), (256, 264, 500), (4, 8, 4), (260, 120, 2052)])
