@@ -267,8 +267,8 @@ static FeaturePlan make_feature_plan(const dipaco_ctx* c, int B, int S, bool wit
   p.planes = pos;
   size_t plane_floats = std::max(gemm_raw_plane_floats(rows, (int)d, (int)A, es == 2), gemm_raw_plane_floats(rows, (int)d, (int)F, es == 2));
   if (es == 2) {
-    p.attn_planes = attn_out_planes(B, S, a.n_heads, a.d_head);
-    plane_floats = std::max(plane_floats, (size_t)attn_out_planes(1, 1, a.n_heads, a.d_head) * std::min(rows, SMALL_FORWARD_ROWS) * d);
+    p.attn_planes = attn_out_planes(B, S, a.n_heads, a.d_head, a.d_model);
+    plane_floats = std::max(plane_floats, (size_t)attn_out_most_planes(a.n_heads, a.d_head) * std::min(rows, SMALL_FORWARD_ROWS) * d);
   }
   take(plane_floats * 4);
   if (p.planes <= DIPACO_STATIC_SCRATCH_BYTES && pos > DIPACO_STATIC_SCRATCH_BYTES) {

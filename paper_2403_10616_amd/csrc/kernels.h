@@ -216,7 +216,8 @@ constexpr int SMALL_FORWARD_ROWS = 256;
 bool small_product_takes(int rows, int N, int K);
 dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, hipStream_t s);
 // attention and output projection, without bias and residual: the planes [n][B S, d] of launch_sum_layernorm.  0: does not take them
-int attn_out_planes(int B, int S, int H, int d_head);
+int attn_out_planes(int B, int S, int H, int d_head, int d);
+int attn_out_most_planes(int H, int d_head);   // of any batch
 dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, hipStream_t s);
 // out[b, :] (fp32) = mean over positions of x[b*S + p, :]
 template <typename T> dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipStream_t s);

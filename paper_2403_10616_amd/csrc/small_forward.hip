@@ -230,9 +230,17 @@ __global__ void __launch_bounds__(AO_WAVES * WAVE) attn_out_kernel(const bf16* _
 bool small_product_takes(int rows, int N, int K) {
   return rows <= SMALL_FORWARD_ROWS && K >= 256 && (long)((N + RP_COLS - 1) / RP_COLS) * ((rows + SF_ROWS - 1) / SF_ROWS) <= 192;
 }
-int attn_out_planes(int B, int S, int H, int d_head) {
+// Every document's workgroups read W_o again, so it is their number that the rule bounds, however short the documents are.  Features of
+// B x S tokens with two launches -> this one, us: d_model 896, 14 heads (98 workgroups a document): 8 x 32 271 -> 254, 16 x 16 266 -> 265, 32 x
+// 8 263 -> 294, 256 x 1 275 -> 683; 512, 8 heads (32): 32 x 8 136 -> 135, 64 x 4 135 -> 148; 256, 4 heads (8): 128 x 2 122 -> 107, 256 x 1 121 -> 119.
+constexpr long AO_MOST = 1024;
+int attn_out_most_planes(int H, int d_head) {
   const int planes = (H + AO_HEADS - 1) / AO_HEADS;
-  return d_head == AO_DH && S <= SF_ROWS && (long)B * S <= SMALL_FORWARD_ROWS && planes >= 2 && planes <= 8 ? planes : 0;
+  return d_head == AO_DH && planes >= 2 && planes <= 8 ? planes : 0;
+}
+int attn_out_planes(int B, int S, int H, int d_head, int d) {
+  const int planes = attn_out_most_planes(H, d_head);
+  return S <= SF_ROWS && (long)B * S <= SMALL_FORWARD_ROWS && (long)((d + 63) / 64) * planes * B <= AO_MOST ? planes : 0;
 }
 
 dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, hipStream_t s) {

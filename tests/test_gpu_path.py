@@ -14,7 +14,7 @@ import torch
 import dipaco_inputs as gen
 import paper_2403_10616_amd as dp
 from oracle import dipaco_oracle as orc
-from gpu_util import DEV, PathState, dev, host, make_arch, per_tensor_maxabs, per_tensor_rel, rel_l2
+from gpu_util import DEV, PathState, dev, host, make_arch, median_us, per_tensor_maxabs, per_tensor_rel, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -287,6 +287,21 @@ SHAPES.update({f"heads{h}": dict(layers_per_level=(1, 1), d_model=d, n_heads=h, 
 def test_prefix_features_of_a_few_rows_match_oracle(name, B, S):
     """Attention and output projection of two heads a workgroup: odd numbers of heads, ragged widths, one position to a whole block."""
     test_prefix_features_match_oracle(name, B, S, dp.BF16, 2e-2)
+
+
+def test_features_of_many_short_prefixes_are_not_slower_than_of_long_ones():
+    """256 tokens as 8 x 32 and as shorter documents, down to one token each: attention shrinks, the products are the same."""
+    cfg = dict(layers_per_level=(3, 3), d_model=896, n_heads=14, d_head=64, d_mlp=3584, vocab=1024, max_seq=64)
+    a, ctx = make_arch(cfg, dp.BF16)
+    theta = dev(gen.random_params(orc.param_count(a), seed=3, scale=0.03).astype(np.float32)).to(torch.bfloat16)
+    times = {}
+    for B, S in ((8, 32), (32, 8), (64, 4), (256, 1)):
+        tok = torch.randint(0, cfg["vocab"], (B, S), device=DEV, dtype=torch.int32)
+        out = torch.empty((B, cfg["d_model"]), device=DEV)
+        ws = torch.empty(dp.dipaco_features_workspace_bytes(ctx, B, S), dtype=torch.uint8, device=DEV)
+        times[B, S] = median_us(lambda: dp.dipaco_path_prefix_features(ctx, None, theta, tok, B, S, out, ws))
+    print("features us", times, flush=True)
+    assert max(times.values()) <= 1.3 * times[8, 32]
 
 
 @pytest.mark.parametrize("name,B,S,compute,mask", [("ragged", 3, 50, dp.F32, 5), ("wide", 4, 160, dp.F32, 32),
