@@ -6,8 +6,9 @@
 // route_kernel: every number taken apart into three bf16 parts (split_tile.h).  A workgroup of four waves owns 128 points and walks
 // the centroids in tiles of 128; ||c_k||^2 is accumulated by the threads that stage the centroid tile, from the very values they load.
 // Two workgroups share a compute unit: one splits, stores and folds scores under the other's MFMAs, which go first (wave priority).
-// Bound by the MFMAs and the power they draw (six part products: 2^20 x 768 x 256 is 2.5 PFLOP of them), as gemm_split.hip.  On the
-// fp32 matrix instruction 256 x 256 tiles took 3230 us there, now 2460; 300000 x 768 x 1000 3970 -> 2870, 1000000 x 64 x 256 488 -> 349.
+// Bound by the MFMAs and the power they draw (six part products: 2^20 x 768 x 256 is 2.5 TFLOP of them), as gemm_split.hip.  On the
+// fp32 matrix instruction 256 x 256 tiles took 3230 us there, now 2470 (2430 without the norms and third scores that near-ties need);
+// 300000 x 768 x 1000 3970 -> 2880, 1000000 x 64 x 256 488 -> 356 (344).
 // Error of the margins against 64 bits 3.6e-7 (1.9e-6 before) at D = 896, 2.2e-7 (6.2e-7) at 64.
 #include <algorithm>
 #include <type_traits>
@@ -65,51 +66,74 @@ template <bool TOP2> __device__ __forceinline__ Best best_merge(const Best& a, c
   return o;
 }
 
-// Near-ties of route_kernel.  A chain of fp32 multiply-adds errs by a few 2^-24 of its sums, the part products by less: what the two
-// order differently lies closer together than NEAR_TIE of the scores, a point in 10^4, and is decided by the chain in the order of
-// v_mfma_f32_32x32x2_f32 over chunks of four K (0, 4, 1, 5, 2, 6, 3, 7 of every eight), so that assignments do not turn with the
-// unit that multiplies.  A wave takes 32 points, lanes 0 .. 31 their best candidates, lanes 32 .. 63 the second ones.
-// Points whose norm, or a centroid's, is so large that part products may overflow (infinities among them) are taken again by their wave
-// against all centroids (again_in_fp32).
-constexpr float LARGE_NORM2 = 8.507059e37f;   // 2^126
-constexpr float NEAR_TIE = 1.0f / 131072.0f;
-__device__ __forceinline__ bool near_tie(const Best& b) {
-  return b.i2 != NO_INDEX && b.s2 - b.s1 < NEAR_TIE * (fabsf(b.s1) + fabsf(b.s2));
+// The third best score beside an entry, before (s, k) is pushed; and of the union of two entries.  A NaN score may put the second best
+// in its place, which makes a near-tie of a point that is none
+__device__ __forceinline__ void third_push(float& s3, const Best& b, float s) { s3 = __builtin_amdgcn_fmed3f(s, b.s2, s3); }
+__device__ __forceinline__ float third_merge(const Best& a, float a3, const Best& b, float b3) {
+  return fminf(fminf(a3, b3), fminf(fmaxf(a.s1, b.s2), fmaxf(a.s2, b.s1)));
 }
+
+// Near-ties of route_kernel.  An assignment must not turn with the unit that multiplies, so what the part products and the fp32 matrix
+// instruction may order differently is decided by the latter's arithmetic.  A chain of D multiply-adds errs by up to 2^-24 of each partial
+// sum, which |z| |c| bounds: 0.42 2^-24 sqrt(D) |z| |c| in the root mean square if every one were that large (evenly growing sums: 0.58 of
+// it), 2^1/2 times that for the difference of two; CHAIN_ERROR is four times as much.  Numbers below 2^-110 lack bits of their third part
+// (split_tile.h): 2^-134 each, held to 2^-24 of the gap.  Two candidates closer together than that (at |z| = 8, |c| = 1, D = 768 a point in
+// 1500) are taken again by decide_near_tie; where a third one is as close, or a norm is so large that part products may
+// overflow (infinities among them), the workgroup takes the wave's points again against all centroids (again_in_fp32).
+constexpr float CHAIN_ERROR = 2.5f / 16777216.0f;
+constexpr float LARGE_NORM2 = 8.507059e37f;   // 2^126
+__device__ __forceinline__ float near_tie_width(float z2, float c2, int D, float dot_mul, float s1, float s2) {
+  const float root = __builtin_amdgcn_sqrtf((float)D);
+  const float z1 = __builtin_amdgcn_sqrtf(z2) + root * 0x1p-60f, c1 = __builtin_amdgcn_sqrtf(c2) + root * 0x1p-60f;   // squares may vanish below
+  const float rounding = z2 > 0.f ? 1.2e-7f * (fabsf(s1) + fabsf(s2)) : 0.f;   // of the scores, where their dot products differ
+  return dot_mul * root * (CHAIN_ERROR * z1 * c1 + 7.7e-34f * (z1 + c1)) + rounding;
+}
+// |c|^2 is the sum of these over a row, eight sums of every eighth piece added as a tree; written out, since a compiler that contracts
+// the plain expression may choose another of its products to round
+__device__ __forceinline__ float piece_squares(float x, float y, float z, float w) {
+  return __builtin_fmaf(w, w, __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x)));
+}
+// The two candidates' scores by a chain of multiply-adds in the order of v_mfma_f32_32x32x2_f32 over chunks of four K (0, 4, 1, 5, 2, 6, 3,
+// 7 of every eight).  Lanes 0 .. 31 of a wave take their points' best candidates, lanes 32 .. 63 the second ones.
 __device__ __forceinline__ void decide_near_tie(Best& b, bool near, const float* __restrict__ z_row, const float* __restrict__ c,
                                                 const float* __restrict__ lin_bias, int D, float dot_mul, int lane) {
-  const int k = near ? (lane < 32 ? b.i1 : b.i2) : 0;
-  const float* const c_row = c + (long)k * D;
-  float dot = 0.f, n[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float4 x[8], y[8];
-  auto load = [&](int k0) {
+  constexpr int DEEP = 16;   // pieces of four K in flight: bound by their latency (D = 896: 11 us; 22 with eight, reloaded together)
+  float s = 0.f;
+  if (near) {   // a lane or two as a rule: the others' rows are not read
+    const int k = lane < 32 ? b.i1 : b.i2;
+    const float* const c_row = c + (long)k * D;
+    float dot = 0.f, n[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float4 x[DEEP];
+    uint4 raw[DEEP];
+    auto load = [&](int q, int k) {
+      const int at = min(k, D - 4);
+      x[q] = *reinterpret_cast<const float4*>(z_row + at);
+      raw[q] = *reinterpret_cast<const uint4*>(c_row + at);
+    };
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {   // K beyond the row counts as zero
-      const bool in = k0 + 4 * q < D;
-      const int at = min(k0 + 4 * q, D - 4);
-      x[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(z_row + at), in));
-      y[q] = __builtin_bit_cast(float4, keep_or_zero(*reinterpret_cast<const uint4*>(c_row + at), in));
-    }
-  };
-  load(0);
+    for (int q = 0; q < DEEP; ++q) load(q, 4 * q);
 #pragma unroll 1
-  for (int k0 = 0; k0 < D; k0 += RBK) {
-    float4 u[8], v[8];
+    for (int k0 = 0; k0 < D; k0 += 4 * DEEP) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) { u[q] = x[q]; v[q] = y[q]; }
-    if (k0 + RBK < D) load(k0 + RBK);
+      for (int q = 0; q < DEEP; q += 2) {
+        float4 u[2], v[2];
 #pragma unroll
-    for (int q = 0; q < 8; q += 2) {
-      dot = __builtin_fmaf(u[q].x, v[q].x, dot); dot = __builtin_fmaf(u[q + 1].x, v[q + 1].x, dot);
-      dot = __builtin_fmaf(u[q].y, v[q].y, dot); dot = __builtin_fmaf(u[q + 1].y, v[q + 1].y, dot);
-      dot = __builtin_fmaf(u[q].z, v[q].z, dot); dot = __builtin_fmaf(u[q + 1].z, v[q + 1].z, dot);
-      dot = __builtin_fmaf(u[q].w, v[q].w, dot); dot = __builtin_fmaf(u[q + 1].w, v[q + 1].w, dot);
+        for (int p = 0; p < 2; ++p) {   // K beyond the row counts as zero (points that come here are finite)
+          u[p] = x[q + p];
+          v[p] = __builtin_bit_cast(float4, keep_or_zero(raw[q + p], k0 + 4 * (q + p) < D));
+          load(q + p, k0 + 4 * (DEEP + q + p));
+          n[(q + p) % 8] += piece_squares(v[p].x, v[p].y, v[p].z, v[p].w);
+        }
+        dot = __builtin_fmaf(u[0].x, v[0].x, dot); dot = __builtin_fmaf(u[1].x, v[1].x, dot);
+        dot = __builtin_fmaf(u[0].y, v[0].y, dot); dot = __builtin_fmaf(u[1].y, v[1].y, dot);
+        dot = __builtin_fmaf(u[0].z, v[0].z, dot); dot = __builtin_fmaf(u[1].z, v[1].z, dot);
+        dot = __builtin_fmaf(u[0].w, v[0].w, dot); dot = __builtin_fmaf(u[1].w, v[1].w, dot);
+      }
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) n[q] += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
+    const float cn = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
+    s = __builtin_fmaf(-dot_mul, dot, lin_bias ? -lin_bias[k] : cn);
   }
-  const float cn = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
-  const float s = __builtin_fmaf(-dot_mul, dot, lin_bias ? -lin_bias[k] : cn), other = __shfl_xor(s, 32, WAVE);
+  const float other = __shfl_xor(s, 32, WAVE);   // both halves of the wave hold the same points
   if (!near) return;
   const float s1 = lane < 32 ? s : other, s2 = lane < 32 ? other : s;
   const int k1 = b.i1, k2 = b.i2;
@@ -118,14 +142,15 @@ __device__ __forceinline__ void decide_near_tie(Best& b, bool near, const float*
   b.s2 = swap ? s1 : s2; b.i2 = swap ? k1 : k2;
 }
 
-// A wave's 32 points (lane l: point l % 32, z_row) against all centroids on the fp32 matrix instruction, K in the order above
+// 32 points (lane l: point l % 32, z_row) against the centroids of tiles `first`, first + `step` .. of 32 on the fp32 matrix instruction, K in
+// the order above
 __device__ __forceinline__ Best again_in_fp32(const float* __restrict__ z_row, const float* __restrict__ c, const float* __restrict__ lin_bias,
-                                              int D, int K, float dot_mul, int lane) {
+                                              int D, int K, int first, int step, float dot_mul, int lane) {
   const int r = lane & 31, h = lane >> 5;
   Best b;
   b.s1 = INFINITY; b.i1 = NO_INDEX; b.s2 = INFINITY; b.i2 = NO_INDEX;
 #pragma unroll 1
-  for (int n0 = 0; n0 < K; n0 += 32) {
+  for (int n0 = 32 * first; n0 < K; n0 += 32 * step) {
     const float* const c_row = c + (long)min(n0 + r, K - 1) * D;
     f32x16 acc;
 #pragma unroll
@@ -153,7 +178,7 @@ __device__ __forceinline__ Best again_in_fp32(const float* __restrict__ z_row, c
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].y, u[q].y, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].z, u[q].z, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[q].w, u[q].w, acc, 0, 0, 0);
-        n[q] += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
+        n[q] += piece_squares(v[q].x, v[q].y, v[q].z, v[q].w);
       }
     }
 #pragma unroll
@@ -181,6 +206,7 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ __attribute__((aligned(16))) float cnorm[RB];
   __shared__ unsigned int lhist[R_MAX_K];
+  __shared__ float third[4][256];   // a thread's own third best scores: registers are full
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kg = lane >> 4;
@@ -224,6 +250,8 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   Best run[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) { run[j].s1 = INFINITY; run[j].i1 = NO_INDEX; run[j].s2 = INFINITY; run[j].i2 = NO_INDEX; }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) third[j][tid] = INFINITY;
   float zn[4] = {0.f, 0.f, 0.f, 0.f};   // |z|^2 of the pieces the lane stages, of their first parts, times the tiles of centroids
   float c2 = 0.f;   // the largest |c|^2 the lane has seen
 
@@ -245,7 +273,7 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        nrm[q] += sc.v[q][0] * sc.v[q][0] + sc.v[q][1] * sc.v[q][1] + sc.v[q][2] * sc.v[q][2] + sc.v[q][3] * sc.v[q][3];
+        nrm[q] += piece_squares(sc.v[q][0], sc.v[q][1], sc.v[q][2], sc.v[q][3]);
         sc.template store<R_PLANE>(smem + store_at[q], q);
       }
 #pragma unroll
@@ -279,6 +307,9 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
     }
     __syncthreads();
     const int k0 = 64 * wc + 4 * kg;   // the lane's rows of block i: k0 + 16 i + e
+    float s3[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s3[j] = third[j][tid];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float4 cn4 = *reinterpret_cast<const float4*>(cnorm + k0 + 16 * i);
@@ -288,34 +319,45 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float s = __builtin_fmaf(-dot_mul, acc[i][j][e], cn[e]);
+          third_push(s3[j], run[j], s);
           best_push_ascending<true>(run[j], s, n0 + k0 + 16 * i + e);
         }
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) third[j][tid] = s3[j];
   }
 
   // the four lane groups of a point, then the two waves that share its points, through LDS (the planes are free: every wave has passed
   // the barriers that end the last stage)
   float* const red_s1 = reinterpret_cast<float*>(smem);
   float* const red_s2 = red_s1 + 2 * RB;
-  int* const red_i1 = reinterpret_cast<int*>(red_s2 + 2 * RB);
+  float* const red_s3 = red_s2 + 2 * RB;
+  int* const red_i1 = reinterpret_cast<int*>(red_s3 + 2 * RB);
   int* const red_i2 = red_i1 + 2 * RB;
   float* const red_z2 = reinterpret_cast<float*>(red_i2 + 2 * RB);   // [4][256]
   float* const red_c2 = red_z2 + 4 * 256;
-  static_assert((16 * RB + 4) * sizeof(float) <= R_LDS, "the merge arrays fit in the planes");
+  int* const red_again = reinterpret_cast<int*>(red_c2 + 4);
+  float* const again_s1 = reinterpret_cast<float*>(red_again + 4);
+  float* const again_s2 = again_s1 + RB;
+  int* const again_i1 = reinterpret_cast<int*>(again_s2 + RB);
+  int* const again_i2 = again_i1 + RB;
+  static_assert((22 * RB + 8) * sizeof(float) <= R_LDS, "the merge arrays fit in the planes");
 #pragma unroll
   for (int q = 0; q < 4; ++q) red_z2[256 * q + tid] = zn[q];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
+    float s3 = third[j][tid];
 #pragma unroll
     for (int m = 16; m < WAVE; m <<= 1) {
       Best o;
       o.s1 = __shfl_xor(run[j].s1, m, WAVE); o.i1 = __shfl_xor(run[j].i1, m, WAVE); o.s2 = __shfl_xor(run[j].s2, m, WAVE);
       o.i2 = __shfl_xor(run[j].i2, m, WAVE);
+      s3 = third_merge(run[j], s3, o, __shfl_xor(s3, m, WAVE));
       run[j] = best_merge<true>(run[j], o);
     }
     if (kg == 0) {
       const int at = wc * RB + 64 * wp + 16 * j + r;
-      red_s1[at] = run[j].s1; red_i1[at] = run[j].i1; red_s2[at] = run[j].s2; red_i2[at] = run[j].i2;
+      red_s1[at] = run[j].s1; red_i1[at] = run[j].i1; red_s2[at] = run[j].s2; red_i2[at] = run[j].i2; red_s3[at] = s3;
     }
   }
   c2 = wave_max(c2);
@@ -325,6 +367,7 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   Best b, o;
   b.s1 = red_s1[point]; b.i1 = red_i1[point]; b.s2 = red_s2[point]; b.i2 = red_i2[point];
   o.s1 = red_s1[RB + point]; o.i1 = red_i1[RB + point]; o.s2 = red_s2[RB + point]; o.i2 = red_i2[RB + point];
+  const float s3 = third_merge(b, red_s3[point], o, red_s3[RB + point]);
   b = best_merge<true>(b, o);
   c2 = fmaxf(fmaxf(red_c2[0], red_c2[1]), fmaxf(red_c2[2], red_c2[3]));
   float z2 = 0.f;   // point p of the wave: the eight lanes 8 (p % 8) + t staged its pieces as their row p / 8
@@ -332,14 +375,35 @@ __global__ void __launch_bounds__(256, 2) route_kernel(const float* __restrict__
   for (int t = 0; t < 8; ++t) z2 += red_z2[256 * ((lane & 31) >> 3) + 64 * wave + 8 * (lane & 7) + t];
   z2 *= __builtin_amdgcn_rcpf((float)((K + RB - 1) / RB));
   const bool on = point < rows_left;
+  const float width = near_tie_width(z2, c2, D, dot_mul, b.s1, b.s2);
   // what is not finite compares false: rows of NaN have no scores, those of infinities are told by their norm
-  const bool again = on && fmaxf(z2, c2) >= LARGE_NORM2;
-  const bool near = on && !again && near_tie(b);
+  const bool again = on && (fmaxf(z2, c2) >= LARGE_NORM2 || s3 - (TOP2 ? b.s2 : b.s1) < width);
+  const bool near = on && !again && b.i2 != NO_INDEX && b.s2 - b.s1 < width;
   const float* const z_row = zb + (long)min(point, rows_left - 1) * ldz;
   if (__any(near)) decide_near_tie(b, near, z_row, c, lin_bias, D, dot_mul, lane);
-  if (__any(again)) {
-    const Best f = again_in_fp32(z_row, c, lin_bias, D, K, dot_mul, lane);
-    if (again) b = f;
+  const bool wave_again = __any(again);
+  if (lane == 0) red_again[wave] = wave_again ? 1 : 0;
+  __syncthreads();
+  for (int w = 0; w < 4; ++w) {
+    if (!red_again[w]) continue;   // uniform
+    // the points of wave w, every wave a quarter of the centroids (two nearest of 200000 x 896 x 200 849 us with wave w alone, 686 so)
+    const Best part = again_in_fp32(zb + (long)min(32 * w + (lane & 31), rows_left - 1) * ldz, c, lin_bias, D, K, wave, 4, dot_mul, lane);
+    if (lane < 32) {
+      const int at = 32 * wave + lane;
+      again_s1[at] = part.s1; again_i1[at] = part.i1; again_s2[at] = part.s2; again_i2[at] = part.i2;
+    }
+    __syncthreads();
+    if (again && wave == w) {
+      b.s1 = b.s2 = INFINITY; b.i1 = b.i2 = NO_INDEX;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int at = 32 * q + (lane & 31);
+        Best o;
+        o.s1 = again_s1[at]; o.i1 = again_i1[at]; o.s2 = again_s2[at]; o.i2 = again_i2[at];
+        b = best_merge<true>(b, o);
+      }
+    }
+    __syncthreads();   // the entries are read: the next points' may be written
   }
   if (lane < 32 && point < rows_left) {
     // A row none of whose scores compares below +inf (NaN or infinite features: a diverged path) never entered an

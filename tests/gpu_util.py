@@ -30,6 +30,17 @@ def rel_l2(a, b):
     return float(np.linalg.norm(a - b) / nb) if nb > 0 else float(np.linalg.norm(a))
 
 
+def fma32(a, b, c):
+    """float32(a * b + c), rounded once: the product of two float32 is exact in 64 bits, the sum is rounded to odd there."""
+    p = a.astype(np.float64) * b.astype(np.float64)
+    c = c.astype(np.float64)
+    s = p + c
+    back = s - p
+    err = (p - (s - back)) + (c - back)
+    even = (s.view(np.int64) & 1) == 0
+    return np.where((err != 0) & even, np.nextafter(s, np.where(err > 0, np.inf, -np.inf)), s).astype(np.float32)
+
+
 def median_us(f, n=5, reps=7):
     """Median time of a call among others, in microseconds."""
     f()
