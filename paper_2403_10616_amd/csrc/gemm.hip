@@ -1,7 +1,8 @@
-// The GEMM entry: argument checks, the choice between the two matrix-core kernels and their K splits, and the sum of
+// The GEMM entry: argument checks, the choice between the matrix-core kernels and their K splits, and the sum of
 // split-K partial planes.
-//   gemm_dlds.hip  bf16, 256 x 256 tiles (and oblong ones), uneven split-K: products that fill the chip with such tiles
-//   gemm_fit.hip   every other product: fp32, ragged contractions, and everything smaller, with tiles fitted to the grid
+//   gemm_dlds.hip   bf16, 256 x 256 tiles (and oblong ones), uneven split-K: products that fill the chip with such tiles
+//   gemm_fit.hip    every other product: ragged contractions, everything smaller, and fp32, with tiles fitted to the grid
+//   gemm_split.hip  of those, the fp32 products that are ahead in three bf16 parts (gemm_fit.hip chooses)
 #include <algorithm>
 #include <atomic>
 #include <type_traits>

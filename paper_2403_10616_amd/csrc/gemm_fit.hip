@@ -1,6 +1,6 @@
-// Matrix-core GEMM for every product that does not fill the chip with 256 x 256 tiles, and for every fp32 product and
-// ragged contraction: bf16 (v_mfma_f32_16x16x32_bf16) or fp32 (v_mfma_f32_16x16x4_f32), all three operand layouts of the
-// path step, any M, N, K that launch_gemm accepts.
+// Matrix-core GEMM for every product that does not fill the chip with 256 x 256 tiles, and for ragged contractions and the fp32
+// products that are not ahead in bf16 parts (gemm_split.hip): bf16 (v_mfma_f32_16x16x32_bf16) or fp32 (v_mfma_f32_16x16x4_f32),
+// all three operand layouts of the path step, any M, N, K that launch_gemm accepts.
 //
 // What bounds these products is the number of compute units at work and the latency of a K loop, not the matrix cores.
 // So the tile is fitted to the grid: its height BM is chosen among 64 .. 160 rows (BN = 128) so that the tiles make whole

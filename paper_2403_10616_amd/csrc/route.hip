@@ -78,7 +78,7 @@ __device__ __forceinline__ float third_merge(const Best& a, float a3, const Best
 // sum, which |z| |c| bounds: 0.42 2^-24 sqrt(D) |z| |c| in the root mean square if every one were that large (evenly growing sums: 0.58 of
 // it), 2^1/2 times that for the difference of two; CHAIN_ERROR is four times as much.  Numbers below 2^-110 lack bits of their third part
 // (split_tile.h): 2^-134 each, held to 2^-24 of the gap.  Two candidates closer together than that (at |z| = 8, |c| = 1, D = 768 a point in
-// 1500) are taken again by decide_near_tie; where a third one is as close, or a norm is so large that part products may
+// 7000) are taken again by decide_near_tie; where a third one is as close, or a norm is so large that part products may
 // overflow (infinities among them), the workgroup takes the wave's points again against all centroids (again_in_fp32).
 constexpr float CHAIN_ERROR = 2.5f / 16777216.0f;
 constexpr float LARGE_NORM2 = 8.507059e37f;   // 2^126

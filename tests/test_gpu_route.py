@@ -442,7 +442,7 @@ def test_tiles_of_bf16_parts_route_as_fp64_does(N, D, K, bias):
 
 
 def test_tiles_of_bf16_parts_with_values_that_are_not_finite():
-    """An infinity has no bf16 parts that multiply as it does: such tiles are taken again in fp32.  Expected: the smallest score that is
+    """An infinity has no bf16 parts that multiply as it does: points that meet one are taken again in fp32.  Expected: the smallest score that is
     not NaN, the lowest index among equals; rows without one go to centroid 0 with a NaN margin."""
     N, D, K = 45000, 68, 130
     g = torch.Generator().manual_seed(5)
