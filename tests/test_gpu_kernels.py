@@ -454,6 +454,15 @@ def test_fp32_products_from_bf16_parts_keep_the_bits_of_small_numbers(ta, tb, M,
         B.mul_(2.0 ** 100)
         run()
         assert rel_l2(host(C) * 2.0 ** 20, ref) <= bound
+        if ta:                                   # cut over K, ragged at the end
+            C.zero_()
+            dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C, splits=3, partial=torch.empty((3, M, N), device=DEV))
+            assert rel_l2(host(C) * 2.0 ** 20, ref) <= bound
+            A[K - 1, 5] = math.inf
+            dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C, splits=3, partial=torch.empty((3, M, N), device=DEV))
+            got = host(C)
+            assert np.array_equal(got[5], np.where(Br[K - 1] > 0, np.inf, -np.inf).astype(np.float32))
+            assert rel_l2(np.delete(got, 5, 0) * 2.0 ** 20, np.delete(ref, 5, 0)) <= bound
     finally:
         dp.dipaco_k_set_gemm_tile(0)
 

@@ -542,6 +542,31 @@ def test_near_ties_of_bf16_parts_are_decided_by_the_fp32_instruction(form, D):
     assert np.array_equal(host(hist), np.bincount(got.ravel(), minlength=K))
 
 
+@pytest.mark.parametrize("linear", [False, True])
+def test_centroids_of_small_numbers_keep_their_bits(linear):
+    """Centroids (weights) around 2^-118: three bf16 parts hold 16 bits of them, the fp32 instruction 24.  Gaps err by a few 2^-24 of the
+    sums, D 2^-24 of the absolute products at the most."""
+    N, D, K = 45000, 64, 256
+    rng = np.random.default_rng(9)
+    z = rng.standard_normal((N, D)).astype(np.float32)
+    c = (rng.standard_normal((K, D)) * 2.0 ** -118).astype(np.float32)
+    dot = z.astype(np.float64) @ c.T.astype(np.float64)
+    score = -dot if linear else (c.astype(np.float64) ** 2).sum(1) - 2 * dot
+    order = np.argsort(score, axis=1)
+    gap = np.take_along_axis(score, order, 1)
+    gap = gap[:, 1] - gap[:, 0]
+    idx, hist, margin = torch.empty(N, dtype=torch.int32, device=DEV), torch.empty(K, dtype=torch.int64, device=DEV), torch.empty(N, device=DEV)
+    if linear:
+        dp.dipaco_route_linear(dev(z), D, dev(c), torch.zeros(K, device=DEV), N, D, K, idx, hist, margin)
+    else:
+        dp.dipaco_route_prefix(dev(z), dev(c), N, D, K, idx, hist, margin)
+    bound = 2 * 2 * math.sqrt(D) * 2.0 ** -24 * np.linalg.norm(z, axis=1) * np.linalg.norm(c.astype(np.float64), axis=1).max()
+    clear = gap > bound
+    assert clear.mean() > 0.99
+    assert np.array_equal(host(idx)[clear], order[clear, 0])
+    assert (np.abs(host(margin) - gap) <= bound).all()
+
+
 def test_rows_that_are_not_finite_do_not_hold_the_others_up():
     """Rows of NaN have no scores and are not multiplied again; infinite ones are, by their wave alone."""
     N, D, K = 65536, 256, 256
