@@ -265,8 +265,8 @@ __global__ void __launch_bounds__(64 * WM * WN * G, 2) gemm_split_kernel(const G
       for (int j = 0; j < SP_T; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) finite = __builtin_fmaf(acc[i][j][e], 0.f, finite);
-    const bool any_tiny = __any(tiny);
-    if (lane == 0) red[wave_all] = any_tiny ? 2.f : __any(finite != 0.f) ? 1.f : 0.f;
+    const bool any_tiny = __any(tiny), any = __any(finite != 0.f);   // votes of all lanes: outside the branch
+    if (lane == 0) red[wave_all] = any_tiny ? 2.f : any ? 1.f : 0.f;
     __syncthreads();
     float seen = 0.f;
 #pragma unroll
