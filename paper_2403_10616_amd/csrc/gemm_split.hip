@@ -39,7 +39,7 @@ template <int WM, int WN, int G> struct SplitGemm {
 // The workgroup's sums that the parts cannot give, on v_mfma_f32_16x16x4_f32.  Where the operands' largest number (NaN aside) is small enough
 // for every product and sum to be finite, a sum that is not comes of a NaN operand and stays.  tiny: numbers below SPLIT_LEAST, each of
 // which errs by up to 2^-134 in its parts; sums of up to `floor` could show that in their 24 bits.
-// 2048^3 146 us: 175 with all sums NaN or small numbers that no sum depends on, 430 - 550 with an infinity in every tile (a serial chain
+// 2048^3 146 us: 175 with all sums NaN or small numbers that no sum depends on, 350 - 530 with an infinity in every tile (a serial chain
 // for each sum: 17 - 33 ms).
 // red: LDS of as many floats as waves
 template <bool A_KC, bool B_KC, int WM, int WN, int G>
@@ -98,29 +98,38 @@ __device__ __forceinline__ void split_again(const GemmDev& g, f32x4 (&acc)[SP_T]
     }
   };
 #pragma unroll
-  for (int i = 0; i < SP_T; ++i) {
-    f32x4 t[SP_T];
+  for (int i = 0; i < SP_T; i += 2) {   // two blocks of 16 rows at a time
+    f32x4 t[2][2][SP_T];   // every second 16 of K each, as in the fitted tile: a chain half as long errs less
+    int row[2];
 #pragma unroll
-    for (int j = 0; j < SP_T; ++j) t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int row = min(m0 + 64 * wm + 16 * i + r, g.M - 1);
+    for (int u = 0; u < 2; ++u) {
+      row[u] = min(m0 + 64 * wm + 16 * (i + u) + r, g.M - 1);
+#pragma unroll
+      for (int j = 0; j < SP_T; ++j) t[0][u][j] = t[1][u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll 1
     for (int k0 = k_begin + 32 * grp; k0 < k_end; k0 += P::BK)   // the group's 32 of every stage
 #pragma unroll
-      for (int h = 0; h < 32; h += 16) {
-        float a[4], b[SP_T][4];
-        load(std::bool_constant<A_KC>{}, A, g.lda, row, k0 + h + 4 * kg, a);
+      for (int h = 0; h < 2; ++h) {
+        float a[2][4], b[SP_T][4];
 #pragma unroll
-        for (int j = 0; j < SP_T; ++j) load(std::bool_constant<B_KC>{}, B, g.ldb, min(n0 + 64 * wn + 16 * j + r, g.N - 1), k0 + h + 4 * kg, b[j]);
+        for (int u = 0; u < 2; ++u) load(std::bool_constant<A_KC>{}, A, g.lda, row[u], k0 + 16 * h + 4 * kg, a[u]);
+#pragma unroll
+        for (int j = 0; j < SP_T; ++j) load(std::bool_constant<B_KC>{}, B, g.ldb, min(n0 + 64 * wn + 16 * j + r, g.N - 1), k0 + 16 * h + 4 * kg, b[j]);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int j = 0; j < SP_T; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[j][q], t[j], 0, 0, 0);
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < SP_T; ++j) t[h][u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][q], b[j][q], t[h][u][j], 0, 0, 0);
       }
 #pragma unroll
-    for (int j = 0; j < SP_T; ++j)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (!holds(acc[i][j][e])) acc[i][j][e] = t[j][e];
+      for (int j = 0; j < SP_T; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!holds(acc[i + u][j][e])) acc[i + u][j][e] = t[0][u][j][e] + t[1][u][j][e];
   }
 }
 

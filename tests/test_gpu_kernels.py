@@ -486,6 +486,31 @@ def test_fp32_products_take_parts_only_where_they_are_ahead(M, N, K, ta, tb, til
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+def test_fp32_products_of_mixed_magnitudes_err_no_more_in_bf16_parts(ta, tb):
+    """Rows from 2^-130 to 2^60, and single numbers from 2^-125 to 2^-100: element by element, in units of the absolute products, against
+    the tile of the fp32 instruction."""
+    M, N, K = 520, 264, 1160
+    g = torch.Generator().manual_seed(3)
+    a, b = torch.randn((M, K), generator=g), torch.randn((K, N), generator=g)
+    for scale, col in ((torch.randint(-130, 60, (M, 1), generator=g), 1.0), (torch.randint(-125, -100, (M, K), generator=g), 2.0 ** 40)):
+        A, B = a * torch.exp2(scale.float()), b * col
+        ref, mag = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+        A, B = (A.t() if ta else A).contiguous().to(DEV), (B.t() if tb else B).contiguous().to(DEV)
+        seen = mag > 2.0 ** -120                 # below, the sums themselves are subnormal
+        errors = []
+        try:
+            for tile in (2, 3, 4):
+                dp.dipaco_k_set_gemm_tile(tile)
+                C = torch.empty((M, N), device=DEV)
+                dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C)
+                errors.append((((C.cpu().double() - ref).abs() / mag)[seen]).max().item())
+        finally:
+            dp.dipaco_k_set_gemm_tile(0)
+        print("largest error, 2^-24 of the absolute products:", [round(e * 2 ** 24, 2) for e in errors], flush=True)
+        assert max(errors[1:]) <= 1.05 * errors[0]
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
 @pytest.mark.parametrize("tile", [3, 4])
 def test_fp32_products_from_bf16_parts_with_one_large_value_in_a_tile(ta, tb, tile):
     """An infinity, or a number whose first part is one, anywhere in an operand: each in a call of its own, so that the sums it reaches
