@@ -8,7 +8,7 @@ from scipy.special import erf
 
 import paper_2403_10616_amd as dp
 from oracle import dipaco_oracle as orc
-from gpu_util import DEV, dev, host, median_us, rel_l2
+from gpu_util import DEV, dev, fma32, host, median_us, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -508,6 +508,29 @@ def test_fp32_products_of_mixed_magnitudes_err_no_more_in_bf16_parts(ta, tb):
             dp.dipaco_k_set_gemm_tile(0)
         print("largest error, 2^-24 of the absolute products:", [round(e * 2 ** 24, 2) for e in errors], flush=True)
         assert max(errors[1:]) <= 1.05 * errors[0]
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+@pytest.mark.parametrize("M,N,K", [(256, 192, 128), (520, 264, 112), (248, 200, 100), (200, 200, 80)])
+def test_fp32_products_over_a_short_k_err_no_more_than_chains_of_sixteen(M, N, K, ta, tb):
+    """Every 16 of K are a chain of their own; chains 64 apart are added first, then the four such sums.  The root mean square of the errors is
+    that of the same sums taken here (over tens of thousands of elements it is known to about 0.5 %); one chain over both steps errs by more."""
+    g = torch.Generator().manual_seed(K)
+    a, b = torch.randn((M, K), generator=g), torch.randn((K, N), generator=g)
+    ref = a.double() @ b.double()
+    sums = np.zeros((4, M, N), np.float32)
+    for k0 in range(0, K, 16):
+        chain = np.zeros((M, N), np.float32)
+        for k in range(k0, min(k0 + 16, K)):
+            chain = fma32(a[:, k:k + 1].numpy(), b[k].numpy(), chain)
+        sums[k0 // 16 % 4] += chain
+    model = ((sums[0] + sums[1]) + sums[2]) + sums[3]
+    A, B = (a.t() if ta else a).contiguous().to(DEV), (b.t() if tb else b).contiguous().to(DEV)
+    C = torch.empty((M, N), device=DEV)
+    dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, A, B, C)
+    mine, theirs = ((x.double() - ref).square().mean().sqrt().item() for x in (C.cpu(), torch.from_numpy(model)))
+    print(f"rms error {mine:.3e}, of chains of sixteen {theirs:.3e}", flush=True)
+    assert mine <= 1.03 * theirs
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
