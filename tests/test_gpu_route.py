@@ -265,6 +265,23 @@ def test_logistic_sums_over_several_rounds_of_rows(N, D, K):
     test_logistic_loss_and_gradients_match_oracle(N, D, K)
 
 
+@pytest.mark.parametrize("N,K", [(900, 256), (20000, 64), (40000, 120)])
+def test_logistic_loss_is_off_by_little_more_than_its_rounding(N, K):
+    """Over 24 draws, against 64 bits: rounding the result is off by 2^-24 / sqrt(3) at most (root mean square); half as much again is left for
+    the rows' own errors and the spread of 24 draws."""
+    D, errors = 8, []
+    for seed in range(24):
+        rng = np.random.default_rng(seed)
+        z, W = rng.standard_normal((N, D)).astype(np.float32), (0.05 * (seed + 4) * rng.standard_normal((K, D))).astype(np.float32)
+        b, y = rng.standard_normal(K).astype(np.float32), rng.integers(0, K, N).astype(np.int32)
+        loss = _logistic(z, y, W, b, want_dw=False)[0]
+        o_loss = orc.logistic_loss_grad(z, y, W, b)[0]
+        errors.append((loss - o_loss) / o_loss)
+    rms = float(np.sqrt(np.mean(np.square(errors))))
+    print(f"logistic N={N} K={K}: rms error {rms:.2e}", flush=True)
+    assert rms <= 1.5 * 2.0 ** -24 / 3 ** 0.5
+
+
 def test_bias_fit_on_gpu_gradients_matches_label_distribution_and_refills_empty_paths():
     """Weights frozen, bias descended with the GPU's dbias: the mean predicted distribution reaches the labels',
     and classes the unfitted classifier never picked get documents again."""
