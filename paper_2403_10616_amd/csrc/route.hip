@@ -629,6 +629,175 @@ __global__ void __launch_bounds__(RS_WAVES * WAVE) route_small_kernel(const floa
   }
 }
 
+// ---- a batch of documents -----------------------------------------------------------------------------------------
+// Fewer points than a round of the kernel above: there 100 x 896 x 256 are seven workgroups of 16 points, whose fp32 MFMAs are 12 us of
+// a compute unit while most idle.  Here a wave takes PTS points and 64 centroids, a lane each: a chain of plain multiply-adds per score,
+// the point's number handed to all lanes through a scalar register.  wc waves of a workgroup take different centroids, 4 / wc
+// different points.  Four stages of 32 K in flight, straight into LDS; the numbers of the next tile are read under the
+// multiply-adds of this one.  No barrier before the end.  Bound by what one compute unit reads through its L1 (every workgroup reads all
+// centroids, 64 bytes a clock: 6 us of 917 KB) and, level with it, by the vector instructions of a tile; 11 us of a call are the two
+// launches and the latencies of their ends.  Microseconds a call, kernel above -> this: 100 x 896 x 256 26.9 -> 18.9, 256 x 896 x 256 27.0 -> 19.8,
+// 500 x 896 x 256 (two points a wave) 27.2 -> 23.6, 256 x 896 x 1000 89 -> 63, 100 x 896 x 64 25.4 -> 17.9, 100 x 64 x 256 11.0 -> 10.9.
+// Left out: v_mfma_f32_4x4x1_16b_f32 with four points a matrix row (a dependent one takes 20 clocks: 27 us for any N up to 2048).
+// The chain of a score takes K as v_mfma_f32_16x16x4_f32 does above (0, 4, 8, 12, 1, 5, .. of every sixteen) and ||c||^2 is
+// added up in the same four sums: the same scores, bit for bit.
+constexpr int RF_WAVES = 4, RF_ST = 4;
+constexpr int RF_STAGE = (64 + 8) * TILE_ROW_BYTES, RF_LOADS = RF_STAGE / 1024;
+constexpr int RF_LDS = RF_WAVES * RF_ST * RF_STAGE;
+
+template <bool TOP2, int PTS>
+__global__ void __launch_bounds__(RF_WAVES * WAVE) route_few_kernel(const float* __restrict__ z, long ldz, const float* __restrict__ c,
+                                                                    const float* __restrict__ lin_bias, long N, int D, int K, int wc,
+                                                                    int* __restrict__ idx, unsigned long long* __restrict__ hist,
+                                                                    float* __restrict__ margin) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ Best red[RF_WAVES][PTS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave & (wc - 1), wp = wave / wc;   // wc is a power of two
+  const long m0 = ((long)blockIdx.x * (RF_WAVES / wc) + wp) * PTS;
+  const int rows_left = (int)max(0L, min((long)PTS, N - m0));   // wave-uniform
+  const float dot_mul = lin_bias ? 1.0f : 2.0f;
+
+  Best run[PTS];
+#pragma unroll
+  for (int p = 0; p < PTS; ++p) { run[p].s1 = INFINITY; run[p].i1 = NO_INDEX; run[p].s2 = INFINITY; run[p].i2 = NO_INDEX; }
+
+  char* const ring = smem + wave * RF_ST * RF_STAGE;
+  const uint32_t ring_addr = (uint32_t)(uintptr_t)ring;
+  const int nst = (D + RBK - 1) / RBK, lrow = lane >> 3;
+  for (int c0 = 64 * wk; rows_left > 0 && c0 < K; c0 += 64 * wc) {   // wave-uniform
+    // load i of a stage covers rows 8 i .. 8 i + 7: 64 centroids, then the points; rows beyond the last re-read it, K beyond D the last
+    // four.  The bases move on with the tiles, which are requested in order
+    const float* base_c = c + (long)c0 * D;
+    const float* base_z = z + m0 * ldz;
+    uint32_t off[RF_LOADS];
+    auto offsets = [&](int last) {   // `last`: the first of the last four K, from the tile's first one
+#pragma unroll
+      for (int i = 0; i < RF_LOADS; ++i) {
+        const long row = i < 8 ? (long)min(8 * i + lrow, K - 1 - c0) * D : min(lrow, rows_left - 1) * ldz;
+        off[i] = (uint32_t)((row + min(4 * ((lane & 7) ^ swz(8 * i + lrow)), last)) * 4);
+      }
+    };
+    offsets(RBK);
+    auto issue = [&](int kt, int stage) {
+      if (D - kt * RBK < RBK) offsets(D - kt * RBK - 4);   // the last tile
+#pragma unroll
+      for (int i = 0; i < RF_LOADS; ++i)
+        load16_to_lds_at(i < 8 ? base_c : base_z, off[i], __builtin_amdgcn_readfirstlane(ring_addr + stage * RF_STAGE + i * 1024));
+      base_c += RBK; base_z += RBK;
+    };
+    auto landed = [&](int kt) {   // own loads of tile kt: all but those of the tiles behind it
+      const int behind = min(RF_ST - 1, nst - 1 - kt);
+      if (behind == 3) wait_vmcnt<3 * RF_LOADS>();
+      else if (behind == 2) wait_vmcnt<2 * RF_LOADS>();
+      else if (behind == 1) wait_vmcnt<RF_LOADS>();
+      else wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+    };
+    float4 fc[2][8];       // the lane's centroid, 32 K
+    int fz[2][PTS];        // lane l: K l % 32 of a point
+    auto read = [&](auto SET, int stage) {
+      constexpr int set = decltype(SET)::value;
+      char* const tile = ring + stage * RF_STAGE;
+#pragma unroll
+      for (int p = 0; p < PTS; ++p) fz[set][p] = reinterpret_cast<const int*>(tile_chunk(tile, 64 + p, (lane >> 2) & 7))[lane & 3];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) fc[set][q] = *reinterpret_cast<const float4*>(tile_chunk(tile, lane, q));
+    };
+    float dot[PTS], nrm[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < PTS; ++p) dot[p] = 0.f;
+    auto multiply = [&](auto SET, auto WHOLE, int left) {   // `left`: K of the tile, a multiple of 4
+      constexpr int set = decltype(SET)::value;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        auto on = [&](int kg) { return decltype(WHOLE)::value || 16 * h + 4 * kg < left; };
+#pragma unroll
+        for (int p = 0; p < PTS; ++p) {   // sixteen scalars together: read and used in turn each pair is a stall
+          float zs[16];
+#pragma unroll
+          for (int k = 0; k < 16; ++k) zs[k] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(fz[set][p], 16 * h + k));
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int kg = 0; kg < 4; ++kg)
+              if (on(kg)) dot[p] = __builtin_fmaf(zs[4 * kg + q], reinterpret_cast<const float*>(&fc[set][4 * h + kg])[q], dot[p]);
+        }
+#pragma unroll
+        for (int kg = 0; kg < 4; ++kg)
+          if (on(kg)) {
+            const float4 v = fc[set][4 * h + kg];
+            nrm[kg] += __builtin_fmaf(v.w, v.w, __builtin_fmaf(v.z, v.z, __builtin_fmaf(v.x, v.x, v.y * v.y)));
+          }
+      }
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    auto registers_filled = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __builtin_amdgcn_sched_barrier(0); };
+#pragma unroll
+    for (int s = 0; s < RF_ST; ++s)
+      if (s < nst) issue(s, s);
+    landed(0);
+    read(C0{}, 0);
+    registers_filled();
+    auto step = [&](auto SET, int kt) {   // tile kt is in registers; its stage takes tile kt + RF_ST
+      constexpr int set = decltype(SET)::value;
+      if (kt + RF_ST < nst) issue(kt + RF_ST, kt % RF_ST);
+      if (kt + 1 < nst) {
+        landed(kt + 1);
+        read(std::integral_constant<int, set ^ 1>{}, (kt + 1) % RF_ST);
+      }
+      if (D - kt * RBK >= RBK) multiply(SET, std::true_type{}, RBK);   // uniform
+      else multiply(SET, std::false_type{}, D - kt * RBK);
+      registers_filled();
+    };
+    for (int kt = 0; kt < nst; kt += 2) {
+      step(C0{}, kt);
+      if (kt + 1 < nst) step(C1{}, kt + 1);
+    }
+    const int mine = c0 + lane;   // beyond K: never enters an entry
+    const float cn = mine < K ? (lin_bias ? -lin_bias[mine] : (nrm[0] + nrm[1]) + (nrm[2] + nrm[3])) : INFINITY;
+#pragma unroll
+    for (int p = 0; p < PTS; ++p) best_push_ascending<TOP2>(run[p], __builtin_fmaf(-dot_mul, dot[p], cn), mine);
+  }
+
+  auto from = [&](const Best& b, int m) {
+    Best o;
+    o.s1 = __shfl_xor(b.s1, m, WAVE); o.i1 = __shfl_xor(b.i1, m, WAVE); o.s2 = __shfl_xor(b.s2, m, WAVE);
+    o.i2 = TOP2 ? __shfl_xor(b.i2, m, WAVE) : NO_INDEX;
+    return o;
+  };
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+    for (int p = 0; p < PTS; ++p) run[p] = best_merge<TOP2>(run[p], from(run[p], m));
+  if (lane == 0) {
+#pragma unroll
+    for (int p = 0; p < PTS; ++p) red[wave][p] = run[p];
+  }
+  __syncthreads();
+  if (wk == 0 && lane < rows_left) {
+    Best b = red[wave][lane];
+    for (int w = wave + 1; w < wave + wc; ++w) b = best_merge<TOP2>(b, red[w][lane]);
+    if (b.i1 == NO_INDEX) {   // no score below +inf (NaN or infinite features): as in route_kernel
+      b.i1 = 0;
+      b.i2 = K > 1 ? 1 : NO_INDEX;
+      b.s1 = b.s2 = __builtin_nanf("");
+    }
+    atomicAdd(&hist[b.i1], 1ull);
+    if (TOP2) {
+      if (b.i2 == NO_INDEX) b.i2 = -1;
+      else atomicAdd(&hist[b.i2], 1ull);
+      idx[2 * (m0 + lane)] = b.i1;
+      idx[2 * (m0 + lane) + 1] = b.i2;
+    } else {
+      idx[m0 + lane] = b.i1;
+    }
+    if (margin) margin[m0 + lane] = b.s2 - b.s1;
+  }
+}
+
 // ---- K-class logistic regression: per-row softmax cross-entropy --------------------------------------------------
 // One wave per row of logits [rows, K] (K a multiple of 4, at most LOGIT_MAX_K): nll[row] = logsumexp - logit[label],
 // and in place logits <- (softmax - onehot(label)) * inv_n.  A row whose label is outside [0, K) gives 0 and zeros.
@@ -814,7 +983,7 @@ static int route_small_wc(int K) { return K > 128 ? 8 : K > 64 ? 4 : K > 32 ? 2 
 // 1 / 2: route_small_kernel with 16 / 32 points per wave, 0: route_kernel.  All take time in whole rounds over the compute units,
 // proportional to D.  Measured at D = 896: 512 workgroups of route_kernel (65536 points) with 256 centroids 169 us, up to 256 of them 125; a
 // round of the small kernel with 32 points per wave (2048 wave tasks) 43 us, with 16 points 28 us.  The 16-point form is taken where one round
-// of it holds everything (100 x 256: 25 us, 45 with 32 points, 120 in route_kernel).  Else route_kernel where 230 us for a round of 65536
+// of it holds everything (1000 x 256: 27 us, 45 with 32 points, 120 in route_kernel), below that route_few_kernel.  Else route_kernel where 230 us for a round of 65536
 // points x 256 centroids would be the cheaper: at 16384 x 256 91 | 125 us, 65536 x 256 328 | 169, 300000 x 768 x 256 1300 | 720, x 16 202 | 371.
 // The line lies where it did when route_kernel took those 230 us: nearer to it the two err differently (the small kernel's chain takes K
 // in another order than decide_near_tie), and a program's assignments would turn at near-ties.
@@ -826,6 +995,15 @@ static int route_pick(int64_t N, int64_t ldz, int D, int K) {
   const int64_t small = 43 * (((N + 31) / 32 * wc + tasks - 1) / tasks) * sweeps;
   const int64_t big = 230 * ((N + 65535) / 65536) * ((K + 255) / 256);
   return small < big ? 2 : 0;
+}
+
+// Points of a wave of route_few_kernel, 0: not taken.  While one round of 256 workgroups, one to a compute unit, holds the batch: a second
+// round costs as much again (500 x 896 x 256 36.6 us with one point a wave, 23.6 with two, 27.2 in the kernel above).  Two points a wave only where a
+// workgroup's waves share them: 1000 x 256 x 100 14.6 us, 12.9 above, 2000 x 896 x 64 33.0 | 26.6.  32-bit byte offsets within a tile.
+static int route_few_points(int64_t N, int64_t ldz, int D, int wc) {
+  if (std::max<int64_t>(64 * (int64_t)D, 2 * ldz) * 4 >= 1LL << 32) return 0;
+  if (N * wc <= 256 * RF_WAVES) return 1;
+  return wc == RF_WAVES && N <= 512 ? 2 : 0;
 }
 
 dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const float* lin_bias, int64_t N, int D, int K,
@@ -847,6 +1025,23 @@ dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const fl
     return DIPACO_OK;
   };
   const int pick = route_pick(N, ldz, D, K);
+  if (pick == 1) {
+    const int fc = K > 128 ? 4 : K > 64 ? 2 : 1;
+    auto few = [&](auto PTC) -> dipaco_status {
+      constexpr int PTS = decltype(PTC)::value;
+      static std::atomic<unsigned long long> set_one{0}, set_two{0};
+      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<false, PTS>), RF_LDS, set_one)) return e;
+      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<true, PTS>), RF_LDS, set_two)) return e;
+      const int64_t pts = PTS * (RF_WAVES / fc), nb = (N + pts - 1) / pts;
+      if (n_best == 2) route_few_kernel<true, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, h, margin);
+      else route_few_kernel<false, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, h, margin);
+      DIPACO_LAUNCH_CHECK();
+      return DIPACO_OK;
+    };
+    const int take = route_few_points(N, ldz, D, fc);
+    if (take == 1) return few(std::integral_constant<int, 1>{});
+    if (take == 2) return few(std::integral_constant<int, 2>{});
+  }
   if (pick == 1) return small(std::integral_constant<int, 1>{});
   if (pick == 2) return small(std::integral_constant<int, 2>{});
   static std::atomic<unsigned long long> lds_one{0}, lds_two{0};

@@ -604,6 +604,41 @@ def test_rows_that_are_not_finite_do_not_hold_the_others_up():
     assert times[0] <= 1.5 * finite and times[1] <= 6 * finite
 
 
+@pytest.mark.parametrize("D,K", [(4, 3), (28, 64), (36, 65), (896, 128), (100, 129), (32, 256), (64, 257), (256, 1000)])
+def test_a_batch_routes_as_its_points_do_among_others(D, K):
+    """Batches of up to 256, 512 or 1024 points (by K) have a kernel of their own, whose scores are those of the larger ones' bit for bit."""
+    N = 1100
+    rng = np.random.default_rng(K)
+    z, c = (rng.standard_normal((n, D)).astype(np.float32) for n in (N, K))
+    z[7, D - 1], z[9, 0] = np.nan, np.inf
+    c[K // 2] = c[0]
+    bias = dev(rng.standard_normal(K).astype(np.float32))
+    zd, cd = dev(z), dev(c)
+
+    def route(lo, hi, form):
+        n = hi - lo
+        idx = torch.full((n, 2) if form == "two nearest" else (n,), -7, dtype=torch.int32, device=DEV)
+        hist, gap = torch.full((K,), -7, dtype=torch.int64, device=DEV), torch.empty(n, dtype=torch.float32, device=DEV)
+        if form == "linear":
+            dp.dipaco_route_linear(zd[lo:hi], D, cd, bias, n, D, K, idx, hist, gap)
+        else:
+            dp.dipaco_route_prefix_top(zd[lo:hi], D, cd, n, D, K, idx.numel() // n, idx, hist, gap)
+        assert np.array_equal(host(hist), np.bincount(host(idx).ravel(), minlength=K))
+        return host(idx), host(gap).view(np.int32)
+
+    for form in ("nearest", "two nearest", "linear"):
+        idx, gap = route(0, N, form)
+        nan = np.isnan(gap.view(np.float32))
+        lo = 0
+        for n in (1, 2, 3, 8, 65, 255, 256):   # each starts behind the one before; one and two points a wave, a last wave that is not full
+            got_idx, got_gap = route(lo, lo + n, form)
+            assert np.array_equal(got_idx, idx[lo:lo + n]) and np.array_equal(got_gap[~nan[lo:lo + n]], gap[lo:lo + n][~nan[lo:lo + n]])
+            lo += n
+        for n in (257, 511, 512, 513, 1023, 1024, 1025):
+            got_idx, got_gap = route(0, n, form)
+            assert np.array_equal(got_idx, idx[:n]) and np.array_equal(got_gap[~nan[:n]], gap[:n][~nan[:n]])
+
+
 def test_more_points_than_one_launch_of_small_workgroups_holds():
     """600,000,000 points and 100 centroids: 64 points a workgroup of 512 threads would pass 2^32 threads in a launch."""
     N, D, K = 600_000_000, 4, 100
