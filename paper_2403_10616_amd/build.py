@@ -19,6 +19,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     # keep the compiler from forming packed fp32 ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first arguments of a kernel arrive in registers instead of through a load in front of everything else: 0.1 us a launch
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 
 

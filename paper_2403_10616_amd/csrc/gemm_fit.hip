@@ -119,10 +119,16 @@ __device__ __forceinline__ void fit_product(const GemmDev& g, int block) {
     split = v / tiles;
     tile_m = (v - split * tiles) % g.tiles_m;
     tile_n = (v - split * tiles) / g.tiles_m;
+  } else if (g.fast_map) {
+    split = 0;
+    gemm_tile_of_block_fast(g, block, tile_m, tile_n);
   } else {
     gemm_tile_of_block(g, block, split, tile_m, tile_n);
   }
   const int m0 = tile_m * BM, n0 = tile_n * BN;
+  constexpr bool EARLY = WM * WN == 1;
+  FitAhead<T> early;
+  if constexpr (EARLY) early = fit_request<T, TN, TM, FIT_WAVES>(g, tid, m0, n0);
   const int k_begin = split * g.k_per_split, k_end = min(g.K, k_begin + g.k_per_split);
   const int nkt = (k_end - k_begin + BK - 1) / BK;
 
@@ -308,7 +314,8 @@ __device__ __forceinline__ void fit_product(const GemmDev& g, int block) {
   if (nkt & 1) multiply_last(C0{});
   else multiply_last(C1{});
 
-  fit_epilogue<T, TC, TM, TN, WM, WN, G, F::IC>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0, tile_m, split);
+  fit_epilogue<T, TC, TM, TN, WM, WN, G, F::IC>(g, acc, reinterpret_cast<float*>(smem), tid, grp, wm, wn, m0, n0, tile_m, split,
+                                                EARLY ? &early : nullptr);
 }
 
 template <typename T, typename TC, bool A_KC, bool B_KC, int TM, int TN, int WM, int WN, int G, int ST, bool FAR>
@@ -352,6 +359,7 @@ template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * D
   constexpr int AHEAD = 2;
   static_assert(DIRECT_K <= 16 * G * AHEAD, "a wave's steps are all in flight");
   float a[AHEAD][2][4], b[AHEAD][TN][4];
+  const FitAhead<float> early = fit_request<float, TN, 2, G>(g, tid, m0, n0);
 #pragma unroll
   for (int s = 0; s < AHEAD; ++s) {
     const int k = 16 * (wave + G * s) + 4 * kg;
@@ -384,7 +392,7 @@ template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * D
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += step[i][j];
-  fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0);
+  fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0, &early);
 }
 
 // The two products of a linear layer's backward pass, X^T dY (blocks 0 .. first - 1) and dY W^T, in one launch of 32 x 64 tiles.
@@ -409,6 +417,7 @@ template <typename F> GemmDev fit_dev(const GemmArgs& a) {
   g.k_per_split = (steps + want - 1) / want * F::BK;
   g.splits = (a.K + g.k_per_split - 1) / g.k_per_split;
   g.colsum_partial = a.colsum ? a.colsum_partial : nullptr;
+  gemm_fast_map(g);
   return g;
 }
 

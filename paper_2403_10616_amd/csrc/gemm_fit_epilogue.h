@@ -12,11 +12,27 @@ constexpr int FIT_PAD = 4;   // floats between rows of the staging region
 // LDS bytes of the staging region: 16 n16 rows of every wave at a time
 constexpr int fit_epilogue_bytes(int n16, int TN, int WM, int WN, int G) { return G * WM * 16 * n16 * (16 * TN * WN + FIT_PAD) * 4; }
 
+// The operands of the epilogue of a tile that is one item a thread (32 x 64 and smaller), requested in front of the product: behind it
+// they are one more trip to memory, 0.5 - 0.7 of a launch of 4 - 6 us.
+template <typename T> struct FitAhead { Raw8<T> bias, in; };
+template <typename T, int TN, int TM, int NW> __device__ __forceinline__ FitAhead<T> fit_request(const GemmDev& g, int tid, int m0, int n0) {
+  constexpr int CG = 2 * TN;
+  static_assert(16 * TM * CG <= 64 * NW, "one item a thread");
+  FitAhead<T> f;
+  const int row = m0 + tid / CG, col = n0 + 8 * (tid % CG);
+  if (g.splits > 1 || col >= g.N) return f;
+  if (g.bias) f.bias = raw8_load(static_cast<const T*>(g.bias) + col);
+  const T* const ahead = static_cast<const T*>(g.act == 2 || g.act == 4 ? g.aux_in : g.resid);
+  if (ahead && tid / CG < 16 * TM && row < g.M) f.in = raw8_load(ahead + (size_t)row * g.ldc + col);
+  return f;
+}
+
 // acc: the wave's TM x TN tiles of 16 x 16 (lane l: column l % 16, rows 4 (l / 16) + e), taken in two passes of IC and TM - IC
 // tile rows.  red: LDS, free once every wave has reached this call.
+// early: what fit_request has asked for, or null.
 template <typename T, typename TC, int TM, int TN, int WM, int WN, int G, int IC>
 __device__ __forceinline__ void fit_epilogue(const GemmDev& g, const f32x4 (&acc)[TM][TN], float* red, int tid, int grp, int wm, int wn,
-                                             int m0, int n0, int tile_m, int split) {
+                                             int m0, int n0, int tile_m, int split, const FitAhead<T>* early = nullptr) {
   static_assert(TM <= 2 * IC, "two passes");
   constexpr int NW = WM * WN * G, BN = 16 * TN * WN, LDW = BN + FIT_PAD, CG = BN / 8;
   const int lane = tid & 63, wave = tid >> 6, r = lane & 15, kg = lane >> 4;
@@ -30,13 +46,15 @@ __device__ __forceinline__ void fit_epilogue(const GemmDev& g, const f32x4 (&acc
   const T* const ahead = want_aux ? aux_in : resid;
   const long ldc = g.ldc;
   float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (bias && col_ok) OutVec<T>::load(bias + col, bv);
+  if (bias && col_ok) raw8_unpack(early ? early->bias : raw8_load(bias + col), bv);
   auto pass = [&](auto I0, auto N16) {   // 16-row blocks I0 .. I0 + N16 - 1 of every wave
     constexpr int i0 = decltype(I0)::value, n16 = decltype(N16)::value;
     constexpr int ROWS = WM * 16 * n16, ITERS = (ROWS * CG + 64 * NW - 1) / (64 * NW);
     auto row_of = [&](int rr) { return m0 + (rr / (16 * n16)) * 16 * TM + 16 * i0 + rr % (16 * n16); };
     Raw8<T> rin[ITERS];
-    if (ahead) {
+    if (early) {
+      rin[0] = early->in;
+    } else if (ahead) {
 #pragma unroll
       for (int it = 0; it < ITERS; ++it) {
         const int rr = (tid + 64 * NW * it) / CG, row = row_of(rr);

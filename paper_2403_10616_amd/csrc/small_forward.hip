@@ -61,6 +61,10 @@ __global__ void __launch_bounds__(RP_WAVES * WAVE) rows_product_kernel(const bf1
   const int c = lane & 15, g = lane >> 4;
   const int n0 = blockIdx.x * RP_COLS, row0 = blockIdx.y * SF_ROWS, rows = min(SF_ROWS, n_rows - row0);
   const int steps = (K + 31) / 32, s1 = (wave + 1) * steps / RP_WAVES;
+  const int row = tid >> 3, col = 4 * (tid & 7);   // of the output: 256 threads of four columns each
+  const bool on = row < rows && n0 + col < N;
+  bf16x4 bi = {};
+  if (on) bi = *reinterpret_cast<const bf16x4*>(bias + n0 + col);
   f32x4 acc[2][2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb)
@@ -102,15 +106,13 @@ __global__ void __launch_bounds__(RP_WAVES * WAVE) rows_product_kernel(const bf1
     for (int e = 0; e < 4; ++e)
       *reinterpret_cast<float2*>(&red[wave][16 * rb + 4 * g + e][2 * c]) = make_float2(acc[rb][0][e], acc[rb][1][e]);
   __syncthreads();
-  const int row = tid >> 3, col = 4 * (tid & 7);
-  if (row >= rows || n0 + col >= N) return;   // 256 threads of four columns each
+  if (!on) return;
   float4 s = *reinterpret_cast<const float4*>(&red[0][row][col]);
 #pragma unroll
   for (int w = 1; w < RP_WAVES; ++w) {   // in order
     const float4 v = *reinterpret_cast<const float4*>(&red[w][row][col]);
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
-  const bf16x4 bi = *reinterpret_cast<const bf16x4*>(bias + n0 + col);
   float v[4] = {s.x + (float)bi[0], s.y + (float)bi[1], s.z + (float)bi[2], s.w + (float)bi[3]};
   bf16x4 y;
 #pragma unroll
