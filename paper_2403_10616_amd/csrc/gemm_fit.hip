@@ -323,16 +323,16 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, (2 * Fit<T, TC, A_KC, B_KC, TM
   fit_product<T, TC, A_KC, B_KC, TM, TN, WM, WN, G, ST, FAR>(g, blockIdx.x);
 }
 
-// fp32 over a short K (up to DIRECT_K): 32 x 64 tiles, or 32 x 32 as below, whose operands go from memory straight into the lanes that
-// multiply them.  Four waves take 16 of K each at a time, two such steps in flight; their sums meet in the epilogue.  Such a product is
-// bound by its launch, one trip to memory and the instructions in front of and behind it: the ring above costs a second trip through LDS,
-// a barrier and the arithmetic of its addresses (256 x 192 x 64 6.0 us there, 4.9 here; 256 x 64 x 64 6.5 | 4.7).
+// fp32 over a short K: 32 x 64 tiles, or 32 x 32 as below, whose operands go from memory straight into the lanes that multiply them.  G waves
+// take 16 of K each at a time, two such steps in flight; their sums meet in the epilogue.  Such a product is bound by its launch, one trip
+// to memory and the instructions in front of and behind it (2 - 3 ns each): the ring above costs a second trip through LDS, a
+// barrier and the arithmetic of its addresses.  Four waves for up to DIRECT_K (256 x 192 x 64 6.0 us there, 4.9 here; 256 x 64 x 64 6.5 | 4.7),
+// eight for twice that while 32 x 32 tiles make one round.
 constexpr int DIRECT_K = 128, DIRECT_G = 4;
-template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * DIRECT_G, 2) gemm_direct_kernel(const GemmDev g) {
-  constexpr int G = DIRECT_G;
+template <bool A_KC, bool B_KC, int TN, int G> __device__ __forceinline__ void direct_product(const GemmDev& g, int block) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, kg = lane >> 4;
-  const int tile_n = (int)blockIdx.x / g.tiles_m, tile_m = (int)blockIdx.x - tile_n * g.tiles_m;
+  const int tile_n = block / g.tiles_m, tile_m = block - tile_n * g.tiles_m;
   const int m0 = tile_m * 32, n0 = tile_n * 16 * TN;
   const float* const A = static_cast<const float*>(g.A);
   const float* const B = static_cast<const float*>(g.B);
@@ -357,7 +357,7 @@ template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * D
     }
   };
   constexpr int AHEAD = 2;
-  static_assert(DIRECT_K <= 16 * G * AHEAD, "a wave's steps are all in flight");
+  static_assert(DIRECT_K / DIRECT_G == 16 * AHEAD, "a wave's steps are all in flight");
   float a[AHEAD][2][4], b[AHEAD][TN][4];
   const FitAhead<float> early = fit_request<float, TN, 2, G>(g, tid, m0, n0);
 #pragma unroll
@@ -394,6 +394,9 @@ template <bool A_KC, bool B_KC, int TN> __global__ void __launch_bounds__(64 * D
     for (int j = 0; j < TN; ++j) acc[i][j] += step[i][j];
   fit_epilogue<float, float, 2, TN, 1, 1, G, 2>(g, acc, reinterpret_cast<float*>(smem), tid, wave, 0, 0, m0, n0, tile_m, 0, &early);
 }
+template <bool A_KC, bool B_KC, int TN, int G> __global__ void __launch_bounds__(64 * G, 2) gemm_direct_kernel(const GemmDev g) {
+  direct_product<A_KC, B_KC, TN, G>(g, blockIdx.x);
+}
 
 // The two products of a linear layer's backward pass, X^T dY (blocks 0 .. first - 1) and dY W^T, in one launch of 32 x 64 tiles.
 // Bound by launches: a step on 256 tokens is fifty of 5 us each, and neither product reads what the other writes (260 -> 209 us).  For
@@ -402,6 +405,13 @@ template <typename T, int TN> __global__ void __launch_bounds__(64 * FIT_WAVES, 
   const int block = blockIdx.x;
   if (block < first) fit_product<T, float, false, false, 2, TN, 1, 1, 8, 3, false>(dw, block);
   else fit_product<T, T, true, true, 2, TN, 1, 1, 8, 3, false>(dx, block - first);
+}
+
+// The same in fp32 where both contractions are short
+template <int G> __global__ void __launch_bounds__(64 * G, 2) gemm_direct_pair_kernel(const GemmDev dw, const GemmDev dx, int first) {
+  const int block = blockIdx.x;
+  if (block < first) direct_product<false, false, 2, G>(dw, block);
+  else direct_product<true, true, 2, G>(dx, block - first);
 }
 
 template <typename F> GemmDev fit_dev(const GemmArgs& a) {
@@ -443,20 +453,20 @@ dipaco_status run_fit(const GemmArgs& a, hipStream_t s) {
   return DIPACO_OK;
 }
 
-// whether a 32 x 64 tile's product is taken by gemm_direct_kernel (32-bit element offsets)
-bool direct_takes(const GemmArgs& a, bool a_kc, bool b_kc) {
+// whether a 32 x 64 tile's product over up to `most_k` is taken by direct_product (32-bit element offsets)
+bool direct_takes(const GemmArgs& a, bool a_kc, bool b_kc, int most_k) {
   const uint64_t most = 1ull << 32;
-  return a.K <= DIRECT_K && std::max(1, a.splits) == 1 && !a.raw_planes && (uint64_t)(a_kc ? a.M : a.K) * a.lda < most &&
+  return a.K <= most_k && std::max(1, a.splits) == 1 && !a.raw_planes && (uint64_t)(a_kc ? a.M : a.K) * a.lda < most &&
          (uint64_t)(b_kc ? a.N : a.K) * a.ldb < most;
 }
 template <int TN> struct DirectTile { static constexpr int BM = 32, BN = 16 * TN, BK = 16; };
-template <bool A_KC, bool B_KC, int TN> dipaco_status run_direct(const GemmArgs& a, hipStream_t s) {
+template <bool A_KC, bool B_KC, int TN, int G> dipaco_status run_direct(const GemmArgs& a, hipStream_t s) {
   const GemmDev g = fit_dev<DirectTile<TN>>(a);
   const long blocks = (long)g.tiles_m * g.tiles_n;
-  if (!launch_fits(blocks, 64 * DIRECT_G)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
-  constexpr int LDS = fit_epilogue_bytes(2, TN, 1, 1, DIRECT_G);
+  if (!launch_fits(blocks, 64 * G)) return fail(DIPACO_ESHAPE, "gemm: too many tiles");
+  constexpr int LDS = fit_epilogue_bytes(2, TN, 1, 1, G);
   static_assert(LDS <= 64 * 1024, "no limit to raise");
-  gemm_direct_kernel<A_KC, B_KC, TN><<<(unsigned)blocks, 64 * DIRECT_G, LDS, s>>>(g);
+  gemm_direct_kernel<A_KC, B_KC, TN, G><<<(unsigned)blocks, 64 * G, LDS, s>>>(g);
   DIPACO_LAUNCH_CHECK();
   if (a.colsum) return launch_sum_rows(a.colsum_partial, a.colsum, g.tiles_m, a.N, s, a.sum_batch);
   return DIPACO_OK;
@@ -553,7 +563,9 @@ template <typename T, typename TC, bool A_KC, bool B_KC> dipaco_status run_fit_s
   const int t = a.raw_planes ? 1 : pick_fit(a.M, a.N, (a.K + splits - 1) / splits, splits, sizeof(T) == 2, A_KC, B_KC);
   if constexpr (sizeof(T) == 4) {
     const bool narrow = narrow_tiles(a.M, a.N) * splits <= 256;
-    if (t == 1 && direct_takes(a, A_KC, B_KC)) return narrow ? run_direct<A_KC, B_KC, 2>(a, s) : run_direct<A_KC, B_KC, 4>(a, s);
+    if (t == 1 && direct_takes(a, A_KC, B_KC, DIRECT_K))
+      return narrow ? run_direct<A_KC, B_KC, 2, DIRECT_G>(a, s) : run_direct<A_KC, B_KC, 4, DIRECT_G>(a, s);
+    if (t == 1 && narrow && direct_takes(a, A_KC, B_KC, 2 * DIRECT_K)) return run_direct<A_KC, B_KC, 2, 2 * DIRECT_G>(a, s);
     if (t == 1 && narrow) return run_fit<T, TC, A_KC, B_KC, 2, 2, 1, 1, 8, 3>(a, s);
   }
   if (t == 1) return run_fit<T, TC, A_KC, B_KC, 2, 4, 1, 1, 8, 3>(a, s);
@@ -604,7 +616,17 @@ template <typename T> dipaco_status launch_gemm_fit_pair(const GemmArgs& dw, con
     return DIPACO_OK;
   };
   if constexpr (sizeof(T) == 4) {
-    if (narrow_tiles(dw.M, dw.N) + narrow_tiles(dx.M, dx.N) <= 256) return run(std::integral_constant<int, 2>{});
+    const long narrow = narrow_tiles(dw.M, dw.N) + narrow_tiles(dx.M, dx.N);
+    if (narrow <= 256 && direct_takes(dw, false, false, 2 * DIRECT_K) && direct_takes(dx, true, true, 2 * DIRECT_K)) {
+      constexpr int G = 2 * DIRECT_G;
+      const GemmDev w = fit_dev<DirectTile<2>>(dw), x = fit_dev<DirectTile<2>>(dx);
+      const int first = w.tiles_m * w.tiles_n;
+      gemm_direct_pair_kernel<G><<<first + x.tiles_m * x.tiles_n, 64 * G, fit_epilogue_bytes(2, 2, 1, 1, G), s>>>(w, x, first);
+      DIPACO_LAUNCH_CHECK();
+      if (dx.colsum) return launch_sum_rows(dx.colsum_partial, dx.colsum, x.tiles_m, dx.N, s, dx.sum_batch);
+      return DIPACO_OK;
+    }
+    if (narrow <= 256) return run(std::integral_constant<int, 2>{});
   }
   return run(std::integral_constant<int, 4>{});
 }

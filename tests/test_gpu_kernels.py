@@ -534,6 +534,24 @@ def test_fp32_products_over_a_short_k_err_no_more_than_chains_of_sixteen(M, N, K
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
+@pytest.mark.parametrize("M,N,K", [(256, 192, 256), (40, 72, 132), (264, 120, 200), (8, 8, 144), (512, 504, 248), (360, 104, 136)])
+def test_fp32_products_of_few_tiles_over_up_to_256_are_chains_of_sixteen(M, N, K, ta, tb):
+    """Eight waves of two chains of sixteen K each, 128 apart: sixteen roundings of the largest partial sum in a chain, and eight of what is
+    added behind them, on every element; and an element of the result that is not finite stays alone with its row or column."""
+    g = torch.Generator().manual_seed(K)
+    a, b = torch.randn((M, K), generator=g), torch.randn((K, N), generator=g)
+    ref, most = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+    C = torch.empty((M, N), device=DEV)
+    dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, (a.t() if ta else a).contiguous().to(DEV), (b.t() if tb else b).contiguous().to(DEV), C)
+    assert bool(((C.cpu().double() - ref).abs() <= 24 * 2.0 ** -24 * most).all())
+    assert (C.cpu().double() - ref).norm() <= 2e-7 * ref.norm()   # 1.2e-7 in chains of sixteen
+    a[M // 2, K - 1], b[K - 4, N - 1] = math.inf, math.nan
+    dp.dipaco_k_gemm(dp.F32, ta, tb, ta, M, N, K, (a.t() if ta else a).contiguous().to(DEV), (b.t() if tb else b).contiguous().to(DEV), C)
+    off = ~torch.isfinite(C.cpu())
+    assert bool(off[M // 2].all()) and bool(off[:, N - 1].all()) and int(off.sum()) == M + N - 1
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)], ids=["A.B", "A.Bt", "At.B"])
 @pytest.mark.parametrize("tile", [3, 4])
 def test_fp32_products_from_bf16_parts_with_one_large_value_in_a_tile(ta, tb, tile):
     """An infinity, or a number whose first part is one, anywhere in an operand: each in a call of its own, so that the sums it reaches
