@@ -308,9 +308,9 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
     return launch_layernorm_fwd<T>(x_new, ln_g, ln_b, buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st);
   };
   // X W + b of a block's input, then GELU; no backward pass: GELU' is neither kept nor written (act 5)
-  auto linear = [&](const T* X, size_t w_off, size_t b_off, T* Y, int N, bool gelu) -> dipaco_status {
+  auto linear = [&](const T* X, size_t w_off, size_t b_off, T* Y, int N, bool gelu, const WeightTiles& ahead) -> dipaco_status {
     if constexpr (std::is_same<T, bf16>::value) {
-      if (small_product_takes(T_, N, d)) return launch_small_product(X, W + w_off, W + b_off, Y, T_, N, d, gelu, st);
+      if (small_product_takes(T_, N, d)) return launch_small_product(X, W + w_off, W + b_off, Y, T_, N, d, gelu, ahead, st);
     }
     return gemm<T>(X, W + w_off, Y, T_, N, d, d, N, N, false, false, W + b_off, nullptr, nullptr, nullptr, gelu ? 5 : 0, false, 1, nullptr, st);
   };
@@ -318,18 +318,35 @@ static dipaco_status run_features(const dipaco_ctx* c, const T* W, const int* to
   auto ln_g = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_g : targets ? W + c->lnf_g : nullptr; };
   auto ln_b = [&](int l) -> const T* { return l < c->n_layers ? W + c->blocks[l].ln1_b : targets ? W + c->lnf_b : nullptr; };
   if (ln_g(0)) TRY(launch_layernorm_fwd<T>(x, ln_g(0), ln_b(0), buf(p.h), fbuf(p.mean), fbuf(p.rstd), T_, d, a.ln_eps, st));
+  // what a launch of a few rows asks for on behalf of a later one (small_forward.hip): the weights of the up-projection, of the
+  // down-projection, and of the next block's q | k | v
+  auto up_weights = [&](const BlockOff& o) -> WeightTiles {
+    if constexpr (std::is_same<T, bf16>::value) { if (small_product_takes(T_, F, d)) return small_product_weights(W + o.w_up, T_, F, d); }
+    return WeightTiles{};
+  };
+  auto down_weights = [&](const BlockOff& o) -> WeightTiles {
+    if constexpr (std::is_same<T, bf16>::value) { if (p.splits_down > 1) return raw_product_weights(W + o.w_down, T_, d, F); }
+    return WeightTiles{};
+  };
+  auto qkv_weights = [&](int l) -> WeightTiles {
+    if constexpr (std::is_same<T, bf16>::value) {
+      if (l < c->n_layers && small_product_takes(T_, 3 * A, d)) return small_product_weights(W + c->blocks[l].w_qkv, T_, 3 * A, d);
+    }
+    return WeightTiles{};
+  };
   for (int l = 0; l < c->n_layers; ++l) {
     const BlockOff& o = c->blocks[l];
-    TRY(linear(buf(p.h), o.w_qkv, o.b_qkv, buf(p.qkv), 3 * A, false));
+    TRY(linear(buf(p.h), o.w_qkv, o.b_qkv, buf(p.qkv), 3 * A, false, up_weights(o)));
     if (p.attn_planes) {
-      if constexpr (std::is_same<T, bf16>::value) TRY(launch_attn_out(buf(p.qkv), W + o.w_o, fbuf(p.planes), B, S, H, d, st));
+      if constexpr (std::is_same<T, bf16>::value)
+        TRY(launch_attn_out(buf(p.qkv), W + o.w_o, fbuf(p.planes), B, S, H, d, down_weights(o), st));
       TRY(launch_sum_layernorm<T>(fbuf(p.planes), p.attn_planes, W + o.b_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b, buf(p.h), T_, d,
                                   a.ln_eps, st));
     } else {
       TRY(launch_attention_fwd<T>(buf(p.qkv), buf(p.o), fbuf(p.lse), B, S, H, dh, st));
       TRY(residual(buf(p.o), o.w_o, o.b_o, A, p.splits_o, x, buf(p.x_mid), W + o.ln2_g, W + o.ln2_b));
     }
-    TRY(linear(buf(p.h), o.w_up, o.b_up, buf(p.act), F, true));
+    TRY(linear(buf(p.h), o.w_up, o.b_up, buf(p.act), F, true, qkv_weights(l + 1)));
     TRY(residual(buf(p.act), o.w_down, o.b_down, F, p.splits_down, buf(p.x_mid), x_other, ln_g(l + 1), ln_b(l + 1)));
     std::swap(x, x_other);
   }

@@ -648,6 +648,12 @@ int gemm_raw_splits(int M, int N, int K, bool bf16_operands) {
   return (steps + per - 1) / per;
 }
 
+WeightTiles raw_product_weights(const bf16* W, int rows, int N, int K) {   // run_fit_shape's tile for planes
+  using F = Fit<bf16, bf16, true, false, 2, 4, 1, 1, 8, 3>;
+  const int splits = gemm_raw_splits(rows, N, K, true), steps = (K + F::BK - 1) / F::BK, tiles_m = (rows + F::BM - 1) / F::BM, tiles_n = (N + F::BN - 1) / F::BN;
+  return WeightTiles{W, 2 * N, K, tiles_m * tiles_n * splits, tiles_m, (steps + splits - 1) / splits * F::BK, tiles_n};
+}
+
 size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands) {
   size_t most = 0;
   for (int m = std::min(M, 32);; m = std::min(M, m + 32)) {   // the split count depends on the rows in steps of 32

@@ -214,11 +214,17 @@ size_t colsum_partial_floats(int rows, int cols);
 constexpr int SMALL_FORWARD_ROWS = 256;
 // out = x W + bias (then GELU): x [rows, K], W [K, N]
 bool small_product_takes(int rows, int N, int K);
-dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, hipStream_t s);
+// The weights [rows, row_bytes] of a later product (items = 0: none): its item v reads piece v / items_per_piece, piece_rows rows of a
+// 128-byte column, pieces_n of them side by side
+struct WeightTiles { const void* base; int row_bytes, rows, items, items_per_piece, piece_rows, pieces_n; };
+WeightTiles small_product_weights(const bf16* W, int rows, int N, int K);
+WeightTiles raw_product_weights(const bf16* W, int rows, int N, int K);   // of a product into planes, bf16
+dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, const WeightTiles& ahead,
+                                   hipStream_t s);
 // attention and output projection, without bias and residual: the planes [n][B S, d] of launch_sum_layernorm.  0: does not take them
 int attn_out_planes(int B, int S, int H, int d_head, int d);
 int attn_out_most_planes(int H, int d_head);   // of any batch
-dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, hipStream_t s);
+dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, const WeightTiles& ahead, hipStream_t s);
 // out[b, :] (fp32) = mean over positions of x[b*S + p, :]
 template <typename T> dipaco_status launch_mean_pool(const T* x, float* out, int B, int S, int d, hipStream_t s);
 // out[b] = -sum_p nll[b*S + p]

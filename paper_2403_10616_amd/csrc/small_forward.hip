@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm_common.h"
 #include "kernels.h"
 
 namespace dipaco {
@@ -49,17 +50,46 @@ template <int COLS> struct Unit {
   }
 };
 
+// ---- weights of a later launch -----------------------------------------------------------------------------------
+// A product of a few rows waits for its weights, 1.5 us of a launch of 5 when they come from memory, and the launches before it leave half
+// of the compute units idle.  So these have workgroups behind their own that read a word of every 128-byte line of the weights that a
+// product one to three launches on will read, each XCD those of its own workgroups: lines stay in an XCD's L2 over the end of a kernel.  One
+// document through 12 blocks of 896, weights from memory 386 -> 332 us, with the last pass's still in the 256 MB cache 331 -> 326; lines
+// dealt to any XCD 347 and 346.  The output projection's weights, whose loads run under the attention, gain nothing from it (334).
+// Item v of that product's `items` (dealt to the XCDs in contiguous ranges) reads piece v / items_per_piece.
+__device__ __forceinline__ void touch(const WeightTiles& w, int block, int part, int parts) {
+  const int x = block % N_XCD, per = w.items / N_XCD, rem = w.items % N_XCD;
+  const int first = x * per + min(x, rem), last = first + per + (x < rem) - 1;
+  if (last < first) return;
+  const int p0 = first / w.items_per_piece, lines = (last / w.items_per_piece - p0 + 1) * w.piece_rows;
+  for (int i = part * (int)blockDim.x + threadIdx.x; i < lines; i += parts * (int)blockDim.x) {
+    const int q = i / w.piece_rows, piece = p0 + q, row_block = piece / w.pieces_n;
+    const int row = row_block * w.piece_rows + (i - q * w.piece_rows), col = 128 * (piece - row_block * w.pieces_n);
+    if (row < w.rows && col < w.row_bytes) (void)*reinterpret_cast<const volatile uint32_t*>(static_cast<const char*>(w.base) + (size_t)row * w.row_bytes + col);
+  }
+}
+// workgroups of `threads` for it, a line a thread
+static unsigned touch_blocks(const WeightTiles& w, int threads) {
+  if (!w.items) return 0;
+  const int lines = ((w.items + N_XCD - 1) / N_XCD / w.items_per_piece + 1) * w.piece_rows;
+  return N_XCD * ((lines + threads - 1) / threads);
+}
+
 // ---- C[rows, N] = x[rows, K] W[K, N] + bias, GELU -----------------------------------------------------------------
 constexpr int RP_WAVES = 7, RP_COLS = 32, RP_AHEAD = 4;
 constexpr int RP_LD = RP_COLS + 4;   // floats between rows of the waves' sums
 
 template <bool GELU>
 __global__ void __launch_bounds__(RP_WAVES * WAVE) rows_product_kernel(const bf16* __restrict__ x, const bf16* __restrict__ W,
-                                                                       const bf16* __restrict__ bias, bf16* __restrict__ out, int n_rows, int N, int K) {
+                                                                       const bf16* __restrict__ bias, bf16* __restrict__ out, int n_rows, int N, int K,
+                                                                       int tiles, WeightTiles ahead) {
+  if ((int)blockIdx.x >= tiles) return touch(ahead, blockIdx.x, (blockIdx.x - tiles) / N_XCD, (gridDim.x - tiles) / N_XCD);
   __shared__ __attribute__((aligned(16))) float red[RP_WAVES][SF_ROWS][RP_LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int n0 = blockIdx.x * RP_COLS, row0 = blockIdx.y * SF_ROWS, rows = min(SF_ROWS, n_rows - row0);
+  // neighbouring columns on one XCD: a 128-byte line of the weights holds two workgroups' columns, and each XCD that reads it fetches all of it
+  const int tile = xcd_contiguous(blockIdx.x, tiles), row_tiles = (n_rows + SF_ROWS - 1) / SF_ROWS, tile_n = tile / row_tiles;
+  const int n0 = tile_n * RP_COLS, row0 = (tile - tile_n * row_tiles) * SF_ROWS, rows = min(SF_ROWS, n_rows - row0);
   const int steps = (K + 31) / 32, s1 = (wave + 1) * steps / RP_WAVES;
   const int row = tid >> 3, col = 4 * (tid & 7);   // of the output: 256 threads of four columns each
   const bool on = row < rows && n0 + col < N;
@@ -132,12 +162,15 @@ constexpr int AO_LD = 64 + 4;
 
 // qkv [B S, 3 A] -> planes [ceil(H / 2)][B S, d]
 __global__ void __launch_bounds__(AO_WAVES * WAVE) attn_out_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ w_o,
-                                                                   float* __restrict__ planes, int S, int H, int d, int n_rows) {
+                                                                   float* __restrict__ planes, int S, int H, int d, int docs, int tiles,
+                                                                   WeightTiles ahead) {
+  if ((int)blockIdx.x >= tiles) return touch(ahead, blockIdx.x, (blockIdx.x - tiles) / N_XCD, (gridDim.x - tiles) / N_XCD);
   __shared__ __attribute__((aligned(16))) char o_[SF_ROWS * AO_ROW];
   __shared__ __attribute__((aligned(16))) float red[AO_STEPS][SF_ROWS][AO_LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4, A = H * AO_DH;
-  const int n0 = blockIdx.x * 64, head0 = blockIdx.y * AO_HEADS, doc = blockIdx.z;
+  const int item = xcd_contiguous(blockIdx.x, tiles), piece = item / docs, doc = item - piece * docs, cols = (d + 63) / 64, plane = piece / cols;
+  const int n0 = (piece - plane * cols) * 64, head0 = plane * AO_HEADS;
   if (wave < AO_ATT) {   // the arithmetic of attn_fwd_short_mfma<64>: probabilities rounded to bf16, sums of the rounded
     const int head = head0 + (wave >> 1), query = 16 * (wave & 1) + c;
     char* const o_row = o_ + query * AO_ROW + 2 * AO_DH * (wave >> 1);
@@ -223,7 +256,7 @@ __global__ void __launch_bounds__(AO_WAVES * WAVE) attn_out_kernel(const bf16* _
     const float4 v = *reinterpret_cast<const float4*>(&red[s][row][col]);
     y.x += v.x; y.y += v.y; y.z += v.z; y.w += v.w;
   }
-  *reinterpret_cast<float4*>(planes + ((size_t)blockIdx.y * n_rows + (size_t)doc * S + row) * d + n0 + col) = y;
+  *reinterpret_cast<float4*>(planes + ((size_t)(plane * docs + doc) * S + row) * d + n0 + col) = y;
 }
 
 }  // namespace
@@ -245,16 +278,23 @@ int attn_out_planes(int B, int S, int H, int d_head, int d) {
   return S <= SF_ROWS && (long)B * S <= SMALL_FORWARD_ROWS && (long)((d + 63) / 64) * planes * B <= AO_MOST ? planes : 0;
 }
 
-dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, hipStream_t s) {
-  const dim3 grid((N + RP_COLS - 1) / RP_COLS, (rows + SF_ROWS - 1) / SF_ROWS);
-  if (gelu) rows_product_kernel<true><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K);
-  else rows_product_kernel<false><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K);
+WeightTiles small_product_weights(const bf16* W, int rows, int N, int K) {   // two tiles' columns a line
+  const int row_tiles = (rows + SF_ROWS - 1) / SF_ROWS, tiles = (N + RP_COLS - 1) / RP_COLS;
+  return WeightTiles{W, 2 * N, K, tiles * row_tiles, 2 * row_tiles, K, (tiles + 1) / 2};
+}
+dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, const WeightTiles& ahead,
+                                   hipStream_t s) {
+  const int tiles = (N + RP_COLS - 1) / RP_COLS * ((rows + SF_ROWS - 1) / SF_ROWS);
+  const unsigned grid = tiles + touch_blocks(ahead, RP_WAVES * WAVE);
+  if (gelu) rows_product_kernel<true><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, ahead);
+  else rows_product_kernel<false><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, ahead);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
 
-dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, hipStream_t s) {
-  attn_out_kernel<<<dim3((d + 63) / 64, (H + AO_HEADS - 1) / AO_HEADS, B), AO_WAVES * WAVE, 0, s>>>(qkv, w_o, planes, S, H, d, B * S);
+dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, const WeightTiles& ahead, hipStream_t s) {
+  const int tiles = (d + 63) / 64 * ((H + AO_HEADS - 1) / AO_HEADS) * B;
+  attn_out_kernel<<<tiles + touch_blocks(ahead, AO_WAVES * WAVE), AO_WAVES * WAVE, 0, s>>>(qkv, w_o, planes, S, H, d, B, tiles, ahead);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
