@@ -185,25 +185,22 @@ static dipaco_status run_fwd_bwd(const dipaco_ctx* c, const T* W, const int* tok
     const LayerBufs& L = p.layers[l];
     const BlockOff& o = c->blocks[l];
     T* x_next = l + 1 < NL ? buf(p.layers[l + 1].x_in) : buf(p.x_final);
-    TRY(launch_layernorm_fwd<T>(buf(L.x_in), W + o.ln1_g, W + o.ln1_b, buf(L.h1), fbuf(L.mean1), fbuf(L.rstd1), T_, d,
-                                a.ln_eps, st));
-    TRY(gemm<T>(buf(L.h1), W + o.w_qkv, buf(L.qkv), T_, 3 * A, d, d, 3 * A, 3 * A, false, false, W + o.b_qkv, nullptr,
-                nullptr, nullptr, 0, false, 1, nullptr, st));
+    TRY(launch_norm_gemm<T>(buf(L.x_in), W + o.ln1_g, W + o.ln1_b, fbuf(L.mean1), fbuf(L.rstd1), a.ln_eps,
+                            gemm_args<T>(buf(L.h1), W + o.w_qkv, buf(L.qkv), T_, 3 * A, d, d, 3 * A, 3 * A, false, false, W + o.b_qkv, nullptr,
+                                         nullptr, nullptr, 0, false, 1, nullptr), st));
     TRY(launch_attention_fwd<T>(buf(L.qkv), buf(L.o), fbuf(L.lse), B, S, H, dh, st));
     TRY(gemm<T>(buf(L.o), W + o.w_o, buf(L.x_mid), T_, d, A, A, d, d, false, false, W + o.b_o, buf(L.x_in), nullptr,
                 nullptr, 0, false, 1, nullptr, st));
-    TRY(launch_layernorm_fwd<T>(buf(L.x_mid), W + o.ln2_g, W + o.ln2_b, buf(L.h2), fbuf(L.mean2), fbuf(L.rstd2), T_, d,
-                                a.ln_eps, st));
     // L.u receives GELU'(pre-activation), the only thing the backward pass needs of it
-    TRY(gemm<T>(buf(L.h2), W + o.w_up, buf(L.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, buf(L.u),
-                nullptr, 3, false, 1, nullptr, st));
+    TRY(launch_norm_gemm<T>(buf(L.x_mid), W + o.ln2_g, W + o.ln2_b, fbuf(L.mean2), fbuf(L.rstd2), a.ln_eps,
+                            gemm_args<T>(buf(L.h2), W + o.w_up, buf(L.act), T_, F, d, d, F, F, false, false, W + o.b_up, nullptr, buf(L.u),
+                                         nullptr, 3, false, 1, nullptr), st));
     TRY(gemm<T>(buf(L.act), W + o.w_down, x_next, T_, d, F, F, d, d, false, false, W + o.b_down, buf(L.x_mid), nullptr,
                 nullptr, 0, false, 1, nullptr, st));
   }
-  TRY(launch_layernorm_fwd<T>(buf(p.x_final), W + c->lnf_g, W + c->lnf_b, buf(p.y), fbuf(p.meanf), fbuf(p.rstdf), T_, d,
-                              a.ln_eps, st));
-  TRY(gemm<T>(buf(p.y), W + c->w_head, buf(p.logits), T_, V, d, d, V, V, false, false, nullptr, nullptr, nullptr,
-              nullptr, 0, false, 1, nullptr, st));
+  TRY(launch_norm_gemm<T>(buf(p.x_final), W + c->lnf_g, W + c->lnf_b, fbuf(p.meanf), fbuf(p.rstdf), a.ln_eps,
+                          gemm_args<T>(buf(p.y), W + c->w_head, buf(p.logits), T_, V, d, d, V, V, false, false, nullptr, nullptr, nullptr,
+                                       nullptr, 0, false, 1, nullptr), st));
   TRY(launch_softmax_xent<T>(buf(p.logits), targets, n_valid, nll, T_, V, true, st));
 
   // ---------------- backward ----------------

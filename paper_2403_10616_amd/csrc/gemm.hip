@@ -213,6 +213,20 @@ template <typename T> dipaco_status launch_gemm(const GemmArgs& a, hipStream_t s
   return launch_gemm_fit<T>(a, s);
 }
 
+template <typename T> dipaco_status launch_norm_gemm(const T* x, const T* gain, const T* shift, float* mean, float* rstd, float eps, const GemmArgs& a, hipStream_t s) {
+  if constexpr (std::is_same<T, float>::value) {
+    if (!g_forced_kernel && gemm_norm_takes(a)) {
+      GemmArgs rows = a;
+      rows.A = x;
+      if (dipaco_status st = check_gemm<T>(a)) return st;
+      if (dipaco_status st = check_gemm<T>(rows)) return st;
+      return launch_gemm_norm(rows, RowNorm{gain, shift, static_cast<float*>(const_cast<void*>(a.A)), mean, rstd, eps}, s);
+    }
+  }
+  if (dipaco_status st = launch_layernorm_fwd<T>(x, gain, shift, static_cast<T*>(const_cast<void*>(a.A)), mean, rstd, a.M, a.K, eps, s)) return st;
+  return launch_gemm<T>(a, s);
+}
+
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
   if (dipaco_status st = check_gemm<T>(dw)) return st;
   if (dipaco_status st = check_gemm<T>(dx)) return st;
@@ -221,6 +235,8 @@ template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const G
   return launch_gemm<T>(dx, s);
 }
 
+template dipaco_status launch_norm_gemm<float>(const float*, const float*, const float*, float*, float*, float, const GemmArgs&, hipStream_t);
+template dipaco_status launch_norm_gemm<bf16>(const bf16*, const bf16*, const bf16*, float*, float*, float, const GemmArgs&, hipStream_t);
 template dipaco_status launch_gemm_pair<float>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template dipaco_status launch_gemm_pair<bf16>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template dipaco_status launch_gemm<float>(const GemmArgs&, hipStream_t);

@@ -327,9 +327,13 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, (2 * Fit<T, TC, A_KC, B_KC, TM
 // take 16 of K each at a time, two such steps in flight; their sums meet in the epilogue.  Such a product is bound by its launch, one trip
 // to memory and the instructions in front of and behind it (2 - 3 ns each): the ring above costs a second trip through LDS, a
 // barrier and the arithmetic of its addresses.  Four waves for up to DIRECT_K (256 x 192 x 64 6.0 us there, 4.9 here; 256 x 64 x 64 6.5 | 4.7),
-// eight for twice that while 32 x 32 tiles make one round.
+// eight for twice that while 32 x 32 tiles make one round.  A step that lies inside the matrix has no clamps and one multiplication an operand
+// for its addresses: both products of a layer's backward pass 5.8 -> 5.2 us.
 constexpr int DIRECT_K = 128, DIRECT_G = 4;
-template <bool A_KC, bool B_KC, int TN, int G> __device__ __forceinline__ void direct_product(const GemmDev& g, int block) {
+// LN: A's rows go through a LayerNorm first, which the waves take together (each holds its K of the 32 rows): a launch of 2.8 us less in front of a
+// product that takes 5.2 us for 3.6 - 4.2 (256 x 64 -> 192; step of a 64-wide path on 256 tokens 155 -> 150 us).  The first column of tiles writes what the backward pass reads.
+template <bool A_KC, bool B_KC, int TN, int G, bool LN = false>
+__device__ __forceinline__ void direct_product(const GemmDev& g, int block, const RowNorm* ln = nullptr) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, kg = lane >> 4;
   const int tile_n = block / g.tiles_m, tile_m = block - tile_n * g.tiles_m;
@@ -343,11 +347,16 @@ template <bool A_KC, bool B_KC, int TN, int G> __device__ __forceinline__ void d
 #pragma unroll
   for (int j = 0; j < TN; ++j) rb[j] = (uint32_t)min(n0 + 16 * j + r, g.N - 1);
   const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
-  auto load = [&](auto KCc, const float* p, uint32_t ld, uint32_t row, int k, float (&v)[4]) {   // K k .. k + 3 of a row
+  auto load = [&](auto KCc, auto WHOLE, const float* p, uint32_t ld, uint32_t row, int k, float (&v)[4]) {   // K k .. k + 3 of a row
+    constexpr bool whole = decltype(WHOLE)::value;   // they lie inside the matrix
     if constexpr (decltype(KCc)::value) {   // K is a multiple of 4
-      const float4 x = *reinterpret_cast<const float4*>(p + (row * ld + (uint32_t)min(k, g.K - 4)));
-      const bool in = k < g.K;
+      const float4 x = *reinterpret_cast<const float4*>(p + (row * ld + (uint32_t)(whole ? k : min(k, g.K - 4))));
+      const bool in = whole || k < g.K;
       v[0] = in ? x.x : 0.f; v[1] = in ? x.y : 0.f; v[2] = in ? x.z : 0.f; v[3] = in ? x.w : 0.f;
+    } else if constexpr (whole) {
+      const uint32_t at = (uint32_t)k * ld + row;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = p[at + q * ld];
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -362,11 +371,88 @@ template <bool A_KC, bool B_KC, int TN, int G> __device__ __forceinline__ void d
   const FitAhead<float> early = fit_request<float, TN, 2, G>(g, tid, m0, n0);
 #pragma unroll
   for (int s = 0; s < AHEAD; ++s) {
-    const int k = 16 * (wave + G * s) + 4 * kg;
+    const int k0 = 16 * (wave + G * s), k = k0 + 4 * kg;   // k0: uniform
+    auto step = [&](auto WHOLE) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) load(std::bool_constant<A_KC>{}, A, lda, ra[i], k, a[s][i]);
+      for (int i = 0; i < 2; ++i) load(std::bool_constant<A_KC>{}, WHOLE, A, lda, ra[i], k, a[s][i]);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) load(std::bool_constant<B_KC>{}, B, ldb, rb[j], k, b[s][j]);
+      for (int j = 0; j < TN; ++j) load(std::bool_constant<B_KC>{}, WHOLE, B, ldb, rb[j], k, b[s][j]);
+    };
+    if (k0 + 16 <= g.K) {
+      step(std::true_type{});
+    } else if (k0 < g.K) {
+      step(std::false_type{});
+    } else {   // not multiplied
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[s][0][q] = a[s][1][q] = 0.f;
+    }
+  }
+  if constexpr (LN) {
+    static_assert(A_KC, "a lane holds four K of a row");
+    float4 gain[AHEAD], shift[AHEAD];
+    bool in[AHEAD];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {
+      const int k = 16 * (wave + G * s) + 4 * kg;
+      in[s] = k < g.K;
+      gain[s] = *reinterpret_cast<const float4*>(ln->gain + min(k, g.K - 4));
+      shift[s] = *reinterpret_cast<const float4*>(ln->shift + min(k, g.K - 4));
+    }
+    float* const part = reinterpret_cast<float*>(smem);   // [2][G][32]
+    auto row_mean = [&](float (&v)[2], int which) {   // over the row's lanes, then the waves in order
+      float* const p = part + which * 32 * G;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        v[i] += __shfl_xor(v[i], 16, WAVE);
+        v[i] += __shfl_xor(v[i], 32, WAVE);
+        if (kg == 0) p[32 * wave + 16 * i + r] = v[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        v[i] = p[16 * i + r];
+#pragma unroll
+        for (int w = 1; w < G; ++w) v[i] += p[32 * w + 16 * i + r];
+        v[i] /= g.K;
+      }
+    };
+    float mu[2] = {0.f, 0.f}, rs[2] = {0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)   // K beyond the row is zero
+#pragma unroll
+      for (int i = 0; i < 2; ++i) mu[i] += (a[s][i][0] + a[s][i][1]) + (a[s][i][2] + a[s][i][3]);
+    row_mean(mu, 0);
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+      if (in[s]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) { const float t = a[s][i][q] - mu[i]; rs[i] += t * t; }
+      }
+    row_mean(rs, 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) rs[i] = 1.0f / sqrtf(rs[i] + ln->eps);
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+      if (in[s]) {
+        const float gs[4] = {gain[s].x, gain[s].y, gain[s].z, gain[s].w}, bs[4] = {shift[s].x, shift[s].y, shift[s].z, shift[s].w};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) a[s][i][q] = (a[s][i][q] - mu[i]) * rs[i] * gs[q] + bs[q];
+          const int row = m0 + 16 * i + r;
+          if (tile_n == 0 && row < g.M)
+            *reinterpret_cast<float4*>(ln->y + (size_t)row * g.K + 16 * (wave + G * s) + 4 * kg) = make_float4(a[s][i][0], a[s][i][1], a[s][i][2], a[s][i][3]);
+        }
+      }
+    if (tile_n == 0 && wave == 0 && kg == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = m0 + 16 * i + r;
+        if (row < g.M) { ln->mean[row] = mu[i]; ln->rstd[row] = rs[i]; }
+      }
+    }
   }
   // each step in sums of its own, as many as the fitted tile's groups: one chain over both errs by a quarter more (K = 128, root mean
   // square, 1.25e-6 against 1.00e-6 on normal numbers) and is no faster
@@ -396,6 +482,9 @@ template <bool A_KC, bool B_KC, int TN, int G> __device__ __forceinline__ void d
 }
 template <bool A_KC, bool B_KC, int TN, int G> __global__ void __launch_bounds__(64 * G, 2) gemm_direct_kernel(const GemmDev g) {
   direct_product<A_KC, B_KC, TN, G>(g, blockIdx.x);
+}
+template <int TN> __global__ void __launch_bounds__(64 * DIRECT_G, 2) gemm_direct_norm_kernel(const GemmDev g, const RowNorm ln) {
+  direct_product<true, false, TN, DIRECT_G, true>(g, blockIdx.x, &ln);
 }
 
 // The two products of a linear layer's backward pass, X^T dY (blocks 0 .. first - 1) and dY W^T, in one launch of 32 x 64 tiles.
@@ -652,6 +741,22 @@ WeightTiles raw_product_weights(const bf16* W, int rows, int N, int K) {   // ru
   using F = Fit<bf16, bf16, true, false, 2, 4, 1, 1, 8, 3>;
   const int splits = gemm_raw_splits(rows, N, K, true), steps = (K + F::BK - 1) / F::BK, tiles_m = (rows + F::BM - 1) / F::BM, tiles_n = (N + F::BN - 1) / F::BN;
   return WeightTiles{W, 2 * N, K, tiles_m * tiles_n * splits, tiles_m, (steps + splits - 1) / splits * F::BK, tiles_n};
+}
+
+// A product behind a LayerNorm in one launch with it: while one round of workgroups holds the product, each of which normalises its rows
+bool gemm_norm_takes(const GemmArgs& a) {
+  return !a.out_f32 && !a.trans_a && !a.trans_b && a.lda == a.K && std::max(1, a.splits) == 1 && !g_forced_fit &&
+         shape_tiles(1, a.M, a.N, false) <= 256 && direct_takes(a, true, false, DIRECT_K) && pick_fit(a.M, a.N, a.K, 1, false, true, false) == 1;
+}
+dipaco_status launch_gemm_norm(const GemmArgs& a, const RowNorm& ln, hipStream_t s) {
+  auto run = [&](auto TNc) -> dipaco_status {
+    constexpr int TN = decltype(TNc)::value;
+    const GemmDev g = fit_dev<DirectTile<TN>>(a);
+    gemm_direct_norm_kernel<TN><<<g.tiles_m * g.tiles_n, 64 * DIRECT_G, fit_epilogue_bytes(2, TN, 1, 1, DIRECT_G), s>>>(g, ln);
+    DIPACO_LAUNCH_CHECK();
+    return DIPACO_OK;
+  };
+  return narrow_tiles(a.M, a.N) <= 256 ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 4>{});
 }
 
 size_t gemm_raw_plane_floats(int M, int N, int K, bool bf16_operands) {

@@ -119,6 +119,10 @@ struct GemmArgs {
 size_t gemm_colsum_partial_floats(int M, int N);
 template <typename T> dipaco_status launch_gemm(const GemmArgs& g, hipStream_t s);
 // X^T dY and dY W^T of a linear layer: neither reads what the other writes
+// gemm_fit.hip: C = LayerNorm(A) B with epilogue in fp32, A [M, K] rows as they lie; y, mean and rstd as launch_layernorm_fwd leaves them
+struct RowNorm { const float* gain; const float* shift; float* y; float* mean; float* rstd; float eps; };
+bool gemm_norm_takes(const GemmArgs& g);
+dipaco_status launch_gemm_norm(const GemmArgs& g, const RowNorm& ln, hipStream_t s);   // of checked arguments
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
 // gemm_dlds.hip: bf16, 256x256 tiles loaded from global memory straight into LDS; takes the shapes for which
 // gemm_dlds_eligible holds (whole K tiles of 32, 16-byte rows); launch_gemm routes to it by itself
@@ -173,6 +177,9 @@ dipaco_status launch_embed(const T* tok_emb, const T* pos_emb, const int* tokens
 template <typename T>
 dipaco_status launch_layernorm_fwd(const T* x, const T* g, const T* b, T* y, float* mean, float* rstd, int rows,
                                    int d, float eps, hipStream_t s);
+// the same into a.A, the rows of the product C = a.A B behind it, and that product; one launch where gemm_norm_takes it
+template <typename T>
+dipaco_status launch_norm_gemm(const T* x, const T* gain, const T* shift, float* mean, float* rstd, float eps, const GemmArgs& a, hipStream_t s);
 // x = sum of n_planes fp32 planes [rows, d] + bias + resid, rounded to T;  y (nullable, with g and b) = LayerNorm of x as stored
 template <typename T>
 dipaco_status launch_sum_layernorm(const float* planes, int n_planes, const T* bias, const T* resid, T* x, const T* g, const T* b,

@@ -134,6 +134,34 @@ def test_both_products_of_a_small_layers_backward_pass_in_one_launch(name, B, S,
     assert rel_l2(grads[0], grads[1]) <= 1e-5
 
 
+@pytest.mark.parametrize("d,B,S", [(8, 1, 1), (16, 3, 11), (40, 1, 33), (64, 4, 64), (120, 2, 48), (128, 5, 50), (136, 2, 40)])
+def test_layernorm_inside_the_product_behind_it(d, B, S):
+    """fp32, rows of up to 128: the waves of a product normalise its rows.  A forced tile takes a LayerNorm launch instead; sums in another order
+    differ by a few 2^-24 each, 1e-5 between them and 1e-4 to the oracle as everywhere."""
+    cfg = dict(layers_per_level=(1, 1), d_model=d, n_heads=2, d_head=32, d_mlp=4 * d, vocab=72, max_seq=64)
+    a, ctx = make_arch(cfg, dp.F32)
+    lay = orc.param_layout(a)
+    theta = gen.random_params(orc.param_count(a), seed=5, scale=0.08)
+    for n_, (off, shape, _) in lay.items():
+        if n_.endswith("_g"):
+            theta[off:off + shape[0]] += 1.0
+    tok, tgt = _batch(cfg, B, S, seed=6)
+    grads, losses = [], []
+    for tile in (0, 1):
+        dp.dipaco_k_set_gemm_tile(tile)
+        try:
+            st = PathState(ctx, theta, B, S)
+            losses.append(st.fwd_bwd(tok, tgt))
+            grads.append(host(st.grads).copy())
+        finally:
+            dp.dipaco_k_set_gemm_tile(0)
+    o_loss, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
+    assert abs(losses[0] - o_loss) <= 1e-5 * abs(o_loss)
+    worst, where = per_tensor_rel(lay, grads[0], o_grad)
+    assert worst <= 1e-4, (where, worst)
+    assert rel_l2(grads[0], grads[1]) <= 1e-5
+
+
 def test_config1_full_round_matches_oracle():
     """Tiny 2x2 grid, fp32: compose -> 2 inner AdamW steps on each of the 4 paths -> outer Nesterov step of the
     4 block modules (2 paths each) and of the stem and head (shared by all 4 paths)."""
