@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "attention_plain.h"
+#include "causal_order.h"
 #include "kernels.h"
 #include "mma_tile.h"
 
@@ -157,14 +158,15 @@ __device__ __forceinline__ void block_column_sums(const f32x4 (&acc)[DH / 16], f
 
 template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW, 2) attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ o,
-                                                             float* __restrict__ lse, int S, int H) {
+                                                             float* __restrict__ lse, int S, int H, bool paired) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
   constexpr int STAGE = 2 * tile_floats<DH>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
-  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const CausalPlace at = causal_place(paired);
+  const int bh = at.bh, b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
-  const int q0 = (gridDim.y - 1 - blockIdx.y) * (16 * NW);   // longest blocks first
+  const int q0 = ((int)gridDim.y - 1 - at.order) * (16 * NW);
   const int qw0 = q0 + 16 * wave, q = qw0 + m;
   const RowFrag<DH> qf = load_row<DH>(base + (long)q * ld, g, q < S);
   const int ntiles = (min(S, q0 + (16 * NW)) + F_TILE - 1) / F_TILE;
@@ -237,11 +239,11 @@ template <int DH> __device__ __forceinline__ float row_dot(const RowFrag<DH>& a,
 template <int DH, int NW>
 __device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
                                          const float* __restrict__ lse, float* __restrict__ dqkv, float* __restrict__ dsum,
-                                         float* __restrict__ colsum, int S, int H, int qb, int n_blocks) {
+                                         float* __restrict__ colsum, int S, int H, int bh, int qb, int n_blocks) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][K | V]
   constexpr int STAGE = 2 * tile_floats<DH>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
-  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const int b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
   const int q0 = qb * (16 * NW);
@@ -292,11 +294,11 @@ __device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const fl
 template <int DH, int NW, bool OWN_D>
 __device__ __forceinline__ void dkv_block(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
                                           const float* __restrict__ lse, const float* __restrict__ dsum, float* __restrict__ dqkv,
-                                          float* __restrict__ colsum, int S, int H, int kb, int n_blocks) {
+                                          float* __restrict__ colsum, int S, int H, int bh, int kb, int n_blocks) {
   extern __shared__ __attribute__((aligned(16))) float f_smem[];   // [stage][Q | dO | lse | D]
   constexpr int STAGE = 2 * tile_floats<DH>() + 2 * F_TILE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
-  const int bh = blockIdx.x, b = bh / H, hd = bh % H, A = H * DH;
+  const int b = bh / H, hd = bh % H, A = H * DH;
   const long ld = 3L * A;
   const float* base = qkv + (long)b * S * ld + hd * DH;
   const float* gbase = d_o + (long)b * S * A + hd * DH;
@@ -383,15 +385,17 @@ template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
                                                                 const float* __restrict__ d_o, const float* __restrict__ lse,
                                                                 float* __restrict__ dqkv, float* __restrict__ dsum,
-                                                                float* __restrict__ colsum, int S, int H) {
-  dq_block<DH, NW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, gridDim.y - 1 - blockIdx.y, gridDim.y);
+                                                                float* __restrict__ colsum, int S, int H, bool paired) {
+  const CausalPlace at = causal_place(paired);
+  dq_block<DH, NW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, at.bh, (int)gridDim.y - 1 - at.order, gridDim.y);
 }
 template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                                  const float* __restrict__ lse, const float* __restrict__ dsum,
                                                                  float* __restrict__ dqkv, float* __restrict__ colsum, int S,
-                                                                 int H) {
-  dkv_block<DH, NW, false>(qkv, nullptr, d_o, lse, dsum, dqkv, colsum, S, H, blockIdx.y, gridDim.y);
+                                                                 int H, bool paired) {
+  const CausalPlace at = causal_place(paired);
+  dkv_block<DH, NW, false>(qkv, nullptr, d_o, lse, dsum, dqkv, colsum, S, H, at.bh, at.order, gridDim.y);
 }
 // Sequences of one block (up to 64 positions on four waves): dQ and dK / dV in one launch, one workgroup each (blockIdx.y), as
 // such launches take as long as any launch: 4 x 2 heads x 64 x 32 6.6 + 7.0 us and a gap, 8.2 in one.
@@ -400,8 +404,8 @@ __global__ void __launch_bounds__(64 * F_FEW, 2) attn_bwd_short_f32(const float*
                                                                       const float* __restrict__ d_o, const float* __restrict__ lse,
                                                                       float* __restrict__ dqkv, float* __restrict__ dsum,
                                                                       float* __restrict__ colsum, int S, int H) {
-  if (blockIdx.y == 0) dkv_block<DH, F_FEW, true>(qkv, o, d_o, lse, nullptr, dqkv, colsum, S, H, 0, 1);
-  else dq_block<DH, F_FEW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, 0, 1);
+  if (blockIdx.y == 0) dkv_block<DH, F_FEW, true>(qkv, o, d_o, lse, nullptr, dqkv, colsum, S, H, blockIdx.x, 0, 1);
+  else dq_block<DH, F_FEW>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, blockIdx.x, 0, 1);
 }
 
 template <int DH> constexpr int fwd_lds() { return 2 * 2 * tile_floats<DH>() * (int)sizeof(float); }
@@ -415,8 +419,11 @@ dipaco_status fwd_rows(const float* qkv, float* o, float* lse, int B, int S, int
   const int step = attention_launch_batch(B, H);
   for (int b = 0; b < B; b += step) {
     const size_t row = (size_t)b * S;
-    attn_fwd_f32<DH, NW><<<dim3(std::min(step, B - b) * H, (S + 16 * NW - 1) / (16 * NW)), 64 * NW, fwd_lds<DH>(), s>>>(
-        qkv + row * 3 * A, o + row * A, lse + row * H, S, H);
+    const dim3 grid(std::min(step, B - b) * H, (S + 16 * NW - 1) / (16 * NW));
+    static std::atomic<int> resident{0};
+    bool paired;
+    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_fwd_f32<DH, NW>), 64 * NW, fwd_lds<DH>(), (long)grid.x * grid.y, resident, paired)) return st;
+    attn_fwd_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, lse + row * H, S, H, paired);
     DIPACO_LAUNCH_CHECK();
   }
   return DIPACO_OK;
@@ -449,11 +456,16 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
         continue;
       }
     }
+    static std::atomic<int> dq_resident{0}, dkv_resident{0};
+    bool dq_paired, dkv_paired;
+    const long n = (long)grid.x * grid.y;
+    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>), 64 * NW, fwd_lds<DH>(), n, dq_resident, dq_paired)) return st;
+    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>), 64 * NW, dkv_lds<DH>(), n, dkv_resident, dkv_paired)) return st;
     attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
-                                                                 dqkv + row * 3 * A, dsum + row * H, cs, S, H);
+                                                                 dqkv + row * 3 * A, dsum + row * H, cs, S, H, dq_paired);
     DIPACO_LAUNCH_CHECK();
     attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv + row * 3 * A, d_o + row * A, lse + row * H, dsum + row * H,
-                                                                  dqkv + row * 3 * A, cs, S, H);
+                                                                  dqkv + row * 3 * A, cs, S, H, dkv_paired);
     DIPACO_LAUNCH_CHECK();
   }
   return DIPACO_OK;

@@ -623,6 +623,16 @@ def test_fp32_attention_above_512_blocks(B, S, H, dh):
     test_attention_forward_backward(dp.F32, B, S, H, dh, 1)
 
 
+@pytest.mark.parametrize("B,S,H,dh", [(16, 130, 5, 64), (43, 100, 3, 32), (16, 200, 8, 32), (19, 330, 3, 64), (24, 450, 4, 64), (8, 257, 17, 32), (64, 200, 4, 32), (8, 320, 13, 128)])
+def test_fp32_attention_of_blocks_that_are_resident_at_once(B, S, H, dh):
+    """240 to 1024 workgroups of 64 positions: one round of the compute units, one more than one, two, a ragged third, four; each block is taken
+    once, whatever its place."""
+    blocks = B * H * -(-S // 64)
+    print(f"{blocks} workgroups", flush=True)
+    assert B * H * -(-S // 128) <= 512 and 240 <= blocks <= 1024
+    test_attention_forward_backward(dp.F32, B, S, H, dh, 1)
+
+
 @pytest.mark.parametrize("B,S,H,dh", [(3, 32, 3, 64), (5, 17, 1, 64), (2, 32, 3, 128), (1, 5, 1, 128), (5, 32, 1, 32), (1, 33, 1, 64)])
 def test_attention_of_short_sequences(B, S, H, dh):
     """Up to 32 positions a wave owns a sequence and head: full and ragged workgroups of four, every head size; 33 is the first
