@@ -349,6 +349,21 @@ inline bool two_groups(int B, int H, int S) {
   const long nqb = (S + 127) / 128, blocks = (long)B * H * nqb;
   return nqb >= 4 && 10 * blocks * (nqb + 1) <= 9 * 512 * nqb;
 }
+// dQ and dK / dV in one launch, behind one that takes their statistics (4 us): each alone ends with its longest blocks, on
+// compute units that hold little else; together the one's blocks run beside the other's.  us, two launches -> one: 42 heads x 1000 x 64 50.7 -> 42.0, 64 x 512 x
+// 128 62.6 -> 53.0, 16 x 900 x 64 36.1 -> 24.2, 24 x 180 x 64 15.5 -> 12.0, 512 x 512 x 64 146 -> 130, 1792 x 256 x 64 215 -> 195; level at
+// 448 x 1024 (3584 blocks; 324), behind at 224 x 2048 (3584) 504 -> 521 and 512 x 1024 x 32 297 -> 302: dQ alone has three waves a SIMD, not two.
+inline bool bwd_one_launch(int B, int H, int S) {
+  const long nqb = (S + 127) / 128;
+  return nqb <= 4 || (long)B * H * nqb <= 3072;
+}
+// Two groups a block there while that is less than a workgroup of each kind a compute unit: one | two groups 14 x 1900 x 64 54.9 | 44.0, 14 x 2048 x 128
+// 135 | 105, 16 x 900 x 64 28.0 | 24.2, 32 x 384 x 32 14.3 | 13.1; 64 x 512 (256 blocks) x 64 22.0 | 23.3, x 128 53.2 | 53.8; 42 x 1000 42.0 | 48.0; of two
+// blocks 24 x 180 x 64 12.0 | 12.3.
+inline bool one_launch_two_groups(int B, int H, int S) {
+  const long nqb = (S + 127) / 128;
+  return nqb >= 3 && (long)B * H * nqb < 256;
+}
 template <int N> __device__ __forceinline__ void hand_over(const f32x16 (&v)[N], float* at, int lane) {   // at: this wave's 16 N x 64 floats
 #pragma unroll
   for (int n = 0; n < N; ++n)
@@ -612,12 +627,43 @@ __global__ void __launch_bounds__(AT_THREADS, DH == 128 ? 1 : 3) attn_fwd_short_
   if (h == 0 && r < S) lse[(long)bh * S + r] = (m + __builtin_amdgcn_logf(l)) * LN2;   // v_log_f32 is log2
 }
 
-// ---- backward, dQ (also writes D = rowsum(dO * O)) --------------------------------------------------------------
-template <int DH, int NG>
-__global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
-                                                                  const bf16* __restrict__ d_o,
-                                                                  const float* __restrict__ lse, bf16* __restrict__ dqkv,
-                                                                  float* __restrict__ dsum, float* __restrict__ colsum, int S, int H, int single) {
+// ---- backward: D = rowsum(dO * O) and -lse log2(e) of every query ------------------------------------------------------
+// For the dQ and the dK / dV blocks, in rows padded to whole query blocks: D is 0 and -lse log2(e) is -inf (probability 0) beyond S, so that those
+// need neither a bounds check nor a rescale.  One workgroup a block of 128 queries of a head.
+template <int DH>
+__global__ void __launch_bounds__(AT_THREADS) attn_stats_mfma(const bf16* __restrict__ o, const bf16* __restrict__ d_o, const float* __restrict__ lse,
+                                                             float* __restrict__ dsum, int S, int H) {
+  constexpr int LANES = DH / 8, ROWS = WAVE / LANES;   // lanes of a query, queries of a wave at a time
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bh = blockIdx.x, b = bh / H, hd = bh - b * H;
+  const long Sp = (long)gridDim.y * 128;
+  const int c = 8 * (lane % LANES);
+#pragma unroll
+  for (int i = 0; i < 32 / ROWS; ++i) {
+    const int q = blockIdx.y * 128 + 32 * wave + ROWS * i + lane / LANES;
+    float D = 0.f;
+    if (q < S) {
+      const size_t at = ((size_t)b * S + q) * H * DH + hd * DH + c;
+      const uint4 gv = *reinterpret_cast<const uint4*>(d_o + at), ov = *reinterpret_cast<const uint4*>(o + at);
+      const bf16* gp = reinterpret_cast<const bf16*>(&gv);
+      const bf16* op = reinterpret_cast<const bf16*>(&ov);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) D += (float)gp[e] * (float)op[e];
+    }
+#pragma unroll
+    for (int m = 1; m < LANES; m <<= 1) D += __shfl_xor(D, m, WAVE);
+    if (lane % LANES == 0) {
+      dsum[bh * Sp + q] = D;
+      dsum[(gridDim.x + bh) * Sp + q] = q < S ? -lse[(long)bh * S + q] * LOG2E : -INFINITY;
+    }
+  }
+}
+
+// ---- backward, dQ ---------------------------------------------------------------------------------------------------
+// STATS: attn_stats_mfma has written dsum; else this takes D itself and leaves both for the dK / dV kernel
+template <int DH, int NG, bool STATS>
+__device__ __forceinline__ void dq_blocks(const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ d_o,
+                                          const float* __restrict__ lse, bf16* __restrict__ dqkv, float* __restrict__ dsum,
+                                          float* __restrict__ colsum, int S, int H, int single, int bh, int n_bh, int bx) {
   constexpr int NS = DQ_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   __shared__ float cs_red[4][DH];
   extern __shared__ __attribute__((aligned(16))) char dq_smem[];   // [group][stage][K | V]
@@ -625,9 +671,7 @@ __global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf1
   const int grp = NG == 1 ? 0 : wave_all >> 2, wave = NG == 1 ? wave_all : wave_all & 3;
   char (*smem)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(dq_smem) + grp * NS;
   const int r = lane & 31, h = lane >> 5;
-  const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
-  const int n_bh = single ? gridDim.x : gridDim.y;
-  const int bx = single ? (int)blockIdx.y : (int)blockIdx.x;   // single: one block per workgroup, longest first
+  const int b = bh / H, hd = bh % H;
   const int A = H * DH;
   const long ld = 3L * A;
   const bf16* base = qkv + (long)b * S * ld + hd * DH;
@@ -654,24 +698,30 @@ __global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf1
     if (q < S) {
       qf[ks] = *reinterpret_cast<const uint4*>(base + (long)q * ld + c);
       gf[ks] = *reinterpret_cast<const uint4*>(d_o + ((long)b * S + q) * A + hd * DH + c);
-      const uint4 ov = *reinterpret_cast<const uint4*>(o + ((long)b * S + q) * A + hd * DH + c);
-      const bf16* gp = reinterpret_cast<const bf16*>(&gf[ks]);
-      const bf16* op = reinterpret_cast<const bf16*>(&ov);
+      if constexpr (!STATS) {
+        const uint4 ov = *reinterpret_cast<const uint4*>(o + ((long)b * S + q) * A + hd * DH + c);
+        const bf16* gp = reinterpret_cast<const bf16*>(&gf[ks]);
+        const bf16* op = reinterpret_cast<const bf16*>(&ov);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) D += (float)gp[i] * (float)op[i];
+        for (int i = 0; i < 8; ++i) D += (float)gp[i] * (float)op[i];
+      }
     } else {
       qf[ks] = make_uint4(0, 0, 0, 0);
       gf[ks] = make_uint4(0, 0, 0, 0);
     }
   }
-  D += __shfl_xor(D, 32, WAVE);
-  const float nlse2 = q < S ? -lse[(long)bh * S + q] * LOG2E : -INFINITY;
-  // per-query statistics for the dK / dV kernel, in rows padded to whole query blocks: D (0 beyond S) and
-  // -lse * log2(e) (-inf beyond S: probability 0), so that kernel needs neither a bounds check nor a rescale
-  if (h == 0 && grp == 0) {
-    const long Sp = (long)nqb * 128;
-    dsum[bh * Sp + q] = q < S ? D : 0.f;
-    dsum[(long)n_bh * Sp + bh * Sp + q] = nlse2;
+  const long Sp = (long)nqb * 128;
+  float nlse2;
+  if constexpr (STATS) {
+    D = dsum[bh * Sp + q];
+    nlse2 = dsum[(n_bh + bh) * Sp + q];
+  } else {
+    D += __shfl_xor(D, 32, WAVE);
+    nlse2 = q < S ? -lse[(long)bh * S + q] * LOG2E : -INFINITY;
+    if (h == 0 && grp == 0) {
+      dsum[bh * Sp + q] = q < S ? D : 0.f;
+      dsum[(n_bh + bh) * Sp + q] = nlse2;
+    }
   }
 
   const int kv_end = min(S, q0 + 128);
@@ -742,10 +792,8 @@ __global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf1
 template <int DH> constexpr int dkv_stage() { return 2 * tile_bytes<DH>() + 2 * 64 * (int)sizeof(float); }   // Q | dO | -lse2 | D
 
 template <int DH, int NG>
-__global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv,
-                                                                   const bf16* __restrict__ d_o,
-                                                                   const float* __restrict__ dsum,
-                                                                   bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H, int single) {
+__device__ __forceinline__ void dkv_blocks(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o, const float* __restrict__ dsum,
+                                           bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H, int single, int bh, int n_bh, int bx) {
   constexpr int NS = DKV_STAGES, KS = DH / 16, DT = DH / 32, TILE_BYTES = tile_bytes<DH>(), LPW = 4 * panels<DH>();
   constexpr int DKV_STAGE = dkv_stage<DH>();
   __shared__ float cs_red[4][DH];
@@ -754,9 +802,7 @@ __global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) 
   const int grp = NG == 1 ? 0 : wave_all >> 2, wave = NG == 1 ? wave_all : wave_all & 3;
   char* const dkv_smem = dkv_rings + grp * NS * DKV_STAGE;
   const int r = lane & 31, h = lane >> 5;
-  const int bh = single ? blockIdx.x : blockIdx.y, b = bh / H, hd = bh % H;
-  const int n_bh = single ? gridDim.x : gridDim.y;
-  const int bx = single ? (int)blockIdx.y : (int)blockIdx.x;   // single: one block per workgroup, longest first
+  const int b = bh / H, hd = bh % H;
   const int A = H * DH;
   const long ld = 3L * A;
   const bf16* base = qkv + (long)b * S * ld + hd * DH;
@@ -766,7 +812,7 @@ __global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) 
   const uint32_t smem_addr = (uint32_t)(uintptr_t)dkv_rings + grp * NS * DKV_STAGE;
   const int nkb = (S + 127) / 128;
   const int ntiles = (S + 63) / 64;
-  // Statistics of a tile's 64 queries (written by the dQ kernel into rows padded to whole query blocks): waves 0
+  // Statistics of a tile's 64 queries (in rows padded to whole query blocks): waves 0
   // and 2 fetch -lse*log2(e), waves 1 and 3 fetch D, one float per lane; the duplicates keep every wave's count of
   // outstanding loads the same.
   const long Sp = (long)nkb * 128;
@@ -893,6 +939,29 @@ __global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) 
   }
 }
 
+// one block per workgroup, longest first (single), or a long and a short one
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_dq_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ d_o,
+                                                                  const float* __restrict__ lse, bf16* __restrict__ dqkv, float* __restrict__ dsum,
+                                                                  float* __restrict__ colsum, int S, int H, int single) {
+  dq_blocks<DH, NG, false>(qkv, o, d_o, lse, dqkv, dsum, colsum, S, H, single, single ? blockIdx.x : blockIdx.y, single ? gridDim.x : gridDim.y,
+                           single ? (int)blockIdx.y : (int)blockIdx.x);
+}
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, NG == 1 && DH == 32 ? 3 : 2) attn_bwd_dkv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
+                                                                   const float* __restrict__ dsum, bf16* __restrict__ dqkv,
+                                                                   float* __restrict__ colsum, int S, int H, int single) {
+  dkv_blocks<DH, NG>(qkv, d_o, dsum, dqkv, colsum, S, H, single, single ? blockIdx.x : blockIdx.y, single ? gridDim.x : gridDim.y,
+                     single ? (int)blockIdx.y : (int)blockIdx.x);
+}
+// Both in one launch, behind attn_stats_mfma: grid (heads, 2 x blocks), longest first
+template <int DH, int NG>
+__global__ void __launch_bounds__(AT_THREADS * NG, 2) attn_bwd_both_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o, float* __restrict__ dsum,
+                                                                    bf16* __restrict__ dqkv, float* __restrict__ colsum, int S, int H) {
+  if (blockIdx.y & 1) dq_blocks<DH, NG, true>(qkv, nullptr, d_o, nullptr, dqkv, dsum, colsum, S, H, 1, blockIdx.x, gridDim.x, blockIdx.y >> 1);
+  else dkv_blocks<DH, NG>(qkv, d_o, dsum, dqkv, colsum, S, H, 1, blockIdx.x, gridDim.x, blockIdx.y >> 1);
+}
+
 }  // namespace
 
 template <int DH>
@@ -926,6 +995,7 @@ dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf
                                         hipStream_t s, SumBatch* batch) {
   const int single = attention_single_block();
   const int nqb = (S + 127) / 128;
+  const bool one = single && bwd_one_launch(B, H, S);
   const size_t A = (size_t)H * DH;
   const int step = attention_launch_batch(B, H);
   auto run = [&](auto NGc) -> dipaco_status {
@@ -938,6 +1008,16 @@ dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf
       const int n_bh = std::min(step, B - b) * H;
       dim3 grid = single ? dim3(n_bh, nqb) : dim3((nqb + 1) / 2, n_bh);   // one or two query (key) blocks per workgroup
       float* const cs = colsum_out ? colsum_partial + (size_t)b * nqb * 3 * A : nullptr;
+      if (one) {
+        constexpr int LDS = DQ_LDS > DKV_LDS ? DQ_LDS : DKV_LDS;
+        static std::atomic<unsigned long long> both_lds{0};
+        if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_both_mfma<DH, NG>), LDS, both_lds)) return st;
+        attn_stats_mfma<DH><<<grid, AT_THREADS, 0, s>>>(o + row * A, d_o + row * A, lse + row * H, dsum, S, H);
+        DIPACO_LAUNCH_CHECK();
+        attn_bwd_both_mfma<DH, NG><<<dim3(n_bh, 2 * nqb), AT_THREADS * NG, LDS, s>>>(qkv + row * 3 * A, d_o + row * A, dsum, dqkv + row * 3 * A, cs, S, H);
+        DIPACO_LAUNCH_CHECK();
+        continue;
+      }
       attn_bwd_dq_mfma<DH, NG><<<grid, AT_THREADS * NG, DQ_LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
                                                                      dqkv + row * 3 * A, dsum, cs, S, H, single);
       DIPACO_LAUNCH_CHECK();
@@ -946,7 +1026,7 @@ dipaco_status launch_attention_bwd_mfma(const bf16* qkv, const bf16* o, const bf
     }
     return DIPACO_OK;
   };
-  if (dipaco_status st = two_groups(B, H, S) ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 1>{})) return st;
+  if (dipaco_status st = (one ? one_launch_two_groups(B, H, S) : two_groups(B, H, S)) ? run(std::integral_constant<int, 2>{}) : run(std::integral_constant<int, 1>{})) return st;
   if (colsum_out) return launch_sum_rows(colsum_partial, colsum_out, B * nqb, 3 * H * DH, s, batch);
   return DIPACO_OK;
 }

@@ -623,6 +623,14 @@ def test_fp32_attention_above_512_blocks(B, S, H, dh):
     test_attention_forward_backward(dp.F32, B, S, H, dh, 1)
 
 
+@pytest.mark.parametrize("B,S,H,dh", [(5, 257, 17, 32), (2, 300, 43, 64), (1, 385, 3, 128), (4, 200, 3, 64), (3, 129, 2, 32), (32, 128, 9, 64), (4, 512, 16, 64),
+                                      (3, 600, 17, 128), (65, 513, 10, 32)])
+def test_bf16_attention_gradients_in_one_launch_and_in_two(B, S, H, dh):
+    """One block of 128 positions to five; 255, 256 and 258 blocks, on the two sides of two groups a block; 3250 blocks of long sequences take two launches."""
+    print(f"{B * H * -(-S // 128)} blocks", flush=True)
+    test_attention_forward_backward(dp.BF16, B, S, H, dh, 1)
+
+
 @pytest.mark.parametrize("B,S,H,dh", [(16, 130, 5, 64), (43, 100, 3, 32), (16, 200, 8, 32), (19, 330, 3, 64), (24, 450, 4, 64), (8, 257, 17, 32), (64, 200, 4, 32), (8, 320, 13, 128)])
 def test_fp32_attention_of_blocks_that_are_resident_at_once(B, S, H, dh):
     """240 to 1024 workgroups of 64 positions: one round of the compute units, one more than one, two, a ragged third, four; each block is taken
