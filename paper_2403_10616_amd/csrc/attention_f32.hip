@@ -235,7 +235,7 @@ template <int DH> __device__ __forceinline__ float row_dot(const RowFrag<DH>& a,
   return sum_groups(d);
 }
 
-// dQ_i = scale * sum_{j<=i} p_ij (dO_i.v_j - D_i) k_j, with D_i = dO_i.o_i (also stored for the dK/dV kernel)
+// dQ_i = scale * sum_{j<=i} p_ij (dO_i.v_j - D_i) k_j, with D_i = dO_i.o_i (stored for a dK/dV kernel behind it unless dsum is null)
 template <int DH, int NW>
 __device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
                                          const float* __restrict__ lse, float* __restrict__ dqkv, float* __restrict__ dsum,
@@ -253,7 +253,7 @@ __device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const fl
   const RowFrag<DH> gf = load_row<DH>(d_o + orow, g, q < S);
   const float D = row_dot<DH>(gf, load_row<DH>(o + orow, g, q < S));
   const float L = q < S ? lse[(long)bh * S + q] : INFINITY;   // +inf beyond the sequence: probability 0
-  if (g == 0 && q < S) dsum[(long)bh * S + q] = D;
+  if (dsum && g == 0 && q < S) dsum[(long)bh * S + q] = D;
   const int ntiles = (min(S, q0 + (16 * NW)) + F_TILE - 1) / F_TILE;
   f32x4 dqt[DH / 16];
   zero_acc<DH>(dqt);
@@ -397,6 +397,28 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
   const CausalPlace at = causal_place(paired);
   dkv_block<DH, NW, false>(qkv, nullptr, d_o, lse, dsum, dqkv, colsum, S, H, at.bh, at.order, gridDim.y);
 }
+// Both in one launch on four waves a block, behind one that takes D_i (by the arithmetic of dq_block: the same bits): each alone ends with its longest
+// blocks.  us, two launches -> one: 64 heads x 500 x 64 102 -> 91, x 32 60.8 -> 50.1, x 128 178 -> 162, 24 x 180 x 64 37.8 -> 24.1, 4 x 1000 x 64 170 ->
+// 100, 32 x 2000 x 64 549 -> 531; 256 x 250 x 128 (1024 blocks) 193 -> 198, and on eight waves 1 - 5 % behind (512 x 130 x 64 111 -> 116).
+constexpr long ONE_LAUNCH_WIDE = 512;   // most blocks with head size 128
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW) attn_stats_f32(const float* __restrict__ o, const float* __restrict__ d_o, float* __restrict__ dsum, int S, int H) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
+  const int bh = blockIdx.x, b = bh / H, hd = bh % H, q = blockIdx.y * (16 * NW) + 16 * wave + m;
+  const long orow = (((long)b * S + q) * H + hd) * DH;
+  const float D = row_dot<DH>(load_row<DH>(d_o + orow, g, q < S), load_row<DH>(o + orow, g, q < S));
+  if (g == 0 && q < S) dsum[(long)bh * S + q] = D;
+}
+// grid (heads, 2 x blocks)
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) attn_bwd_both_f32(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                                                  const float* __restrict__ lse, const float* __restrict__ dsum, float* __restrict__ dqkv,
+                                                                  float* __restrict__ colsum, int S, int H, bool paired) {
+  const CausalPlace at = causal_place(paired);
+  const int blocks = gridDim.y >> 1, order = at.order >> 1;   // by length, longest first
+  if (at.order & 1) dq_block<DH, NW>(qkv, o, d_o, lse, dqkv, nullptr, colsum, S, H, at.bh, blocks - 1 - order, blocks);
+  else dkv_block<DH, NW, false>(qkv, nullptr, d_o, lse, dsum, dqkv, colsum, S, H, at.bh, order, blocks);
+}
 // Sequences of one block (up to 64 positions on four waves): dQ and dK / dV in one launch, one workgroup each (blockIdx.y), as
 // such launches take as long as any launch: 4 x 2 heads x 64 x 32 6.6 + 7.0 us and a gap, 8.2 in one.
 template <int DH>
@@ -436,9 +458,6 @@ template <int DH, int NW>
 dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const float* lse, float* dqkv, float* dsum,
                   float* colsum, int B, int S, int H, hipStream_t s) {
   static_assert(NW * DH <= 2 * 2 * tile_floats<DH>(), "the column sums' scratch fits in the stages");
-  static std::atomic<unsigned long long> dq{0}, dkv{0};
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>), fwd_lds<DH>(), dq)) return st;
-  if (dipaco_status st = ensure_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>), dkv_lds<DH>(), dkv)) return st;
   const size_t A = (size_t)H * DH;
   const int step = attention_launch_batch(B, H), blocks = (S + 16 * NW - 1) / (16 * NW);
   for (int b = 0; b < B; b += step) {
@@ -456,17 +475,41 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
         continue;
       }
     }
-    static std::atomic<int> dq_resident{0}, dkv_resident{0};
-    bool dq_paired, dkv_paired;
     const long n = (long)grid.x * grid.y;
-    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>), 64 * NW, fwd_lds<DH>(), n, dq_resident, dq_paired)) return st;
-    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>), 64 * NW, dkv_lds<DH>(), n, dkv_resident, dkv_paired)) return st;
-    attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
-                                                                 dqkv + row * 3 * A, dsum + row * H, cs, S, H, dq_paired);
-    DIPACO_LAUNCH_CHECK();
-    attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv + row * 3 * A, d_o + row * A, lse + row * H, dsum + row * H,
-                                                                  dqkv + row * 3 * A, cs, S, H, dkv_paired);
-    DIPACO_LAUNCH_CHECK();
+    if constexpr (NW == F_FEW) {
+      if (DH < 128 || n <= ONE_LAUNCH_WIDE) {
+        static std::atomic<unsigned long long> both{0};
+        static std::atomic<int> resident{0};
+        bool paired;
+        constexpr int LDS = std::max(fwd_lds<DH>(), dkv_lds<DH>());
+        const void* const kern = reinterpret_cast<const void*>(attn_bwd_both_f32<DH, NW>);
+        if (dipaco_status st = ensure_dynamic_lds(kern, LDS, both)) return st;
+        if (dipaco_status st = causal_paired(kern, 64 * NW, LDS, 2 * n, resident, paired)) return st;
+        attn_stats_f32<DH, NW><<<grid, 64 * NW, 0, s>>>(o + row * A, d_o + row * A, dsum + row * H, S, H);
+        DIPACO_LAUNCH_CHECK();
+        attn_bwd_both_f32<DH, NW><<<dim3(grid.x, 2 * grid.y), 64 * NW, LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H, dsum + row * H,
+                                                                                dqkv + row * 3 * A, cs, S, H, paired);
+        DIPACO_LAUNCH_CHECK();
+        continue;
+      }
+    }
+    if constexpr (NW != F_FEW || DH == 128) {
+      static std::atomic<unsigned long long> dq{0}, dkv{0};
+      static std::atomic<int> dq_resident{0}, dkv_resident{0};
+      bool dq_paired, dkv_paired;
+      const void* const dq_kern = reinterpret_cast<const void*>(attn_bwd_dq_f32<DH, NW>);
+      const void* const dkv_kern = reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>);
+      if (dipaco_status st = ensure_dynamic_lds(dq_kern, fwd_lds<DH>(), dq)) return st;
+      if (dipaco_status st = ensure_dynamic_lds(dkv_kern, dkv_lds<DH>(), dkv)) return st;
+      if (dipaco_status st = causal_paired(dq_kern, 64 * NW, fwd_lds<DH>(), n, dq_resident, dq_paired)) return st;
+      if (dipaco_status st = causal_paired(dkv_kern, 64 * NW, dkv_lds<DH>(), n, dkv_resident, dkv_paired)) return st;
+      attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
+                                                                   dqkv + row * 3 * A, dsum + row * H, cs, S, H, dq_paired);
+      DIPACO_LAUNCH_CHECK();
+      attn_bwd_dkv_f32<DH, NW><<<grid, 64 * NW, dkv_lds<DH>(), s>>>(qkv + row * 3 * A, d_o + row * A, lse + row * H, dsum + row * H,
+                                                                    dqkv + row * 3 * A, cs, S, H, dkv_paired);
+      DIPACO_LAUNCH_CHECK();
+    }
   }
   return DIPACO_OK;
 }
