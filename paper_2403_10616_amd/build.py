@@ -32,7 +32,7 @@ EXTRA_FLAGS = {"attention_mfma.hip": ["-fno-honor-nans"]}
 
 # Kernels whose accumulators must stay in registers: a build in which the compiler moves them to scratch memory
 # (it does when an unrolled loop outgrows its limits) still passes every test and runs fifteen times slower.
-NO_SCRATCH = ("gemm_dlds_kernel", "gemm_fit_kernel", "gemm_fit_pair_kernel", "gemm_direct_kernel", "gemm_direct_pair_kernel", "gemm_direct_norm_kernel", "gemm_split_kernel", "attn_", "route_kernel", "route_small_kernel", "route_few_kernel", "sum_layernorm_kernel", "rows_product_kernel", "attn_out_kernel")
+NO_SCRATCH = ("gemm_dlds_kernel", "gemm_fit_kernel", "gemm_fit_pair_kernel", "gemm_fit_pair_wide_kernel", "gemm_direct_kernel", "gemm_direct_pair_kernel", "gemm_direct_norm_kernel", "gemm_split_kernel", "attn_", "route_kernel", "route_small_kernel", "route_few_kernel", "sum_layernorm_kernel", "rows_product_kernel", "attn_out_kernel")
 
 
 def _check_scratch(src: str, remarks: str) -> None:

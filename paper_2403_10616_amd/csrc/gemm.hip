@@ -82,7 +82,7 @@ static double plane_cost(int M, int N, int splits) { return splits > 1 ? splits 
 // Most slices a weight gradient (K = tokens) is cut into: a slice keeps at least 256 of K, and a small output under a
 // very long fp32 contraction (the router's 256 x 768 gradient over 2^20 documents) may still fill the chip.
 constexpr int GEMM_SLICE_CAP_F32 = 128;
-struct SplitPlan { int splits; bool dlds; };
+struct SplitPlan { int splits; bool dlds; double us; };
 
 // The cheaper of the two kernels for C[M, N] = X^T dY over K tokens, by the times of gemm_fit_cost and of the
 // direct-to-LDS kernel (8 us + 23 us per 1000 of the longest workgroup's K).  Measured in bf16, product + reduction: 1024 x 4096
@@ -91,14 +91,14 @@ struct SplitPlan { int splits; bool dlds; };
 // apart and re-read their panels, and the direct-to-LDS plan is taken wherever there is one.
 static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_allowed, int limit = GEMM_SLICE_CAP_F32) {
   const int cap = std::max(1, std::min({bf16_operands ? GEMM_SLICE_CAP : GEMM_SLICE_CAP_F32, K / 256, limit}));
-  SplitPlan best{1, false};
+  SplitPlan best{1, false, 1e30};
   double cost = 1e30;
   const GemmFitTiles tiles = gemm_fit_tiles(M, N, bf16_operands, false);
   for (int s = 1; s <= cap; ++s) {
     const double planes = plane_cost(M, N, s) + reduce_cost(M, N, s);
     if (planes > cost) break;   // grows with s
     const double c = gemm_fit_cost(tiles, (K + s - 1) / s, s) + planes;
-    if (c < cost) { cost = c; best.splits = s; }
+    if (c < cost) { cost = best.us = c; best.splits = s; }
   }
   if (bf16_operands && dlds_allowed && K % 32 == 0) {
     double length = 0.0;
@@ -107,7 +107,7 @@ static SplitPlan plan_splits(int M, int N, int K, bool bf16_operands, bool dlds_
     if (!s) { s = 1; length = (double)((tiles + 255) / 256) * K; }
     const bool fills = tiles * s >= 160;
     const double c = 8.0 + 0.023 * length + plane_cost(M, N, s) + reduce_cost(M, N, s);
-    if (fills && (c < cost || K > 16384)) best = SplitPlan{s, true};
+    if (fills && (c < cost || K > 16384)) best = SplitPlan{s, true, c};
   }
   return best;
 }
@@ -227,10 +227,32 @@ template <typename T> dipaco_status launch_norm_gemm(const T* x, const T* gain, 
   return launch_gemm<T>(a, s);
 }
 
+// Whether dW and dX in one launch of fitted tiles (gemm_fit_pair_wide_kernel, dW uncut) are modelled clearly below two launches.  Backward passes
+// of the 150M path, whole steps, us, two -> one: 1 x 1000 tokens 4473 -> 4000, 2 x 700 4774 -> 4247, 6 x 900 9440 -> 9080, 3 x 1000 6374 -> 6291;
+// with no margin a 1024-wide one of 4096 tokens, whose products are whole rounds, is 0.3 % behind.  Contractions above 16384 stay with the
+// direct-to-LDS kernel (plan_splits).
+static bool pays_as_wide_pair(const GemmArgs& dw, const GemmArgs& dx) {
+  if (dw.K > 16384) return false;
+  GemmArgs whole = dw;
+  whole.splits = 1;
+  const double one = gemm_fit_pair_wide_us(whole, dx);
+  const double w = plan_splits(dw.M, dw.N, dw.K, true, true, std::max(1, dw.splits)).us;
+  const double rounds = (double)(((long)((dx.M + 255) / 256) * ((dx.N + 255) / 256) + 255) / 256);
+  const double x = want_dlds(dx) && gemm_dlds_eligible(dx) ? 3.0 + rounds * (8.0 + 0.023 * dx.K) : gemm_fit_cost(gemm_fit_tiles(dx.M, dx.N, true, true), dx.K, 1);
+  return one < 0.93 * (w + 1.0 + x);
+}
+
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
   if (dipaco_status st = check_gemm<T>(dw)) return st;
   if (dipaco_status st = check_gemm<T>(dx)) return st;
   if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32 && gemm_fit_pair_takes<T>(dw, dx)) return launch_gemm_fit_pair<T>(dw, dx, s);
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32 && pays_as_wide_pair(dw, dx)) {
+      GemmArgs whole = dw;
+      whole.splits = 1;
+      return launch_gemm_fit_pair_wide(whole, dx, s);
+    }
+  }
   if (dipaco_status st = launch_gemm<T>(dw, s)) return st;
   return launch_gemm<T>(dx, s);
 }

@@ -496,6 +496,14 @@ template <typename T, int TN> __global__ void __launch_bounds__(64 * FIT_WAVES, 
   else fit_product<T, T, true, true, 2, TN, 1, 1, 8, 3, false>(dx, block - first);
 }
 
+// The same in bf16 for products of a round or a few, a workgroup to a compute unit: dW in 128 x 128 tiles, dX in 32 TX x 128 ones.  Each alone
+// ends, or never fills, the chip with units idle: 896 x 3584 over 1400 tokens are 196 tiles on 256 units, the dX beside it 105 - 154.
+template <int TX> __global__ void __launch_bounds__(64 * FIT_WAVES, 2) gemm_fit_pair_wide_kernel(const GemmDev dw, const GemmDev dx, int n_first, bool dw_first) {
+  const int block = blockIdx.x, behind = block - n_first;
+  if ((behind < 0) == dw_first) fit_product<bf16, float, false, false, 4, 4, 2, 2, 2, 4, false>(dw, dw_first ? block : behind);
+  else fit_product<bf16, bf16, true, true, TX, 4, 2, 2, 2, 4, false>(dx, dw_first ? behind : block);
+}
+
 // The same in fp32 where both contractions are short
 template <int G> __global__ void __launch_bounds__(64 * G, 2) gemm_direct_pair_kernel(const GemmDev dw, const GemmDev dx, int first) {
   const int block = blockIdx.x;
@@ -583,15 +591,15 @@ long shape_tiles(int t, int M, int N, bool bf16_operands) {
   const int bm = t == 3 && !bf16_operands ? 64 : 32 * t, bn = t == 1 ? 64 : 128;
   return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
 }
+constexpr double BF16_FIXED[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, BF16_PER_K[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
 inline __attribute__((always_inline)) double shape_cost(int t, long tiles, int K, bool bf16_operands, bool a_kc) {
-  static const double fixed[6] = {0, 3.0, 3.5, 4.5, 5.0, 6.0}, per_k[6] = {0, 1.8, 4.2, 5.2, 6.4, 8.1};
   if (t == 3 && !bf16_operands) return tiles <= 256 ? 8.0 + 27.0 * K * 1e-3 : 1e30;
   if (t == 4 && !bf16_operands) {
     const long full = tiles / 512, rest = tiles % 512;   // rounds of two workgroups a unit; behind them up to one a unit, or on the way to two
     const double round = 18.0 + 88.0 * K * 1e-3, single = 10.5 + 60.0 * K * 1e-3;
     return 3.0 + (double)full * round + (rest == 0 ? 0.0 : single + std::max(0L, rest - 256) / 256.0 * (round - single));
   }
-  const double f = bf16_operands ? fixed[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? per_k[t] : t == 1 ? 8.7 : 32.5;
+  const double f = bf16_operands ? BF16_FIXED[t] : t == 1 ? 4.0 : 3.6, k = bf16_operands ? BF16_PER_K[t] : t == 1 ? 8.7 : 32.5;
   const long rounds = t == 2 && !a_kc && tiles > 256 ? (tiles + 511) / 512 * 2 : (tiles + 255) / 256;
   if (t == 2 && a_kc && bf16_operands) return 4.9 + (double)rounds * (1.6 + k * K * 1e-3);
   return 3.0 + (double)rounds * (f + k * K * 1e-3);
@@ -685,7 +693,76 @@ template <typename T> bool pair_fits(const GemmArgs& dw, const GemmArgs& dx) {
          fit_span(true, F::BM, F::BK, dx.M, dx.K, dx.lda, sizeof(T)) < most && fit_span(true, F::BN, F::BK, dx.N, dx.K, dx.ldb, sizeof(T)) < most;
 }
 
+// Microseconds until `n` tiles of `us` and then `n2` of `us2` are done, dealt to 256 compute units as they come free
+double dealt(long n, double us, long n2, double us2) {
+  constexpr int MOST = 64;   // times at which some units come free; far more than a pair's tiles make
+  double at[MOST];
+  long units[MOST];
+  int count = 1;
+  at[0] = 0.0;
+  units[0] = 256;
+  double end = 0.0;
+  for (int kind = 0; kind < 2; ++kind)
+    for (long left = kind ? n2 : n; left > 0;) {
+      int k = 0;
+      for (int i = 1; i < count; ++i)
+        if (at[i] < at[k]) k = i;
+      const long take = std::min(left, units[k]);
+      const double done = at[k] + (kind ? us2 : us);
+      end = std::max(end, done);
+      left -= take;
+      if (take == units[k]) at[k] = done;
+      else if (count == MOST) return 1e30;
+      else { units[k] -= take; at[count] = done; units[count++] = take; }
+    }
+  return end;
+}
+struct WidePair { int tx; bool dw_first; double us; };   // the longer tiles first
+WidePair pick_wide(const GemmArgs& dw, const GemmArgs& dx) {
+  const long nw = shape_tiles(4, dw.M, dw.N, true);
+  const double cw = BF16_FIXED[4] + BF16_PER_K[4] * dw.K * 1e-3;
+  WidePair best{0, true, 1e30};
+  for (int t = 3; t <= 5; ++t) {
+    const long nx = shape_tiles(t, dx.M, dx.N, true);
+    if (nw + nx > 256 * 8) continue;
+    const double cx = BF16_FIXED[t] + BF16_PER_K[t] * dx.K * 1e-3;
+    const bool dw_first = cw >= cx;
+    const double us = 3.0 + (dw_first ? dealt(nw, cw, nx, cx) : dealt(nx, cx, nw, cw));
+    if (us < best.us) best = WidePair{t, dw_first, us};
+  }
+  return best;
+}
+
 }  // namespace
+
+double gemm_fit_pair_wide_us(const GemmArgs& dw, const GemmArgs& dx) {
+  constexpr uint64_t most = 1ull << 32;
+  if (g_forced_fit || dw.splits > 1 || dx.splits > 1 || dw.raw_planes || dx.raw_planes) return 1e30;
+  if (fit_span(false, 128, 64, dw.M, dw.K, dw.lda, 2) >= most || fit_span(false, 128, 64, dw.N, dw.K, dw.ldb, 2) >= most ||
+      fit_span(true, 160, 64, dx.M, dx.K, dx.lda, 2) >= most || fit_span(true, 128, 64, dx.N, dx.K, dx.ldb, 2) >= most) return 1e30;
+  return pick_wide(dw, dx).us;
+}
+dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
+  const WidePair p = pick_wide(dw, dx);
+  auto run = [&](auto TXc) -> dipaco_status {
+    constexpr int TX = decltype(TXc)::value;
+    using W = Fit<bf16, float, false, false, 4, 4, 2, 2, 2, 4>;
+    using X = Fit<bf16, bf16, true, true, TX, 4, 2, 2, 2, 4>;
+    constexpr int LDS = W::LDS > X::LDS ? W::LDS : X::LDS;
+    auto kern = gemm_fit_pair_wide_kernel<TX>;
+    static std::atomic<unsigned long long> lds_set{0};   // per instantiation
+    if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_set)) return e;
+    const GemmDev w = fit_dev<W>(dw), x = fit_dev<X>(dx);
+    const int nw = w.tiles_m * w.tiles_n, nx = x.tiles_m * x.tiles_n;
+    kern<<<nw + nx, 64 * FIT_WAVES, LDS, s>>>(w, x, p.dw_first ? nw : nx, p.dw_first);
+    DIPACO_LAUNCH_CHECK();
+    if (dx.colsum) return launch_sum_rows(dx.colsum_partial, dx.colsum, x.tiles_m, dx.N, s, dx.sum_batch);
+    return DIPACO_OK;
+  };
+  if (p.tx == 3) return run(std::integral_constant<int, 3>{});
+  if (p.tx == 4) return run(std::integral_constant<int, 4>{});
+  return run(std::integral_constant<int, 5>{});
+}
 
 template <typename T> bool gemm_fit_pair_takes(const GemmArgs& dw, const GemmArgs& dx) { return pair_fits<T>(dw, dx); }
 template <typename T> dipaco_status launch_gemm_fit_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {

@@ -124,6 +124,8 @@ struct RowNorm { const float* gain; const float* shift; float* y; float* mean; f
 bool gemm_norm_takes(const GemmArgs& g);
 dipaco_status launch_gemm_norm(const GemmArgs& g, const RowNorm& ln, hipStream_t s);   // of checked arguments
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
+double gemm_fit_pair_wide_us(const GemmArgs& dw, const GemmArgs& dx);
+dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
 // gemm_dlds.hip: bf16, 256x256 tiles loaded from global memory straight into LDS; takes the shapes for which
 // gemm_dlds_eligible holds (whole K tiles of 32, 16-byte rows); launch_gemm routes to it by itself
 bool gemm_dlds_eligible(const GemmArgs& g);

@@ -264,6 +264,34 @@ def test_bf16_loss_and_gradients_close_to_oracle(name, B, S, mask):
     assert st.fwd_bwd(tok, tgt) == loss and np.array_equal(g0, host(st.grads))
 
 
+@pytest.mark.parametrize("d,heads,F,V,B,S", [(640, 10, 2400, 1000, 2, 515), (896, 14, 3584, 2000, 1, 700), (512, 8, 2048, 8000, 3, 777), (768, 12, 1544, 4104, 5, 330)])
+def test_both_products_of_a_wide_layers_backward_pass_in_one_launch(d, heads, F, V, B, S):
+    """Fitted tiles of both products on the compute units as they come free; against the oracle as above, and against one forced tile for
+    every product, whose sums are in another order: roundings of the bf16 gradients between the layers, 2e-3 here."""
+    cfg = dict(layers_per_level=(1, 1), d_model=d, n_heads=heads, d_head=64, d_mlp=F, vocab=V, max_seq=S)
+    print(f"bf16 wide pairs d={d} F={F} tokens={B * S}", flush=True)
+    a, ctx = make_arch(cfg, dp.BF16)
+    lay = orc.param_layout(a)
+    theta = gen.init_params(lay, a.n_layers, seed=8) + gen.random_params(orc.param_count(a), seed=9, scale=0.02)
+    theta = torch.from_numpy(theta).to(torch.bfloat16).float().numpy()
+    tok, tgt = _batch(cfg, B, S, seed=10, mask_prefix=5, zipf=True)
+    grads, losses = [], []
+    for tile in (0, 4):
+        dp.dipaco_k_set_gemm_tile(tile)
+        try:
+            st = PathState(ctx, theta, B, S)
+            losses.append(st.fwd_bwd(tok, tgt))
+            grads.append(host(st.grads).copy())
+            assert st.fwd_bwd(tok, tgt) == losses[-1] and np.array_equal(grads[-1], host(st.grads))
+        finally:
+            dp.dipaco_k_set_gemm_tile(0)
+    assert rel_l2(grads[0], grads[1]) <= 8e-3
+    o_loss, o_grad = orc.path_loss_and_grad(theta, a, tok, tgt)
+    assert abs(losses[0] - o_loss) <= 2e-3 * abs(o_loss)
+    worst, where = per_tensor_rel(lay, grads[0], o_grad)
+    assert worst <= 3e-2, (where, worst)
+
+
 # ---- router features: forward through the blocks, mean over the prefix ------------------------------------------
 def _features_gpu(ctx, theta, tok):
     B, S = tok.shape
