@@ -858,65 +858,64 @@ __global__ void __launch_bounds__(256) logistic_rows_kernel(float* __restrict__ 
 
 // The same for K <= 256, where a row is at most one 16-byte vector per lane: a wave takes ROWS rows at once, so that
 // ROWS loads are in flight per lane instead of one (a million one-kilobyte rows are latency-bound otherwise), and the
-// reductions run on the DPP lanes.  A workgroup walks `groups` times 32 rows and leaves one row of partial sums: the column sums of what it
-// stores (the bias gradient) and, in column K, its rows' losses; logistic_finish_kernel adds these rows.  The sums cost the
-// kernel nothing, its reads and writes bound it: a pass over the gradients and three launches less (router gradient of 50000 x 768 x 256
-// 300 -> 293 us).
+// reductions run on the DPP lanes.  Rows behind the last are that one again, without a label, so that nothing branches between
+// rows and their chains interleave; what a row has once (the quotient, the logarithm) is taken for all of them together, a lane each.
+// Groups of ROWS rows are dealt to at most 1024 workgroups, each of which leaves one row of partial sums: the column sums of what it
+// stores (the bias gradient) and, in column K, its rows' losses; logistic_finish_kernel adds these rows.  Bound by its vector instructions and
+// HBM together: 50000 x 256 28.7 us with the rows one behind the other, 22.1 so (the next group's rows requested ahead: 23.2); gradient of
+// 1000000 x 64 x 128 833 -> 719, 300000 x 64 x 256 404 -> 372, 3000 x 64 x 256 27.1 -> 24.7.
 constexpr int LOGIT_SMALL_ROWS = 8, LOGIT_SMALL_BLOCKS = 1024;
-inline int logistic_groups(int64_t rows) {
-  const int64_t blocks = (rows + 4 * LOGIT_SMALL_ROWS - 1) / (4 * LOGIT_SMALL_ROWS);
-  return (int)((blocks + LOGIT_SMALL_BLOCKS - 1) / LOGIT_SMALL_BLOCKS);
-}
 constexpr int logistic_stride(int K) { return K + 4; }   // floats between rows of partial sums
 __global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits,
                                                                   const int* __restrict__ labels, long rows, int K,
-                                                                  float inv_n, float* __restrict__ partial, int groups) {
+                                                                  float inv_n, float* __restrict__ partial) {
   constexpr int ROWS = LOGIT_SMALL_ROWS;
   __shared__ __attribute__((aligned(16))) float red[4][logistic_stride(256)];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool on = lane < (K >> 2);
   float sums[4] = {0.f, 0.f, 0.f, 0.f};
-  double loss = 0.0;
-  for (int gi = 0; gi < groups; ++gi) {
-    const long row0 = (((long)blockIdx.x * groups + gi) * 4 + wave) * ROWS;
-    if (row0 >= rows) break;   // whole waves: the reductions below see all 64 lanes
+  double loss = 0.0;   // of lane r: of the r-th row of each group
+  const long step = (long)gridDim.x * 4 * ROWS;
+  for (long row0 = ((long)blockIdx.x * 4 + wave) * ROWS; row0 < rows; row0 += step) {   // whole waves: the reductions see all 64 lanes
     float4 v[ROWS];
-    float at[ROWS];
-    int label[ROWS];
+    int own_label = -1;
+    if (lane < ROWS && row0 + lane < rows) own_label = labels[row0 + lane];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-      const long row = row0 + r;
-      const bool ok = row < rows;   // wave-uniform
       v[r] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      label[r] = -1;
-      at[r] = 0.f;
-      if (ok) {
-        if (on) v[r] = reinterpret_cast<const float4*>(logits + row * K)[lane];
-        const int l = labels[row];
-        if (l >= 0 && l < K) { label[r] = l; at[r] = logits[row * K + l]; }   // read before the row is overwritten
-      }
+      if (on) v[r] = reinterpret_cast<const float4*>(logits + std::min(row0 + r, rows - 1) * K)[lane];
     }
+    const bool own_valid = own_label >= 0 && own_label < K;
+    if (!own_valid) own_label = -1;
+    float own_sum = 1.f, own_at = 0.f;   // own_at: logit[label] - max
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-      const long row = row0 + r;
-      if (row >= rows) break;
-      const bool valid = label[r] >= 0;
+      const int label = __builtin_amdgcn_readlane(own_label, r);
       const float mx = wave_max(fmaxf(fmaxf(v[r].x, v[r].y), fmaxf(v[r].z, v[r].w)));
-      float e[4] = {expf(v[r].x - mx), expf(v[r].y - mx), expf(v[r].z - mx), expf(v[r].w - mx)};   // exp(-inf) = 0 off the row
-      const float sum = wave_sum((e[0] + e[1]) + (e[2] + e[3]));
-      const float scale = valid ? inv_n / sum : 0.f;
-      if (on) {
-        float o[4];
+      const float pick = label & 2 ? (label & 1 ? v[r].w : v[r].z) : (label & 1 ? v[r].y : v[r].x);
+      const float at = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pick), label < 0 ? 0 : label >> 2));
+      v[r] = make_float4(expf(v[r].x - mx), expf(v[r].y - mx), expf(v[r].z - mx), expf(v[r].w - mx));   // exp(-inf) = 0 off the row
+      const float sum = wave_sum((v[r].x + v[r].y) + (v[r].z + v[r].w));
+      if (lane == r) { own_sum = sum; own_at = at - mx; }
+    }
+    const float own_scale = own_valid ? inv_n / own_sum : 0.f;
+    loss += (double)(own_valid ? logf(own_sum) - own_at : 0.f);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          o[q] = e[q] * scale - ((valid && 4 * lane + q == label[r]) ? inv_n : 0.f);
-          sums[q] += o[q];
-        }
-        reinterpret_cast<float4*>(logits + row * K)[lane] = make_float4(o[0], o[1], o[2], o[3]);
+    for (int r = 0; r < ROWS; ++r) {
+      const int label = __builtin_amdgcn_readlane(own_label, r);
+      const float scale = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, own_scale), r));
+      const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+      float o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        o[q] = e[q] * scale - (4 * lane + q == label ? inv_n : 0.f);
+        sums[q] += o[q];
       }
-      loss += (double)(valid ? logf(sum) - (at[r] - mx) : 0.f);
+      if (on && row0 + r < rows) reinterpret_cast<float4*>(logits + (row0 + r) * K)[lane] = make_float4(o[0], o[1], o[2], o[3]);
     }
   }
+#pragma unroll
+  for (int o = 1; o < ROWS; o <<= 1) loss += __shfl_xor(loss, o, 64);
   if (on) *reinterpret_cast<float4*>(&red[wave][4 * lane]) = make_float4(sums[0], sums[1], sums[2], sums[3]);
   if (lane == 0) red[wave][K] = (float)loss;
   __syncthreads();
@@ -957,10 +956,8 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
   if (K < 4 || K % 4 || K > LOGIT_MAX_K) return fail(DIPACO_ESHAPE, "logistic rows: K must be a multiple of 4 in [4, 4096]");
   const float inv_n = (float)(1.0 / (double)rows);
   if (K <= 256) {
-    const int groups = logistic_groups(rows);
-    const int64_t per = (int64_t)groups * 4 * LOGIT_SMALL_ROWS;
-    const int blocks = (int)((rows + per - 1) / per);
-    logistic_rows_small_kernel<<<blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial, groups);
+    const int blocks = (int)std::min<int64_t>((rows + 4 * LOGIT_SMALL_ROWS - 1) / (4 * LOGIT_SMALL_ROWS), LOGIT_SMALL_BLOCKS);
+    logistic_rows_small_kernel<<<blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
     DIPACO_LAUNCH_CHECK();
     logistic_finish_kernel<<<(K + 1 + LF_COLS - 1) / LF_COLS, LF_COLS * LF_PHASES, 0, s>>>(partial, blocks, K, (float)rows, db, loss);
     DIPACO_LAUNCH_CHECK();
