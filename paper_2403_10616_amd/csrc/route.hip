@@ -860,67 +860,98 @@ __global__ void __launch_bounds__(256) logistic_rows_kernel(float* __restrict__ 
 // ROWS loads are in flight per lane instead of one (a million one-kilobyte rows are latency-bound otherwise), and the
 // reductions run on the DPP lanes.  Rows behind the last are that one again, without a label, so that nothing branches between
 // rows and their chains interleave; what a row has once (the quotient, the logarithm) is taken for all of them together, a lane each.
-// Groups of ROWS rows are dealt to at most 1024 workgroups, each of which leaves one row of partial sums: the column sums of what it
+// Up to 128 (64, 32) classes a vector holds two (four, eight) rows, LANES lanes each: the instructions are a vector's, whatever it holds.
+// Groups of ROWS vectors are dealt to at most 1024 workgroups, each of which leaves one row of partial sums: the column sums of what it
 // stores (the bias gradient) and, in column K, its rows' losses; logistic_finish_kernel adds these rows.  Bound by its vector instructions and
 // HBM together: 50000 x 256 28.7 us with the rows one behind the other, 22.1 so (the next group's rows requested ahead: 23.2); gradient of
-// 1000000 x 64 x 128 833 -> 719, 300000 x 64 x 256 404 -> 372, 3000 x 64 x 256 27.1 -> 24.7.
+// 300000 x 64 x 256 404 -> 372, 3000 x 64 x 256 27.1 -> 24.7, 1000000 x 64 x 128 833 -> 719, 676 with two rows a vector, 200000 x 64 x 64
+// 182 -> 162, 130 with four, 1000000 x 64 x 8 579 -> 524, 351 with four, 327 with eight; 3000 x 64 x 64 and x 128 level.
 constexpr int LOGIT_SMALL_ROWS = 8, LOGIT_SMALL_BLOCKS = 1024;
 constexpr int logistic_stride(int K) { return K + 4; }   // floats between rows of partial sums
-__global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits,
-                                                                  const int* __restrict__ labels, long rows, int K,
-                                                                  float inv_n, float* __restrict__ partial) {
-  constexpr int ROWS = LOGIT_SMALL_ROWS;
-  __shared__ __attribute__((aligned(16))) float red[4][logistic_stride(256)];
+__device__ __forceinline__ float lane_value(float v, int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane)); }
+// over a row's LANES lanes, in each of them
+template <int LANES> __device__ __forceinline__ float row_max(float v) {
+  if constexpr (LANES == 64) return wave_max(v);
+  v = fmaxf(v, dpp_fetch<0xb1, 0xf>(v, -INFINITY));
+  v = fmaxf(v, dpp_fetch<0x4e, 0xf>(v, -INFINITY));
+  v = fmaxf(v, dpp_fetch<0x141, 0xf>(v, -INFINITY));
+  if constexpr (LANES > 8) v = fmaxf(v, dpp_fetch<0x140, 0xf>(v, -INFINITY));
+  return LANES == 32 ? fmaxf(v, __shfl_xor(v, 16, 64)) : v;
+}
+template <int LANES> __device__ __forceinline__ float row_sum(float v) {
+  if constexpr (LANES == 64) return wave_sum(v);
+  v += dpp_fetch<0xb1, 0xf>(v, 0.f);
+  v += dpp_fetch<0x4e, 0xf>(v, 0.f);
+  v += dpp_fetch<0x141, 0xf>(v, 0.f);
+  if constexpr (LANES > 8) v += dpp_fetch<0x140, 0xf>(v, 0.f);
+  return LANES == 32 ? v + __shfl_xor(v, 16, 64) : v;
+}
+template <int LANES> __global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits, const int* __restrict__ labels,
+                                                                                       long rows, int K, float inv_n, float* __restrict__ partial) {
+  constexpr int ROWS = LOGIT_SMALL_ROWS, PER = 64 / LANES, GROUP = ROWS * PER;   // K <= 4 LANES
+  __shared__ __attribute__((aligned(16))) float red[4 * PER * logistic_stride(4 * LANES)];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool on = lane < (K >> 2);
+  const int piece = lane / LANES, x = lane % LANES;   // the lane's row of a vector, its place in it
+  const bool on = x < (K >> 2);
   float sums[4] = {0.f, 0.f, 0.f, 0.f};
-  double loss = 0.0;   // of lane r: of the r-th row of each group
-  const long step = (long)gridDim.x * 4 * ROWS;
-  for (long row0 = ((long)blockIdx.x * 4 + wave) * ROWS; row0 < rows; row0 += step) {   // whole waves: the reductions see all 64 lanes
+  double loss = 0.0;   // of lane i: of the i-th row of each group
+  const long step = (long)gridDim.x * 4 * GROUP;
+  for (long row0 = ((long)blockIdx.x * 4 + wave) * GROUP; row0 < rows; row0 += step) {   // whole waves: the reductions see all 64 lanes
     float4 v[ROWS];
     int own_label = -1;
-    if (lane < ROWS && row0 + lane < rows) own_label = labels[row0 + lane];
+    if (lane < GROUP && row0 + lane < rows) own_label = labels[row0 + lane];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       v[r] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (on) v[r] = reinterpret_cast<const float4*>(logits + std::min(row0 + r, rows - 1) * K)[lane];
+      if (on) v[r] = reinterpret_cast<const float4*>(logits + std::min(row0 + r * PER + piece, rows - 1) * K)[x];
     }
     const bool own_valid = own_label >= 0 && own_label < K;
     if (!own_valid) own_label = -1;
+    auto label_of = [&](int r) { return PER == 1 ? __builtin_amdgcn_readlane(own_label, r) : __shfl(own_label, r * PER + piece, 64); };
+    // the lane that holds the first of the row of which lane i is the owner, and the label's
+    const int own_first = lane % PER * LANES, own_holder = own_first + (own_valid ? own_label >> 2 : 0);
     float own_sum = 1.f, own_at = 0.f;   // own_at: logit[label] - max
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-      const int label = __builtin_amdgcn_readlane(own_label, r);
-      const float mx = wave_max(fmaxf(fmaxf(v[r].x, v[r].y), fmaxf(v[r].z, v[r].w)));
+      const int label = label_of(r);
+      const float mx = row_max<LANES>(fmaxf(fmaxf(v[r].x, v[r].y), fmaxf(v[r].z, v[r].w)));
+      v[r] = make_float4(v[r].x - mx, v[r].y - mx, v[r].z - mx, v[r].w - mx);
       const float pick = label & 2 ? (label & 1 ? v[r].w : v[r].z) : (label & 1 ? v[r].y : v[r].x);
-      const float at = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pick), label < 0 ? 0 : label >> 2));
-      v[r] = make_float4(expf(v[r].x - mx), expf(v[r].y - mx), expf(v[r].z - mx), expf(v[r].w - mx));   // exp(-inf) = 0 off the row
-      const float sum = wave_sum((v[r].x + v[r].y) + (v[r].z + v[r].w));
-      if (lane == r) { own_sum = sum; own_at = at - mx; }
+      const float at = PER == 1 ? lane_value(pick, label < 0 ? 0 : label >> 2) : __shfl(pick, own_holder, 64);
+      v[r] = make_float4(expf(v[r].x), expf(v[r].y), expf(v[r].z), expf(v[r].w));   // exp(-inf) = 0 off the row
+      float sum = row_sum<LANES>((v[r].x + v[r].y) + (v[r].z + v[r].w));
+      if constexpr (PER > 1) sum = __shfl(sum, own_first, 64);
+      if (lane / PER == r) { own_sum = sum; own_at = at; }
     }
     const float own_scale = own_valid ? inv_n / own_sum : 0.f;
     loss += (double)(own_valid ? logf(own_sum) - own_at : 0.f);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-      const int label = __builtin_amdgcn_readlane(own_label, r);
-      const float scale = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, own_scale), r));
+      const int label = label_of(r);
+      const float scale = PER == 1 ? lane_value(own_scale, r) : __shfl(own_scale, r * PER + piece, 64);
       const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
       float o[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        o[q] = e[q] * scale - (4 * lane + q == label ? inv_n : 0.f);
+        o[q] = e[q] * scale - (4 * x + q == label ? inv_n : 0.f);
         sums[q] += o[q];
       }
-      if (on && row0 + r < rows) reinterpret_cast<float4*>(logits + (row0 + r) * K)[lane] = make_float4(o[0], o[1], o[2], o[3]);
+      const long row = row0 + r * PER + piece;
+      if (on && row < rows) reinterpret_cast<float4*>(logits + row * K)[x] = make_float4(o[0], o[1], o[2], o[3]);
     }
   }
 #pragma unroll
-  for (int o = 1; o < ROWS; o <<= 1) loss += __shfl_xor(loss, o, 64);
-  if (on) *reinterpret_cast<float4*>(&red[wave][4 * lane]) = make_float4(sums[0], sums[1], sums[2], sums[3]);
-  if (lane == 0) red[wave][K] = (float)loss;
+  for (int o = 1; o < GROUP; o <<= 1) loss += __shfl_xor(loss, o, 64);
+  float* mine = red + (wave * PER + piece) * logistic_stride(4 * LANES);
+  if (on) *reinterpret_cast<float4*>(mine + 4 * x) = make_float4(sums[0], sums[1], sums[2], sums[3]);
+  if (x == 0) mine[K] = piece ? 0.f : (float)loss;
   __syncthreads();
-  for (int c = threadIdx.x; c <= K; c += 256)
-    partial[(size_t)blockIdx.x * logistic_stride(K) + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+  for (int c = threadIdx.x; c <= K; c += 256) {
+    float t = red[c];
+#pragma unroll
+    for (int k = 1; k < 4 * PER; ++k) t += red[k * logistic_stride(4 * LANES) + c];
+    partial[(size_t)blockIdx.x * logistic_stride(K) + c] = t;
+  }
 }
 // columns 0 .. K - 1 of the partial rows' sum to db, column K over n to loss.  Losses are of one sign and a chain of them drifts: both kernels
 // add them in 64 bits.  In 32 the mean was off by 9.0e-8 (root mean square, 1000 .. 20000 rows), where a tree over the rows had 6.5e-8; so it
@@ -956,8 +987,10 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
   if (K < 4 || K % 4 || K > LOGIT_MAX_K) return fail(DIPACO_ESHAPE, "logistic rows: K must be a multiple of 4 in [4, 4096]");
   const float inv_n = (float)(1.0 / (double)rows);
   if (K <= 256) {
-    const int blocks = (int)std::min<int64_t>((rows + 4 * LOGIT_SMALL_ROWS - 1) / (4 * LOGIT_SMALL_ROWS), LOGIT_SMALL_BLOCKS);
-    logistic_rows_small_kernel<<<blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
+    const int64_t per = 4 * LOGIT_SMALL_ROWS * (K <= 32 ? 8 : K <= 64 ? 4 : K <= 128 ? 2 : 1);
+    const int blocks = (int)std::min<int64_t>((rows + per - 1) / per, LOGIT_SMALL_BLOCKS);
+    auto kern = K <= 32 ? logistic_rows_small_kernel<8> : K <= 64 ? logistic_rows_small_kernel<16> : K <= 128 ? logistic_rows_small_kernel<32> : logistic_rows_small_kernel<64>;
+    kern<<<blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
     DIPACO_LAUNCH_CHECK();
     logistic_finish_kernel<<<(K + 1 + LF_COLS - 1) / LF_COLS, LF_COLS * LF_PHASES, 0, s>>>(partial, blocks, K, (float)rows, db, loss);
     DIPACO_LAUNCH_CHECK();

@@ -265,6 +265,13 @@ def test_logistic_sums_over_several_rounds_of_rows(N, D, K):
     test_logistic_loss_and_gradients_match_oracle(N, D, K)
 
 
+@pytest.mark.parametrize("N,D,K", [(1, 8, 8), (15, 8, 64), (129, 8, 64), (131073, 8, 64), (130, 16, 72), (65, 8, 128), (65537, 8, 128),
+                                   (63, 8, 136), (63, 8, 24), (257, 8, 32), (262145, 8, 16), (140000, 8, 40)])
+def test_logistic_rows_that_share_a_vector(N, D, K):
+    """Eight rows of up to 32 classes, four of up to 64, two of up to 128, one above: ragged vectors and groups, one round of the workgroups and more."""
+    test_logistic_loss_and_gradients_match_oracle(N, D, K)
+
+
 @pytest.mark.parametrize("N,K", [(900, 256), (20000, 64), (40000, 120)])
 def test_logistic_loss_is_off_by_little_more_than_its_rounding(N, K):
     """Over 24 draws, against 64 bits: rounding the result is off by 2^-24 / sqrt(3) at most (root mean square); half as much again is left for
