@@ -856,8 +856,8 @@ __global__ void __launch_bounds__(256) logistic_rows_kernel(float* __restrict__ 
   if (lane == 0) nll[row] = valid ? logf(sum) - at_label : 0.f;
 }
 
-// The same for K <= 256, where a row is at most one 16-byte vector per lane: a wave takes ROWS rows at once, so that
-// ROWS loads are in flight per lane instead of one (a million one-kilobyte rows are latency-bound otherwise), and the
+// The same for K <= 1024, where a row is at most four 16-byte vectors per lane: a wave takes up to eight rows at once, so that
+// eight loads are in flight per lane instead of one (a million one-kilobyte rows are latency-bound otherwise), and the
 // reductions run on the DPP lanes.  Rows behind the last are that one again, without a label, so that nothing branches between
 // rows and their chains interleave; what a row has once (the quotient, the logarithm) is taken for all of them together, a lane each.
 // Up to 128 (64, 32) classes a vector holds two (four, eight) rows, LANES lanes each: the instructions are a vector's, whatever it holds.
@@ -865,8 +865,10 @@ __global__ void __launch_bounds__(256) logistic_rows_kernel(float* __restrict__ 
 // stores (the bias gradient) and, in column K, its rows' losses; logistic_finish_kernel adds these rows.  Bound by its vector instructions and
 // HBM together: 50000 x 256 28.7 us with the rows one behind the other, 22.1 so (the next group's rows requested ahead: 23.2); gradient of
 // 300000 x 64 x 256 404 -> 372, 3000 x 64 x 256 27.1 -> 24.7, 1000000 x 64 x 128 833 -> 719, 676 with two rows a vector, 200000 x 64 x 64
-// 182 -> 162, 130 with four, 1000000 x 64 x 8 579 -> 524, 351 with four, 327 with eight; 3000 x 64 x 64 and x 128 level.
-constexpr int LOGIT_SMALL_ROWS = 8, LOGIT_SMALL_BLOCKS = 1024;
+// 182 -> 162, 130 with four, 1000000 x 64 x 8 579 -> 524, 351 with four, 327 with eight; 3000 x 64 x 64 and x 128 level.  Above 256
+// classes a lane has VEC vectors of a row, and the row's loss, its mean and the column sums need no kernels and no pass of their own: 50000 x 768 x 512
+// 614 -> 582, 50000 x 64 x 512 162 -> 127, 3000 x 64 x 512 51 -> 30, 50000 x 64 x 1024 256 -> 225; more than four would not leave the registers.
+constexpr int LOGIT_SMALL_ROWS = 8, LOGIT_SMALL_BLOCKS = 1024, LOGIT_SMALL_K = 1024;
 constexpr int logistic_stride(int K) { return K + 4; }   // floats between rows of partial sums
 __device__ __forceinline__ float lane_value(float v, int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane)); }
 // over a row's LANES lanes, in each of them
@@ -886,25 +888,36 @@ template <int LANES> __device__ __forceinline__ float row_sum(float v) {
   if constexpr (LANES > 8) v += dpp_fetch<0x140, 0xf>(v, 0.f);
   return LANES == 32 ? v + __shfl_xor(v, 16, 64) : v;
 }
-template <int LANES> __global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits, const int* __restrict__ labels,
-                                                                                       long rows, int K, float inv_n, float* __restrict__ partial) {
-  constexpr int ROWS = LOGIT_SMALL_ROWS, PER = 64 / LANES, GROUP = ROWS * PER;   // K <= 4 LANES
-  __shared__ __attribute__((aligned(16))) float red[4 * PER * logistic_stride(4 * LANES)];
+template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits, const int* __restrict__ labels,
+                                                                                                long rows, int K, float inv_n,
+                                                                                                float* __restrict__ partial) {
+  constexpr int ROWS = LOGIT_SMALL_ROWS / VEC, PER = 64 / LANES, GROUP = ROWS * PER;   // K <= 4 LANES VEC
+  static_assert(VEC == 1 || LANES == 64);
+  constexpr int STRIDE = logistic_stride(4 * LANES * VEC);
+  __shared__ __attribute__((aligned(16))) float red[4 * PER * STRIDE];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int piece = lane / LANES, x = lane % LANES;   // the lane's row of a vector, its place in it
-  const bool on = x < (K >> 2);
-  float sums[4] = {0.f, 0.f, 0.f, 0.f};
+  bool on[VEC];
+  float sums[VEC][4];
+#pragma unroll
+  for (int k = 0; k < VEC; ++k) {
+    on[k] = x + LANES * k < (K >> 2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sums[k][q] = 0.f;
+  }
   double loss = 0.0;   // of lane i: of the i-th row of each group
   const long step = (long)gridDim.x * 4 * GROUP;
   for (long row0 = ((long)blockIdx.x * 4 + wave) * GROUP; row0 < rows; row0 += step) {   // whole waves: the reductions see all 64 lanes
-    float4 v[ROWS];
+    float4 v[ROWS][VEC];
     int own_label = -1;
     if (lane < GROUP && row0 + lane < rows) own_label = labels[row0 + lane];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-      v[r] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (on) v[r] = reinterpret_cast<const float4*>(logits + std::min(row0 + r * PER + piece, rows - 1) * K)[x];
-    }
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        v[r][k] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (on[k]) v[r][k] = reinterpret_cast<const float4*>(logits + std::min(row0 + r * PER + piece, rows - 1) * K)[x + LANES * k];
+      }
     const bool own_valid = own_label >= 0 && own_label < K;
     if (!own_valid) own_label = -1;
     auto label_of = [&](int r) { return PER == 1 ? __builtin_amdgcn_readlane(own_label, r) : __shfl(own_label, r * PER + piece, 64); };
@@ -914,12 +927,21 @@ template <int LANES> __global__ void __launch_bounds__(256) logistic_rows_small_
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       const int label = label_of(r);
-      const float mx = row_max<LANES>(fmaxf(fmaxf(v[r].x, v[r].y), fmaxf(v[r].z, v[r].w)));
-      v[r] = make_float4(v[r].x - mx, v[r].y - mx, v[r].z - mx, v[r].w - mx);
-      const float pick = label & 2 ? (label & 1 ? v[r].w : v[r].z) : (label & 1 ? v[r].y : v[r].x);
-      const float at = PER == 1 ? lane_value(pick, label < 0 ? 0 : label >> 2) : __shfl(pick, own_holder, 64);
-      v[r] = make_float4(expf(v[r].x), expf(v[r].y), expf(v[r].z), expf(v[r].w));   // exp(-inf) = 0 off the row
-      float sum = row_sum<LANES>((v[r].x + v[r].y) + (v[r].z + v[r].w));
+      float mx = -INFINITY, sum = 0.f, pick = 0.f;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) mx = fmaxf(mx, fmaxf(fmaxf(v[r][k].x, v[r][k].y), fmaxf(v[r][k].z, v[r][k].w)));
+      mx = row_max<LANES>(mx);
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        float4& w = v[r][k];
+        w = make_float4(w.x - mx, w.y - mx, w.z - mx, w.w - mx);
+        const float p = label & 2 ? (label & 1 ? w.w : w.z) : (label & 1 ? w.y : w.x);
+        if (k == 0 || label >> 8 == k) pick = p;
+        w = make_float4(expf(w.x), expf(w.y), expf(w.z), expf(w.w));   // exp(-inf) = 0 off the row
+        sum += (w.x + w.y) + (w.z + w.w);
+      }
+      const float at = PER == 1 ? lane_value(pick, label < 0 ? 0 : (label >> 2) % 64) : __shfl(pick, own_holder, 64);
+      sum = row_sum<LANES>(sum);
       if constexpr (PER > 1) sum = __shfl(sum, own_first, 64);
       if (lane / PER == r) { own_sum = sum; own_at = at; }
     }
@@ -929,27 +951,32 @@ template <int LANES> __global__ void __launch_bounds__(256) logistic_rows_small_
     for (int r = 0; r < ROWS; ++r) {
       const int label = label_of(r);
       const float scale = PER == 1 ? lane_value(own_scale, r) : __shfl(own_scale, r * PER + piece, 64);
-      const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-      float o[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        o[q] = e[q] * scale - (4 * x + q == label ? inv_n : 0.f);
-        sums[q] += o[q];
-      }
       const long row = row0 + r * PER + piece;
-      if (on && row < rows) reinterpret_cast<float4*>(logits + row * K)[x] = make_float4(o[0], o[1], o[2], o[3]);
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        const float e[4] = {v[r][k].x, v[r][k].y, v[r][k].z, v[r][k].w};
+        float o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          o[q] = e[q] * scale - (4 * (x + LANES * k) + q == label ? inv_n : 0.f);
+          sums[k][q] += o[q];
+        }
+        if (on[k] && row < rows) reinterpret_cast<float4*>(logits + row * K)[x + LANES * k] = make_float4(o[0], o[1], o[2], o[3]);
+      }
     }
   }
 #pragma unroll
   for (int o = 1; o < GROUP; o <<= 1) loss += __shfl_xor(loss, o, 64);
-  float* mine = red + (wave * PER + piece) * logistic_stride(4 * LANES);
-  if (on) *reinterpret_cast<float4*>(mine + 4 * x) = make_float4(sums[0], sums[1], sums[2], sums[3]);
+  float* mine = red + (wave * PER + piece) * STRIDE;
+#pragma unroll
+  for (int k = 0; k < VEC; ++k)
+    if (on[k]) *reinterpret_cast<float4*>(mine + 4 * (x + LANES * k)) = make_float4(sums[k][0], sums[k][1], sums[k][2], sums[k][3]);
   if (x == 0) mine[K] = piece ? 0.f : (float)loss;
   __syncthreads();
   for (int c = threadIdx.x; c <= K; c += 256) {
     float t = red[c];
 #pragma unroll
-    for (int k = 1; k < 4 * PER; ++k) t += red[k * logistic_stride(4 * LANES) + c];
+    for (int k = 1; k < 4 * PER; ++k) t += red[k * STRIDE + c];
     partial[(size_t)blockIdx.x * logistic_stride(K) + c] = t;
   }
 }
@@ -986,18 +1013,26 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
                                    float* db, hipStream_t s) {
   if (K < 4 || K % 4 || K > LOGIT_MAX_K) return fail(DIPACO_ESHAPE, "logistic rows: K must be a multiple of 4 in [4, 4096]");
   const float inv_n = (float)(1.0 / (double)rows);
-  if (K <= 256) {
-    const int64_t per = 4 * LOGIT_SMALL_ROWS * (K <= 32 ? 8 : K <= 64 ? 4 : K <= 128 ? 2 : 1);
-    const int blocks = (int)std::min<int64_t>((rows + per - 1) / per, LOGIT_SMALL_BLOCKS);
-    auto kern = K <= 32 ? logistic_rows_small_kernel<8> : K <= 64 ? logistic_rows_small_kernel<16> : K <= 128 ? logistic_rows_small_kernel<32> : logistic_rows_small_kernel<64>;
-    kern<<<blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
+  const int64_t blocks = (rows + 3) / 4;
+  if (K > 256 && !launch_fits(blocks, 256)) return fail(DIPACO_ESHAPE, "logistic rows: too many rows");
+  if (K <= LOGIT_SMALL_K) {
+    auto run = [&](auto lanes, auto vec) {
+      const int64_t per = 4 * LOGIT_SMALL_ROWS / vec * (64 / lanes);
+      const int n = (int)std::min<int64_t>((rows + per - 1) / per, LOGIT_SMALL_BLOCKS);
+      logistic_rows_small_kernel<lanes, vec><<<n, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
+      return n;
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, 1> one{};
+    const int n = K <= 32 ? run(integral_constant<int, 8>{}, one) : K <= 64 ? run(integral_constant<int, 16>{}, one)
+                  : K <= 128 ? run(integral_constant<int, 32>{}, one) : K <= 256 ? run(integral_constant<int, 64>{}, one)
+                  : K <= 512 ? run(integral_constant<int, 64>{}, integral_constant<int, 2>{})
+                             : run(integral_constant<int, 64>{}, integral_constant<int, 4>{});
     DIPACO_LAUNCH_CHECK();
-    logistic_finish_kernel<<<(K + 1 + LF_COLS - 1) / LF_COLS, LF_COLS * LF_PHASES, 0, s>>>(partial, blocks, K, (float)rows, db, loss);
+    logistic_finish_kernel<<<(K + 1 + LF_COLS - 1) / LF_COLS, LF_COLS * LF_PHASES, 0, s>>>(partial, n, K, (float)rows, db, loss);
     DIPACO_LAUNCH_CHECK();
     return DIPACO_OK;
   }
-  const int64_t blocks = (rows + 3) / 4;
-  if (!launch_fits(blocks, 256)) return fail(DIPACO_ESHAPE, "logistic rows: too many rows");
   logistic_rows_kernel<<<(unsigned)blocks, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, nll);
   DIPACO_LAUNCH_CHECK();
   dipaco_status st = launch_fill_i32(n_valid, (int)rows, 1, s);

@@ -266,9 +266,11 @@ def test_logistic_sums_over_several_rounds_of_rows(N, D, K):
 
 
 @pytest.mark.parametrize("N,D,K", [(1, 8, 8), (15, 8, 64), (129, 8, 64), (131073, 8, 64), (130, 16, 72), (65, 8, 128), (65537, 8, 128),
-                                   (63, 8, 136), (63, 8, 24), (257, 8, 32), (262145, 8, 16), (140000, 8, 40)])
+                                   (63, 8, 136), (63, 8, 24), (257, 8, 32), (262145, 8, 16), (140000, 8, 40), (17, 8, 264), (33000, 8, 512),
+                                   (5, 8, 520), (20000, 8, 1024), (9, 8, 1032)])
 def test_logistic_rows_that_share_a_vector(N, D, K):
-    """Eight rows of up to 32 classes, four of up to 64, two of up to 128, one above: ragged vectors and groups, one round of the workgroups and more."""
+    """Eight rows of up to 32 classes, four of up to 64, two of up to 128, one above, which takes two vectors from 257 on and four
+    from 513 on: ragged vectors and groups, one round of the workgroups and more."""
     test_logistic_loss_and_gradients_match_oracle(N, D, K)
 
 
