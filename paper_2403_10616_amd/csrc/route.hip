@@ -868,6 +868,9 @@ __global__ void __launch_bounds__(256) logistic_rows_kernel(float* __restrict__ 
 // 182 -> 162, 130 with four, 1000000 x 64 x 8 579 -> 524, 351 with four, 327 with eight; 3000 x 64 x 64 and x 128 level.  Above 256
 // classes a lane has VEC vectors of a row, and the row's loss, its mean and the column sums need no kernels and no pass of their own: 50000 x 768 x 512
 // 614 -> 582, 50000 x 64 x 512 162 -> 127, 3000 x 64 x 512 51 -> 30, 50000 x 64 x 1024 256 -> 225; more than four would not leave the registers.
+// A lane's rows grow with N (256 of 2^20): a group's are added in 32 bits, groups in 64, at no cost that shows (1048576 x 64 x 512 2561 us both ways).
+// In one 32-bit chain like rows drift: weights of zero, 2^20 rows, K = 64 / 512 / 1024 off by 6.0e-7 / 2.6e-6 / 3.2e-6 of the summands'
+// magnitude, so by 1.4e-7 - 1.6e-7, the rounding of a row's own values.
 constexpr int LOGIT_SMALL_ROWS = 8, LOGIT_SMALL_BLOCKS = 1024, LOGIT_SMALL_K = 1024;
 constexpr int logistic_stride(int K) { return K + 4; }   // floats between rows of partial sums
 __device__ __forceinline__ float lane_value(float v, int lane) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane)); }
@@ -898,12 +901,12 @@ template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_ro
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int piece = lane / LANES, x = lane % LANES;   // the lane's row of a vector, its place in it
   bool on[VEC];
-  float sums[VEC][4];
+  double sums[VEC][4];
 #pragma unroll
   for (int k = 0; k < VEC; ++k) {
     on[k] = x + LANES * k < (K >> 2);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sums[k][q] = 0.f;
+    for (int q = 0; q < 4; ++q) sums[k][q] = 0.0;
   }
   double loss = 0.0;   // of lane i: of the i-th row of each group
   const long step = (long)gridDim.x * 4 * GROUP;
@@ -947,6 +950,7 @@ template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_ro
     }
     const float own_scale = own_valid ? inv_n / own_sum : 0.f;
     loss += (double)(own_valid ? logf(own_sum) - own_at : 0.f);
+    float group[VEC][4] = {};
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       const int label = label_of(r);
@@ -959,18 +963,22 @@ template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_ro
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           o[q] = e[q] * scale - (4 * (x + LANES * k) + q == label ? inv_n : 0.f);
-          sums[k][q] += o[q];
+          group[k][q] += o[q];
         }
         if (on[k] && row < rows) reinterpret_cast<float4*>(logits + row * K)[x + LANES * k] = make_float4(o[0], o[1], o[2], o[3]);
       }
     }
+#pragma unroll
+    for (int k = 0; k < VEC; ++k)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sums[k][q] += (double)group[k][q];
   }
 #pragma unroll
   for (int o = 1; o < GROUP; o <<= 1) loss += __shfl_xor(loss, o, 64);
   float* mine = red + (wave * PER + piece) * STRIDE;
 #pragma unroll
   for (int k = 0; k < VEC; ++k)
-    if (on[k]) *reinterpret_cast<float4*>(mine + 4 * (x + LANES * k)) = make_float4(sums[k][0], sums[k][1], sums[k][2], sums[k][3]);
+    if (on[k]) *reinterpret_cast<float4*>(mine + 4 * (x + LANES * k)) = make_float4((float)sums[k][0], (float)sums[k][1], (float)sums[k][2], (float)sums[k][3]);
   if (x == 0) mine[K] = piece ? 0.f : (float)loss;
   __syncthreads();
   for (int c = threadIdx.x; c <= K; c += 256) {

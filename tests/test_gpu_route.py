@@ -291,6 +291,23 @@ def test_logistic_loss_is_off_by_little_more_than_its_rounding(N, K):
     assert rms <= 1.5 * 2.0 ** -24 / 3 ** 0.5
 
 
+@pytest.mark.parametrize("K", [64, 256, 264, 512, 1024])
+def test_a_long_sum_of_like_rows_does_not_drift(K):
+    """2^20 rows of the same probabilities (weights not yet trained): up to 256 rows a lane, which in one fp32 chain leave the bias gradient off by 6e-7
+    (64 classes) to 3e-6 (1024) of the summands' magnitude.  Bound: four roundings of a row's own value (exponential, sum, quotient, product),
+    alike in every row; 1.4e-7 - 1.6e-7 measured."""
+    N, D = 1 << 20, 8
+    rng = np.random.default_rng(K)
+    b, y = rng.standard_normal(K).astype(np.float32), rng.integers(0, K, N).astype(np.int32)
+    _, _, db = _logistic(np.zeros((N, D), np.float32), y, np.zeros((K, D), np.float32), b, want_dw=False)
+    p = np.exp(b.astype(np.float64) - b.max())
+    p /= p.sum()
+    hits = np.bincount(y, minlength=K) / N
+    off = float(np.abs((db - (p - hits)) / (p * (1.0 - hits) + (1.0 - p) * hits)).max())
+    print(f"logistic bias gradient K={K}: off by {off:.2e} of the magnitudes", flush=True)
+    assert off <= 4 * 2.0 ** -24
+
+
 def test_bias_fit_on_gpu_gradients_matches_label_distribution_and_refills_empty_paths():
     """Weights frozen, bias descended with the GPU's dbias: the mean predicted distribution reaches the labels',
     and classes the unfitted classifier never picked get documents again."""
