@@ -57,6 +57,12 @@ dipaco_status dipaco_k_set_gemm_tile(int32_t tile);
  * total never exceeds the 256 compute units. */
 dipaco_status dipaco_k_gemm_split_plan(int32_t M, int32_t N, int32_t K, int32_t max_slices, int32_t* out);
 
+/* Host-only: how a bf16 step takes the gradients of a linear layer of k_in x n_out weights over `tokens` tokens, dW = X^T dY (in at most
+ * max_slices K slices) and dX = dY W^T.  out (host int32 [4]): rows of dX's tile where both are one launch, 0 where they are
+ * two; 1 if dW's tiles come first in it; K of the longest chain of sums in dW in one launch (0: two launches), and in two: the first never exceeds
+ * the second.  k_in, n_out: multiples of 8. */
+dipaco_status dipaco_k_gemm_pair_plan(int32_t tokens, int32_t k_in, int32_t n_out, int32_t max_slices, int32_t* out);
+
 /* How the bf16 attention kernels deal the blocks of the causal triangle to workgroups, for every later call in this
  * process (tuning and tests): 0 = a long and a short block per workgroup, 1 = one block per workgroup, launched
  * longest first.  Results are identical. */

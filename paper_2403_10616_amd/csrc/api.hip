@@ -1022,6 +1022,13 @@ dipaco_status dipaco_k_gemm_split_plan(int32_t M, int32_t N, int32_t K, int32_t 
   return DIPACO_OK;
 }
 
+dipaco_status dipaco_k_gemm_pair_plan(int32_t tokens, int32_t k_in, int32_t n_out, int32_t max_slices, int32_t* out) {
+  if (!out || tokens < 1 || k_in < 8 || n_out < 8 || k_in % 8 || n_out % 8 || max_slices < 1)
+    return fail(DIPACO_EINVAL, "dipaco_k_gemm_pair_plan: bad argument");
+  gemm_pair_plan_info(tokens, k_in, n_out, max_slices, out);
+  return DIPACO_OK;
+}
+
 dipaco_status dipaco_k_set_attention_blocks(int32_t single_block) {
   if (single_block != 0 && single_block != 1) return fail(DIPACO_EINVAL, "dipaco_k_set_attention_blocks: 0 or 1");
   set_attention_single_block(single_block);

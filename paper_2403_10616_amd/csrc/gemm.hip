@@ -227,19 +227,30 @@ template <typename T> dipaco_status launch_norm_gemm(const T* x, const T* gain, 
   return launch_gemm<T>(a, s);
 }
 
-// Whether dW and dX in one launch of fitted tiles (gemm_fit_pair_wide_kernel, dW uncut) are modelled clearly below two launches.  Backward passes
-// of the 150M path, whole steps, us, two -> one: 1 x 1000 tokens 4473 -> 4000, 2 x 700 4774 -> 4247, 6 x 900 9440 -> 9080, 3 x 1000 6374 -> 6291;
-// with no margin a 1024-wide one of 4096 tokens, whose products are whole rounds, is 0.3 % behind.  Contractions above 16384 stay with the
-// direct-to-LDS kernel (plan_splits).
-static bool pays_as_wide_pair(const GemmArgs& dw, const GemmArgs& dx) {
-  if (dw.K > 16384) return false;
+// K of the longest chain of sums in dW's own launch: a slice in the direct-to-LDS kernel, a group of waves' part of one in a fitted tile
+static int dw_chain(const GemmArgs& dw) {
+  const int splits = std::max(1, dw.splits), k = (dw.K + splits - 1) / splits;
+  const int groups = want_dlds(dw) && gemm_dlds_eligible(dw) ? 1 : gemm_fit_groups(dw.M, dw.N, k, splits);
+  return (k + groups - 1) / groups;
+}
+
+// dW and dX in one launch of fitted tiles (gemm_fit_pair_wide_kernel, dW uncut) where that is modelled clearly below two launches and dW's chains of
+// sums are no longer than there (896 x 896 over 3000 tokens is two slices of two groups: in one launch 1.3e-7 off where it was 1.0e-7).
+// Whole forward and backward passes, us, two launches -> one: 150M path, 1 x 1000 tokens 3689 -> 3204, 2 x 700 3996 -> 3452, 6 x 900 8760 ->
+// 8454, 3 x 1000 5753 -> 5616, 8 x 1000 11998 -> 11696; 512 wide, 3 x 777 1565 -> 1406; level at 1024 wide, 8 x 512, and 512 wide, 12 x 700.  The price
+// knows no epilogue.  The down-projection's dX, with GELU' and column sums, is 93 of the 485 us at 1 x 1000, 71 of 544 at 2 x 700, 22 - 40 of 137 at 3 x
+// 1000, level at 8 x 1000, and loses 13 of 1921 at 1024 wide, 2 x 512.  With no margin a 1024-wide path of 4096 tokens, whose products are
+// whole rounds, is 0.3 % behind.  Contractions above 16384 stay with the direct-to-LDS kernel (plan_splits).
+static GemmWidePair pick_wide_pair(const GemmArgs& dw, const GemmArgs& dx) {
+  const GemmWidePair none{0, true, 1e30};
+  if (dw.K > 16384 || (dw.K + GEMM_WIDE_GROUPS - 1) / GEMM_WIDE_GROUPS > dw_chain(dw)) return none;
   GemmArgs whole = dw;
   whole.splits = 1;
-  const double one = gemm_fit_pair_wide_us(whole, dx);
+  const GemmWidePair one = gemm_fit_pair_wide(whole, dx);
   const double w = plan_splits(dw.M, dw.N, dw.K, true, true, std::max(1, dw.splits)).us;
   const double rounds = (double)(((long)((dx.M + 255) / 256) * ((dx.N + 255) / 256) + 255) / 256);
   const double x = want_dlds(dx) && gemm_dlds_eligible(dx) ? 3.0 + rounds * (8.0 + 0.023 * dx.K) : gemm_fit_cost(gemm_fit_tiles(dx.M, dx.N, true, true), dx.K, 1);
-  return one < 0.93 * (w + 1.0 + x);
+  return one.us < 0.93 * (w + 1.0 + x) ? one : none;
 }
 
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
@@ -247,14 +258,28 @@ template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const G
   if (dipaco_status st = check_gemm<T>(dx)) return st;
   if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32 && gemm_fit_pair_takes<T>(dw, dx)) return launch_gemm_fit_pair<T>(dw, dx, s);
   if constexpr (std::is_same<T, bf16>::value) {
-    if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32 && pays_as_wide_pair(dw, dx)) {
+    if (!g_forced_kernel && dw.out_f32 && dx.trans_b && !dx.out_f32) {
       GemmArgs whole = dw;
       whole.splits = 1;
-      return launch_gemm_fit_pair_wide(whole, dx, s);
+      const GemmWidePair pair = pick_wide_pair(dw, dx);
+      if (pair.rows) return launch_gemm_fit_pair_wide(whole, dx, pair, s);
     }
   }
   if (dipaco_status st = launch_gemm<T>(dw, s)) return st;
   return launch_gemm<T>(dx, s);
+}
+
+void gemm_pair_plan_info(int tokens, int k_in, int n_out, int max_slices, int* out) {
+  GemmArgs dw{}, dx{};
+  dw.M = k_in; dw.N = n_out; dw.K = tokens; dw.lda = k_in; dw.ldb = dw.ldc = n_out; dw.trans_a = dw.out_f32 = 1;
+  dw.splits = gemm_plan_splits(k_in, n_out, tokens, true, max_slices);
+  dx.M = tokens; dx.N = k_in; dx.K = n_out; dx.lda = dx.ldb = n_out; dx.ldc = k_in; dx.trans_b = 1; dx.splits = 1;
+  const bool small = !g_forced_kernel && gemm_fit_pair_takes<bf16>(dw, dx);
+  const GemmWidePair pair = g_forced_kernel || small ? GemmWidePair{0, true, 1e30} : pick_wide_pair(dw, dx);
+  out[0] = small ? 32 : pair.rows;
+  out[1] = small || (pair.rows && pair.dw_first);
+  out[3] = dw_chain(dw);
+  out[2] = small ? out[3] : pair.rows ? (tokens + GEMM_WIDE_GROUPS - 1) / GEMM_WIDE_GROUPS : 0;
 }
 
 template dipaco_status launch_norm_gemm<float>(const float*, const float*, const float*, float*, float*, float, const GemmArgs&, hipStream_t);

@@ -717,37 +717,38 @@ double dealt(long n, double us, long n2, double us2) {
     }
   return end;
 }
-struct WidePair { int tx; bool dw_first; double us; };   // the longer tiles first
-WidePair pick_wide(const GemmArgs& dw, const GemmArgs& dx) {
+GemmWidePair pick_wide(const GemmArgs& dw, const GemmArgs& dx) {   // the longer tiles first
   const long nw = shape_tiles(4, dw.M, dw.N, true);
   const double cw = BF16_FIXED[4] + BF16_PER_K[4] * dw.K * 1e-3;
-  WidePair best{0, true, 1e30};
+  GemmWidePair best{0, true, 1e30};
   for (int t = 3; t <= 5; ++t) {
     const long nx = shape_tiles(t, dx.M, dx.N, true);
     if (nw + nx > 256 * 8) continue;
     const double cx = BF16_FIXED[t] + BF16_PER_K[t] * dx.K * 1e-3;
     const bool dw_first = cw >= cx;
     const double us = 3.0 + (dw_first ? dealt(nw, cw, nx, cx) : dealt(nx, cx, nw, cw));
-    if (us < best.us) best = WidePair{t, dw_first, us};
+    if (us < best.us) best = GemmWidePair{32 * t, dw_first, us};
   }
   return best;
 }
 
 }  // namespace
 
-double gemm_fit_pair_wide_us(const GemmArgs& dw, const GemmArgs& dx) {
+int gemm_fit_groups(int M, int N, int K, int splits) { return pick_fit(M, N, K, splits, true, false, false) == 1 ? 8 : 2; }
+
+GemmWidePair gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx) {
   constexpr uint64_t most = 1ull << 32;
-  if (g_forced_fit || dw.splits > 1 || dx.splits > 1 || dw.raw_planes || dx.raw_planes) return 1e30;
+  const GemmWidePair none{0, true, 1e30};
+  if (g_forced_fit || dw.splits > 1 || dx.splits > 1 || dw.raw_planes || dx.raw_planes) return none;
   if (fit_span(false, 128, 64, dw.M, dw.K, dw.lda, 2) >= most || fit_span(false, 128, 64, dw.N, dw.K, dw.ldb, 2) >= most ||
-      fit_span(true, 160, 64, dx.M, dx.K, dx.lda, 2) >= most || fit_span(true, 128, 64, dx.N, dx.K, dx.ldb, 2) >= most) return 1e30;
-  return pick_wide(dw, dx).us;
+      fit_span(true, 160, 64, dx.M, dx.K, dx.lda, 2) >= most || fit_span(true, 128, 64, dx.N, dx.K, dx.ldb, 2) >= most) return none;
+  return pick_wide(dw, dx);
 }
-dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s) {
-  const WidePair p = pick_wide(dw, dx);
+dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, const GemmWidePair& p, hipStream_t s) {
   auto run = [&](auto TXc) -> dipaco_status {
     constexpr int TX = decltype(TXc)::value;
-    using W = Fit<bf16, float, false, false, 4, 4, 2, 2, 2, 4>;
-    using X = Fit<bf16, bf16, true, true, TX, 4, 2, 2, 2, 4>;
+    using W = Fit<bf16, float, false, false, 4, 4, 2, 2, GEMM_WIDE_GROUPS, 4>;
+    using X = Fit<bf16, bf16, true, true, TX, 4, 2, 2, GEMM_WIDE_GROUPS, 4>;
     constexpr int LDS = W::LDS > X::LDS ? W::LDS : X::LDS;
     auto kern = gemm_fit_pair_wide_kernel<TX>;
     static std::atomic<unsigned long long> lds_set{0};   // per instantiation
@@ -759,8 +760,8 @@ dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, 
     if (dx.colsum) return launch_sum_rows(dx.colsum_partial, dx.colsum, x.tiles_m, dx.N, s, dx.sum_batch);
     return DIPACO_OK;
   };
-  if (p.tx == 3) return run(std::integral_constant<int, 3>{});
-  if (p.tx == 4) return run(std::integral_constant<int, 4>{});
+  if (p.rows == 96) return run(std::integral_constant<int, 3>{});
+  if (p.rows == 128) return run(std::integral_constant<int, 4>{});
   return run(std::integral_constant<int, 5>{});
 }
 

@@ -124,8 +124,9 @@ struct RowNorm { const float* gain; const float* shift; float* y; float* mean; f
 bool gemm_norm_takes(const GemmArgs& g);
 dipaco_status launch_gemm_norm(const GemmArgs& g, const RowNorm& ln, hipStream_t s);   // of checked arguments
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
-double gemm_fit_pair_wide_us(const GemmArgs& dw, const GemmArgs& dx);
-dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
+// how launch_gemm_pair takes bf16 products of these sizes (dW cut into at most max_slices), for tests.  out[0]: rows of dX's tile in one launch with
+// dW, 0: two launches; out[1]: dW's tiles come first; out[2], out[3]: K of dW's longest chain of sums in one launch, in two
+void gemm_pair_plan_info(int tokens, int k_in, int n_out, int max_slices, int* out);
 // gemm_dlds.hip: bf16, 256x256 tiles loaded from global memory straight into LDS; takes the shapes for which
 // gemm_dlds_eligible holds (whole K tiles of 32, 16-byte rows); launch_gemm routes to it by itself
 bool gemm_dlds_eligible(const GemmArgs& g);
@@ -136,6 +137,12 @@ template <typename T> dipaco_status launch_gemm_fit(const GemmArgs& g, hipStream
 // X^T dY (fp32) and dY W^T of a linear layer in one launch, where both are small
 template <typename T> bool gemm_fit_pair_takes(const GemmArgs& dw, const GemmArgs& dx);
 template <typename T> dipaco_status launch_gemm_fit_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
+// the same in bf16 for larger ones, dW uncut (splits of 1): rows of dX's tile, order and modelled microseconds (1e30: not taken)
+struct GemmWidePair { int rows; bool dw_first; double us; };
+GemmWidePair gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx);
+dipaco_status launch_gemm_fit_pair_wide(const GemmArgs& dw, const GemmArgs& dx, const GemmWidePair& p, hipStream_t s);
+constexpr int GEMM_WIDE_GROUPS = 2;   // groups of waves along K there, each with a chain of sums of its own
+int gemm_fit_groups(int M, int N, int K, int splits);   // the same of launch_gemm_fit for a bf16 dW in slices of K
 // gemm_split.hip: fp32 on the bf16 matrix cores, tiles of 64 or 128 rows x 128; rows less than 4 GiB apart within a tile
 dipaco_status launch_gemm_split(const GemmArgs& g, int rows, hipStream_t s);
 void set_gemm_fit_shape(int shape);   // 0 = automatic, 1 = 32 x 64, 2 .. 5 = 64, 96, 128, 160 x 128

@@ -165,6 +165,21 @@ def test_uneven_split_plan_of_the_step_shapes():
         dp.dipaco_k_gemm_split_plan(896, 3584, 1000, 32)
 
 
+@pytest.mark.parametrize("d,F,V", [(896, 3584, 32000), (1024, 4096, 16000), (640, 2400, 8000), (512, 2048, 8192), (768, 3072, 16000), (200, 696, 1000)])
+def test_one_launch_for_both_gradients_adds_weights_in_no_longer_chains(d, F, V):
+    """A weight gradient that is cut over its tokens in a launch of its own, or whose groups of waves are eight there, is not left whole for two."""
+    taken = 0
+    for tokens in list(range(1, 260, 37)) + list(range(300, 17000, 211)) + [1000, 1400, 3000, 4096, 5400]:
+        for k_in, n_out in ((d, F), (F, d), (d, d), (d, 3 * d), (d, V)):
+            p = dp.dipaco_k_gemm_pair_plan(tokens, k_in, n_out, 1 << 20)
+            taken += p["rows"] > 0
+            assert p["rows"] in (0, 32, 96, 128, 160) and (p["rows"] == 0) == (p["chain"] == 0)
+            assert p["chain"] <= p["chain_alone"], (tokens, k_in, n_out, p)
+    assert taken > 10
+    with pytest.raises(dp.DipacoError):
+        dp.dipaco_k_gemm_pair_plan(100, d, d + 4, 1)
+
+
 @pytest.mark.parametrize("compute", [dp.F32, dp.BF16])
 @pytest.mark.parametrize("arch", [([6, 6], 896, 14, 64, 3584, 32000), ([1, 1], 64, 2, 32, 256, 256), ([3, 3], 1024, 8, 128, 4096, 16000),
                                   ([1], 736, 3, 64, 3000, 1000), ([1], 32, 1, 32, 32, 40)])
