@@ -624,9 +624,10 @@ def test_fp32_attention_above_512_blocks(B, S, H, dh):
 
 
 @pytest.mark.parametrize("B,S,H,dh", [(5, 257, 17, 32), (2, 300, 43, 64), (1, 385, 3, 128), (4, 200, 3, 64), (3, 129, 2, 32), (32, 128, 9, 64), (4, 512, 16, 64),
-                                      (3, 600, 17, 128), (65, 513, 10, 32)])
+                                      (3, 600, 17, 128), (65, 513, 10, 32), (40, 641, 9, 32), (30, 1025, 5, 64)])
 def test_bf16_attention_gradients_in_one_launch_and_in_two(B, S, H, dh):
-    """One block of 128 positions to five; 255, 256 and 258 blocks, on the two sides of two groups a block; 3250 blocks of long sequences take two launches."""
+    """One block of 128 positions to five; 255, 256 and 258 blocks, on the two sides of two groups a block; two launches for 3250 blocks, and
+    for 2160 and 1350 of sequences of six and nine with narrow heads."""
     print(f"{B * H * -(-S // 128)} blocks", flush=True)
     test_attention_forward_backward(dp.BF16, B, S, H, dh, 1)
 
