@@ -444,7 +444,7 @@ dipaco_status fwd_rows(const float* qkv, float* o, float* lse, int B, int S, int
     const dim3 grid(std::min(step, B - b) * H, (S + 16 * NW - 1) / (16 * NW));
     static std::atomic<int> resident{0};
     bool paired;
-    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_fwd_f32<DH, NW>), 64 * NW, fwd_lds<DH>(), (long)grid.x * grid.y, resident, paired)) return st;
+    if (dipaco_status st = causal_paired(reinterpret_cast<const void*>(attn_fwd_f32<DH, NW>), 64 * NW, fwd_lds<DH>(), grid.x, (long)grid.x * grid.y, resident, paired)) return st;
     attn_fwd_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, lse + row * H, S, H, paired);
     DIPACO_LAUNCH_CHECK();
   }
@@ -484,7 +484,7 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
         constexpr int LDS = std::max(fwd_lds<DH>(), dkv_lds<DH>());
         const void* const kern = reinterpret_cast<const void*>(attn_bwd_both_f32<DH, NW>);
         if (dipaco_status st = ensure_dynamic_lds(kern, LDS, both)) return st;
-        if (dipaco_status st = causal_paired(kern, 64 * NW, LDS, 2 * n, resident, paired)) return st;
+        if (dipaco_status st = causal_paired(kern, 64 * NW, LDS, grid.x, 2 * n, resident, paired)) return st;
         attn_stats_f32<DH, NW><<<grid, 64 * NW, 0, s>>>(o + row * A, d_o + row * A, dsum + row * H, S, H);
         DIPACO_LAUNCH_CHECK();
         attn_bwd_both_f32<DH, NW><<<dim3(grid.x, 2 * grid.y), 64 * NW, LDS, s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H, dsum + row * H,
@@ -501,8 +501,8 @@ dipaco_status bwd(const float* qkv, const float* o, const float* d_o, const floa
       const void* const dkv_kern = reinterpret_cast<const void*>(attn_bwd_dkv_f32<DH, NW>);
       if (dipaco_status st = ensure_dynamic_lds(dq_kern, fwd_lds<DH>(), dq)) return st;
       if (dipaco_status st = ensure_dynamic_lds(dkv_kern, dkv_lds<DH>(), dkv)) return st;
-      if (dipaco_status st = causal_paired(dq_kern, 64 * NW, fwd_lds<DH>(), n, dq_resident, dq_paired)) return st;
-      if (dipaco_status st = causal_paired(dkv_kern, 64 * NW, dkv_lds<DH>(), n, dkv_resident, dkv_paired)) return st;
+      if (dipaco_status st = causal_paired(dq_kern, 64 * NW, fwd_lds<DH>(), grid.x, n, dq_resident, dq_paired)) return st;
+      if (dipaco_status st = causal_paired(dkv_kern, 64 * NW, dkv_lds<DH>(), grid.x, n, dkv_resident, dkv_paired)) return st;
       attn_bwd_dq_f32<DH, NW><<<grid, 64 * NW, fwd_lds<DH>(), s>>>(qkv + row * 3 * A, o + row * A, d_o + row * A, lse + row * H,
                                                                    dqkv + row * 3 * A, dsum + row * H, cs, S, H, dq_paired);
       DIPACO_LAUNCH_CHECK();

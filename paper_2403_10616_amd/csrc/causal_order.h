@@ -5,8 +5,9 @@
 // hardware's ids: in 256, 336, 512 and 768 workgroups of 256 and 512 threads, every one), and then longest first puts long blocks with
 // long ones: 64 heads of 8 blocks give one unit 8 + 4, another 5 + 1.  Such a launch pairs its rounds of 256 instead, so that a unit's blocks
 // add up to about the same.  Forward | backward, us, longest first -> paired: 64 heads x 500 x 64 40.3 -> 36.3 | 113.8 -> 102.6, x 128 67.1 ->
-// 58.7 | 205.0 -> 177.5, 128 heads x 500 x 64 57.3 -> 53.4 | 172.4 -> 168.9, 32 x 2000 x 64 209 -> 183 | 583 -> 547, 256 x 256 x 64 (four even
-// rounds) 32.8 -> 33.0 | 102.8 -> 104.7.  The bf16 kernels, which wait more and multiply less, gain nothing (42 x 1900 forward 38.3 -> 38.6)
+// 58.7 | 205.0 -> 177.5, 128 heads x 500 x 64 57.3 -> 53.4 | 172.4 -> 168.9, 32 x 2000 x 64 209 -> 183 | 583 -> 547.  A multiple of 256 heads has
+// nothing to pair, each round being one block of every head, and keeps a head's blocks on one unit: 256 heads x 70 x 128 forward 18.0 us longest first,
+// 19.7 paired, x 130 x 64 19.5 | 20.5, x 250 x 32 20.1 | 20.7, backward level.  The bf16 kernels, which wait more and multiply less, gain nothing (42 x 1900 forward 38.3 -> 38.6)
 // or lose (64 x 700 x 64 backward 60.2 -> 62.5): they stay longest first.
 #pragma once
 #include "common.h"
@@ -33,10 +34,10 @@ __device__ __forceinline__ CausalPlace causal_place(bool paired) {
   return {rank - order * n_bh, order, n_bh};
 }
 
-// whether a launch of n workgroups pairs its rounds: they are resident at once.  `seen`: the kernel's own, workgroups to a unit + 1
-inline dipaco_status causal_paired(const void* kernel, int threads, int lds, long n, std::atomic<int>& seen, bool& paired) {
+// whether a launch of n workgroups, blocks of n_bh heads, pairs its rounds: they are resident at once.  `seen`: the kernel's own, workgroups to a unit + 1
+inline dipaco_status causal_paired(const void* kernel, int threads, int lds, long n_bh, long n, std::atomic<int>& seen, bool& paired) {
   paired = false;
-  if (n <= CAUSAL_UNITS || n > CAUSAL_UNITS * CAUSAL_MOST_ROUNDS) return DIPACO_OK;
+  if (n_bh % CAUSAL_UNITS == 0 || n <= CAUSAL_UNITS || n > CAUSAL_UNITS * CAUSAL_MOST_ROUNDS) return DIPACO_OK;
   int resident = seen.load(std::memory_order_relaxed) - 1;
   if (resident < 0) {
     DIPACO_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, threads, lds));
