@@ -355,10 +355,10 @@ inline bool two_groups(int B, int H, int S) {
 // Ahead up to 1152 blocks at every head size and 5 to 32 blocks a sequence (1 - 23 %), and up to four blocks a sequence.  Above, dQ and dK / dV fill
 // the chip alone, and long sequences of narrow heads are behind (dQ alone has three waves a SIMD, not two; head size 32 has three for dK / dV too):
 // 1536 | 2048 | 2560 blocks of sequences of 16 at head size 32 +1.6 | +4.4 | +5.1 %, 64 +3.7 | +6.1 | +5.5, 128 -1.4 | -1.5 | +0.5; of 12 at 64 +2.1 | -0.2 |
-// -1.1; of 8 at 32 -0.7 | +0.1 | -0.1, 64 -2.2 | +2.6 | -3.4, 128 -6.1 | -6.5 | -3.3; of 5 at 32 -4.0 | -1.3 | -0.8.  Level at 3072.
+// -1.1; of 8 at 32 -0.7 | +0.1 | -0.1, 64 -2.2 | +2.6 | -3.4, 128 -6.1 | -6.5 | -3.3; of 5 at 32 -4.0 | -1.3 | -0.8; 3072 of 8 at 64 -1.6, 128 -2.2.
 template <int DH> inline bool bwd_one_launch(int B, int H, int S) {
   const long nqb = (S + 127) / 128, blocks = (long)B * H * nqb;
-  return nqb <= 4 || blocks <= 1280 || (blocks < 3072 && nqb <= (DH == 32 ? 5 : DH == 64 ? 8 : 16));
+  return nqb <= 4 || blocks <= 1280 || (blocks <= 3072 && nqb <= (DH == 32 ? 5 : DH == 64 ? 8 : 16));
 }
 // Two groups a block there while that is less than a workgroup of each kind a compute unit: one | two groups 14 x 1900 x 64 54.9 | 44.0, 14 x 2048 x 128
 // 135 | 105, 16 x 900 x 64 28.0 | 24.2, 32 x 384 x 32 14.3 | 13.1; 64 x 512 (256 blocks) x 64 22.0 | 23.3, x 128 53.2 | 53.8; 42 x 1000 42.0 | 48.0; of two
