@@ -821,9 +821,10 @@ WeightTiles raw_product_weights(const bf16* W, int rows, int N, int K) {   // ru
   return WeightTiles{W, 2 * N, K, tiles_m * tiles_n * splits, tiles_m, (steps + splits - 1) / splits * F::BK, tiles_n};
 }
 
-// A product behind a LayerNorm in one launch with it: while one round of workgroups holds the product, each of which normalises its rows
+// A product behind a LayerNorm in one launch with it: while one round of workgroups holds the product, each of which normalises its rows.  Where the
+// 32 x 64 tile is the cheapest: above 16 of K.  Without column sums, which nothing behind it would add up.
 bool gemm_norm_takes(const GemmArgs& a) {
-  return !a.out_f32 && !a.trans_a && !a.trans_b && a.lda == a.K && std::max(1, a.splits) == 1 && !g_forced_fit &&
+  return !a.out_f32 && !a.colsum && !a.trans_a && !a.trans_b && a.lda == a.K && std::max(1, a.splits) == 1 && !g_forced_fit &&
          shape_tiles(1, a.M, a.N, false) <= 256 && direct_takes(a, true, false, DIRECT_K) && pick_fit(a.M, a.N, a.K, 1, false, true, false) == 1;
 }
 dipaco_status launch_gemm_norm(const GemmArgs& a, const RowNorm& ln, hipStream_t s) {
