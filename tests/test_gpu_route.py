@@ -261,7 +261,7 @@ def test_logistic_loss_and_gradients_match_oracle(N, D, K):
 
 @pytest.mark.parametrize("N,D,K", [(31, 8, 256), (33, 16, 200), (32768, 16, 256), (32769, 16, 256), (70001, 8, 120), (65568, 8, 8)])
 def test_logistic_sums_over_several_rounds_of_rows(N, D, K):
-    """A workgroup takes 32 rows up to 32768 rows, above that 32 several times: the sums of whole and ragged rounds."""
+    """Up to 1024 workgroups take 32 rows of 129 to 256 classes at a time, 64 of 65 to 128, 128 of 33 to 64, else 256: the sums of whole and ragged rounds."""
     test_logistic_loss_and_gradients_match_oracle(N, D, K)
 
 
