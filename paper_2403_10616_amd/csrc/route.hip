@@ -648,8 +648,7 @@ constexpr int RF_LDS = RF_WAVES * RF_ST * RF_STAGE;
 template <bool TOP2, int PTS>
 __global__ void __launch_bounds__(RF_WAVES * WAVE) route_few_kernel(const float* __restrict__ z, long ldz, const float* __restrict__ c,
                                                                     const float* __restrict__ lin_bias, long N, int D, int K, int wc,
-                                                                    int* __restrict__ idx, unsigned long long* __restrict__ hist,
-                                                                    float* __restrict__ margin) {
+                                                                    int* __restrict__ idx, float* __restrict__ margin) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ Best red[RF_WAVES][PTS];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -785,17 +784,36 @@ __global__ void __launch_bounds__(RF_WAVES * WAVE) route_few_kernel(const float*
       b.i2 = K > 1 ? 1 : NO_INDEX;
       b.s1 = b.s2 = __builtin_nanf("");
     }
-    atomicAdd(&hist[b.i1], 1ull);
     if (TOP2) {
-      if (b.i2 == NO_INDEX) b.i2 = -1;
-      else atomicAdd(&hist[b.i2], 1ull);
       idx[2 * (m0 + lane)] = b.i1;
-      idx[2 * (m0 + lane) + 1] = b.i2;
+      idx[2 * (m0 + lane) + 1] = b.i2 == NO_INDEX ? -1 : b.i2;
     } else {
       idx[m0 + lane] = b.i1;
     }
     if (margin) margin[m0 + lane] = b.s2 - b.s1;
   }
+}
+// Its histogram, in place of the zeros that the other kernels add to: hist[k] = how many of the n indices are k.  The few points of a workgroup
+// share no centroid in general, and additions to memory take 9 ns each behind the others of their 128-byte line: 900 x 256 x 4 19.1 us with them, 11.2 so (11.4 in
+// route_small_kernel), 900 x 640 x 30 18.4 -> 14.2, 1000 x 896 x 64 22.6 -> 18.1; where all points are of one centroid 500 x 896 x 256 26.8 -> 22.1 us
+// (26.6), their two nearest 900 x 64 x 4 27.2 -> 11.3 (10.9); 100 x 896 x 256 18.6 -> 17.9.
+constexpr int RF_MOST = 2 * 256 * RF_WAVES, RF_COUNT_THREADS = 512, MOST_CENTROIDS = 4096;   // indices of a launch; centroids of a call
+__global__ void __launch_bounds__(RF_COUNT_THREADS) route_count_kernel(const int* __restrict__ idx, int n, int K, unsigned long long* __restrict__ hist) {
+  __shared__ int counts[MOST_CENTROIDS];
+  const int tid = threadIdx.x;
+  int mine[RF_MOST / RF_COUNT_THREADS];
+#pragma unroll
+  for (int i = 0; i < RF_MOST / RF_COUNT_THREADS; ++i) {
+    const int at = tid + RF_COUNT_THREADS * i;
+    mine[i] = at < n ? idx[at] : -1;
+  }
+  for (int k = tid; k < K; k += RF_COUNT_THREADS) counts[k] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < RF_MOST / RF_COUNT_THREADS; ++i)
+    if ((unsigned)mine[i] < (unsigned)K) atomicAdd(&counts[mine[i]], 1);
+  __syncthreads();
+  for (int k = tid; k < K; k += RF_COUNT_THREADS) hist[k] = (unsigned long long)counts[k];
 }
 
 // ---- K-class logistic regression: per-row softmax cross-entropy --------------------------------------------------
@@ -1081,10 +1099,30 @@ static int route_few_points(int64_t N, int64_t ldz, int D, int wc) {
 
 dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const float* lin_bias, int64_t N, int D, int K,
                            int n_best, int* idx, long long* hist, float* margin, hipStream_t s) {
+  auto* h = reinterpret_cast<unsigned long long*>(hist);
+  const int pick = N ? route_pick(N, ldz, D, K) : 0;
+  if (N && pick == 1) {
+    const int fc = K > 128 ? 4 : K > 64 ? 2 : 1;
+    auto few = [&](auto PTC) -> dipaco_status {
+      constexpr int PTS = decltype(PTC)::value;
+      static std::atomic<unsigned long long> set_one{0}, set_two{0};
+      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<false, PTS>), RF_LDS, set_one)) return e;
+      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<true, PTS>), RF_LDS, set_two)) return e;
+      const int64_t pts = PTS * (RF_WAVES / fc), nb = (N + pts - 1) / pts;
+      if (n_best == 2) route_few_kernel<true, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, margin);
+      else route_few_kernel<false, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, margin);
+      DIPACO_LAUNCH_CHECK();
+      route_count_kernel<<<1, RF_COUNT_THREADS, 0, s>>>(idx, (int)(N * n_best), K, h);
+      DIPACO_LAUNCH_CHECK();
+      return DIPACO_OK;
+    };
+    const int take = route_few_points(N, ldz, D, fc);
+    if (take == 1) return few(std::integral_constant<int, 1>{});
+    if (take == 2) return few(std::integral_constant<int, 2>{});
+  }
   dipaco_status st = launch_fill_i64(hist, 0, (size_t)K, s);
   if (st != DIPACO_OK) return st;
   if (N == 0) return DIPACO_OK;
-  auto* h = reinterpret_cast<unsigned long long*>(hist);
   const int wc = route_small_wc(K);
   auto small = [&](auto PTC) -> dipaco_status {
     constexpr int PT = decltype(PTC)::value, LDS = RouteSmall<PT>::LDS;
@@ -1097,24 +1135,6 @@ dipaco_status launch_route(const float* z, int64_t ldz, const float* c, const fl
     DIPACO_LAUNCH_CHECK();
     return DIPACO_OK;
   };
-  const int pick = route_pick(N, ldz, D, K);
-  if (pick == 1) {
-    const int fc = K > 128 ? 4 : K > 64 ? 2 : 1;
-    auto few = [&](auto PTC) -> dipaco_status {
-      constexpr int PTS = decltype(PTC)::value;
-      static std::atomic<unsigned long long> set_one{0}, set_two{0};
-      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<false, PTS>), RF_LDS, set_one)) return e;
-      if (dipaco_status e = ensure_dynamic_lds(reinterpret_cast<const void*>(route_few_kernel<true, PTS>), RF_LDS, set_two)) return e;
-      const int64_t pts = PTS * (RF_WAVES / fc), nb = (N + pts - 1) / pts;
-      if (n_best == 2) route_few_kernel<true, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, h, margin);
-      else route_few_kernel<false, PTS><<<(unsigned)nb, RF_WAVES * WAVE, RF_LDS, s>>>(z, (long)ldz, c, lin_bias, (long)N, D, K, fc, idx, h, margin);
-      DIPACO_LAUNCH_CHECK();
-      return DIPACO_OK;
-    };
-    const int take = route_few_points(N, ldz, D, fc);
-    if (take == 1) return few(std::integral_constant<int, 1>{});
-    if (take == 2) return few(std::integral_constant<int, 2>{});
-  }
   if (pick == 1) return small(std::integral_constant<int, 1>{});
   if (pick == 2) return small(std::integral_constant<int, 2>{});
   static std::atomic<unsigned long long> lds_one{0}, lds_two{0};

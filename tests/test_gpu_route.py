@@ -665,6 +665,20 @@ def test_a_batch_routes_as_its_points_do_among_others(D, K):
             assert np.array_equal(got_idx, idx[:n]) and np.array_equal(got_gap[~nan[:n]], gap[:n][~nan[:n]])
 
 
+def test_points_of_one_centroid_take_a_batch_no_longer():
+    """Added to a histogram in memory, 1800 indices of the same line are 27 us; 64 points take 11."""
+    D, K = 64, 4
+    c = np.random.default_rng(3).standard_normal((K, D)).astype(np.float32)
+    times = {}
+    for N in (64, 900):
+        idx, hist = torch.empty((N, 2), dtype=torch.int32, device=DEV), torch.empty(K, dtype=torch.int64, device=DEV)
+        z, cd = dev(np.repeat(c[1:2], N, axis=0)), dev(c)
+        times[N] = median_us(lambda: dp.dipaco_route_prefix_top(z, D, cd, N, D, K, 2, idx, hist, None), n=50)
+        assert host(hist)[1] == N and host(hist).sum() == 2 * N and (host(idx)[:, 0] == 1).all()
+    print(f"two nearest of 4: 64 points {times[64]:.1f} us, 900 {times[900]:.1f}", flush=True)
+    assert times[900] <= 1.5 * times[64]
+
+
 def test_more_points_than_one_launch_of_small_workgroups_holds():
     """600,000,000 points and 100 centroids: 64 points a workgroup of 512 threads would pass 2^32 threads in a launch."""
     N, D, K = 600_000_000, 4, 100
