@@ -911,7 +911,7 @@ template <int LANES> __device__ __forceinline__ float row_sum(float v) {
 }
 template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_rows_small_kernel(float* __restrict__ logits, const int* __restrict__ labels,
                                                                                                 long rows, int K, float inv_n,
-                                                                                                float* __restrict__ partial) {
+                                                                                                float* __restrict__ partial, int blocks) {
   constexpr int ROWS = LOGIT_SMALL_ROWS / VEC, PER = 64 / LANES, GROUP = ROWS * PER;   // K <= 4 LANES VEC
   static_assert(VEC == 1 || LANES == 64);
   constexpr int STRIDE = logistic_stride(4 * LANES * VEC);
@@ -927,7 +927,7 @@ template <int LANES, int VEC> __global__ void __launch_bounds__(256) logistic_ro
     for (int q = 0; q < 4; ++q) sums[k][q] = 0.0;
   }
   double loss = 0.0;   // of lane i: of the i-th row of each group
-  const long step = (long)gridDim.x * 4 * GROUP;
+  const long step = (long)blocks * 4 * GROUP;
   for (long row0 = ((long)blockIdx.x * 4 + wave) * GROUP; row0 < rows; row0 += step) {   // whole waves: the reductions see all 64 lanes
     float4 v[ROWS][VEC];
     int own_label = -1;
@@ -1045,7 +1045,7 @@ dipaco_status launch_logistic_rows(float* logits, const int* labels, int64_t row
     auto run = [&](auto lanes, auto vec) {
       const int64_t per = 4 * LOGIT_SMALL_ROWS / vec * (64 / lanes);
       const int n = (int)std::min<int64_t>((rows + per - 1) / per, LOGIT_SMALL_BLOCKS);
-      logistic_rows_small_kernel<lanes, vec><<<n, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial);
+      logistic_rows_small_kernel<lanes, vec><<<n, 256, 0, s>>>(logits, labels, (long)rows, K, inv_n, partial, n);
       return n;
     };
     using std::integral_constant;

@@ -56,20 +56,22 @@ template <int COLS> struct Unit {
 // product one to three launches on will read, each XCD those of its own workgroups: lines stay in an XCD's L2 over the end of a kernel.  One
 // document through 12 blocks of 896, weights from memory 386 -> 332 us, with the last pass's still in the 256 MB cache 331 -> 326; lines
 // dealt to any XCD 347 and 346.  The output projection's weights, whose loads run under the attention, gain nothing from it (334).
-// Item v of that product's `items` (dealt to the XCDs in contiguous ranges) reads piece v / items_per_piece.
-__device__ __forceinline__ void touch(const WeightTiles& w, int block, int part, int parts) {
+// Item v of that product's `items` (dealt to the XCDs in contiguous ranges) reads piece v / items_per_piece.  The launch's size comes as an
+// argument: gridDim and blockDim bring 256 bytes of hidden ones, which a process whose host writes arguments slowly shows (issuing the 75 launches
+// of a pass, 12 blocks of 256: 270 us with them, 253 so; in others 200 both ways).
+template <int THREADS> __device__ __forceinline__ void touch(const WeightTiles& w, int block, int part, int parts) {
   const int x = block % N_XCD, per = w.items / N_XCD, rem = w.items % N_XCD;
   const int first = x * per + min(x, rem), last = first + per + (x < rem) - 1;
   if (last < first) return;
   const int p0 = first / w.items_per_piece, lines = (last / w.items_per_piece - p0 + 1) * w.piece_rows;
-  for (int i = part * (int)blockDim.x + threadIdx.x; i < lines; i += parts * (int)blockDim.x) {
+  for (int i = part * THREADS + (int)threadIdx.x; i < lines; i += parts * THREADS) {
     const int q = i / w.piece_rows, piece = p0 + q, row_block = piece / w.pieces_n;
     const int row = row_block * w.piece_rows + (i - q * w.piece_rows), col = 128 * (piece - row_block * w.pieces_n);
     if (row < w.rows && col < w.row_bytes) (void)*reinterpret_cast<const volatile uint32_t*>(static_cast<const char*>(w.base) + (size_t)row * w.row_bytes + col);
   }
 }
 // workgroups of `threads` for it, a line a thread
-static unsigned touch_blocks(const WeightTiles& w, int threads) {
+static int touch_blocks(const WeightTiles& w, int threads) {
   if (!w.items) return 0;
   const int lines = ((w.items + N_XCD - 1) / N_XCD / w.items_per_piece + 1) * w.piece_rows;
   return N_XCD * ((lines + threads - 1) / threads);
@@ -82,8 +84,8 @@ constexpr int RP_LD = RP_COLS + 4;   // floats between rows of the waves' sums
 template <bool GELU>
 __global__ void __launch_bounds__(RP_WAVES * WAVE) rows_product_kernel(const bf16* __restrict__ x, const bf16* __restrict__ W,
                                                                        const bf16* __restrict__ bias, bf16* __restrict__ out, int n_rows, int N, int K,
-                                                                       int tiles, WeightTiles ahead) {
-  if ((int)blockIdx.x >= tiles) return touch(ahead, blockIdx.x, (blockIdx.x - tiles) / N_XCD, (gridDim.x - tiles) / N_XCD);
+                                                                       int tiles, int blocks, WeightTiles ahead) {
+  if ((int)blockIdx.x >= tiles) return touch<RP_WAVES * WAVE>(ahead, blockIdx.x, ((int)blockIdx.x - tiles) / N_XCD, (blocks - tiles) / N_XCD);
   __shared__ __attribute__((aligned(16))) float red[RP_WAVES][SF_ROWS][RP_LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
@@ -163,8 +165,8 @@ constexpr int AO_LD = 64 + 4;
 // qkv [B S, 3 A] -> planes [ceil(H / 2)][B S, d]
 __global__ void __launch_bounds__(AO_WAVES * WAVE) attn_out_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ w_o,
                                                                    float* __restrict__ planes, int S, int H, int d, int docs, int tiles,
-                                                                   WeightTiles ahead) {
-  if ((int)blockIdx.x >= tiles) return touch(ahead, blockIdx.x, (blockIdx.x - tiles) / N_XCD, (gridDim.x - tiles) / N_XCD);
+                                                                   int blocks, WeightTiles ahead) {
+  if ((int)blockIdx.x >= tiles) return touch<AO_WAVES * WAVE>(ahead, blockIdx.x, ((int)blockIdx.x - tiles) / N_XCD, (blocks - tiles) / N_XCD);
   __shared__ __attribute__((aligned(16))) char o_[SF_ROWS * AO_ROW];
   __shared__ __attribute__((aligned(16))) float red[AO_STEPS][SF_ROWS][AO_LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -285,16 +287,17 @@ WeightTiles small_product_weights(const bf16* W, int rows, int N, int K) {   // 
 dipaco_status launch_small_product(const bf16* x, const bf16* W, const bf16* bias, bf16* out, int rows, int N, int K, bool gelu, const WeightTiles& ahead,
                                    hipStream_t s) {
   const int tiles = (N + RP_COLS - 1) / RP_COLS * ((rows + SF_ROWS - 1) / SF_ROWS);
-  const unsigned grid = tiles + touch_blocks(ahead, RP_WAVES * WAVE);
-  if (gelu) rows_product_kernel<true><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, ahead);
-  else rows_product_kernel<false><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, ahead);
+  const int grid = tiles + touch_blocks(ahead, RP_WAVES * WAVE);
+  if (gelu) rows_product_kernel<true><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, grid, ahead);
+  else rows_product_kernel<false><<<grid, RP_WAVES * WAVE, 0, s>>>(x, W, bias, out, rows, N, K, tiles, grid, ahead);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
 
 dipaco_status launch_attn_out(const bf16* qkv, const bf16* w_o, float* planes, int B, int S, int H, int d, const WeightTiles& ahead, hipStream_t s) {
   const int tiles = (d + 63) / 64 * ((H + AO_HEADS - 1) / AO_HEADS) * B;
-  attn_out_kernel<<<tiles + touch_blocks(ahead, AO_WAVES * WAVE), AO_WAVES * WAVE, 0, s>>>(qkv, w_o, planes, S, H, d, B, tiles, ahead);
+  const int grid = tiles + touch_blocks(ahead, AO_WAVES * WAVE);
+  attn_out_kernel<<<grid, AO_WAVES * WAVE, 0, s>>>(qkv, w_o, planes, S, H, d, B, tiles, grid, ahead);
   DIPACO_LAUNCH_CHECK();
   return DIPACO_OK;
 }
