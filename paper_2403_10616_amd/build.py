@@ -19,7 +19,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     # keep the compiler from forming packed fp32 ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the first arguments of a kernel arrive in registers instead of through a load in front of everything else: 0.1 us a launch
+    # the first plain arguments of a kernel (attention, LayerNorm, routing, products of a few rows) arrive in registers instead of through a load
+    # in front of everything else, 0.1 us a launch; a struct by value, as the matrix products take, is still loaded.  Without | with, us: 64 tokens
+    # of the 150M path 1984 | 1957, 256 tokens of a 64-wide one 140.7 | 138.7, features of one document 327 | 320; long calls level
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 

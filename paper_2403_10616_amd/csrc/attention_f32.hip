@@ -399,7 +399,9 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_bwd_dkv_f32(const float* __re
 }
 // Both in one launch on four waves a block, behind one that takes D_i (by the arithmetic of dq_block: the same bits): each alone ends with its longest
 // blocks.  us, two launches -> one: 64 heads x 500 x 64 102 -> 91, x 32 60.8 -> 50.1, x 128 178 -> 162, 24 x 180 x 64 37.8 -> 24.1, 4 x 1000 x 64 170 ->
-// 100, 32 x 2000 x 64 549 -> 531; 256 x 250 x 128 (1024 blocks) 193 -> 198, and on eight waves 1 - 5 % behind (512 x 130 x 64 111 -> 116).
+// 100, 32 x 2000 x 64 549 -> 531; 256 x 250 x 128 (1024 blocks) 193 -> 198, and on eight waves 1 - 5 % behind (512 x 130 x 64 111 -> 116).  Over 90
+// sizes of 96 to 1024 blocks 1 - 42 % ahead but for whole rounds of short or very long sequences: 512 blocks of 2 and of 32 at head size 128 (73 -> 75, 610 ->
+// 636), 684 and 768 of 3 at 64 (52 -> 54, 53 -> 55).
 constexpr long ONE_LAUNCH_WIDE = 512;   // most blocks with head size 128
 template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW) attn_stats_f32(const float* __restrict__ o, const float* __restrict__ d_o, float* __restrict__ dsum, int S, int H) {

@@ -25,13 +25,13 @@ __host__ __device__ __forceinline__ int causal_rank(int i, int n) {
   if (rounds == 3) return c < m ? c : U - 1 - (c - m);             // the other units hold one block more length as c falls
   return r == 0 ? c : 2 * U - 1 - c;                               // four rounds: the first two are pairs of their own
 }
-struct CausalPlace { int bh, order, n_bh; };   // sequence and head; block, longest first
+struct CausalPlace { int bh, order; };   // sequence and head; block, longest first
 // grid (sequences x heads, blocks)
 __device__ __forceinline__ CausalPlace causal_place(bool paired) {
   const int n_bh = gridDim.x;
-  if (!paired) return {(int)blockIdx.x, (int)blockIdx.y, n_bh};
+  if (!paired) return {(int)blockIdx.x, (int)blockIdx.y};
   const int rank = causal_rank(blockIdx.x + n_bh * blockIdx.y, n_bh * gridDim.y), order = rank / n_bh;
-  return {rank - order * n_bh, order, n_bh};
+  return {rank - order * n_bh, order};
 }
 
 // whether a launch of n workgroups, blocks of n_bh heads, pairs its rounds: they are resident at once.  `seen`: the kernel's own, workgroups to a unit + 1

@@ -118,11 +118,11 @@ struct GemmArgs {
 };
 size_t gemm_colsum_partial_floats(int M, int N);
 template <typename T> dipaco_status launch_gemm(const GemmArgs& g, hipStream_t s);
-// X^T dY and dY W^T of a linear layer: neither reads what the other writes
 // gemm_fit.hip: C = LayerNorm(A) B with epilogue in fp32, A [M, K] rows as they lie; y, mean and rstd as launch_layernorm_fwd leaves them
 struct RowNorm { const float* gain; const float* shift; float* y; float* mean; float* rstd; float eps; };
 bool gemm_norm_takes(const GemmArgs& g);
 dipaco_status launch_gemm_norm(const GemmArgs& g, const RowNorm& ln, hipStream_t s);   // of checked arguments
+// X^T dY and dY W^T of a linear layer, side by side in one launch where that is ahead: neither may read or write what the other writes
 template <typename T> dipaco_status launch_gemm_pair(const GemmArgs& dw, const GemmArgs& dx, hipStream_t s);
 // how launch_gemm_pair takes bf16 products of these sizes (dW cut into at most max_slices), for tests.  out[0]: rows of dX's tile in one launch with
 // dW, 0: two launches; out[1]: dW's tiles come first; out[2], out[3]: K of dW's longest chain of sums in one launch, in two

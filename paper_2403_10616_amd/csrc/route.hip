@@ -636,8 +636,9 @@ __global__ void __launch_bounds__(RS_WAVES * WAVE) route_small_kernel(const floa
 // different points.  Four stages of 32 K in flight, straight into LDS; the numbers of the next tile are read under the
 // multiply-adds of this one.  No barrier before the end.  Bound by what one compute unit reads through its L1 (every workgroup reads all
 // centroids, 64 bytes a clock: 6 us of 917 KB) and, level with it, by the vector instructions of a tile; 11 us of a call are the two
-// launches and the latencies of their ends.  Microseconds a call, kernel above -> this: 100 x 896 x 256 26.9 -> 18.9, 256 x 896 x 256 27.0 -> 19.8,
-// 500 x 896 x 256 (two points a wave) 27.2 -> 23.6, 256 x 896 x 1000 89 -> 63, 100 x 896 x 64 25.4 -> 17.9, 100 x 64 x 256 11.0 -> 10.9.
+// launches and the latencies of their ends.  Microseconds a call, kernel above -> this: 100 x 896 x 256 27.0 -> 17.9, 250 x 896 x 256 27.0 -> 19.0,
+// 500 x 896 x 256 (two points a wave) 27.2 -> 23.1, 256 x 896 x 1000 89 -> 57, 100 x 896 x 64 25.9 -> 17.2, 100 x 64 x 256 level (11.1); with points and
+// centroids from memory, every workgroup's trip to them on the way, 100 x 896 x 256 27.8 -> 20.7, one point 27.4 -> 22.5.
 // Left out: v_mfma_f32_4x4x1_16b_f32 with four points a matrix row (a dependent one takes 20 clocks: 27 us for any N up to 2048).
 // The chain of a score takes K as v_mfma_f32_16x16x4_f32 does above (0, 4, 8, 12, 1, 5, .. of every sixteen) and ||c||^2 is
 // added up in the same four sums: the same scores, bit for bit.

@@ -55,7 +55,10 @@ template <int COLS> struct Unit {
 // of the compute units idle.  So these have workgroups behind their own that read a word of every 128-byte line of the weights that a
 // product one to three launches on will read, each XCD those of its own workgroups: lines stay in an XCD's L2 over the end of a kernel.  One
 // document through 12 blocks of 896, weights from memory 386 -> 332 us, with the last pass's still in the 256 MB cache 331 -> 326; lines
-// dealt to any XCD 347 and 346.  The output projection's weights, whose loads run under the attention, gain nothing from it (334).
+// dealt to any XCD 347 and 346.  More documents have more workgroups of their own and gain less: from memory 3 | 4 | 6 | 8 documents 436 -> 422 | 450 ->
+// 432 | 523 -> 499 | 594 -> 562, level at 2 and from 12 on; from the last-level cache 1 - 2 % at 3 - 8, level from 12 on, and 2 documents 344 -> 348.  Up to
+// 384 wide level (a pass's weights stay in the L2s), 512 wide 1 | 4 documents from memory 327 -> 303 | 339 -> 332.  The output projection's
+// weights, whose loads run under the attention, gain nothing from it (334).
 // Item v of that product's `items` (dealt to the XCDs in contiguous ranges) reads piece v / items_per_piece.  The launch's size comes as an
 // argument: gridDim and blockDim bring 256 bytes of hidden ones, which a process whose host writes arguments slowly shows (issuing the 75 launches
 // of a pass, 12 blocks of 256: 270 us with them, 253 so; in others 200 both ways).
